@@ -106,8 +106,8 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         // sums (no workspace of its own); 1x1: its own workspace and sums
         constexpr bool RHSD = B == 3;
         if (!g->sready && (rc = sym_prepare(g, s))) return rc;
-        if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)std::max<int64_t>(g->ulen, 1) * BB))) return rc;
-        if (!RHSD && (rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B))) return rc;
+        if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)std::max<int64_t>(g->ulen, 1) * BB + kSegPad))) return rc;
+        if (!RHSD && (rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
         a.contrib = g->contrib;
         a.rcontrib = RHSD ? nullptr : g->rcontrib;
         a.tent = g->tent;
@@ -149,7 +149,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
     if (o->variant == FEA_TILECOLOUR) {
         if (!g->sready && (rc = sym_prepare(g, s))) return rc;
         if (!g->tcready && (rc = tile_colour_prepare(g, s))) return rc;
-        if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B))) return rc;
+        if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
         double *tv = (double *)vals;
         if (f32) {
             if ((rc = ensure_ws((void **)&g->acc64, &g->acc64_bytes, sizeof(double) * (size_t)std::max<int64_t>(nv, 1)))) return rc;
@@ -195,8 +195,8 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.contrib = ws.contrib;
             a.rcontrib = ws.rcontrib;
         } else {
-            if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)g->map_len * BB))) return rc;
-            if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B))) return rc;
+            if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)g->map_len * BB + kSegPad))) return rc;
+            if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
             a.contrib = g->contrib;
             a.rcontrib = g->rcontrib;
         }

@@ -585,8 +585,8 @@ int launch_batch(fea_batch *b, const fea_options *o, hipStream_t s, void *vals, 
     int rc;
     if (SYM && (rc = sym_prepare_batch(b, s))) return rc;
     if ((rc = worker_count<MODEL, CT, VAR>(b))) return rc;
-    const size_t need_c = sizeof(CT) * (size_t)std::max<int64_t>(SYM ? b->total_sym_slots : b->total_slots, 1) * BB;
-    const size_t need_r = sizeof(CT) * (size_t)b->total_inc * B;
+    const size_t need_c = sizeof(CT) * (size_t)std::max<int64_t>(SYM ? b->total_sym_slots : b->total_slots, 1) * BB + kSegPad;
+    const size_t need_r = sizeof(CT) * (size_t)b->total_inc * B + kSegPad;
     if (b->contrib_bytes < need_c) {
         dfree(b->contrib);
         b->contrib = nullptr;

@@ -20,8 +20,8 @@ namespace fea {
 // segment.
 //
 // Launch shape per workspace type: bytes per load, rounds (segments per
-// thread) and LDS bytes per chunk. Measured on MI355X over the hybrid96
-// workspaces: FP64 streams best with 8-byte loads and one segment per
+// thread) and LDS bytes per chunk. Measured on MI355X over the workspaces of
+// the 96^3-cell hybrid mesh: FP64 streams best with 8-byte loads and one segment per
 // thread; FP32 segments are half as long, and 16-byte loads with four
 // segments per thread amortise the per-workgroup work (about 15% faster than
 // one 4-byte load per segment and thread).
@@ -32,75 +32,95 @@ struct SegCfg {
     static constexpr int CHUNK_BYTES = 16384;
 };
 
+// Bytes a workspace is allocated beyond its values: a workgroup reads whole
+// vectors of up to 16 bytes.
+constexpr size_t kSegPad = 16;
+
+template <int W, typename CT, int LOAD_BYTES, int CHUNK_BYTES>
+struct SegStage {
+    static constexpr int VEC = LOAD_BYTES / (int)sizeof(CT);    // values per load
+    static constexpr int CAPV = CHUNK_BYTES / (int)sizeof(CT);  // staged values per chunk
+    static constexpr int NV = CAPV / VEC;
+    static constexpr int LV = NV / 256;                         // loads per thread per chunk
+    static constexpr int CAPS = (CAPV - 2 * VEC) / W;           // slots per chunk (room for the alignment shift)
+    struct alignas(VEC * sizeof(CT)) Vec {
+        CT x[VEC];
+    };
+
+    // Slots base .. base + ns (0 < ns <= CAPS) of the workspace into sv, by the
+    // whole workgroup; returns the place of the first one's value 0 in sv.
+    // Whole vectors are read, so up to VEC - 1 values on either side of the
+    // range come along (the workspace is padded by one vector, see
+    // kSegPad). Threads beyond the range repeat its last vector: every load
+    // of a chunk is issued before the first is waited for, without branches
+    // inside a wave. again: the previous chunk's readers have to be waited for.
+    static __device__ inline int load(Vec *sv, const CT *data, int64_t base, int ns, bool again)
+    {
+        const int tid = threadIdx.x;
+        const int64_t f0 = base * W, a0 = f0 & ~(int64_t)(VEC - 1);
+        const int o = (int)(f0 - a0);
+        const int nvec = __builtin_amdgcn_readfirstlane((o + ns * W + VEC - 1) / VEC);
+        const char *src = reinterpret_cast<const char *>(data + a0);
+        char *dst = reinterpret_cast<char *>(sv);
+        const unsigned last = (unsigned)(nvec - 1) * sizeof(Vec);
+        Vec v[LV];
+#pragma unroll
+        for (int q = 0; q < LV; ++q)
+            if (q * 256 < nvec) {
+                const unsigned off = min((unsigned)(tid + q * 256) * (unsigned)sizeof(Vec), last);
+                v[q] = *reinterpret_cast<const Vec *>(src + off);
+            }
+        if (again) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < LV; ++q)
+            if (q * 256 < nvec) {
+                const unsigned off = min((unsigned)(tid + q * 256) * (unsigned)sizeof(Vec), last);
+                *reinterpret_cast<Vec *>(dst + off) = v[q];
+            }
+        __syncthreads();
+        return o;
+    }
+};
+
 template <int W, typename CT, typename OT>
 __global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, const CT *data, OT *out)
 {
     constexpr int TPS = 256 / W;                // segments per round
     constexpr int R = SegCfg<CT>::ROUNDS;       // rounds per workgroup
     constexpr int BPW = TPS * R;                // segments per workgroup
-    constexpr int VEC = SegCfg<CT>::LOAD_BYTES / (int)sizeof(CT);  // values per load
-    constexpr int CAPV = SegCfg<CT>::CHUNK_BYTES / (int)sizeof(CT);  // staged values per chunk
-    constexpr int LV = CAPV / (256 * VEC);                    // loads per thread per chunk
-    constexpr int CAPS = (CAPV - VEC) / W;      // slots per chunk (room for the alignment shift)
-    struct alignas(VEC * sizeof(CT)) Vec {
-        CT x[VEC];
-    };
-    __shared__ Vec sv[CAPV / VEC];
+    using Stage = SegStage<W, CT, SegCfg<CT>::LOAD_BYTES, SegCfg<CT>::CHUNK_BYTES>;
+    __shared__ typename Stage::Vec sv[Stage::NV];
     const CT *svs = sv[0].x;
     const int tid = threadIdx.x;
     const int64_t m0 = (int64_t)blockIdx.x * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
+    const int64_t s0 = ptr[m0], s1 = ptr[mend];
     const int lb = tid / W, c = tid - lb * W;
-    int64_t k[R], j0[R], j1[R];
+    int64_t j0[R], j1[R];
     double acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t m = m0 + lb + r * TPS;
-        const bool act = lb < TPS && m < mend;
-        k[r] = act ? m : -1;
-        j0[r] = act ? ptr[k[r]] : 0;
-        j1[r] = act ? ptr[k[r] + 1] : 0;
+        const int64_t mc = m < mend ? m : mend - 1;
+        j0[r] = ptr[mc];
+        j1[r] = ptr[mc + 1];
         acc[r] = 0.0;
     }
-    const int64_t s0 = ptr[m0];
-    const int64_t s1 = ptr[mend];
-    for (int64_t base = s0; base < s1; base += CAPS) {
-        const int64_t ns = s1 - base < CAPS ? s1 - base : CAPS;
-        const int64_t f0 = base * W, f1 = f0 + ns * W;  // value range of this chunk
-        const int64_t a0 = f0 & ~(int64_t)(VEC - 1);      // aligned start
-        const int o = (int)(f0 - a0);
-        const int nvec = (int)((f1 - a0 + VEC - 1) / VEC);
-        Vec v[LV];
-#pragma unroll
-        for (int q = 0; q < LV; ++q) {
-            const int i = tid + q * 256;
-            const int64_t g = a0 + (int64_t)i * VEC;
-            if (i < nvec && g >= f0 && g + VEC <= f1) {
-                v[q] = *reinterpret_cast<const Vec *>(data + g);
-            } else {
-                // the partial vectors at the two ends of the range
-#pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    v[q].x[e] = (i < nvec && g + e >= f0 && g + e < f1) ? data[g + e] : (CT)0;
-            }
-        }
-        __syncthreads();  // the previous chunk's readers are done
-#pragma unroll
-        for (int q = 0; q < LV; ++q) {
-            const int i = tid + q * 256;
-            if (i < nvec) sv[i] = v[q];
-        }
-        __syncthreads();
+    for (int64_t base = s0; base < s1; base += Stage::CAPS) {
+        const int ns = __builtin_amdgcn_readfirstlane((int)(s1 - base < Stage::CAPS ? s1 - base : Stage::CAPS));
+        const int o = Stage::load(sv, data, base, ns, base != s0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int64_t lo = j0[r] > base ? j0[r] : base, hi = j1[r] < base + ns ? j1[r] : base + ns;
-            for (int64_t j = lo; j < hi; ++j) acc[r] += (double)svs[o + (j - base) * W + c];
+            const int64_t d0 = j0[r] - base, d1 = j1[r] - base;
+            const int lo = d0 > 0 ? (int)(d0 < ns ? d0 : ns) : 0, hi = d1 < ns ? (int)(d1 > 0 ? d1 : 0) : ns;
+            const CT *v = svs + o + lo * W + c;
+            for (int j = lo; j < hi; ++j, v += W) acc[r] += (double)*v;
         }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (k[r] < 0) continue;
-        out[k[r] * W + c] = (OT)acc[r];
+        const int64_t m = m0 + lb + r * TPS;
+        if (lb < TPS && m < mend) out[m * W + c] = (OT)acc[r];
     }
 }
 
@@ -113,22 +133,45 @@ __global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, c
 // strictly lower entries (3, 6, 7) carry row v's right-hand side: those
 // sums go to rhs[3v .. 3v+2], and entries 1, 2, 5 are written to their
 // mirror positions too, so that every diagonal block is symmetric
-// bitwise. Every per-output index is read at
-// position m, so a workgroup's index loads are contiguous and independent
-// of each other, and its workspace range (uptr[m0] .. uptr[m0 + BPW]) is
-// known after one load; R rounds of 256 / W outputs per workgroup.
-// Measured on MI355X (FP64 / FP32 tile sums, ms): hybrid256 1 round
-// 16.55 / 15.15, 2 rounds 17.24-17.43 / 12.20-12.25, 4 rounds - / 12.53;
-// hybrid96 1 round 0.92-0.94 / 0.88, 2 rounds 0.95 / 0.70, 4 rounds - /
-// 0.71 (with the right-hand side carried in the diagonal tile sums).
-// 16-byte FP64 loads, 32 KB chunks with 4-8 rounds (fewer workgroups per
-// CU) and an XCD-contiguous workgroup order were all slower.
+// bitwise. Every per-output index is read at position m, so a workgroup's
+// index loads are contiguous and independent of each other, and its workspace
+// range (uptr[m0] .. uptr[m0 + BPW]) is known after one load; R rounds of
+// 256 / W outputs per workgroup.
+// What bounds it is memory: the tile sums stream in (4.6 TB/s with the stores
+// left out), the lower blocks go out as scattered 72-byte pieces. Two things
+// cost time beyond that. The block and partner indices were waited for before
+// the segment bounds were even loaded (three dependent loads where two do);
+// and the pieces of one line of lower blocks were written by workgroups on
+// different XCDs (see sym_run_tile). Measured on MI355X, before -> after, ms,
+// FP64 / FP32 tile sums: 96^3-cell hybrid mesh (11.6M outputs) 0.92 -> 0.80 /
+// 0.70 -> 0.53, 160^3 cells (50M) 4.01 -> 3.49 FP64. The first change alone
+// gave 0.96 / 0.55: without the runs it only brings the scattered writers
+// closer together. 8 KB chunks: 16 KB hold FP32 back (0.80), a workgroup's
+// outputs having about 4 KB of tile sums. FP64 with 16-byte loads 0.83, two
+// rounds 0.84; runs of 16 / 128 / 512 / 1024 / 2048 / 8192 ranges 0.89 / 0.82
+// / 0.79 / 0.80 / 0.81 / 0.87 (160^3: - / 3.77 / 3.54 / 3.49 / 3.51 / 3.62);
+// non-temporal loads 0.85.
 template <typename CT>
 struct SymSegCfg {
     static constexpr int LOAD_BYTES = sizeof(CT) == 8 ? 8 : 16;
     static constexpr int ROUNDS = sizeof(CT) == 8 ? 1 : 2;
-    static constexpr int CHUNK_BYTES = 16384;
+    static constexpr int CHUNK_BYTES = 8192;
 };
+
+// Position of workgroup b's outputs: runs of kSymRun consecutive ranges go to
+// one XCD (workgroup b runs on XCD b % 8), the XCDs taking turns; the last,
+// shorter group is split into eight equal runs. A row's lower blocks are
+// written, 72 bytes at a time, by the ranges of the rows next to it; within a
+// run they meet in one L2 and leave it as whole lines.
+constexpr int64_t kSymRun = 1024;
+__device__ inline int64_t sym_run_tile(int64_t b, int64_t nblk)
+{
+    const int64_t g = b / (8 * kSymRun) * (8 * kSymRun), i = b - g, left = nblk - g;
+    const int64_t x = i & 7, r = i >> 3;
+    if (left >= 8 * kSymRun) return g + x * kSymRun + r;
+    const int64_t q = left >> 3, rem = left & 7;
+    return g + x * q + (x < rem ? x : rem) + r;
+}
 
 template <int W, typename CT, typename OT, bool RHSD>
 __global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *blk, const int32_t *lp,
@@ -137,77 +180,54 @@ __global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *bl
     constexpr int TPS = 256 / W;                                      // outputs per round
     constexpr int R = SymSegCfg<CT>::ROUNDS;                          // rounds per workgroup
     constexpr int BPW = TPS * R;                                      // outputs per workgroup
-    constexpr int VEC = SymSegCfg<CT>::LOAD_BYTES / (int)sizeof(CT);  // values per load
-    constexpr int CAPV = SymSegCfg<CT>::CHUNK_BYTES / (int)sizeof(CT);
-    constexpr int LV = CAPV / (256 * VEC);                            // loads per thread per chunk
-    constexpr int CAPS = (CAPV - VEC) / W;                            // slots per chunk
-    struct alignas(VEC * sizeof(CT)) Vec {
-        CT x[VEC];
-    };
-    __shared__ Vec sv[CAPV / VEC];
+    using Stage = SegStage<W, CT, SymSegCfg<CT>::LOAD_BYTES, SymSegCfg<CT>::CHUNK_BYTES>;
+    __shared__ typename Stage::Vec sv[Stage::NV];
     const CT *svs = sv[0].x;
     const int tid = threadIdx.x;
-    const int64_t m0 = (int64_t)blockIdx.x * BPW;
+    const int64_t m0 = sym_run_tile(blockIdx.x, gridDim.x) * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
+    const int64_t s0 = uptr[m0], s1 = uptr[mend];
     const int lb = tid / W, c = tid - lb * W;
     const int ct = W == 9 ? (c % 3) * 3 + c / 3 : c;
-    int64_t k[R], l[R], j0[R], j1[R];
+    // unconditional loads at clamped positions, nothing derived from them
+    // here: the workspace loads below are issued without waiting for them
+    int32_t kb[R], lw[R];
+    int64_t j0[R], j1[R];
     double acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t m = m0 + lb + r * TPS;
-        const bool act = lb < TPS && m < mend;
-        k[r] = act ? (int64_t)blk[m] : -1;
-        l[r] = act ? (int64_t)lp[m] : -1;
-        j0[r] = act ? uptr[m] : 0;
-        j1[r] = act ? uptr[m + 1] : 0;
+        const int64_t mc = m < mend ? m : mend - 1;
+        kb[r] = blk[mc];
+        lw[r] = lp[mc];
+        j0[r] = uptr[mc];
+        j1[r] = uptr[mc + 1];
         acc[r] = 0.0;
     }
-    const int64_t s0 = uptr[m0], s1 = uptr[mend];
-    for (int64_t base = s0; base < s1; base += CAPS) {
-        const int64_t ns = s1 - base < CAPS ? s1 - base : CAPS;
-        const int64_t f0 = base * W, f1 = f0 + ns * W;  // value range of this chunk
-        const int64_t a0 = f0 & ~(int64_t)(VEC - 1);      // aligned start
-        const int o = (int)(f0 - a0);
-        const int nvec = (int)((f1 - a0 + VEC - 1) / VEC);
-        Vec v[LV];
-#pragma unroll
-        for (int q = 0; q < LV; ++q) {
-            const int i = tid + q * 256;
-            const int64_t g = a0 + (int64_t)i * VEC;
-            if (i < nvec && g >= f0 && g + VEC <= f1) {
-                v[q] = *reinterpret_cast<const Vec *>(data + g);
-            } else {
-#pragma unroll
-                for (int e = 0; e < VEC; ++e)
-                    v[q].x[e] = (i < nvec && g + e >= f0 && g + e < f1) ? data[g + e] : (CT)0;
-            }
-        }
-        __syncthreads();  // the previous chunk's readers are done
-#pragma unroll
-        for (int q = 0; q < LV; ++q) {
-            const int i = tid + q * 256;
-            if (i < nvec) sv[i] = v[q];
-        }
-        __syncthreads();
+    for (int64_t base = s0; base < s1; base += Stage::CAPS) {
+        const int ns = __builtin_amdgcn_readfirstlane((int)(s1 - base < Stage::CAPS ? s1 - base : Stage::CAPS));
+        const int o = Stage::load(sv, data, base, ns, base != s0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int64_t lo = j0[r] > base ? j0[r] : base, hi = j1[r] < base + ns ? j1[r] : base + ns;
-            for (int64_t j = lo; j < hi; ++j) acc[r] += (double)svs[o + (j - base) * W + c];
+            const int64_t d0 = j0[r] - base, d1 = j1[r] - base;
+            const int lo = d0 > 0 ? (int)(d0 < ns ? d0 : ns) : 0, hi = d1 < ns ? (int)(d1 > 0 ? d1 : 0) : ns;
+            const CT *v = svs + o + lo * W + c;
+            for (int j = lo; j < hi; ++j, v += W) acc[r] += (double)*v;
         }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (k[r] < 0) continue;
-        if (l[r] >= 0) {
-            out[k[r] * W + c] = (OT)acc[r];
-            out[l[r] * W + ct] = (OT)acc[r];
-        } else if (RHSD && (c == 3 || c == 6 || c == 7)) {
-            rhs[(-l[r] - 1) * 3 + (c == 3 ? 0 : c == 6 ? 1 : 2)] = (OT)acc[r];
-        } else {
-            out[k[r] * W + c] = (OT)acc[r];
-            if (RHSD && ct != c) out[k[r] * W + ct] = (OT)acc[r];
+        if (!(lb < TPS && m0 + lb + r * TPS < mend)) continue;
+        const int32_t k = kb[r], l = lw[r];
+        OT *p = out + (int64_t)k * W + c;       // this component's place
+        OT *q = out + (int64_t)k * W + ct;      // and its mirror's: the lower partner's, or the diagonal block's own
+        if (l >= 0) q = out + (int64_t)l * W + ct;
+        if (RHSD && l < 0 && (c == 3 || c == 6 || c == 7)) {
+            p = rhs + (int64_t)(-l - 1) * 3 + (c == 3 ? 0 : c - 5);
+            q = p;
         }
+        *p = (OT)acc[r];
+        if (q != p) *q = (OT)acc[r];
     }
 }
 
