@@ -162,7 +162,7 @@ int fea_graph_sizes(const fea_graph *g, int64_t *n_nodes, int64_t *n_elems,
 /* Sizes of the upper-triangle (FEA_ROWSYM) layout, built by the first
  * FEA_ROWSYM assembly on the graph: element tiles (per family, 256 / (n(n+1)/2)
  * consecutive elements of the type-sorted order), tile entries (one per
- * (element, local pair a <= b), two where nodes a and b coincide), tile-blocks
+ * (element, local pair a <= b)), tile-blocks
  * (distinct (tile, upper block) pairs = workspace slots, each 3x3 or 1x1) and
  * upper blocks (col >= row). Any output pointer may be NULL. FEA_EINVAL if the
  * layout has not been built yet. */

@@ -110,8 +110,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         if (!RHSD && (rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
         a.contrib = g->contrib;
         a.rcontrib = RHSD ? nullptr : g->rcontrib;
-        a.tent = g->tent;
-        a.tb_eend = g->tb_eend;
+        a.tb_rng = g->tb_rng;
         a.tb_slot = g->tb_slot;
         mark(g, 0, o, s);
         for (int t = 0; t < 4; ++t) {
@@ -119,7 +118,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.n = g->seg[t + 1] - g->seg[t];
             a.pnodes = g->pnodes + g->node_base[t];
             a.prdest = g->prdest + g->node_base[t];
-            a.tent_ptr = g->tent_ptr + g->tile_base[t];
+            a.tpos = g->tpos + g->pair_base[t];
             a.ttb_ptr = g->ttb_ptr + g->tile_base[t];
             launch_type<MODEL, V_ROWSYM, CT>(t, a, s);
         }
@@ -157,8 +156,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         }
         a.rcontrib = g->rcontrib;
         a.vals = tv;
-        a.tent = g->tent;
-        a.tb_eend = g->tb_eend;
+        a.tb_rng = g->tb_rng;
         a.tb_blk = g->tb_blk;
         a.lpart = g->lpart;
         mark(g, 0, o, s);
@@ -171,7 +169,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
                 a.n = g->seg[t + 1] - g->seg[t];
                 a.pnodes = g->pnodes + g->node_base[t];
                 a.prdest = g->prdest + g->node_base[t];
-                a.tent_ptr = g->tent_ptr + g->tile_base[t];
+                a.tpos = g->tpos + g->pair_base[t];
                 a.ttb_ptr = g->ttb_ptr + g->tile_base[t];
                 a.tiles = g->ctile + b;
                 a.ntiles = e - b;

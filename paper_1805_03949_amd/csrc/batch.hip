@@ -35,6 +35,7 @@ struct BatchMesh {
     int64_t coff;    // first slot of this mesh in the slot workspace
     int64_t roff;    // first incidence of this mesh in the rhs workspace
     int64_t tile_base[5];  // upper-triangle form: family starts in the tile ranges
+    int64_t pair_base[5];  // and in tpos
     int64_t scoff;         // first tile-block of this mesh in its workspace
 };
 
@@ -474,12 +475,12 @@ int sym_prepare_batch(fea_batch *b, hipStream_t s)
         noff[m + 1] = noff[m] + g->n_nodes;
         b->sym_empty_rows += g->sym_empty_rows;
         BatchMesh &M = b->hmeshes[m];
-        M.a.tent_ptr = g->tent_ptr;
         M.a.ttb_ptr = g->ttb_ptr;
-        M.a.tent = g->tent;
-        M.a.tb_eend = g->tb_eend;
+        M.a.tpos = g->tpos;
+        M.a.tb_rng = g->tb_rng;
         M.a.tb_slot = g->tb_slot;
         std::copy(g->tile_base, g->tile_base + 5, M.tile_base);
+        std::copy(g->pair_base, g->pair_base + 5, M.pair_base);
         M.scoff = soff[m];
     }
     dfree(b->d_sym_ublk);
@@ -536,8 +537,8 @@ int ensure_itemargs(fea_batch *b, hipStream_t s)
         A.rcontrib = (CT *)b->rcontrib + M.roff * B;
         if (VAR == V_ROWSYM) {
             const int64_t tl = M.tile_base[t] + z / sym_epb(t);
-            A.tent_ptr = M.a.tent_ptr + tl;
             A.ttb_ptr = M.a.ttb_ptr + tl;
+            A.tpos = M.a.tpos + M.pair_base[t] + (int64_t)z * (nn * (nn + 1) / 2);
         }
         A.elems = M.a.elems + M.seg[t] + z;
         A.n = b->items[4 * it + 3];

@@ -182,13 +182,12 @@ struct ElemArgs {
     void *contrib;   // ROWOWNER slot workspace (compute type)
     void *rcontrib;  // right-hand-side workspace (ROWOWNER, TILECOL; ROWSYM with 1x1 blocks)
     int32_t *status;
-    // upper-triangle form, indexed by the launch-local tile index: entry and
-    // tile-block ranges, entries (lane << 1 | transposed), tile-block entry
-    // ends and workspace slots
-    const int64_t *tent_ptr;
+    // upper-triangle form: tile-block ranges, indexed by the launch-local
+    // tile index; per (element, pair) of the launch its staged place (see
+    // sym_pair); per tile-block its entries' range and workspace slot
     const int64_t *ttb_ptr;
-    const uint16_t *tent;
-    const uint16_t *tb_eend;
+    const uint16_t *tpos;
+    const uint16_t *tb_rng;
     const int32_t *tb_slot;
     // tile-coloured form: the launch's tiles (launch-local tile indices,
     // ntiles of them), every tile-block's block and every block's lower
@@ -230,10 +229,9 @@ struct ElemArgsGlobal {
     FEA_G(void) contrib;
     FEA_G(void) rcontrib;
     FEA_G(int32_t) status;
-    FEA_G(const int64_t) tent_ptr;
     FEA_G(const int64_t) ttb_ptr;
-    FEA_G(const uint16_t) tent;
-    FEA_G(const uint16_t) tb_eend;
+    FEA_G(const uint16_t) tpos;
+    FEA_G(const uint16_t) tb_rng;
     FEA_G(const int32_t) tb_slot;
     FEA_G(const int32_t) tiles;
     int64_t ntiles;
@@ -273,10 +271,9 @@ __device__ __forceinline__ ElemArgs from_global(const ElemArgsGlobal &g)
     a.contrib = (void *)g.contrib;
     a.rcontrib = (void *)g.rcontrib;
     a.status = (int32_t *)g.status;
-    a.tent_ptr = (const int64_t *)g.tent_ptr;
     a.ttb_ptr = (const int64_t *)g.ttb_ptr;
-    a.tent = (const uint16_t *)g.tent;
-    a.tb_eend = (const uint16_t *)g.tb_eend;
+    a.tpos = (const uint16_t *)g.tpos;
+    a.tb_rng = (const uint16_t *)g.tb_rng;
     a.tb_slot = (const int32_t *)g.tb_slot;
     a.tiles = (const int32_t *)g.tiles;
     a.ntiles = g.ntiles;
@@ -462,9 +459,12 @@ struct ElemSmem : ElemDims<T, MODEL, VAR, CT>, ElemPre<ElemDims<T, MODEL, VAR, C
     int64_t sM[D::RO ? 1 : D::EPB];   // first slot of each element
     int64_t sCP[D::RO ? 1 : D::EPB];  // first conn position of each element
     int32_t sD[D::STAGE && !D::SYM ? D::EPB * D::PW : 1];
-    uint16_t sEnt[D::SYM ? D::MAXENT : 1];   // the tile's entries
-    uint16_t sEend[D::SYM ? D::MAXENT : 1];  // and tile-block ends
-    int32_t sSlot[D::SYM ? D::MAXENT : 1];   // workspace slot (tile-coloured: block) of every tile-block
+    // per tile-block its workspace slot (tile-coloured: its block), its first
+    // entry and entries - 1
+    struct alignas(8) TileBlock {
+        int32_t slot;
+        uint32_t rng;
+    } sTb[D::SYM ? D::MAXENT : 1];
     int32_t sLp[D::TCOL ? D::MAXENT : 1];    // tile-coloured: lower partner of every tile-block's block
 };
 
@@ -914,18 +914,35 @@ __device__ void elem_tile_full(const ElemArgs &A, int64_t first, ElemSmem<T, MOD
 
 // Upper-triangle form (V_ROWSYM) and its tile-coloured variant (V_TILECOL):
 // tile first / EPB, one thread per local pair a <= b of every element.
-// Every global load of the tile -- node ids, coordinates, right-hand-side
-// destinations (where b has a workspace of its own), element data and
-// source, the tile's entries, tile-block ends and slots (tile-coloured:
-// blocks and their lower partners) -- is
-// issued in the first phase, so that a tile waits for two dependent load
-// latencies (range -> entries, node id -> coordinates) before its
-// arithmetic, and none after it.
+//
+// What bounds it is latency and instruction issue, not HBM: a workgroup
+// lives for a few dependent loads and a few hundred instructions. The global
+// loads of a tile are therefore arranged as two levels that all waves go
+// through at once: every thread first issues the loads that depend on nothing
+// (its pair's place, a tile-block's range and slot), then waves 0 and 1 take
+// the nodes (id -> coordinates), wave 2 the element data (id -> material and
+// source) and wave 3 the reference tables, at clamped indices rather than
+// under per-lane conditions, so that no wave waits for one group before it
+// issues the next. Under per-lane conditions the compiler waited after each
+// group, and wave 0 went through eight dependent loads instead of two: a third
+// to a half of the kernel's time (with tile sums, blocks and geometry left
+// out, 0.34 of 1.06 ms for 885k hex8 and 0.24 of 0.62 ms for 1.3M pyr5).
+//
+// A pair's block is staged in LDS at its place in the order of the tile's
+// (block, lane) entries, already transposed where node a > node b, so that the
+// contributions to a tile-block are consecutive: its sum needs one read of
+// the tile-block's record and then the values (before: its range, its
+// entries, then the values, each read waiting for the one before).
+// Measured on MI355X, element phase of pure meshes, before -> after, ms, FP64
+// / mixed: tet4 (1.3M elements) 0.29 -> 0.22 / 0.25 -> 0.20, pyr5 (1.3M) 0.62
+// -> 0.48 / 0.43 -> 0.37, pen6 (1.0M) 0.64 -> 0.54 / 0.48 -> 0.41, hex8 (885k)
+// 1.06 -> 0.86 / 0.83 -> 0.70; 96^3-cell hybrid mesh 1.39 -> 1.12 / 1.09 ->
+// 0.92.
 template <int T, int MODEL, int VAR, typename CT>
 __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
 {
     using Smem = ElemSmem<T, MODEL, VAR, CT>;
-    constexpr int NN = Fam<T>::NN;
+    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ;
     constexpr int PW = Smem::PW, EPB = Smem::EPB, B = Smem::B, BB = Smem::BB;
     constexpr bool ELAS = Smem::ELAS, NHK = Smem::NHK, TCOL = Smem::TCOL, ALIAS = Smem::ALIAS;
     // 3x3 blocks of the upper-triangle form: the right-hand side of node a
@@ -935,46 +952,76 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
     // kernel writes it out (no right-hand-side workspace, no reduction of
     // its own)
     constexpr bool RHSD = !TCOL && B == 3;
+    static_assert(EPB * NN <= 128 && EPB <= 64 && NQ * NN <= 64, "one wave group per kind of load");
     CT *sK = S.buf + Smem::KOFF;
-    __syncthreads();  // the previous tile's readers of S are done
-    elem_ref_tables(S, tid);
     const int64_t tl = first / EPB;
-    const int64_t e0 = A.tent_ptr[tl], d0 = A.ttb_ptr[tl];
-    const int ne = (int)(A.tent_ptr[tl + 1] - e0), nd = (int)(A.ttb_ptr[tl + 1] - d0);
+    const int64_t left = A.n - first;
+    const int cnt = __builtin_amdgcn_readfirstlane((int)(left < EPB ? left : EPB));  // elements of this tile
+    const int64_t d0 = A.ttb_ptr[tl];
+    const int nd = (int)(A.ttb_ptr[tl + 1] - d0);
+    // loads that depend on nothing
+    const int pel = tid / PW;
+    const bool pact = pel < cnt;  // this thread has a pair
+    const int nel = tid / NN, na = tid - nel * NN;
+    const bool nact = nel < cnt;  // and an (element, node)
+    const uint16_t *tp = A.tpos + first * PW;
+    const unsigned pos = tp[pact ? tid : 0];
+    unsigned rpos = 0;
     int32_t rdest = 0;  // right-hand-side destination of (element, node) tid
-    if (tid < EPB * NN) {
-        const int el = tid / NN, a = tid % NN;
-        const int64_t i = first + el;
-        if (i < A.n) {
-            const int32_t v = A.pnodes[i * NN + a];
-            if constexpr (!RHSD) rdest = A.prdest[i * NN + a];
-            S.sX[el][a][0] = A.x[v];
-            S.sX[el][a][1] = A.y[v];
-            S.sX[el][a][2] = A.z[v];
+    if constexpr (RHSD)
+        rpos = tp[nact ? nel * PW + na * NN - na * (na - 1) / 2 : 0];  // pair (a, a)
+    else
+        rdest = A.prdest[first * NN + (nact ? tid : 0)];
+    const int td = tid < nd ? tid : nd - 1;
+    const uint32_t rng = A.tb_rng[d0 + td];
+    const int32_t slot = TCOL ? A.tb_blk[d0 + td] : A.tb_slot[d0 + td];
+    __syncthreads();  // the previous tile's readers of S are done
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave < 2) {
+        const int32_t v = A.pnodes[first * NN + (nact ? tid : 0)];
+        const double x = A.x[v], y = A.y[v], z = A.z[v];
+        double u[3] = {0.0, 0.0, 0.0};
+        if constexpr (NHK) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) u[c] = A.u[3 * (int64_t)v + c];
+        }
+        if (nact) {
+            S.sX[nel][na][0] = x;
+            S.sX[nel][na][1] = y;
+            S.sX[nel][na][2] = z;
             if constexpr (NHK) {
-                for (int c = 0; c < 3; ++c) S.sU[el][a][c] = A.u[3 * (int64_t)v + c];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) S.sU[nel][na][c] = u[c];
             }
         }
-    } else if (tid < EPB * NN + EPB) {
-        const int el = tid - EPB * NN;
-        const int64_t i = first + el;
-        const int32_t e = i < A.n ? A.elems[i] : -1;
-        S.sE[el] = e;
-        S.sNH[el] = (ELAS && e >= 0 && A.nh_flag) ? (int)A.nh_flag[e] : 0;
-        if constexpr (ELAS) elem_lame(A, e, S.sLM[el]);
+    } else if (wave == 2) {
+        const int el = tid - 128;
+        const int32_t e = A.elems[first + (el < cnt ? el : 0)];
+        const int nh = (ELAS && A.nh_flag) ? (int)A.nh_flag[e] : 0;
+        double src[B], lm[2] = {0.0, 0.0};
 #pragma unroll
-        for (int c = 0; c < B; ++c) S.sSrc[el][c] = e >= 0 ? A.source[(int64_t)e * B + c] : 0.0;
-    }
-    for (int i = tid; i < ne; i += 256) S.sEnt[i] = A.tent[e0 + i];
-    for (int i = tid; i < nd; i += 256) {
-        S.sEend[i] = A.tb_eend[d0 + i];
-        if constexpr (TCOL) {
-            const int32_t k = A.tb_blk[d0 + i];
-            S.sSlot[i] = k;
-            S.sLp[i] = A.lpart[k];
-        } else {
-            S.sSlot[i] = A.tb_slot[d0 + i];
+        for (int c = 0; c < B; ++c) src[c] = A.source[(int64_t)e * B + c];
+        if constexpr (ELAS) elem_lame(A, e, lm);
+        if (el < EPB) {
+            S.sE[el] = el < cnt ? e : -1;
+            S.sNH[el] = nh;
+            if constexpr (ELAS) {
+                S.sLM[el][0] = lm[0];
+                S.sLM[el][1] = lm[1];
+            }
+#pragma unroll
+            for (int c = 0; c < B; ++c) S.sSrc[el][c] = src[c];
         }
+    } else {
+        const int i = tid - 192 < NQ * NN ? tid - 192 : 0;
+        const int q = i / NN, a = i % NN;
+        S.sNr[q][a] = c_ref.N[T][q][a];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) S.sDN[q][a][c] = c_ref.dN[T][q][a][c];
+    }
+    if (tid < nd) S.sTb[tid] = {slot, rng};
+    if constexpr (TCOL) {
+        if (tid < nd) S.sLp[tid] = A.lpart[slot];
     }
     __syncthreads();
 
@@ -986,97 +1033,85 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
     CT Ks[BB];
 #pragma unroll
     for (int c = 0; c < BB; ++c) Ks[c] = 0;
-    bool diag = false;
-    // the block's staged entries; on a diagonal lane with RHSD the
-    // strictly lower ones belong to the right-hand side
+    const SymPair pr = sym_pair(pos);
+    const bool diag = pr.a == pr.b;
+    // the block at its place; a diagonal block with RHSD leaves the strictly
+    // lower entries to the right-hand side
     auto stage = [&] {
-#pragma unroll
-        for (int c = 0; c < BB; ++c)
-            if (!(RHSD && diag && (c == 3 || c == 6 || c == 7))) sK[tid * BB + c] = Ks[c];
-    };
-    if (tid < EPB * PW) {
-        const int el = tid / PW, w = tid % PW;
-        // w-th pair of the row-major upper triangle
-        int a = 0, r = w;
-#pragma unroll
-        for (int k = 0; k < NN - 1; ++k) {
-            const bool step = r >= NN - a;
-            r -= step ? NN - a : 0;
-            a += step ? 1 : 0;
-        }
-        const int b = a + r;
-        diag = a == b;
-        if (S.sE[el] >= 0) {
-            elem_block(S, el, a, b, Ks);
-            if (!RHSD && diag) {
-                // a diagonal block is symmetric; copying its upper entries
-                // makes it so bitwise (the products G_i (w G_j) and
-                // G_j (w G_i) round differently), and with it A (with
-                // RHSD the block-value kernel writes the copies)
-#pragma unroll
-                for (int i = 0; i < B; ++i)
-#pragma unroll
-                    for (int j = i + 1; j < B; ++j) Ks[j * B + i] = Ks[i * B + j];
+        CT *k = sK + pr.place * BB;
+        if constexpr (B == 3) {
+            const bool tr = pr.transposed;
+            k[0] = Ks[0];
+            k[4] = Ks[4];
+            k[8] = Ks[8];
+            k[1] = tr ? Ks[3] : Ks[1];
+            k[2] = tr ? Ks[6] : Ks[2];
+            k[5] = tr ? Ks[7] : Ks[5];
+            if (!(RHSD && diag)) {
+                k[3] = tr ? Ks[1] : Ks[3];
+                k[6] = tr ? Ks[2] : Ks[6];
+                k[7] = tr ? Ks[5] : Ks[7];
             }
+        } else {
+            k[0] = Ks[0];
+        }
+    };
+    if (pact) {
+        elem_block(S, pel, pr.a, pr.b, Ks);
+        if (!RHSD && diag) {
+            // a diagonal block is symmetric; copying its upper entries
+            // makes it so bitwise (the products G_i (w G_j) and
+            // G_j (w G_i) round differently), and with it A (with
+            // RHSD the block-value kernel writes the copies)
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+#pragma unroll
+                for (int j = i + 1; j < B; ++j) Ks[j * B + i] = Ks[i * B + j];
         }
         if constexpr (!ALIAS) stage();
     }
     CT f[B];
-    int flane = -1;  // RHSD: the diagonal lane that carries f
-    if (tid < EPB * NN) {
-        const int el = tid / NN, a = tid % NN;
-        if (S.sE[el] >= 0) {
-            elem_rhs(S, el, a, S.sSrc[el], f);
-            if constexpr (RHSD) {
-                flane = el * PW + a * NN - a * (a - 1) / 2;  // pair (a, a)
-            } else {
-                CT *dst = (CT *)A.rcontrib + (int64_t)rdest * B;
+    if (nact) {
+        elem_rhs(S, nel, na, S.sSrc[nel], f);
+        if constexpr (!RHSD) {
+            CT *dst = (CT *)A.rcontrib + (int64_t)rdest * B;
 #pragma unroll
-                for (int i = 0; i < B; ++i) dst[i] = f[i];
-            }
+            for (int i = 0; i < B; ++i) dst[i] = f[i];
         }
     }
     if constexpr (ALIAS) {
         __syncthreads();  // every lane has read the gradients that sK overwrites
-        if (tid < EPB * PW) stage();
+        if (pact) stage();
     }
     if constexpr (RHSD) {
-        if (flane >= 0) {
-            sK[flane * BB + 3] = f[0];
-            sK[flane * BB + 6] = f[1];
-            sK[flane * BB + 7] = f[2];
+        if (nact) {
+            CT *k = sK + sym_pair(rpos).place * BB;
+            k[3] = f[0];
+            k[6] = f[1];
+            k[7] = f[2];
         }
     }
     __syncthreads();
 
     // tile sums, the block's entries added in ascending lane (element)
     // order, in FP64: either one thread per tile-block adding all BB
-    // components, or one thread per (tile-block, component), which walks
-    // the block's entry list BB times but spreads a tile's sums over more
-    // threads. Measured on MI355X (element phase, ms, FP64, hybrid256 /
-    // hybrid96): per component everywhere 24.56 / 1.62, per block for pen6
-    // and hex8 24.70 / 1.67, per block everywhere 26.2 / 1.71; FP32 staged
-    // blocks: per block in every family (per component for tet4 and pyr5
-    // was slightly slower). Both give bitwise the same sums.
+    // components (FP32), or one thread per (tile-block, component) (FP64).
+    // Both give bitwise the same sums.
     CT *out = (CT *)A.contrib;
     constexpr bool PER_BLOCK = sizeof(CT) == 4;
     if constexpr (PER_BLOCK) {
         for (int d = tid; d < nd; d += 256) {
+            const auto t = S.sTb[d];
+            const CT *k = sK + (t.rng & 255) * BB;
             double acc[BB];
 #pragma unroll
-            for (int c = 0; c < BB; ++c) acc[c] = 0.0;
-            const int q1 = S.sEend[d];
-            for (int q = d ? S.sEend[d - 1] : 0; q < q1; ++q) {
-                const int u = S.sEnt[q];
-                const CT *k = sK + (u >> 1) * BB;
-                CT v[BB];
+            for (int c = 0; c < BB; ++c) acc[c] = (double)k[c];
+            for (int q = t.rng >> 8; q > 0; --q) {
+                k += BB;
 #pragma unroll
-                for (int c = 0; c < BB; ++c) v[c] = k[c];
-                const bool tr = (u & 1) != 0;
-#pragma unroll
-                for (int c = 0; c < BB; ++c) acc[c] += (double)(tr ? v[(c % B) * B + c / B] : v[c]);
+                for (int c = 0; c < BB; ++c) acc[c] += (double)k[c];
             }
-            const int64_t blk = S.sSlot[d];
+            const int64_t blk = t.slot;
             if constexpr (TCOL) {
                 // blk is the block; no other tile of this colour touches it
                 // or its partner
@@ -1094,17 +1129,16 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
         }
     } else {
         for (int idx = tid; idx < nd * BB; idx += 256) {
-            const int d = idx / BB, c = idx - d * BB, ct = (c % B) * B + c / B;
-            double acc = 0.0;
-            for (int q = d ? S.sEend[d - 1] : 0; q < S.sEend[d]; ++q) {
-                const int u = S.sEnt[q];
-                acc += (double)sK[(u >> 1) * BB + ((u & 1) ? ct : c)];
-            }
-            const int64_t blk = S.sSlot[d];
+            const int d = idx / BB, c = idx - d * BB;
+            const auto t = S.sTb[d];
+            const CT *k = sK + (t.rng & 255) * BB + c;
+            double acc = (double)*k;
+            for (int q = t.rng >> 8; q > 0; --q) acc += (double)*(k += BB);
+            const int64_t blk = t.slot;
             if constexpr (TCOL) {
                 const int64_t l = S.sLp[d];
                 A.vals[blk * BB + c] += acc;
-                if (l >= 0) A.vals[l * BB + ct] += acc;
+                if (l >= 0) A.vals[l * BB + (c % B) * B + c / B] += acc;
             } else {
                 out[blk * BB + c] = (CT)acc;
             }

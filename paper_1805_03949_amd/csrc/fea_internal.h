@@ -17,6 +17,22 @@ __host__ __device__ constexpr inline int nodes_of(int t) { return 4 + t + (t == 
 // a <= b, 256 lanes per workgroup.
 __host__ __device__ constexpr inline int sym_epb(int t) { return 256 / (nodes_of(t) * (nodes_of(t) + 1) / 2); }
 
+// A pair of the upper-triangle form in 16 bits: the place of its block among
+// the tile's entries (ordered by destination block, then lane), whether the
+// destination holds it transposed, and its local nodes a <= b.
+struct SymPair {
+    int place, a, b;
+    bool transposed;
+};
+__host__ __device__ inline SymPair sym_pair(unsigned w)
+{
+    return {(int)(w & 255u), (int)(w >> 9 & 7u), (int)(w >> 12 & 7u), (w >> 8 & 1u) != 0};
+}
+__host__ __device__ inline uint16_t sym_pair_word(int place, bool transposed, int a, int b)
+{
+    return (uint16_t)(place | (transposed ? 256 : 0) | a << 9 | b << 12);
+}
+
 // Records a message for fea_last_error() and returns `code`.
 int set_error(int code, const char *fmt, ...);
 void clear_error();
@@ -151,18 +167,19 @@ struct fea_graph {
     // Element tiles: family t's elements in type-sorted order, EPB_t =
     // 256 / (n(n+1)/2) consecutive ones per tile, tiles tile_base[t] ..
     // tile_base[t+1]. Lane l = el * n(n+1)/2 + w of a tile is the w-th local
-    // pair a <= b of its el-th element. Tile τ's entries tent[tent_ptr[τ] ..
-    // tent_ptr[τ+1]) (lane << 1 | transposed) are sorted by destination
-    // upper block, then lane; its distinct blocks are tile-blocks ttb_ptr[τ]
-    // .. ttb_ptr[τ+1], tile-block d holding entries up to tb_eend[d]
-    // (exclusive, within the tile), block id tb_blk[d] and workspace slot
-    // tb_slot[d]. The workspace lies sorted by block, then tile: block k's
-    // tile sums are ts_ptr[k] .. ts_ptr[k+1]; ulen = tile-blocks.
+    // pair a <= b of its el-th element; a tile's entries are its pairs sorted
+    // by destination upper block, then lane. Pair w of the i-th element of
+    // family t is tpos[pair_base[t] + i * n(n+1)/2 + w] (sym_pair). The
+    // tile's distinct blocks are tile-blocks ttb_ptr[τ] .. ttb_ptr[τ+1],
+    // tile-block d holding the entries from tb_rng[d] & 255 on, (tb_rng[d]
+    // >> 8) + 1 of them, block id tb_blk[d] and workspace slot tb_slot[d].
+    // The workspace lies sorted by block, then tile: block k's tile sums are
+    // ts_ptr[k] .. ts_ptr[k+1]; ulen = tile-blocks.
     int64_t tile_base[5] = {0, 0, 0, 0, 0};
-    int64_t *tent_ptr = nullptr;
+    int64_t pair_base[5] = {0, 0, 0, 0, 0};
     int64_t *ttb_ptr = nullptr;
-    uint16_t *tent = nullptr;
-    uint16_t *tb_eend = nullptr;
+    uint16_t *tpos = nullptr;
+    uint16_t *tb_rng = nullptr;
     int32_t *tb_blk = nullptr;
     int32_t *tb_slot = nullptr;
     int64_t *ts_ptr = nullptr;

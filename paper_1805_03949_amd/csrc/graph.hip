@@ -359,106 +359,85 @@ __global__ void k_flag_upper(int64_t nnz, const int32_t *upart, int32_t *flag)
 }
 
 struct TileBases {
-    int64_t seg[5], node[5], tile[5];
+    int64_t seg[5], node[5], tile[5], pair[5];
 };
 
-// One workgroup per tile: the tile's contributions (lane, transposed?) keyed
-// by destination upper block, sorted (bitonic, in LDS) by block then lane.
-// Pass 1 (!WRITE) stores the entry and distinct-block counts; pass 2 writes
-// the entries and the tile-blocks at the scanned offsets.
+// One workgroup per tile: the tile's contributions (one per lane) keyed by
+// destination upper block, sorted (bitonic, in LDS) by block then lane.
+// Pass 1 (!WRITE) stores the distinct-block count; pass 2 writes every pair's
+// place and the tile-blocks at the scanned offsets. (The graph build rejects
+// an element that repeats a node, so a lane has exactly one destination.)
 template <bool WRITE>
 __global__ void __launch_bounds__(256) k_tile_entries(TileBases tb, const int32_t *perm, const int32_t *pnodes,
                                                       const int64_t *map_ptr, const int32_t *e2nnz,
-                                                      int32_t *cnt_ent, int32_t *cnt_blk, const int64_t *tent_ptr,
-                                                      const int64_t *ttb_ptr, uint16_t *tent, int32_t *tb_blk,
-                                                      uint16_t *tb_eend)
+                                                      int32_t *cnt_blk, const int64_t *ttb_ptr, uint16_t *tpos,
+                                                      int32_t *tb_blk, uint16_t *tb_rng)
 {
-    constexpr int K = 512;
+    constexpr int K = 256;
     constexpr uint64_t NONE = ~0ull;
     __shared__ uint64_t key[K];
-    __shared__ int part[256];
+    __shared__ int part[4];
+    __shared__ uint16_t beg[K + 1];  // first entry of every tile-block
+    __shared__ uint16_t word[K];     // lane -> transposed, a, b
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
     int t = 0;
     while (t < 3 && tile >= tb.tile[t + 1]) ++t;
     const int n = nodes_of(t), pw = n * (n + 1) / 2, epb = 256 / pw;
-    const int64_t first = tb.seg[t] + (tile - tb.tile[t]) * epb;
-    uint64_t k0 = NONE, k1 = NONE;
-    if (tid < epb * pw) {
-        const int el = tid / pw;
+    const int64_t i0 = (tile - tb.tile[t]) * epb;  // first element, within the family
+    const int el = tid / pw;
+    const int64_t p = tb.seg[t] + i0 + el;
+    uint64_t mine = NONE;
+    if (el < epb && p < tb.seg[t + 1]) {
         int w = tid - el * pw, a = 0;
         while (w >= n - a) {
             w -= n - a;
             ++a;
         }
         const int b = a + w;
-        const int64_t p = first + el;
-        if (p < tb.seg[t + 1]) {
-            const int32_t *pn = pnodes + tb.node[t] + (p - tb.seg[t]) * n;
-            const int32_t na = pn[a], nb = pn[b];
-            const int64_t m0 = map_ptr[perm[p]];
-            const uint64_t kab = (uint64_t)e2nnz[m0 + a * n + b];
-            const uint64_t lane = (uint64_t)tid << 1;
-            if (a == b || na < nb) {
-                k0 = kab << 10 | lane;
-            } else if (na > nb) {
-                k0 = (uint64_t)e2nnz[m0 + b * n + a] << 10 | lane | 1;
-            } else {  // coincident nodes: both blocks land on the diagonal
-                k0 = kab << 10 | lane;
-                k1 = kab << 10 | lane | 1;
-            }
-        }
+        const int32_t *pn = pnodes + tb.node[t] + (i0 + el) * n;
+        const bool tr = pn[a] > pn[b];
+        mine = (uint64_t)e2nnz[map_ptr[perm[p]] + (tr ? b * n + a : a * n + b)] << 8 | (uint64_t)tid;
+        word[tid] = sym_pair_word(0, tr, a, b);
     }
-    key[tid] = k0;
-    key[tid + 256] = k1;
+    key[tid] = mine;
     __syncthreads();
     for (int size = 2; size <= K; size <<= 1)
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < K; i += 256) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const uint64_t x = key[i], y = key[j];
-                    if ((x > y) == ((i & size) == 0)) {
-                        key[i] = y;
-                        key[j] = x;
-                    }
-                }
-            }
+            const uint64_t x = key[tid], y = key[tid ^ stride];
+            __syncthreads();
+            const bool low = (tid & stride) == 0, up = (tid & size) == 0;
+            key[tid] = (low == up) == (x < y) ? x : y;
             __syncthreads();
         }
-    // new-block flags of entries 2 tid and 2 tid + 1, and their scan
-    int f[2];
-    for (int q = 0; q < 2; ++q) {
-        const int i = 2 * tid + q;
-        f[q] = key[i] != NONE && (i == 0 || (key[i] >> 10) != (key[i - 1] >> 10));
+    // new-block flags and their scan
+    const uint64_t k = key[tid];
+    const bool f = k != NONE && (tid == 0 || (k >> 8) != (key[tid - 1] >> 8));
+    const uint64_t m = __ballot(f);
+    const int lane = tid & 63, wave = tid >> 6;
+    if (lane == 0) part[wave] = __popcll(m);
+    const int nent = __syncthreads_count(k != NONE);
+    int before = 0, nblk = 0;
+    for (int q = 0; q < 4; ++q) {
+        if (q < wave) before += part[q];
+        nblk += part[q];
     }
-    part[tid] = f[0] + f[1];
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int v = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    const int nblk = part[255];
-    const int nent = __syncthreads_count(key[2 * tid] != NONE) + __syncthreads_count(key[2 * tid + 1] != NONE);
     if constexpr (!WRITE) {
-        if (tid == 0) {
-            cnt_ent[tile] = nent;
-            cnt_blk[tile] = nblk;
-        }
+        if (tid == 0) cnt_blk[tile] = nblk;
     } else {
-        const int64_t e0 = tent_ptr[tile], d0 = ttb_ptr[tile];
-        int d = part[tid] - f[0] - f[1] - 1;  // tile-block of the entry before 2 tid
-        for (int q = 0; q < 2; ++q) {
-            const int i = 2 * tid + q;
-            if (key[i] == NONE) break;
-            d += f[q];
-            tent[e0 + i] = (uint16_t)(key[i] & 1023);
-            if (i + 1 == nent || (key[i + 1] >> 10) != (key[i] >> 10)) {
-                tb_blk[d0 + d] = (int32_t)(key[i] >> 10);
-                tb_eend[d0 + d] = (uint16_t)(i + 1);
-            }
+        const int d = before + __popcll(m & ((2ull << lane) - 1)) - 1;  // tile-block of entry tid
+        if (f) beg[d] = (uint16_t)tid;
+        if (tid == 0) beg[nblk] = (uint16_t)nent;
+        __syncthreads();
+        const int64_t d0 = ttb_ptr[tile];
+        if (k != NONE) {
+            const int l = (int)(k & 255);
+            tpos[tb.pair[t] + i0 * pw + l] = (uint16_t)(word[l] | tid);
+        }
+        if (tid < nblk) {
+            const int e = beg[tid];
+            tb_blk[d0 + tid] = (int32_t)(key[e] >> 8);
+            tb_rng[d0 + tid] = (uint16_t)(e | (beg[tid + 1] - e - 1) << 8);
         }
     }
 }
@@ -526,8 +505,8 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     constexpr int BS = 256;
     const int64_t N = g->n_nodes, nnz = g->nnz;
     int rc;
-    void **bufs[] = {(void **)&g->upart, (void **)&g->ublk,    (void **)&g->lpart,  (void **)&g->tent_ptr,
-                     (void **)&g->ttb_ptr, (void **)&g->tent,  (void **)&g->tb_eend, (void **)&g->tb_blk,
+    void **bufs[] = {(void **)&g->upart, (void **)&g->ublk,    (void **)&g->lpart,
+                     (void **)&g->ttb_ptr, (void **)&g->tpos,  (void **)&g->tb_rng, (void **)&g->tb_blk,
                      (void **)&g->tb_slot, (void **)&g->ts_ptr, (void **)&g->ulp, (void **)&g->uptr};
     for (void **b : bufs) {
         dfree(*b);
@@ -548,18 +527,24 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     if ((rc = dalloc(&uoff.p, sizeof(int64_t) * (nnz + 1)))) return rc;
     // the scan scratch serves the tile and block scans below as well
     TileBases tb;
-    int64_t nt = 0;
+    int64_t nt = 0, nent = 0;  // tiles; entries, one per (element, pair a <= b)
     for (int t = 0; t < 4; ++t) {
         tb.seg[t] = g->seg[t];
         tb.node[t] = g->node_base[t];
         tb.tile[t] = nt;
+        tb.pair[t] = nent;
         const int epb = sym_epb(t);
         nt += (g->seg[t + 1] - g->seg[t] + epb - 1) / epb;
+        nent += (g->seg[t + 1] - g->seg[t]) * (nodes_of(t) * (nodes_of(t) + 1) / 2);
     }
     tb.seg[4] = g->seg[4];
     tb.node[4] = g->node_base[4];
     tb.tile[4] = nt;
-    for (int t = 0; t < 5; ++t) g->tile_base[t] = tb.tile[t];
+    tb.pair[4] = nent;
+    for (int t = 0; t < 5; ++t) {
+        g->tile_base[t] = tb.tile[t];
+        g->pair_base[t] = tb.pair[t];
+    }
     const int64_t nscan = std::max<int64_t>(std::max<int64_t>(nnz, nt), 1);
     if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(nscan) + 64)))) return rc;
     if (N) k_sym_partner<<<grid_for(N, BS), BS, 0, s>>>(N, g->row_ptr, g->col, g->upart);
@@ -571,44 +556,29 @@ int sym_prepare(fea_graph *g, hipStream_t s)
         FEA_HIP(hipMemcpyAsync(&g->nup, (int64_t *)uoff.p + nnz, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     }
     FEA_HIP(hipGetLastError());
-    // tiles: entry and tile-block counts, offsets, then the entries
-    TmpBuf cent, cblk;
-    if ((rc = dalloc(&cent.p, sizeof(int32_t) * std::max<int64_t>(nt, 1)))) return rc;
+    // tiles: tile-block counts, offsets, then the pairs' places
+    TmpBuf cblk;
     if ((rc = dalloc(&cblk.p, sizeof(int32_t) * std::max<int64_t>(nt, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->tent_ptr, sizeof(int64_t) * (nt + 1)))) return rc;
     if ((rc = dalloc((void **)&g->ttb_ptr, sizeof(int64_t) * (nt + 1)))) return rc;
-    int64_t nent = 0, ntb = 0;
+    int64_t ntb = 0;
     if (nt) {
         k_tile_entries<false><<<(unsigned)nt, 256, 0, s>>>(tb, g->perm, g->pnodes, g->map_ptr, g->e2nnz,
-                                                          (int32_t *)cent.p, (int32_t *)cblk.p, nullptr, nullptr,
-                                                          nullptr, nullptr, nullptr);
-        if ((rc = scan_to_ptr_i32((int32_t *)cent.p, nt, g->tent_ptr, (int64_t *)tmp.p, s))) return rc;
+                                                          (int32_t *)cblk.p, nullptr, nullptr, nullptr, nullptr);
         if ((rc = scan_to_ptr_i32((int32_t *)cblk.p, nt, g->ttb_ptr, (int64_t *)tmp.p, s))) return rc;
-        FEA_HIP(hipMemcpyAsync(&nent, g->tent_ptr + nt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         FEA_HIP(hipMemcpyAsync(&ntb, g->ttb_ptr + nt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     } else {
-        FEA_HIP(hipMemsetAsync(g->tent_ptr, 0, sizeof(int64_t), s));
         FEA_HIP(hipMemsetAsync(g->ttb_ptr, 0, sizeof(int64_t), s));
     }
     FEA_HIP(hipStreamSynchronize(s));
     if (ntb > INT32_MAX) return set_error(FEA_ERANGE, "%lld tile-blocks exceed the int32 slot range", (long long)ntb);
-    // one entry per (element, pair a <= b): the element kernels size their
-    // tile buffers by it (an element repeating a node would add entries, and
-    // the graph build rejects such elements)
-    int64_t lanes = 0;
-    for (int t = 0; t < 4; ++t) lanes += (g->seg[t + 1] - g->seg[t]) * (nodes_of(t) * (nodes_of(t) + 1) / 2);
-    if (nent != lanes)
-        return set_error(FEA_EMESH, "upper-triangle layout: %lld entries for %lld element pairs", (long long)nent,
-                         (long long)lanes);
-    if ((rc = dalloc((void **)&g->tent, sizeof(uint16_t) * std::max<int64_t>(nent, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->tb_eend, sizeof(uint16_t) * std::max<int64_t>(ntb, 1)))) return rc;
+    if ((rc = dalloc((void **)&g->tpos, sizeof(uint16_t) * std::max<int64_t>(nent, 1)))) return rc;
+    if ((rc = dalloc((void **)&g->tb_rng, sizeof(uint16_t) * std::max<int64_t>(ntb, 1)))) return rc;
     if ((rc = dalloc((void **)&g->tb_blk, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
     if ((rc = dalloc((void **)&g->tb_slot, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
     if ((rc = dalloc((void **)&g->ts_ptr, sizeof(int64_t) * (nnz + 1)))) return rc;
     if (nt)
         k_tile_entries<true><<<(unsigned)nt, 256, 0, s>>>(tb, g->perm, g->pnodes, g->map_ptr, g->e2nnz, nullptr,
-                                                         nullptr, g->tent_ptr, g->ttb_ptr, g->tent, g->tb_blk,
-                                                         g->tb_eend);
+                                                         g->ttb_ptr, g->tpos, g->tb_blk, g->tb_rng);
     // workspace segments: per block its tile-blocks, ascending tile
     TmpBuf lst;
     if ((rc = dalloc(&lst.p, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
@@ -774,8 +744,8 @@ static void destroy(fea_graph *g)
     if (!g) return;
     void *bufs[] = {g->row_ptr, g->col, g->map_ptr, g->e2nnz, g->inv_ptr, g->inv, g->pnodes, g->pdest, g->prdest,
                     g->n2e_ptr, g->n2e, g->n2a, g->perm, g->colour, g->cperm,
-                    g->contrib, g->rcontrib, g->acc64, g->gtile, g->gnodes, g->gdesc, g->upart, g->ublk, g->lpart, g->tent_ptr, g->ttb_ptr,
-                    g->tent, g->tb_eend, g->tb_blk, g->tb_slot, g->ts_ptr, g->ctile, g->gp_ptr, g->ulp, g->uptr};
+                    g->contrib, g->rcontrib, g->acc64, g->gtile, g->gnodes, g->gdesc, g->upart, g->ublk, g->lpart, g->ttb_ptr,
+                    g->tpos, g->tb_rng, g->tb_blk, g->tb_slot, g->ts_ptr, g->ctile, g->gp_ptr, g->ulp, g->uptr};
     for (void *b : bufs) dfree(b);
     for (hipEvent_t e : g->ev)
         if (e) (void)hipEventDestroy(e);
