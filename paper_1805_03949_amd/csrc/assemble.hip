@@ -310,9 +310,9 @@ static int assemble_impl(fea_graph *g, const double *x, const double *y, const d
                          int32_t *st, const Workspace &ws)
 {
     int rc;
-    k_status_init<<<1, 1, 0, stream>>>(st);
-
     ElemArgs a = {};
+    if ((rc = ensure_tables(&a.ref))) return rc;
+    k_status_init<<<1, 1, 0, stream>>>(st);
     a.x = x; a.y = y; a.z = z;
     a.conn_ptr = conn_ptr;
     a.conn = conn;
@@ -398,7 +398,6 @@ extern "C" int fea_assemble(const fea_graph *gc, const double *x, const double *
     const fea_options *o = opt ? opt : &dflt;
     int rc = check_assemble(g, x, y, z, types, conn_ptr, conn, mat, source, o, vals, rhs);
     if (rc) return rc;
-    if ((rc = ensure_tables())) return rc;
     if (o->timing) {
         for (hipEvent_t &e : g->ev)
             if (!e) FEA_HIP(hipEventCreate(&e));

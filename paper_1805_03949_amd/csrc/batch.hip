@@ -755,10 +755,13 @@ int build(int n, const fea_mesh_desc *md, int model, const int32_t *tile, hipStr
 
     // per-mesh kernel views and the concatenated segment bounds
     std::vector<BatchMesh> bm(n);
+    const double *ref = nullptr;
+    if ((rc = ensure_tables(&ref))) return rc;
     for (int m = 0; m < n; ++m) {
         const fea_mesh_desc &d = md[m];
         const fea_graph *g = b->graphs[m];
         ElemArgs a = {};
+        a.ref = ref;
         a.x = d.x; a.y = d.y; a.z = d.z;
         a.conn_ptr = d.conn_ptr;
         a.conn = d.conn;

@@ -27,12 +27,19 @@
 
 #include "fea_internal.h"
 
+// Multiply-adds are fused within an expression, as the source writes them, and
+// not across statements: the same element code then rounds alike in every
+// kernel it is inlined into, and the forms that promise equal bits (batched
+// and one-mesh) keep them whatever the compiler does around it.
+#pragma clang fp contract(on)
+
 namespace fea {
 
 struct RefTables {
     double N[4][8][8];      // [family][gauss point][node]
     double dN[4][8][8][3];  // [family][gauss point][node][reference direction]
     double w[4][8];
+    double flat[4][256];    // family's dN and N as [gauss point][node][4], back to back
 };
 
 // one copy per translation unit, uploaded by that unit's ensure_tables()
@@ -42,6 +49,8 @@ template <int T>
 struct Fam {
     static constexpr int NN = 4 + T + (T == 3);
     static constexpr int NQ = T == 0 ? 1 : (T == 2 ? 6 : 8);
+    // weight of every Gauss point (as in the reference tables)
+    static constexpr double W = (T == 0 || T == 2) ? 1.0 / 6.0 : 1.0;
 };
 
 // Reference shape functions and Gauss rules (host side, uploaded once per
@@ -139,27 +148,37 @@ static void build_tables(RefTables *R)
                 R->N[t][q][a] = N[a];
                 for (int j = 0; j < 3; ++j) R->dN[t][q][a][j] = dN[a][j];
             }
+            const int nn = nodes_of(t);
+            for (int a = 0; a < nn; ++a)
+                for (int j = 0; j < 4; ++j) R->flat[t][(q * nn + a) * 4 + j] = j < 3 ? dN[a][j] : N[a];
         }
     }
 }
 
-static int ensure_tables()
+// Reference tables on the current device; flat (may be NULL) receives the
+// device address of RefTables::flat.
+static int ensure_tables(const double **flat = nullptr)
 {
     static std::mutex mtx;
-    static bool done[64] = {false};
+    static const double *done[64] = {nullptr};
     int dev = 0;
     FEA_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64) return set_error(FEA_EINVAL, "device index %d unsupported", dev);
     std::lock_guard<std::mutex> lock(mtx);
-    if (done[dev]) return FEA_OK;
-    RefTables R;
-    build_tables(&R);
-    FEA_HIP(hipMemcpyToSymbol(HIP_SYMBOL(c_ref), &R, sizeof(R), 0, hipMemcpyHostToDevice));
-    done[dev] = true;
+    if (!done[dev]) {
+        RefTables R;
+        build_tables(&R);
+        FEA_HIP(hipMemcpyToSymbol(HIP_SYMBOL(c_ref), &R, sizeof(R), 0, hipMemcpyHostToDevice));
+        void *p = nullptr;
+        FEA_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(c_ref)));
+        done[dev] = reinterpret_cast<const RefTables *>(p)->flat[0];
+    }
+    if (flat) *flat = done[dev];
     return FEA_OK;
 }
 
 struct ElemArgs {
+    const double *ref;  // RefTables::flat
     const double *x, *y, *z;
     const int64_t *conn_ptr;
     const int32_t *conn;
@@ -207,6 +226,7 @@ struct ElemArgs {
 // instructions, as kernel arguments do.
 #define FEA_G(T) T __attribute__((address_space(1))) *
 struct ElemArgsGlobal {
+    FEA_G(const double) ref;
     FEA_G(const double) x;
     FEA_G(const double) y;
     FEA_G(const double) z;
@@ -249,6 +269,7 @@ static_assert(offsetof(ElemArgsGlobal, n) == offsetof(ElemArgs, n), "ElemArgsGlo
 __device__ __forceinline__ ElemArgs from_global(const ElemArgsGlobal &g)
 {
     ElemArgs a;
+    a.ref = (const double *)g.ref;
     a.x = (const double *)g.x;
     a.y = (const double *)g.y;
     a.z = (const double *)g.z;
@@ -380,12 +401,9 @@ struct ElemDims {
     // most as many tile-blocks
     static constexpr int MAXENT = EPB * PW;
     static constexpr int NC = NHK ? 4 : 1;
-    // Row-owner stores staged in LDS so that BB consecutive threads write one
-    // block's BB contiguous values. Measured per family on MI355X: a gain
-    // everywhere except FP64 pyramids of the neo-Hookean kernel, where the
-    // extra LDS costs more occupancy than it saves. The upper-triangle form
-    // always stages (its tile sums read the staged blocks).
-    static constexpr bool STAGE = RO && (SYM || sizeof(CT) == 4 || T != 1 || !NHK);
+    // Row-owner and upper-triangle stores are staged in LDS (BB consecutive
+    // threads write one block's BB contiguous values; tile sums read them)
+    static constexpr bool STAGE = RO;
     // physical gradients sG[EPB][NQ][NN][3], neo-Hookean gradients pushed
     // through F^-T sH[EU][NQ][NN][3], staged blocks sK[EPB * PW * BB].
     // Per-element gradient records are padded by one value where their size
@@ -395,20 +413,23 @@ struct ElemDims {
     using GradRec = GradRecT<CT, NQ, NN, (NQ * NN * 3 * (int)sizeof(CT) / 4) % 64 == 0>;
     static constexpr int NG = EPB * (int)(sizeof(GradRec) / sizeof(CT)), NHG = EU * (int)(sizeof(GradRec) / sizeof(CT)),
                          NK = STAGE ? EPB * PW * BB : 1;
-    // Upper-triangle form: the staged blocks overwrite the gradients (one
-    // barrier more, after every lane has read them) where the gradient
-    // records are large enough for the shared space to decide occupancy,
-    // and always in FP64; FP32 tet4 blocks get a space of their own.
-    static constexpr bool ALIAS = SYM && ((NG + NHG) * (int)sizeof(CT) > 4096 || sizeof(CT) == 8);
+    // The staged blocks overwrite the gradients (one barrier more, after
+    // every lane has read them) where the gradient records are large enough
+    // for the shared space to decide occupancy, and always in FP64; FP32 tet4
+    // blocks get a space of their own.
+    static constexpr bool ALIAS = STAGE && ((NG + NHG) * (int)sizeof(CT) > 4096 || sizeof(CT) == 8);
     static constexpr int NBUF = ALIAS ? (NG + NHG > NK ? NG + NHG : NK) : NG + NHG + NK;
     static constexpr int KOFF = ALIAS ? 0 : NG + NHG;  // where sK starts in buf
     // FP64 upper-triangle form: the per-element inputs, Gauss-point
     // coefficients and reference tables are dead once the blocks are
     // staged, and share the staged blocks' space beyond the gradients where
     // they fit
-    static constexpr int SRC = SYM ? EPB : 1, NLM = ELAS ? EPB : 1;
+    static constexpr int SRC = RO ? EPB : 1, NLM = ELAS ? EPB : 1;
+    // reference table in LDS: [gauss point][node][4], padded per point so that
+    // the points a wave reads at once start in different banks
+    static constexpr int RQ = NN * 4 + 2;
     static constexpr int PRE_BYTES =
-        (EPB * NN * 3 + EU * NN * 3 + NLM * 2 + SRC * B + NQ * NN * 3 + NQ * NN) * 8 +
+        (EPB * NN * 3 + EU * NN * 3 + NLM * 2 + SRC * B + NQ * RQ) * 8 +
         EPB * NQ * NC * (int)sizeof(CT) + 2 * EPB * 4;
     static constexpr bool PRE_ALIAS =
         ALIAS && sizeof(CT) == 8 && (NG + NHG) * (int)sizeof(CT) + PRE_BYTES <= NBUF * (int)sizeof(CT);
@@ -422,9 +443,8 @@ struct ElemPreArrays {
     double sX[D::EPB][D::NN][3];
     double sU[D::EU][D::NN][3];
     double sLM[D::NLM][2];        // lam, mu of every element (elasticity)
-    double sSrc[D::SRC][D::B];    // source of every element (upper-triangle form)
-    double sDN[D::NQ][D::NN][3];  // reference gradients of this family
-    double sNr[D::NQ][D::NN];     // reference shape functions
+    double sSrc[D::SRC][D::B];    // source of every element (element-tile forms)
+    double sRef[D::NQ][D::RQ];    // reference gradients and shape functions of this family
     CT sC[D::EPB][D::NQ][D::NC];  // wd, and for neo-Hookean wd*lam, wd*c2, wd*mu
     int32_t sE[D::EPB];
     int sNH[D::EPB];
@@ -444,8 +464,7 @@ struct ElemPre<D, true> {
             double sU[D::EU][D::NN][3];
             double sLM[D::NLM][2];
             double sSrc[D::SRC][D::B];
-            double sDN[D::NQ][D::NN][3];
-            double sNr[D::NQ][D::NN];
+            double sRef[D::NQ][D::RQ];
             CT sC[D::EPB][D::NQ][D::NC];
             int32_t sE[D::EPB];
             int sNH[D::EPB];
@@ -504,26 +523,26 @@ constexpr int one_tile_min_waves()
     return (MODEL == FEA_ELASTIC && S::SYM && sizeof(CT) == 8) ? lds_waves<S>() : 1;
 }
 
-// Reference shape functions and gradients of family T into LDS.
+// Place in LDS of entry i of family T's reference table.
 template <int T, int MODEL, int VAR, typename CT>
-__device__ inline void elem_ref_tables(ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
+__device__ inline double &elem_ref(ElemSmem<T, MODEL, VAR, CT> &S, const int i)
 {
-    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ;
-    for (int i = tid; i < NQ * NN; i += 256) {
-        const int q = i / NN, a = i % NN;
-        S.sNr[q][a] = c_ref.N[T][q][a];
-        S.sDN[q][a][0] = c_ref.dN[T][q][a][0];
-        S.sDN[q][a][1] = c_ref.dN[T][q][a][1];
-        S.sDN[q][a][2] = c_ref.dN[T][q][a][2];
-    }
+    constexpr int R = Fam<T>::NN * 4;
+    return S.sRef[i / R][i % R];
 }
 
-// Lame parameters of element e into LDS (elasticity).
+// Lame parameters.
+__device__ __forceinline__ void lame(const double E, const double nu, double lm[2])
+{
+    const double s = 1.0 + nu;
+    lm[0] = E * nu / (s * (1.0 - 2.0 * nu));
+    lm[1] = E / (2.0 * s);
+}
+
+// Lame parameters of element e (elasticity; e < 0: any).
 __device__ inline void elem_lame(const ElemArgs &A, int32_t e, double lm[2])
 {
-    const double E = (e >= 0 && A.young) ? A.young[e] : 1.0, nu = e >= 0 ? A.nu[e] : 0.25;
-    lm[0] = E * nu / ((1.0 + nu) * (1.0 - 2.0 * nu));
-    lm[1] = E / (2.0 * (1.0 + nu));
+    lame((e >= 0 && A.young) ? A.young[e] : 1.0, e >= 0 ? A.nu[e] : 0.25, lm);
 }
 
 // Geometry: one thread per (element, Gauss point), in FP64. Reads sX, sU,
@@ -555,7 +574,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
 #pragma unroll
                 for (int a = 0; a < NN; ++a)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) Jr[j] += S.sX[el][a][r] * S.sDN[q][a][j];
+                    for (int j = 0; j < 3; ++j) Jr[j] += S.sX[el][a][r] * S.sRef[q][a * 4 + j];
                 const int g0 = lane - r;
                 double J[3][3];
 #pragma unroll
@@ -571,8 +590,8 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
                         sG[el].v[q][a][i] =
-                            (CT)(Ji[0][i] * S.sDN[q][a][0] + Ji[1][i] * S.sDN[q][a][1] + Ji[2][i] * S.sDN[q][a][2]);
-                if (r == 0) S.sC[el][q][0] = (CT)(c_ref.w[T][q] * d);
+                            (CT)(Ji[0][i] * S.sRef[q][a * 4 + 0] + Ji[1][i] * S.sRef[q][a * 4 + 1] + Ji[2][i] * S.sRef[q][a * 4 + 2]);
+                if (r == 0) S.sC[el][q][0] = (CT)(Fam<T>::W * d);
             }
         }
         return;
@@ -587,7 +606,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
 #pragma unroll
                 for (int i = 0; i < 3; ++i)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) J[i][j] += S.sX[el][a][i] * S.sDN[q][a][j];
+                    for (int j = 0; j < 3; ++j) J[i][j] += S.sX[el][a][i] * S.sRef[q][a * 4 + j];
             double d = det3(J);
             if (!(d > 0.0)) atomicMin(A.status, e);
             double Ji[3][3];
@@ -597,10 +616,10 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
             for (int a = 0; a < NN; ++a)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    G[a][i] = Ji[0][i] * S.sDN[q][a][0] + Ji[1][i] * S.sDN[q][a][1] + Ji[2][i] * S.sDN[q][a][2];
+                    G[a][i] = Ji[0][i] * S.sRef[q][a * 4 + 0] + Ji[1][i] * S.sRef[q][a * 4 + 1] + Ji[2][i] * S.sRef[q][a * 4 + 2];
                     sG[el].v[q][a][i] = (CT)G[a][i];
                 }
-            double wd = c_ref.w[T][q] * d;
+            double wd = Fam<T>::W * d;
             S.sC[el][q][0] = (CT)wd;
             if constexpr (NHK) {
                 if (S.sNH[el]) {
@@ -724,14 +743,11 @@ __device__ inline void elem_rhs(const ElemSmem<T, MODEL, VAR, CT> &S, const int 
     using GradRec = typename Smem::GradRec;
     const GradRec *sG = reinterpret_cast<const GradRec *>(S.buf);
     const GradRec *sH = reinterpret_cast<const GradRec *>(S.buf + Smem::NG);
+    CT wn = 0;
 #pragma unroll
-    for (int i = 0; i < B; ++i) f[i] = 0;
+    for (int q = 0; q < NQ; ++q) wn += S.sC[el][q][0] * (CT)S.sRef[q][a * 4 + 3];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        CT wn = S.sC[el][q][0] * (CT)S.sNr[q][a];
-#pragma unroll
-        for (int i = 0; i < B; ++i) f[i] += wn * (CT)src[i];
-    }
+    for (int i = 0; i < B; ++i) f[i] = wn * (CT)src[i];
     if constexpr (RES) {
         // f -= f_int_a = sum_q w detJ P grad N_a. Neo-Hookean:
         // P grad N_a = mu F grad N_a + (lam ln J - mu) F^-T grad N_a,
@@ -775,6 +791,89 @@ __device__ inline void elem_rhs(const ElemSmem<T, MODEL, VAR, CT> &S, const int 
     }
 }
 
+// Inputs of the cnt elements A.elems[first ..] of a position-ordered tile into
+// LDS, for kernels with one wave group per kind of load. The loads form two
+// levels that all waves go through together and without per-lane conditions
+// (clamped indices): ids first (waves 0 and 1 an (element, node)'s node, waves 2
+// and 3 an element) with the reference table, one value per thread; then
+// three values behind the id: coordinates, material (wave 2), source (wave 3).
+// Under per-lane conditions the compiler waits after every group of loads, and
+// a wave goes through as many dependent loads as there are groups.
+struct TileLevel1 {
+    int32_t id;
+    double ref;
+};
+
+template <int T, int MODEL, int VAR, typename CT>
+__device__ __forceinline__ TileLevel1 tile_level1(const ElemArgs &A, const int64_t first, const int cnt, const int tid)
+{
+    using Smem = ElemSmem<T, MODEL, VAR, CT>;
+    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, EPB = Smem::EPB;
+    static_assert(EPB * NN <= 128 && EPB <= 64 && NQ * NN * 4 <= 256, "one wave group per kind of load");
+    const bool nodes = __builtin_amdgcn_readfirstlane(tid >> 6) < 2;
+    const int32_t *p = nodes ? A.pnodes + first * NN : A.elems + first;
+    const int l = tid & 63, lim = nodes ? cnt * NN : cnt, i = nodes ? tid : l;
+    return {p[(unsigned)(i < lim ? i : 0)], A.ref[(unsigned)(T * 256 + (tid < NQ * NN * 4 ? tid : 0))]};
+}
+
+template <int T, int MODEL, int VAR, typename CT>
+__device__ __forceinline__ void tile_level2(const ElemArgs &A, const int cnt, ElemSmem<T, MODEL, VAR, CT> &S,
+                                            const TileLevel1 &in, const int tid)
+{
+    using Smem = ElemSmem<T, MODEL, VAR, CT>;
+    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, EPB = Smem::EPB, B = Smem::B;
+    constexpr bool ELAS = Smem::ELAS, NHK = Smem::NHK;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const double *pa = A.x, *pb = A.y, *pc = A.z;
+    int stride = 1;
+    if (ELAS && wave == 2) {
+        pa = pc = A.nu;
+        pb = A.young ? A.young : A.nu;
+    } else if (wave >= 2) {
+        pa = A.source;
+        pb = A.source + (B > 1 ? 1 : 0);
+        pc = A.source + (B > 1 ? 2 : 0);
+        stride = B;
+    }
+    const int64_t at = (int64_t)in.id * stride;
+    const double va = pa[at], vb = pb[at], vc = pc[at];
+    double u[3] = {0.0, 0.0, 0.0};
+    int nh = 0;
+    if constexpr (NHK) {
+        if (wave < 2) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) u[c] = A.u[3 * (int64_t)in.id + c];
+        } else if (A.nh_flag) {
+            nh = (int)A.nh_flag[in.id];
+        }
+    }
+    if (tid < NQ * NN * 4) elem_ref(S, tid) = in.ref;
+    if (wave < 2) {
+        const int el = tid / NN, a = tid - el * NN;
+        if (el < cnt) {
+            S.sX[el][a][0] = va;
+            S.sX[el][a][1] = vb;
+            S.sX[el][a][2] = vc;
+            if constexpr (NHK) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) S.sU[el][a][c] = u[c];
+            }
+        }
+    } else if (wave == 2) {
+        if (l < EPB) {
+            S.sE[l] = l < cnt ? in.id : -1;
+            S.sNH[l] = nh;
+            if constexpr (ELAS) lame(A.young ? vb : 1.0, va, S.sLM[l]);
+        }
+    } else if (l < EPB) {
+        S.sSrc[l][0] = va;
+        if constexpr (B == 3) {
+            S.sSrc[l][1] = vb;
+            S.sSrc[l][2] = vc;
+        }
+    }
+}
+
 // Row-owner, atomic and colour forms: the EPB elements A.elems[first ..
 // first + EPB) (ids beyond A.n are skipped) with the calling workgroup's 256
 // threads and LDS S; one thread per block (a, b) of every element.
@@ -782,55 +881,44 @@ template <int T, int MODEL, int VAR, typename CT>
 __device__ void elem_tile_full(const ElemArgs &A, int64_t first, ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
 {
     using Smem = ElemSmem<T, MODEL, VAR, CT>;
-    constexpr int NN = Fam<T>::NN, P = NN * NN;
-    constexpr int PW = Smem::PW, EPB = Smem::EPB, B = Smem::B, BB = Smem::BB;
+    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, P = NN * NN;
+    constexpr int EPB = Smem::EPB, B = Smem::B, BB = Smem::BB;
     constexpr bool ELAS = Smem::ELAS, NHK = Smem::NHK, RO = Smem::RO, STAGE = Smem::STAGE;
-    CT *sK = S.buf + Smem::NG + Smem::NHG;
-    __syncthreads();  // the previous tile's readers of S are done
-    elem_ref_tables(S, tid);
-
-    // element data (threads below EPB) and, for the row-owner layout, node
-    // data (the next EPB*NN threads) are fetched in the same phase
-    if (tid < EPB) {
-        int64_t i = first + tid;
-        int32_t e = i < A.n ? A.elems[i] : -1;
-        S.sE[tid] = e;
-        if constexpr (!RO) {
-            S.sM[tid] = e >= 0 ? A.map_ptr[e] : 0;
-            S.sCP[tid] = e >= 0 ? A.conn_ptr[e] : 0;
-        }
-        S.sNH[tid] = (ELAS && e >= 0 && A.nh_flag) ? (int)A.nh_flag[e] : 0;
-        if constexpr (ELAS) elem_lame(A, e, S.sLM[tid]);
-    }
+    CT *sK = S.buf + Smem::KOFF;
+    const int64_t left = A.n - first;
+    const int cnt = __builtin_amdgcn_readfirstlane((int)(left < EPB ? left : EPB));  // elements of this tile
+    const int pel = tid / P, p = tid - pel * P, nel = tid / NN, na = tid - nel * NN;
+    const bool pact = pel < cnt, nact = nel < cnt;
+    // destinations of this thread's block and right-hand-side entry
+    int32_t dest = 0, rdest = 0;
     if constexpr (RO) {
-        if (tid >= EPB && tid < EPB + EPB * NN) {
-            const int k = tid - EPB, el = k / NN, a = k % NN;
-            const int64_t i = first + el;
-            if (i < A.n) {
-                const int32_t v = A.pnodes[i * NN + a];
-                S.sX[el][a][0] = A.x[v];
-                S.sX[el][a][1] = A.y[v];
-                S.sX[el][a][2] = A.z[v];
-                if constexpr (NHK) {
-                    for (int c = 0; c < 3; ++c) S.sU[el][a][c] = A.u[3 * (int64_t)v + c];
-                }
-            }
-        }
+        dest = A.pdest[first * P + (pact ? tid : 0)];
+        rdest = A.prdest[first * NN + (nact ? tid : 0)];
+        const TileLevel1 in = tile_level1<T, MODEL, VAR, CT>(A, first, cnt, tid);
+        __syncthreads();  // the previous tile's readers of S are done
+        tile_level2(A, cnt, S, in, tid);
         __syncthreads();
     } else {
         __syncthreads();
-        if (tid < EPB * NN) {
-            int el = tid / NN, a = tid % NN;
-            int32_t e = S.sE[el];
-            if (e >= 0) {
-                int32_t v = A.conn[S.sCP[el] + a];
-                S.sX[el][a][0] = A.x[v];
-                S.sX[el][a][1] = A.y[v];
-                S.sX[el][a][2] = A.z[v];
-                if constexpr (NHK) {
-                    bool nh = S.sNH[el] != 0 || MODEL == M_ELASTIC_RES;
-                    for (int c = 0; c < 3; ++c) S.sU[el][a][c] = nh ? A.u[3 * (int64_t)v + c] : 0.0;
-                }
+        if (tid < NQ * NN * 4) elem_ref(S, tid) = A.ref[T * 256 + tid];
+        if (tid < EPB) {
+            const int32_t e = tid < cnt ? A.elems[first + tid] : -1;
+            S.sE[tid] = e;
+            S.sM[tid] = e >= 0 ? A.map_ptr[e] : 0;
+            S.sCP[tid] = e >= 0 ? A.conn_ptr[e] : 0;
+            S.sNH[tid] = (ELAS && e >= 0 && A.nh_flag) ? (int)A.nh_flag[e] : 0;
+            if constexpr (ELAS) elem_lame(A, e, S.sLM[tid]);
+        }
+        __syncthreads();
+        if (pact) dest = A.e2nnz[S.sM[pel] + p];
+        if (nact) {
+            const int32_t v = A.conn[S.sCP[nel] + na];
+            S.sX[nel][na][0] = A.x[v];
+            S.sX[nel][na][1] = A.y[v];
+            S.sX[nel][na][2] = A.z[v];
+            if constexpr (NHK) {
+                bool nh = S.sNH[nel] != 0 || MODEL == M_ELASTIC_RES;
+                for (int c = 0; c < 3; ++c) S.sU[nel][na][c] = nh ? A.u[3 * (int64_t)v + c] : 0.0;
             }
         }
         __syncthreads();
@@ -840,74 +928,59 @@ __device__ void elem_tile_full(const ElemArgs &A, int64_t first, ElemSmem<T, MOD
     __syncthreads();
 
     // element matrix: one thread per (element, block a-b)
-    if (tid < EPB * PW) {
-        const int el = tid / PW, w = tid % PW;
-        const int a = w / NN, b = w % NN;
-        const int p = a * NN + b;
-        int32_t e = S.sE[el];
-        // destination of this block, fetched before the contraction
-        const int64_t dest = e < 0 ? -1
-                             : RO  ? (int64_t)A.pdest[(first + el) * P + p]
-                                   : (int64_t)A.e2nnz[S.sM[el] + p];
-        if (dest >= 0) {
-            CT K[BB];
-            elem_block(S, el, a, b, K);
-            if constexpr (STAGE) {
-                S.sD[el * P + p] = (int32_t)dest;
+    CT K[BB];
+    if (pact) {
+        elem_block(S, pel, p / NN, p % NN, K);
+        if constexpr (!RO) {
+            double *dst = A.vals + (int64_t)dest * BB;
 #pragma unroll
-                for (int c = 0; c < BB; ++c) sK[(el * P + p) * BB + c] = K[c];
-            } else if constexpr (RO) {
-                // row-owner: the workspace is sorted by destination block
-                CT *dst = (CT *)A.contrib + dest * BB;
-#pragma unroll
-                for (int c = 0; c < BB; ++c) dst[c] = K[c];
-            } else {
-                double *dst = A.vals + dest * BB;
-#pragma unroll
-                for (int c = 0; c < BB; ++c) {
-                    if constexpr (VAR == V_ATOMIC)
-                        unsafeAtomicAdd(dst + c, (double)K[c]);
-                    else
-                        dst[c] += (double)K[c];
-                }
+            for (int c = 0; c < BB; ++c) {
+                if constexpr (VAR == V_ATOMIC)
+                    unsafeAtomicAdd(dst + c, (double)K[c]);
+                else
+                    dst[c] += (double)K[c];
             }
         }
     }
 
     // right-hand side: one thread per (element, node)
-    if (tid < EPB * NN) {
-        int el = tid / NN, a = tid % NN;
-        int32_t e = S.sE[el];
-        if (e >= 0) {
-            double src[B];
+    if (nact) {
+        double src[B];
 #pragma unroll
-            for (int i = 0; i < B; ++i) src[i] = A.source[(int64_t)e * B + i];
-            CT f[B];
-            elem_rhs(S, el, a, src, f);
-            if constexpr (RO) {
-                CT *dst = (CT *)A.rcontrib + (int64_t)A.prdest[(first + el) * NN + a] * B;
+        for (int i = 0; i < B; ++i) src[i] = RO ? S.sSrc[RO ? nel : 0][i] : A.source[(int64_t)S.sE[nel] * B + i];
+        CT f[B];
+        elem_rhs(S, nel, na, src, f);
+        if constexpr (RO) {
+            CT *dst = (CT *)A.rcontrib + (int64_t)rdest * B;
 #pragma unroll
-                for (int i = 0; i < B; ++i) dst[i] = f[i];
-            } else {
-                int64_t v = A.conn[S.sCP[el] + a];
-                double *dst = A.rhs + v * B;
+            for (int i = 0; i < B; ++i) dst[i] = f[i];
+        } else {
+            const int64_t v = A.conn[S.sCP[nel] + na];
+            double *dst = A.rhs + v * B;
 #pragma unroll
-                for (int i = 0; i < B; ++i) {
-                    if constexpr (VAR == V_ATOMIC)
-                        unsafeAtomicAdd(dst + i, (double)f[i]);
-                    else
-                        dst[i] += (double)f[i];
-                }
+            for (int i = 0; i < B; ++i) {
+                if constexpr (VAR == V_ATOMIC)
+                    unsafeAtomicAdd(dst + i, (double)f[i]);
+                else
+                    dst[i] += (double)f[i];
             }
         }
     }
 
     if constexpr (STAGE) {
+        // row-owner: the workspace is sorted by destination block; the blocks
+        // go through LDS so that BB consecutive threads write one block
+        if constexpr (Smem::ALIAS) __syncthreads();  // every lane has read what sK overwrites
+        if (pact) {
+            S.sD[tid] = dest;
+#pragma unroll
+            for (int c = 0; c < BB; ++c) sK[tid * BB + c] = K[c];
+        }
         __syncthreads();
         CT *out = (CT *)A.contrib;
-        for (int idx = tid; idx < EPB * PW * BB; idx += 256) {
+        for (int idx = tid; idx < cnt * P * BB; idx += 256) {
             const int blk = idx / BB;
-            if (first + blk / PW < A.n) out[(int64_t)S.sD[blk] * BB + (idx - blk * BB)] = sK[idx];
+            out[(int64_t)S.sD[blk] * BB + (idx - blk * BB)] = sK[idx];
         }
     }
 }
@@ -917,16 +990,12 @@ __device__ void elem_tile_full(const ElemArgs &A, int64_t first, ElemSmem<T, MOD
 //
 // What bounds it is latency and instruction issue, not HBM: a workgroup
 // lives for a few dependent loads and a few hundred instructions. The global
-// loads of a tile are therefore arranged as two levels that all waves go
-// through at once: every thread first issues the loads that depend on nothing
-// (its pair's place, a tile-block's range and slot), then waves 0 and 1 take
-// the nodes (id -> coordinates), wave 2 the element data (id -> material and
-// source) and wave 3 the reference tables, at clamped indices rather than
-// under per-lane conditions, so that no wave waits for one group before it
-// issues the next. Under per-lane conditions the compiler waited after each
-// group, and wave 0 went through eight dependent loads instead of two: a third
-// to a half of the kernel's time (with tile sums, blocks and geometry left
-// out, 0.34 of 1.06 ms for 885k hex8 and 0.24 of 0.62 ms for 1.3M pyr5).
+// loads of a tile are therefore issued in two levels (see tile_level1), its
+// pairs' places and tile-block records with the first, and nothing is loaded
+// after them. With a condition around each group of loads the first wave
+// went through eight dependent loads, a third to a half of the kernel's time
+// (with tile sums, blocks and geometry left out, 0.34 of 1.06 ms for 885k
+// hex8 and 0.24 of 0.62 ms for 1.3M pyr5).
 //
 // A pair's block is staged in LDS at its place in the order of the tile's
 // (block, lane) entries, already transposed where node a > node b, so that the
@@ -942,9 +1011,9 @@ template <int T, int MODEL, int VAR, typename CT>
 __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
 {
     using Smem = ElemSmem<T, MODEL, VAR, CT>;
-    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ;
+    constexpr int NN = Fam<T>::NN;
     constexpr int PW = Smem::PW, EPB = Smem::EPB, B = Smem::B, BB = Smem::BB;
-    constexpr bool ELAS = Smem::ELAS, NHK = Smem::NHK, TCOL = Smem::TCOL, ALIAS = Smem::ALIAS;
+    constexpr bool TCOL = Smem::TCOL, ALIAS = Smem::ALIAS;
     // 3x3 blocks of the upper-triangle form: the right-hand side of node a
     // of an element rides in the strictly lower entries (3, 6, 7) of the
     // element's diagonal block (a, a), which symmetry makes redundant; the
@@ -952,73 +1021,30 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
     // kernel writes it out (no right-hand-side workspace, no reduction of
     // its own)
     constexpr bool RHSD = !TCOL && B == 3;
-    static_assert(EPB * NN <= 128 && EPB <= 64 && NQ * NN <= 64, "one wave group per kind of load");
     CT *sK = S.buf + Smem::KOFF;
     const int64_t tl = first / EPB;
     const int64_t left = A.n - first;
     const int cnt = __builtin_amdgcn_readfirstlane((int)(left < EPB ? left : EPB));  // elements of this tile
     const int64_t d0 = A.ttb_ptr[tl];
     const int nd = (int)(A.ttb_ptr[tl + 1] - d0);
-    // loads that depend on nothing
     const int pel = tid / PW;
     const bool pact = pel < cnt;  // this thread has a pair
     const int nel = tid / NN, na = tid - nel * NN;
     const bool nact = nel < cnt;  // and an (element, node)
     const uint16_t *tp = A.tpos + first * PW;
-    const unsigned pos = tp[pact ? tid : 0];
+    const unsigned pos = tp[(unsigned)(pact ? tid : 0)];
     unsigned rpos = 0;
     int32_t rdest = 0;  // right-hand-side destination of (element, node) tid
     if constexpr (RHSD)
-        rpos = tp[nact ? nel * PW + na * NN - na * (na - 1) / 2 : 0];  // pair (a, a)
+        rpos = tp[(unsigned)(nact ? nel * PW + ((na * (2 * NN + 1 - na)) >> 1) : 0)];  // pair (a, a)
     else
         rdest = A.prdest[first * NN + (nact ? tid : 0)];
-    const int td = tid < nd ? tid : nd - 1;
-    const uint32_t rng = A.tb_rng[d0 + td];
-    const int32_t slot = TCOL ? A.tb_blk[d0 + td] : A.tb_slot[d0 + td];
+    const TileLevel1 in = tile_level1<T, MODEL, VAR, CT>(A, first, cnt, tid);
+    const unsigned td = (unsigned)(tid < nd ? tid : nd - 1);
+    const uint32_t rng = (A.tb_rng + d0)[td];
+    const int32_t slot = ((TCOL ? A.tb_blk : A.tb_slot) + d0)[td];
     __syncthreads();  // the previous tile's readers of S are done
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (wave < 2) {
-        const int32_t v = A.pnodes[first * NN + (nact ? tid : 0)];
-        const double x = A.x[v], y = A.y[v], z = A.z[v];
-        double u[3] = {0.0, 0.0, 0.0};
-        if constexpr (NHK) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) u[c] = A.u[3 * (int64_t)v + c];
-        }
-        if (nact) {
-            S.sX[nel][na][0] = x;
-            S.sX[nel][na][1] = y;
-            S.sX[nel][na][2] = z;
-            if constexpr (NHK) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) S.sU[nel][na][c] = u[c];
-            }
-        }
-    } else if (wave == 2) {
-        const int el = tid - 128;
-        const int32_t e = A.elems[first + (el < cnt ? el : 0)];
-        const int nh = (ELAS && A.nh_flag) ? (int)A.nh_flag[e] : 0;
-        double src[B], lm[2] = {0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < B; ++c) src[c] = A.source[(int64_t)e * B + c];
-        if constexpr (ELAS) elem_lame(A, e, lm);
-        if (el < EPB) {
-            S.sE[el] = el < cnt ? e : -1;
-            S.sNH[el] = nh;
-            if constexpr (ELAS) {
-                S.sLM[el][0] = lm[0];
-                S.sLM[el][1] = lm[1];
-            }
-#pragma unroll
-            for (int c = 0; c < B; ++c) S.sSrc[el][c] = src[c];
-        }
-    } else {
-        const int i = tid - 192 < NQ * NN ? tid - 192 : 0;
-        const int q = i / NN, a = i % NN;
-        S.sNr[q][a] = c_ref.N[T][q][a];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) S.sDN[q][a][c] = c_ref.dN[T][q][a][c];
-    }
+    tile_level2(A, cnt, S, in, tid);
     if (tid < nd) S.sTb[tid] = {slot, rng};
     if constexpr (TCOL) {
         if (tid < nd) S.sLp[tid] = A.lpart[slot];
