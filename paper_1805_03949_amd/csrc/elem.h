@@ -390,7 +390,8 @@ struct ElemDims {
     static constexpr bool NHK = MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES;
     static constexpr int B = ELAS ? 3 : 1;
     static constexpr int BB = B * B;
-    static constexpr int EU = NHK ? EPB : 1;
+    static constexpr bool RES = MODEL == M_ELASTIC_RES && sizeof(CT) == 8;  // Newton residual
+    static constexpr int EU = NHK ? EPB : 1, ER = RES ? EPB : 1;
     static constexpr bool RO = VAR == V_ROWOWNER || VAR == V_ROWSYM || VAR == V_TILECOL;
 
     static constexpr bool SYM = VAR == V_ROWSYM || VAR == V_TILECOL;  // tile sums
@@ -401,6 +402,11 @@ struct ElemDims {
     // most as many tile-blocks
     static constexpr int MAXENT = EPB * PW;
     static constexpr int NC = NHK ? 4 : 1;
+    // lanes per Gauss point in the geometry: three where the tile's points fit
+    // one round of the workgroup (four waves of 21 groups), one otherwise (the
+    // upper-triangle pyr5 tile: two rounds of three lanes measured 0.53, one
+    // lane 0.48 ms FP64, 0.37 and 0.34 mixed)
+    static constexpr int GEO_LANES = EPB * NQ <= 84 ? 3 : 1;
     // Row-owner and upper-triangle stores are staged in LDS (BB consecutive
     // threads write one block's BB contiguous values; tile sums read them)
     static constexpr bool STAGE = RO;
@@ -429,7 +435,7 @@ struct ElemDims {
     // the points a wave reads at once start in different banks
     static constexpr int RQ = NN * 4 + 2;
     static constexpr int PRE_BYTES =
-        (EPB * NN * 3 + EU * NN * 3 + NLM * 2 + SRC * B + NQ * RQ) * 8 +
+        (EPB * NN * 3 + EU * NN * 3 + NLM * 2 + SRC * B + NQ * RQ + ER * NQ * 9) * 8 +
         EPB * NQ * NC * (int)sizeof(CT) + 2 * EPB * 4;
     static constexpr bool PRE_ALIAS =
         ALIAS && sizeof(CT) == 8 && (NG + NHG) * (int)sizeof(CT) + PRE_BYTES <= NBUF * (int)sizeof(CT);
@@ -445,6 +451,7 @@ struct ElemPreArrays {
     double sLM[D::NLM][2];        // lam, mu of every element (elasticity)
     double sSrc[D::SRC][D::B];    // source of every element (element-tile forms)
     double sRef[D::NQ][D::RQ];    // reference gradients and shape functions of this family
+    double sP[D::ER][D::NQ][9];   // residual: w detJ times the stress (P or sigma) at every Gauss point
     CT sC[D::EPB][D::NQ][D::NC];  // wd, and for neo-Hookean wd*lam, wd*c2, wd*mu
     int32_t sE[D::EPB];
     int sNH[D::EPB];
@@ -465,6 +472,7 @@ struct ElemPre<D, true> {
             double sLM[D::NLM][2];
             double sSrc[D::SRC][D::B];
             double sRef[D::NQ][D::RQ];
+            double sP[D::ER][D::NQ][9];
             CT sC[D::EPB][D::NQ][D::NC];
             int32_t sE[D::EPB];
             int sNH[D::EPB];
@@ -545,109 +553,304 @@ __device__ inline void elem_lame(const ElemArgs &A, int32_t e, double lm[2])
     lame((e >= 0 && A.young) ? A.young[e] : 1.0, e >= 0 ? A.nu[e] : 0.25, lm);
 }
 
-// Geometry: one thread per (element, Gauss point), in FP64. Reads sX, sU,
-// sE, sNH, sLM and the reference tables; writes the physical gradients (and
-// the neo-Hookean pushed gradients) and the Gauss-point coefficients.
+// A Gauss point of family T in factored form: the 1D (hex8, pyr5) or triangle
+// and 1D (pen6) factors of its shape functions. Derivatives of a field and
+// gradients of the nodes then take sums over one direction after the other,
+// in registers, instead of a table entry from LDS per node and direction.
+template <int T>
+struct GeoPoint {
+    double fx[2], fy[2], fz[2];  // 1D shape functions at -1 and +1 (pen6: fz)
+    double L[3];                 // pen6: triangle coordinates
+};
+
+template <int T>
+__device__ __forceinline__ GeoPoint<T> geo_point(const int q)
+{
+    GeoPoint<T> p;
+    constexpr double g = 0.57735026918962576451;  // 1/sqrt(3)
+    constexpr double M = 0.5 * (1.0 - g), P = 0.5 * (1.0 + g);
+    if constexpr (T == 1 || T == 3) {
+        const bool bx = q & 1, by = q & 2, bz = q & 4;
+        p.fx[0] = bx ? M : P;
+        p.fx[1] = bx ? P : M;
+        p.fy[0] = by ? M : P;
+        p.fy[1] = by ? P : M;
+        p.fz[0] = bz ? M : P;
+        p.fz[1] = bz ? P : M;
+    } else if constexpr (T == 2) {
+        const bool bz = q >= 3;
+        const int i = bz ? q - 3 : q;
+        p.fz[0] = bz ? M : P;
+        p.fz[1] = bz ? P : M;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p.L[k] = k == i ? 2.0 / 3.0 : 1.0 / 6.0;
+    }
+    return p;
+}
+
+// Reference derivatives d[j] = sum_a v(a) dN_a/dxi_j of a nodal field at the
+// point.
+template <int T, typename V>
+__device__ __forceinline__ void geo_row(const GeoPoint<T> &p, const V &v, double d[3])
+{
+    if constexpr (T == 0) {
+        const double v0 = v(0);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) d[j] = v(j + 1) - v0;
+    } else if constexpr (T == 2) {
+        double c[3], t[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double lo = v(k), hi = v(k + 3);
+            c[k] = p.fz[0] * lo + p.fz[1] * hi;
+            t[k] = hi - lo;
+        }
+        d[0] = c[1] - c[0];
+        d[1] = c[2] - c[0];
+        d[2] = 0.5 * (p.L[0] * t[0] + p.L[1] * t[1] + p.L[2] * t[2]);
+    } else {
+        // corner (x, y) of the bottom face is node LO, of the top face LO + 4
+        // (the apex for the collapsed pyramid)
+        constexpr int LO[2][2] = {{0, 3}, {1, 2}};
+        double vy[2], dy[2], tz[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            double c[2], t[2];
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const double lo = v(LO[x][y]), hi = v(T == 1 ? 4 : LO[x][y] + 4);
+                c[y] = p.fz[0] * lo + p.fz[1] * hi;
+                t[y] = hi - lo;
+            }
+            vy[x] = p.fy[0] * c[0] + p.fy[1] * c[1];
+            dy[x] = c[1] - c[0];
+            tz[x] = p.fy[0] * t[0] + p.fy[1] * t[1];
+        }
+        d[0] = 0.5 * (vy[1] - vy[0]);
+        d[1] = 0.5 * (p.fx[0] * dy[0] + p.fx[1] * dy[1]);
+        d[2] = 0.5 * (p.fx[0] * tz[0] + p.fx[1] * tz[1]);
+    }
+}
+
+// out(a, sum_j c[j] dN_a/dxi_j) for every node a.
+template <int T, typename Out>
+__device__ __forceinline__ void geo_nodes(const GeoPoint<T> &p, const double c[3], const Out &out)
+{
+    if constexpr (T == 0) {
+        out(0, -(c[0] + c[1] + c[2]));
+#pragma unroll
+        for (int j = 0; j < 3; ++j) out(j + 1, c[j]);
+    } else if constexpr (T == 2) {
+        const double m[3] = {-(c[0] + c[1]), c[0], c[1]}, h = 0.5 * c[2];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double t = p.L[k] * h;
+            out(k, p.fz[0] * m[k] - t);
+            out(k + 3, p.fz[1] * m[k] + t);
+        }
+    } else {
+        constexpr int LO[2][2] = {{0, 3}, {1, 2}};
+        const double h0 = 0.5 * c[0], h1 = 0.5 * c[1], h2 = 0.5 * c[2];
+        double hx[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) hx[x] = h2 * p.fx[x];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                const double m = (x ? h0 : -h0) * p.fy[y] + (y ? h1 : -h1) * p.fx[x], t = hx[x] * p.fy[y];
+                out(LO[x][y], p.fz[0] * m - t);
+                if constexpr (T == 3) out(LO[x][y] + 4, p.fz[1] * m + t);
+            }
+        if constexpr (T == 1) out(4, h2);
+    }
+}
+
+// Row r of a 3x3 matrix, one row per lane of a group of three that starts at
+// lane g0: column r of its cofactors, c[k] = cof(r, k) = det * inverse[k][r],
+// and the determinant by this row's expansion.
+__device__ __forceinline__ double geo_cofactors(const double row[3], const int g0, const int r, double c[3])
+{
+    const int l1 = g0 + (r == 2 ? 0 : r + 1), l2 = g0 + (r == 0 ? 2 : r - 1);
+    double b[3], e[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        b[j] = __shfl(row[j], l1);
+        e[j] = __shfl(row[j], l2);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] = b[(k + 1) % 3] * e[(k + 2) % 3] - b[(k + 2) % 3] * e[(k + 1) % 3];
+    return row[0] * c[0] + row[1] * c[1] + row[2] * c[2];
+}
+
+// Geometry, in FP64, three lanes per (element, Gauss point), 21 such groups
+// per wave (lane 63 idle, so that a group never spans two waves): lane r forms
+// row r of J, takes the other two rows from its neighbours, and with them
+// column r of J^-1 and component r of every node's gradient. A neo-Hookean
+// point goes the same way once more: row r of F = I + (du/dxi) J^-1, column r
+// of F^-1 and of J^-1 F^-1, component r of the gradients pushed through F^-T.
+// For the Newton residual each point also leaves w detJ times its stress, so
+// that a node's internal force is one 3x3 product per point; summed from the
+// displacements at every node instead, it took a fifth of that kernel.
+// (GEO_LANES = 1: the same with a point's three rows in one lane.)
+// Writes the gradients and the Gauss-point coefficients.
+// What bounds these kernels most is LDS: 79% of its cycles were busy for hex8
+// when the reference derivatives were read from a table there and every
+// lane formed the whole inverse. Per hex8 point the lanes now read 24
+// coordinates and exchange 18 values, before 24 + 99 and 27. Measured on
+// MI355X, element phase before -> after, ms, FP64 / mixed: tet4 (1.3M elements)
+// 0.215 -> 0.194 / 0.19 -> 0.19, pen6 (1.0M) 0.55 -> 0.49 / 0.40 -> 0.38, hex8
+// (885k) 0.83 -> 0.77 / 0.66 -> 0.63; Newton step of a 64^3-cell mesh with 30%
+// neo-Hookean elements 0.60 -> 0.49; one lane per neo-Hookean point 0.50, and
+// mixed tangent of 96^3 cells 0.95 against 0.89 with three.
 template <int T, int MODEL, int VAR, typename CT>
 __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
 {
     using Smem = ElemSmem<T, MODEL, VAR, CT>;
-    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, EPB = Smem::EPB;
+    constexpr int NQ = Fam<T>::NQ, EPB = Smem::EPB;
     constexpr bool NHK = Smem::NHK;
     using GradRec = typename Smem::GradRec;
     GradRec *sG = reinterpret_cast<GradRec *>(S.buf);
     GradRec *sH = reinterpret_cast<GradRec *>(S.buf + Smem::NG);
-    if constexpr (!NHK && EPB * NQ <= 4 * 21) {
-        // Three lanes per (element, Gauss point), 21 such groups per wave
-        // (lane 63 idle, so that a group never spans two waves): lane r of a
-        // group forms row r of J, the rows are exchanged across the group's
-        // lanes, each lane inverts J and writes the gradients of nodes
-        // r, r + 3, ... Same operations per value as one lane per point,
-        // spread over up to four waves instead of one or two.
-        const int lane = tid & 63, r = lane % 3;
-        const int grp = (tid >> 6) * 21 + lane / 3;
-        if (lane < 63 && grp < EPB * NQ) {
-            const int el = grp / NQ, q = grp % NQ;
+    if constexpr (Smem::GEO_LANES == 1) {
+        for (int i = tid; i < EPB * NQ; i += 256) {
+            const int el = i / NQ, q = i - el * NQ;
             const int32_t e = S.sE[el];
-            if (e >= 0) {
-                double Jr[3] = {0, 0, 0};
+            if (e < 0) continue;
+            const GeoPoint<T> pt = geo_point<T>(q);
+            double J[3][3], Ji[3][3];
 #pragma unroll
-                for (int a = 0; a < NN; ++a)
+            for (int r = 0; r < 3; ++r) geo_row<T>(pt, [&](int a) { return S.sX[el][a][r]; }, J[r]);
+            const double d = det3(J);
+            if (!(d > 0.0)) atomicMin(A.status, e);
+            inv3(J, d, Ji);
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) Jr[j] += S.sX[el][a][r] * S.sRef[q][a * 4 + j];
-                const int g0 = lane - r;
-                double J[3][3];
+            for (int r = 0; r < 3; ++r) {
+                const double c[3] = {Ji[0][r], Ji[1][r], Ji[2][r]};
+                geo_nodes<T>(pt, c, [&](int a, double v) { sG[el].v[q][a][r] = (CT)v; });
+            }
+            const double wd = Fam<T>::W * d;
+            S.sC[el][q][0] = (CT)wd;
+            if constexpr (NHK) {
+                const bool nh = S.sNH[el] != 0;
+                if (nh || Smem::RES) {
+                    const double lam = S.sLM[el][0], mu = S.sLM[el][1];
+                    double H[3][3];  // du/dx
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+                    for (int r = 0; r < 3; ++r) {
+                        double h[3];
+                        geo_row<T>(pt, [&](int a) { return S.sU[el][a][r]; }, h);
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) J[i][j] = __shfl(Jr[j], g0 + i);
-                const double d = det3(J);
-                if (r == 0 && !(d > 0.0)) atomicMin(A.status, e);
-                double Ji[3][3];
-                inv3(J, d, Ji);
+                        for (int j = 0; j < 3; ++j) H[r][j] = h[0] * Ji[0][j] + h[1] * Ji[1][j] + h[2] * Ji[2][j];
+                    }
+                    if (nh) {
+                        double Fi[3][3];
 #pragma unroll
-                for (int a = r; a < NN; a += 3)
+                        for (int j = 0; j < 3; ++j) H[j][j] += 1.0;  // F
+                        const double jf = det3(H);
+                        if (!(jf > 0.0)) atomicMin(A.status, e);
+                        inv3(H, jf, Fi);
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
-                        sG[el].v[q][a][i] =
-                            (CT)(Ji[0][i] * S.sRef[q][a * 4 + 0] + Ji[1][i] * S.sRef[q][a * 4 + 1] + Ji[2][i] * S.sRef[q][a * 4 + 2]);
-                if (r == 0) S.sC[el][q][0] = (CT)(Fam<T>::W * d);
+                        for (int r = 0; r < 3; ++r) {
+                            double c[3];
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                c[k] = Ji[k][0] * Fi[0][r] + Ji[k][1] * Fi[1][r] + Ji[k][2] * Fi[2][r];
+                            geo_nodes<T>(pt, c, [&](int a, double v) { sH[el].v[q][a][r] = (CT)v; });
+                        }
+                        const double c2 = mu - lam * log(jf);
+                        S.sC[el][q][1] = (CT)(wd * lam);
+                        S.sC[el][q][2] = (CT)(wd * c2);
+                        S.sC[el][q][3] = (CT)(wd * mu);
+                        if constexpr (Smem::RES) {
+                            // P = mu F - (mu - lam ln J) F^-T
+#pragma unroll
+                            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                                for (int j = 0; j < 3; ++j)
+                                    S.sP[el][q][3 * i + j] = wd * (mu * H[i][j] - c2 * Fi[j][i]);
+                        }
+                    } else if constexpr (Smem::RES) {
+                        // sigma = lam tr(H) I + mu (H + H^T)
+                        const double t = lam * (H[0][0] + H[1][1] + H[2][2]);
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+#pragma unroll
+                            for (int j = 0; j < 3; ++j)
+                                S.sP[el][q][3 * i + j] = wd * ((i == j ? t : 0.0) + mu * (H[i][j] + H[j][i]));
+                    }
+                }
             }
         }
         return;
     }
-    if (tid < EPB * NQ) {
-        int el = tid / NQ, q = tid % NQ;
-        int32_t e = S.sE[el];
-        if (e >= 0) {
-            double J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    const int lane = tid & 63, r = lane % 3, g0 = lane - r;
+    const int grp = (tid >> 6) * 21 + lane / 3;
+    if (lane == 63 || grp >= EPB * NQ) return;
+    const int el = grp / NQ, q = grp - el * NQ;
+    const int32_t e = S.sE[el];
+    if (e < 0) return;
+    const GeoPoint<T> pt = geo_point<T>(q);
+    double J[3], c[3], Ji[3];
+    geo_row<T>(pt, [&](int a) { return S.sX[el][a][r]; }, J);
+    const double d = geo_cofactors(J, g0, r, c);
+    const double id = 1.0 / d;
 #pragma unroll
-            for (int a = 0; a < NN; ++a)
+    for (int k = 0; k < 3; ++k) Ji[k] = c[k] * id;
+    geo_nodes<T>(pt, Ji, [&](int a, double v) { sG[el].v[q][a][r] = (CT)v; });
+    const double wd = Fam<T>::W * d;
+    if (r == 0) {
+        if (!(d > 0.0)) atomicMin(A.status, e);
+        S.sC[el][q][0] = (CT)wd;
+    }
+    if constexpr (NHK) {
+        const bool nh = S.sNH[el] != 0;
+        if (nh || Smem::RES) {
+            const double lam = S.sLM[el][0], mu = S.sLM[el][1];
+            double I[3][3];  // J^-1, column j from lane j of the group
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+            for (int k = 0; k < 3; ++k)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) J[i][j] += S.sX[el][a][i] * S.sRef[q][a * 4 + j];
-            double d = det3(J);
-            if (!(d > 0.0)) atomicMin(A.status, e);
-            double Ji[3][3];
-            inv3(J, d, Ji);
-            double G[NN][3];
+                for (int j = 0; j < 3; ++j) I[k][j] = __shfl(Ji[k], g0 + j);
+            double h[3], F[3];  // row r of du/dxi, of du/dx, then of F
+            geo_row<T>(pt, [&](int a) { return S.sU[el][a][r]; }, h);
 #pragma unroll
-            for (int a = 0; a < NN; ++a)
+            for (int j = 0; j < 3; ++j) F[j] = h[0] * I[0][j] + h[1] * I[1][j] + h[2] * I[2][j];
+            if (nh) {
+                double Q[3], Fi[3];  // column r of J^-1 F^-1 and of F^-1
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    G[a][i] = Ji[0][i] * S.sRef[q][a * 4 + 0] + Ji[1][i] * S.sRef[q][a * 4 + 1] + Ji[2][i] * S.sRef[q][a * 4 + 2];
-                    sG[el].v[q][a][i] = (CT)G[a][i];
-                }
-            double wd = Fam<T>::W * d;
-            S.sC[el][q][0] = (CT)wd;
-            if constexpr (NHK) {
-                if (S.sNH[el]) {
-                    const double lam = S.sLM[el][0], mu = S.sLM[el][1];
-                    double F[3][3];
+                for (int j = 0; j < 3; ++j) F[j] += r == j ? 1.0 : 0.0;
+                const double jf = geo_cofactors(F, g0, r, c);
+                const double ij = 1.0 / jf;
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
+                for (int k = 0; k < 3; ++k) Fi[k] = c[k] * ij;
 #pragma unroll
-                        for (int j = 0; j < 3; ++j) {
-                            double acc = (i == j) ? 1.0 : 0.0;
-#pragma unroll
-                            for (int a = 0; a < NN; ++a) acc += S.sU[el][a][i] * G[a][j];
-                            F[i][j] = acc;
-                        }
-                    double jf = det3(F);
+                for (int k = 0; k < 3; ++k) Q[k] = I[k][0] * Fi[0] + I[k][1] * Fi[1] + I[k][2] * Fi[2];
+                geo_nodes<T>(pt, Q, [&](int a, double v) { sH[el].v[q][a][r] = (CT)v; });
+                const double c2 = mu - lam * log(jf);
+                if (r == 0) {
                     if (!(jf > 0.0)) atomicMin(A.status, e);
-                    double Fi[3][3];
-                    inv3(F, jf, Fi);
-#pragma unroll
-                    for (int a = 0; a < NN; ++a)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j)
-                            sH[el].v[q][a][j] =
-                                (CT)(G[a][0] * Fi[0][j] + G[a][1] * Fi[1][j] + G[a][2] * Fi[2][j]);
                     S.sC[el][q][1] = (CT)(wd * lam);
-                    S.sC[el][q][2] = (CT)(wd * (mu - lam * log(jf)));
+                    S.sC[el][q][2] = (CT)(wd * c2);
                     S.sC[el][q][3] = (CT)(wd * mu);
                 }
+                if constexpr (Smem::RES) {
+                    // row r of P = mu F - (mu - lam ln J) F^-T
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) S.sP[el][q][3 * r + j] = wd * (mu * F[j] - c2 * Fi[j]);
+                }
+            } else if constexpr (Smem::RES) {
+                // row r of sigma = lam tr(H) I + mu (H + H^T)
+                double t = 0.0, col[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const double f0 = __shfl(F[0], g0 + k), f1 = __shfl(F[1], g0 + k), f2 = __shfl(F[2], g0 + k);
+                    col[k] = r == 0 ? f0 : r == 1 ? f1 : f2;
+                    t += k == 0 ? f0 : k == 1 ? f1 : f2;
+                }
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    S.sP[el][q][3 * r + j] = wd * ((r == j ? lam * t : 0.0) + mu * (F[j] + col[j]));
             }
         }
     }
@@ -738,55 +941,22 @@ __device__ inline void elem_rhs(const ElemSmem<T, MODEL, VAR, CT> &S, const int 
                                 CT *f)
 {
     using Smem = ElemSmem<T, MODEL, VAR, CT>;
-    constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, B = Smem::B;
-    constexpr bool RES = MODEL == M_ELASTIC_RES && sizeof(CT) == 8;
+    constexpr int NQ = Fam<T>::NQ, B = Smem::B;
     using GradRec = typename Smem::GradRec;
     const GradRec *sG = reinterpret_cast<const GradRec *>(S.buf);
-    const GradRec *sH = reinterpret_cast<const GradRec *>(S.buf + Smem::NG);
     CT wn = 0;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) wn += S.sC[el][q][0] * (CT)S.sRef[q][a * 4 + 3];
 #pragma unroll
     for (int i = 0; i < B; ++i) f[i] = wn * (CT)src[i];
-    if constexpr (RES) {
-        // f -= f_int_a = sum_q w detJ P grad N_a. Neo-Hookean:
-        // P grad N_a = mu F grad N_a + (lam ln J - mu) F^-T grad N_a,
-        // with F grad N_a = grad N_a + sum_b u_b (grad N_b . grad N_a)
-        // and h_a = F^-T grad N_a from the tangent's records.
-        // Linear: sigma = lam tr(H) I + mu (H + H^T), H = sum_b u_b (x) grad N_b.
-        const bool nh = S.sNH[el] != 0;
-        const double lam = S.sLM[el][0], mu = S.sLM[el][1];
-#pragma unroll 1
+    if constexpr (Smem::RES) {
+        // f -= f_int_a = sum_q w detJ P grad N_a
+#pragma unroll 2
         for (int q = 0; q < NQ; ++q) {
-            const double ga[3] = {sG[el].v[q][a][0], sG[el].v[q][a][1], sG[el].v[q][a][2]};
-            double uh[3] = {0.0, 0.0, 0.0};  // sum_b u_b (G_b . G_a)
-            double hu[3] = {0.0, 0.0, 0.0};  // sum_b (u_b . G_a) G_b
-            double trh = 0.0;                // sum_b u_b . G_b
-            // both loops rolled: unrolled, every node's gradient and
-            // displacement is hoisted into registers for the whole kernel
-            // (residual instances at 133-188 VGPRs)
-#pragma unroll 1
-            for (int b = 0; b < NN; ++b) {
-                const double gb[3] = {sG[el].v[q][b][0], sG[el].v[q][b][1], sG[el].v[q][b][2]};
-                const double ub[3] = {S.sU[el][b][0], S.sU[el][b][1], S.sU[el][b][2]};
-                const double gg = gb[0] * ga[0] + gb[1] * ga[1] + gb[2] * ga[2];
-                const double ug = ub[0] * ga[0] + ub[1] * ga[1] + ub[2] * ga[2];
-                trh += ub[0] * gb[0] + ub[1] * gb[1] + ub[2] * gb[2];
+            const double *P = S.sP[el][q];
+            const CT *g = sG[el].v[q][a];
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    uh[i] += ub[i] * gg;
-                    hu[i] += ug * gb[i];
-                }
-            }
-            if (nh) {
-                const double c0 = S.sC[el][q][3], c2 = S.sC[el][q][2];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) f[i] -= c0 * (ga[i] + uh[i]) - c2 * (double)sH[el].v[q][a][i];
-            } else {
-                const double wd = S.sC[el][q][0];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) f[i] -= wd * (lam * trh * ga[i] + mu * (uh[i] + hu[i]));
-            }
+            for (int i = 0; i < 3; ++i) f[i] -= P[3 * i] * g[0] + P[3 * i + 1] * g[1] + P[3 * i + 2] * g[2];
         }
     }
 }
