@@ -9,9 +9,9 @@
 //
 // Layouts: parameters W1[64][12], b1[64], W2[64][64], b2[64], W3[64], b3;
 // features row-major [n][12]; activations row-major [n][64].
-// Gradients are reduced in a fixed order (per chunk of 64 samples in
-// ascending order, then chunks in ascending order), so training is
-// deterministic.
+// Gradients are reduced in a fixed order that depends on n alone (per wave its
+// tiles of 16 samples in ascending order, then the waves, then the workgroups,
+// the last in FP64), so training is deterministic.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -26,189 +26,384 @@ constexpr int NI = 12, NH = 64;
 constexpr int OW1 = 0, OB1 = OW1 + NH * NI, OW2 = OB1 + NH, OB2 = OW2 + NH * NH, OW3 = OB2 + NH,
               OB3 = OW3 + NH, NPAR = OB3 + 1;
 static_assert(NPAR == FEA_COST_PARAMS, "parameter count");
-constexpr int CHUNK = 64;
 
-// Forward pass, one thread per sample; parameters staged in LDS. When
-// h1/h2/z are given the activations are stored for the backward pass.
-__global__ void __launch_bounds__(256) k_mlp_forward(const float *P, const float *mean, const float *scale,
-                                                     const float *X, int64_t n, float *y, float *z_out,
-                                                     float *h1_out, float *h2_out)
+// The layers are matrix products over the samples, done with FP32 matrix
+// instructions (v_mfma_f32_16x16x4_f32: FP32 products and sums). A wave takes
+// 16 samples through the forward pass, the backward pass and the parameter
+// gradients by itself, its activations in LDS rows of its own and the whole
+// gradient of the three layers in accumulators, so the only barriers are
+// around the weights' load and the final sum over the workgroup's waves.
+//
+// Operand layout of the instruction: lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16] of a 16x4 and a 4x16 factor, and rows 4 (l / 16) + r,
+// column l % 16 of the product. Row strides of 68 (activations, W2) and 20
+// (inputs, W1) words put the 64 operands of one instruction in 64 different
+// banks, except W2 read along its columns (about two per bank).
+//
+// Bound: the matrix instructions, 220 per 16 samples (7,040 cycles of one
+// SIMD), 12 us for 60,000 samples. Measured on MI355X for 60,000 samples: a
+// training step 37 us (this kernel 32, the sum with Adam 5), a prediction 11
+// us; before, 573 and 105 us (one thread per sample in the forward and
+// backward passes, activations through HBM, partial gradients of 64 samples, a
+// 938-term sum per parameter on 20 workgroups). What is left beside the
+// products is the start (weights to LDS) and the end (10 MB of partials) of
+// workgroups that live for one or two tiles per wave.
+constexpr int SW = 68, SX = 20;  // row strides in LDS
+constexpr int WAVE_LDS = 2 * 16 * SW + 16 * SX;
+constexpr int MLP_LDS = NH * SW + NH * SX + 3 * NH + 4 * WAVE_LDS;
+constexpr int MAX_PART = 512;  // workgroups of a training step: two per CU
+static_assert(MLP_LDS >= 3 * (NPAR + 1), "three waves' gradients are summed in the same LDS");
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS written by other lanes of the wave may be read after this.
+__device__ __forceinline__ void wave_lds_sync()
 {
-    __shared__ float sP[NPAR];
-    __shared__ float sM[NI], sS[NI];
-    for (int i = threadIdx.x; i < NPAR; i += 256) sP[i] = P[i];
-    if (threadIdx.x < NI) {
-        sM[threadIdx.x] = mean[threadIdx.x];
-        sS[threadIdx.x] = scale[threadIdx.x];
-    }
-    __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= n) return;
-    float z[NI], h1[NH];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        z[k] = (X[s * NI + k] - sM[k]) / sS[k];
-        if (z_out) z_out[s * NI + k] = z[k];
-    }
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        float a = sP[OB1 + j];
-#pragma unroll
-        for (int k = 0; k < NI; ++k) a += sP[OW1 + j * NI + k] * z[k];
-        h1[j] = a > 0.f ? a : 0.f;
-        if (h1_out) h1_out[s * NH + j] = h1[j];
-    }
-    float out = sP[OB3];
-    for (int i = 0; i < NH; ++i) {
-        float a = sP[OB2 + i];
-#pragma unroll
-        for (int j = 0; j < NH; ++j) a += sP[OW2 + i * NH + j] * h1[j];
-        const float h = a > 0.f ? a : 0.f;
-        if (h2_out) h2_out[s * NH + i] = h;
-        out += sP[OW3 + i] * h;
-    }
-    y[s] = out;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Backward pass per sample: dy = 2 (y - t) / n, da2 = dy W3 (.) [h2 > 0],
-// da1 = (W2^T da2) (.) [h1 > 0]. Also the squared residual for the loss.
-__global__ void __launch_bounds__(256) k_mlp_backward(const float *P, const float *y, const float *t,
-                                                      int64_t n, const float *h1, const float *h2,
-                                                      float *dy_out, float *da1_out, float *da2_out,
-                                                      float *r2_out)
+// Sample tiles of 16: wave w of workgroup b takes tiles 4 b + w, then every
+// (4 gridDim)-th. TRAIN: part[b] receives the workgroup's gradient sums in
+// parameter order and, after them, its sum of squared residuals; otherwise y
+// receives the predictions.
+template <bool TRAIN>
+__global__ void __launch_bounds__(256, 2) k_mlp(const float *P, const float *mean, const float *scale, const float *X,
+                                                const float *target, int64_t n, float *y, float *part)
 {
-    __shared__ float sW2[NH * NH];
-    __shared__ float sW3[NH];
-    for (int i = threadIdx.x; i < NH * NH; i += 256) sW2[i] = P[OW2 + i];
-    if (threadIdx.x < NH) sW3[threadIdx.x] = P[OW3 + threadIdx.x];
-    __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= n) return;
-    const float r = y[s] - t[s];
-    const float dy = 2.f * r / (float)n;
-    dy_out[s] = dy;
-    r2_out[s] = r * r;
-    float da2[NH];
+    __shared__ __align__(16) float lds[MLP_LDS];
+    float *sW2 = lds, *sW1 = sW2 + NH * SW, *sB1 = sW1 + NH * SX, *sB2 = sB1 + NH, *sW3 = sB2 + NH;
+    const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63, c = l & 15, kb = l >> 4;
+    float *sH = sW3 + NH + wave * WAVE_LDS, *sD = sH + 16 * SW, *sZ = sD + 16 * SW;
+    {
+        // all loads before the first use: one memory latency
+        f32x4 w2[4];
+        float w1[3], v = 0.f;
 #pragma unroll
-    for (int i = 0; i < NH; ++i) {
-        da2[i] = h2[s * NH + i] > 0.f ? dy * sW3[i] : 0.f;
-        da2_out[s * NH + i] = da2[i];
-    }
-    for (int j = 0; j < NH; ++j) {
-        float a = 0.f;
+        for (int k = 0; k < 4; ++k) w2[k] = reinterpret_cast<const f32x4 *>(P + OW2)[tid + 256 * k];
 #pragma unroll
-        for (int i = 0; i < NH; ++i) a += sW2[i * NH + j] * da2[i];
-        da1_out[s * NH + j] = h1[s * NH + j] > 0.f ? a : 0.f;
+        for (int k = 0; k < 3; ++k) w1[k] = P[OW1 + tid + 256 * k];
+        if (tid < 3 * NH) v = P[tid < NH ? OB1 + tid : tid < 2 * NH ? OB2 + tid - NH : OW3 + tid - 2 * NH];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = 4 * (tid + 256 * k);
+            *reinterpret_cast<f32x4 *>(sW2 + (i / NH) * SW + i % NH) = w2[k];
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int i = tid + 256 * k;
+            sW1[(i / NI) * SX + i % NI] = w1[k];
+        }
+        if (tid < 3 * NH) sB1[tid] = v;  // b1, b2, W3 back to back
     }
-}
-
-// Partial gradients of one chunk of CHUNK samples, summed in sample order.
-// part[c][p] for every parameter p; part[c][NPAR] = sum of squared residuals.
-__global__ void __launch_bounds__(256) k_mlp_grad_chunk(const float *z, const float *h1, const float *h2,
-                                                        const float *dy, const float *da1,
-                                                        const float *da2, const float *r2, int64_t n,
-                                                        float *part)
-{
-    __shared__ float sz[CHUNK][NI], sh1[CHUNK][NH], sh2[CHUNK][NH], sd1[CHUNK][NH], sd2[CHUNK][NH];
-    __shared__ float sdy[CHUNK], sr2[CHUNK];
-    const int64_t s0 = (int64_t)blockIdx.x * CHUNK;
-    const int cn = (int)std::min<int64_t>(CHUNK, n - s0);
-    for (int i = threadIdx.x; i < cn * NH; i += 256) {
-        const int s = i / NH, j = i % NH;
-        sh1[s][j] = h1[(s0 + s) * NH + j];
-        sh2[s][j] = h2[(s0 + s) * NH + j];
-        sd1[s][j] = da1[(s0 + s) * NH + j];
-        sd2[s][j] = da2[(s0 + s) * NH + j];
-    }
-    for (int i = threadIdx.x; i < cn * NI; i += 256) sz[i / NI][i % NI] = z[(s0 + i / NI) * NI + i % NI];
-    for (int i = threadIdx.x; i < cn; i += 256) {
-        sdy[i] = dy[s0 + i];
-        sr2[i] = r2[s0 + i];
-    }
+    const float b3 = P[OB3];
+    const int zk = l & 15;  // this lane's input feature
+    const float zm = zk < NI ? mean[zk] : 0.f, zs = zk < NI ? scale[zk] : 1.f;
     __syncthreads();
-    float *out = part + (int64_t)blockIdx.x * (NPAR + 1);
-    for (int p = threadIdx.x; p <= NPAR; p += 256) {
-        float acc = 0.f;
-        if (p < OB1) {
-            const int j = (p - OW1) / NI, k = (p - OW1) % NI;
-            for (int s = 0; s < cn; ++s) acc += sd1[s][j] * sz[s][k];
-        } else if (p < OW2) {
-            const int j = p - OB1;
-            for (int s = 0; s < cn; ++s) acc += sd1[s][j];
-        } else if (p < OB2) {
-            const int i = (p - OW2) / NH, j = (p - OW2) % NH;
-            for (int s = 0; s < cn; ++s) acc += sd2[s][i] * sh1[s][j];
-        } else if (p < OW3) {
-            const int i = p - OB2;
-            for (int s = 0; s < cn; ++s) acc += sd2[s][i];
-        } else if (p < OB3) {
-            const int i = p - OW3;
-            for (int s = 0; s < cn; ++s) acc += sdy[s] * sh2[s][i];
-        } else if (p == OB3) {
-            for (int s = 0; s < cn; ++s) acc += sdy[s];
+    float b1[4], b2[4], w3[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        b1[j] = sB1[16 * j + c];
+        b2[j] = sB2[16 * j + c];
+        w3[j] = sW3[16 * j + c];
+    }
+    f32x4 gW2[4][4], gW1[4];
+    float gW3[4], gB2[4], gB1[4], gB3 = 0.f, loss = 0.f;
+    if constexpr (TRAIN) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            gW1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            gW3[i] = gB2[i] = gB1[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) gW2[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    const int64_t tiles = (n + 15) / 16, step = (int64_t)gridDim.x * 4;
+    // a tile's inputs and targets, at clamped positions (beyond n they are not
+    // used), loaded one tile ahead
+    float xn[4], tn[4] = {0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](int64_t t0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t s = t0 * 16 + kb + 4 * i;
+            xn[i] = X[(s < n ? s : n - 1) * NI + (zk < NI ? zk : 0)];
+            if constexpr (TRAIN) {
+                const int64_t q = t0 * 16 + 4 * kb + i;
+                tn[i] = target[q < n ? q : n - 1];
+            }
+        }
+    };
+    fetch((int64_t)blockIdx.x * 4 + wave);
+    for (int64_t t0 = (int64_t)blockIdx.x * 4 + wave; t0 < tiles; t0 += step) {
+        const int64_t s0 = t0 * 16;
+        // standardised inputs, columns 12 .. 15 zero
+        float tv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = kb + 4 * i;
+            sZ[s * SX + zk] = zk < NI && s0 + s < n ? (xn[i] - zm) / zs : 0.f;
+            tv[i] = tn[i];
+        }
+        fetch(t0 + step);
+        wave_lds_sync();
+        f32x4 h1[4], h2[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            h1[j] = f32x4{b1[j], b1[j], b1[j], b1[j]};
+            h2[j] = f32x4{b2[j], b2[j], b2[j], b2[j]};
+        }
+#pragma unroll
+        for (int t = 0; t < NI / 4; ++t) {
+            const float a = sZ[c * SX + 4 * t + kb];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                h1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sW1[(16 * j + c) * SX + 4 * t + kb], h1[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                h1[j][r] = h1[j][r] > 0.f ? h1[j][r] : 0.f;
+                sH[(4 * kb + r) * SW + 16 * j + c] = h1[j][r];
+            }
+        wave_lds_sync();
+#pragma unroll 4
+        for (int t = 0; t < NH / 4; ++t) {
+            const float a = sH[c * SW + 4 * t + kb];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                h2[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sW2[(16 * j + c) * SW + 4 * t + kb], h2[j], 0, 0, 0);
+        }
+        float out[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                h2[j][r] = h2[j][r] > 0.f ? h2[j][r] : 0.f;
+                out[r] += w3[j] * h2[j][r];
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) out[r] += __shfl_xor(out[r], o);
+            out[r] += b3;
+        }
+        if constexpr (!TRAIN) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (c == r && s0 + 4 * kb + r < n) y[s0 + 4 * kb + r] = out[r];
         } else {
-            for (int s = 0; s < cn; ++s) acc += sr2[s];
+            // dy = 2 (y - t) / n, dA2 = dy W3 (.) [h2 > 0]
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool ok = s0 + 4 * kb + r < n;
+                const float res = ok ? out[r] - tv[r] : 0.f, dy = ok ? 2.f * res / (float)n : 0.f;
+                loss += res * res;
+                gB3 += dy;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float d = h2[j][r] > 0.f ? dy * w3[j] : 0.f;
+                    gW3[j] += dy * h2[j][r];
+                    gB2[j] += d;
+                    sD[(4 * kb + r) * SW + 16 * j + c] = d;
+                }
+            }
+            wave_lds_sync();
+            // dA1 = (dA2 W2) (.) [h1 > 0]
+            f32x4 d1[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d1[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int t = 0; t < NH / 4; ++t) {
+                const float a = sD[c * SW + 4 * t + kb];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    d1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sW2[(4 * t + kb) * SW + 16 * j + c], d1[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    d1[j][r] = h1[j][r] > 0.f ? d1[j][r] : 0.f;
+                    gB1[j] += d1[j][r];
+                }
+            // gradient of W2: sum over the samples of dA2 (x) h1
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float a[4], b[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    a[j] = sD[(t + 4 * kb) * SW + 16 * j + c];
+                    b[j] = sH[(t + 4 * kb) * SW + 16 * j + c];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        gW2[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], gW2[i][j], 0, 0, 0);
+            }
+            wave_lds_sync();
+            // and of W1: dA1 (x) z, dA1 in the place of h1
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sH[(4 * kb + r) * SW + 16 * j + c] = d1[j][r];
+            wave_lds_sync();
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float b = sZ[(t + 4 * kb) * SX + c];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    gW1[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sH[(t + 4 * kb) * SW + 16 * i + c], b, gW1[i], 0, 0, 0);
+            }
         }
-        out[p] = acc;
+        wave_lds_sync();  // the tile's rows are no longer read
     }
-}
-
-// Sum of the chunk partials in chunk order; loss = sum r^2 / n.
-__global__ void k_mlp_grad_final(const float *part, int64_t nchunks, int64_t n, float *grad, float *loss)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p > NPAR) return;
-    float acc = 0.f;
-    for (int64_t c = 0; c < nchunks; ++c) acc += part[c * (NPAR + 1) + p];
-    if (p < NPAR) {
-        if (grad) grad[p] = acc;
-    } else if (loss) {
-        *loss = acc / (float)n;
-    }
-}
-
-__global__ void k_adam(float *P, float *m, float *v, const float *g, float lr, float b1, float b2,
-                       float eps, float c1, float c2)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= NPAR) return;
-    const float gp = g[p];
-    const float mp = b1 * m[p] + (1.f - b1) * gp;
-    const float vp = b2 * v[p] + (1.f - b2) * gp * gp;
-    m[p] = mp;
-    v[p] = vp;
-    P[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
-}
-
-// Per-feature mean and population standard deviation, one workgroup per
-// feature, fixed reduction order.
-__global__ void __launch_bounds__(256) k_norm(const float *X, int64_t n, float *mean, float *scale)
-{
-    __shared__ double s1[256], s2[256];
-    const int k = blockIdx.x;
-    double a = 0.0, b = 0.0;
-    for (int64_t s = threadIdx.x; s < n; s += 256) {
-        const double x = X[s * NI + k];
-        a += x;
-        b += x * x;
-    }
-    s1[threadIdx.x] = a;
-    s2[threadIdx.x] = b;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) {
-            s1[threadIdx.x] += s1[threadIdx.x + off];
-            s2[threadIdx.x] += s2[threadIdx.x + off];
+    if constexpr (TRAIN) {
+        // the vectors' sums over the lanes' four row groups; b3 and the loss
+        // are the same in the 16 lanes of a row group
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                gW3[j] += __shfl_xor(gW3[j], o);
+                gB2[j] += __shfl_xor(gB2[j], o);
+                gB1[j] += __shfl_xor(gB1[j], o);
+            }
+            gB3 += __shfl_xor(gB3, o);
+            loss += __shfl_xor(loss, o);
         }
+        // waves 1 .. 3 to regions of their own, wave 0 added to wave 1's, then
+        // the sum of the three
+        float *mine = lds + (wave ? wave - 1 : 0) * (NPAR + 1);
+        auto put = [&](bool add) {
+            auto at = [&](int p, float v) { mine[p] = add ? v + mine[p] : v; };
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int u = 16 * i + 4 * kb + r;
+                    if (c < NI) at(OW1 + u * NI + c, gW1[i][r]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) at(OW2 + u * NH + 16 * j + c, gW2[i][j][r]);
+                }
+            if (kb == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    at(OB1 + 16 * j + c, gB1[j]);
+                    at(OB2 + 16 * j + c, gB2[j]);
+                    at(OW3 + 16 * j + c, gW3[j]);
+                }
+            }
+            if (l == 0) {
+                at(OB3, gB3);
+                at(NPAR, loss);
+            }
+        };
         __syncthreads();
+        if (wave) put(false);
+        __syncthreads();
+        if (!wave) put(true);
+        __syncthreads();
+        for (int p = tid; p <= NPAR; p += 256)
+            part[(int64_t)blockIdx.x * (NPAR + 1) + p] = lds[p] + lds[NPAR + 1 + p] + lds[2 * (NPAR + 1) + p];
     }
-    if (threadIdx.x == 0) {
-        const double mu = s1[0] / (double)n;
-        const double var = std::max(0.0, s2[0] / (double)n - mu * mu);
-        const double sd = sqrt(var);
-        mean[k] = (float)mu;
-        scale[k] = sd > 1e-12 ? (float)sd : 1.f;
+}
+
+// Sum of the workgroups' partials in FP64, 64 parameters per workgroup: wave w
+// of 16 takes rows w, w + 16, ... in order, then the 16 sums are added in
+// order. grad and loss (sum r^2 / n) may be NULL; ADAM: the parameters' step
+// with this gradient.
+struct AdamArgs {
+    float *P, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+template <bool ADAM>
+__global__ void __launch_bounds__(1024) k_mlp_reduce(const float *part, int rows, int64_t n, float *grad, float *loss,
+                                                     AdamArgs A)
+{
+    __shared__ double sum[16][64];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = blockIdx.x * 64 + l;
+    double acc = 0.0;
+    if (p <= NPAR) {
+#pragma unroll 8
+        for (int r = w; r < rows; r += 16) acc += (double)part[(int64_t)r * (NPAR + 1) + p];
     }
+    sum[w][l] = acc;
+    __syncthreads();
+    if (w || p > NPAR) return;
+#pragma unroll
+    for (int k = 1; k < 16; ++k) acc += sum[k][l];
+    if (p == NPAR) {
+        if (loss) *loss = (float)acc / (float)n;
+        return;
+    }
+    const float g = (float)acc;
+    if (grad) grad[p] = g;
+    if constexpr (ADAM) {
+        const float mp = A.b1 * A.m[p] + (1.f - A.b1) * g;
+        const float vp = A.b2 * A.v[p] + (1.f - A.b2) * g * g;
+        A.m[p] = mp;
+        A.v[p] = vp;
+        A.P[p] -= A.lr * (mp / A.c1) / (sqrtf(vp / A.c2) + A.eps);
+    }
+}
+
+// Per-feature mean and population standard deviation, in FP64 and a fixed
+// order: thread t of workgroup b sums elements 252 b + t + k * 252 * gridDim of
+// the row-major features (252 = 21 rows, so an element's feature is t % 12),
+// the workgroup its 21 threads of a feature, the last kernel the workgroups.
+// 11 us for 60,000 samples; with one workgroup per feature (12 of 256 CUs) 68.
+constexpr int NORM_T = 21 * NI, NORM_WG = 128;
+
+__global__ void __launch_bounds__(256) k_norm_part(const float *X, int64_t n, double *part)
+{
+    __shared__ double s1[NORM_T], s2[NORM_T];
+    const int t = threadIdx.x;
+    if (t < NORM_T) {
+        double a = 0.0, b = 0.0;
+        for (int64_t i = (int64_t)blockIdx.x * NORM_T + t; i < n * NI; i += (int64_t)gridDim.x * NORM_T) {
+            const double x = X[i];
+            a += x;
+            b += x * x;
+        }
+        s1[t] = a;
+        s2[t] = b;
+    }
+    __syncthreads();
+    if (t < 2 * NI) {
+        const double *s = t < NI ? s1 : s2;
+        double a = 0.0;
+        for (int r = 0; r < 21; ++r) a += s[r * NI + t % NI];
+        part[blockIdx.x * 2 * NI + t] = a;
+    }
+}
+
+constexpr int NORM_SEG = 32;
+
+__global__ void __launch_bounds__(2 * NI * NORM_SEG) k_norm_final(const double *part, int rows, int64_t n, float *mean,
+                                                                  float *scale)
+{
+    __shared__ double s[NORM_SEG][2 * NI];
+    const int c = threadIdx.x % (2 * NI), seg = threadIdx.x / (2 * NI);
+    double a = 0.0;
+    for (int r = seg; r < rows; r += NORM_SEG) a += part[r * 2 * NI + c];
+    s[seg][c] = a;
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k >= NI) return;
+    double s1 = 0.0, s2 = 0.0;
+    for (int r = 0; r < NORM_SEG; ++r) {
+        s1 += s[r][k];
+        s2 += s[r][NI + k];
+    }
+    const double mu = s1 / (double)n;
+    const double var = std::max(0.0, s2 / (double)n - mu * mu);
+    const double sd = sqrt(var);
+    mean[k] = (float)mu;
+    scale[k] = sd > 1e-12 ? (float)sd : 1.f;
 }
 
 __global__ void k_log_cycles(const uint64_t *c, int64_t n, float *t)
@@ -223,12 +418,12 @@ using namespace fea;
 
 struct fea_cost {
     int device = 0;
-    float *P = nullptr, *m = nullptr, *v = nullptr, *g = nullptr, *mean = nullptr, *scale = nullptr;
-    float *loss = nullptr;
+    float *P = nullptr, *m = nullptr, *v = nullptr, *mean = nullptr, *scale = nullptr;
+    double *norm = nullptr;  // partial sums of fit_norm
     int64_t step = 0;
-    // activations workspace
+    // partial gradients, one row of NPAR + 1 per workgroup
     float *ws = nullptr;
-    int64_t ws_n = 0;
+    int64_t ws_rows = 0;
 };
 
 namespace {
@@ -252,56 +447,38 @@ double normal(uint64_t &x)
 void destroy_cost(fea_cost *c)
 {
     if (!c) return;
-    void *bufs[] = {c->P, c->m, c->v, c->g, c->mean, c->scale, c->loss, c->ws};
-    for (void *p : bufs) dfree(p);
+    dfree(c->P);  // with it m, v, mean, scale and norm
+    dfree(c->ws);
     delete c;
 }
 
-// workspace: z[n][12], h1, h2, da1, da2 [n][64], y, dy, r2 [n], partials
+// Workgroups of a training step over n samples (four waves of 16 samples).
+int64_t part_rows(int64_t n) { return std::min<int64_t>(MAX_PART, (n + 63) / 64); }
+
 int ensure_ws(fea_cost *c, int64_t n)
 {
-    if (c->ws && c->ws_n >= n) return FEA_OK;
+    const int64_t rows = part_rows(n);
+    if (c->ws && c->ws_rows >= rows) return FEA_OK;
     dfree(c->ws);
     c->ws = nullptr;
-    c->ws_n = 0;
-    const int64_t nch = (n + CHUNK - 1) / CHUNK;
-    const size_t floats = (size_t)n * (NI + 4 * NH + 3) + (size_t)nch * (NPAR + 1);
-    int rc = dalloc((void **)&c->ws, sizeof(float) * std::max<size_t>(floats, 1));
+    c->ws_rows = 0;
+    int rc = dalloc((void **)&c->ws, sizeof(float) * (size_t)rows * (NPAR + 1));
     if (rc) return rc;
-    c->ws_n = n;
+    c->ws_rows = rows;
     return FEA_OK;
 }
 
-struct Ws {
-    float *z, *h1, *h2, *da1, *da2, *y, *dy, *r2, *part;
-};
-
-Ws carve(const fea_cost *c, int64_t n)
-{
-    Ws w;
-    float *p = c->ws;
-    w.z = p; p += n * NI;
-    w.h1 = p; p += n * NH;
-    w.h2 = p; p += n * NH;
-    w.da1 = p; p += n * NH;
-    w.da2 = p; p += n * NH;
-    w.y = p; p += n;
-    w.dy = p; p += n;
-    w.r2 = p; p += n;
-    w.part = p;
-    return w;
-}
-
+// One pass over the samples and the sum of its partials; with adam, the step.
 int grad_impl(const fea_cost *c, const float *X, const float *t, int64_t n, float *grad, float *loss,
-              hipStream_t s)
+              const AdamArgs *adam, hipStream_t s)
 {
-    Ws w = carve(c, n);
-    const unsigned nb = grid_for(n, 256);
-    k_mlp_forward<<<nb, 256, 0, s>>>(c->P, c->mean, c->scale, X, n, w.y, w.z, w.h1, w.h2);
-    k_mlp_backward<<<nb, 256, 0, s>>>(c->P, w.y, t, n, w.h1, w.h2, w.dy, w.da1, w.da2, w.r2);
-    const int64_t nch = (n + CHUNK - 1) / CHUNK;
-    k_mlp_grad_chunk<<<(unsigned)nch, 256, 0, s>>>(w.z, w.h1, w.h2, w.dy, w.da1, w.da2, w.r2, n, w.part);
-    k_mlp_grad_final<<<grid_for(NPAR + 1, 256), 256, 0, s>>>(w.part, nch, n, grad, loss);
+    const int rows = (int)part_rows(n);
+    k_mlp<true><<<rows, 256, 0, s>>>(c->P, c->mean, c->scale, X, t, n, nullptr, c->ws);
+    const unsigned nb = grid_for(NPAR + 1, 64);
+    if (adam)
+        k_mlp_reduce<true><<<nb, 1024, 0, s>>>(c->ws, rows, n, grad, loss, *adam);
+    else
+        k_mlp_reduce<false><<<nb, 1024, 0, s>>>(c->ws, rows, n, grad, loss, AdamArgs());
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
@@ -328,28 +505,26 @@ extern "C" int fea_cost_create(uint64_t seed, fea_cost **out)
     *out = nullptr;
     fea_cost *c = new (std::nothrow) fea_cost();
     if (!c) return set_error(FEA_ENOMEM, "host allocation failed");
-    int rc = 0;
     (void)hipGetDevice(&c->device);
-    float **bufs[] = {&c->P, &c->m, &c->v, &c->g};
-    for (float **b : bufs)
-        if (!rc) rc = dalloc((void **)b, sizeof(float) * NPAR);
-    if (!rc) rc = dalloc((void **)&c->mean, sizeof(float) * NI);
-    if (!rc) rc = dalloc((void **)&c->scale, sizeof(float) * NI);
-    if (!rc) rc = dalloc((void **)&c->loss, sizeof(float));
+    // one block: parameters, Adam moments, standardisation, partial sums
+    constexpr size_t PP = (NPAR + 63) / 64 * 64, HEAD = 3 * PP + 64;
+    int rc = dalloc((void **)&c->P, sizeof(float) * HEAD + sizeof(double) * NORM_WG * 2 * NI);
     if (rc) {
         destroy_cost(c);
         return rc;
     }
-    std::vector<float> P(NPAR, 0.f), zero(NPAR, 0.f), mean(NI, 0.f), scale(NI, 1.f);
+    c->m = c->P + PP;
+    c->v = c->m + PP;
+    c->mean = c->v + PP;
+    c->scale = c->mean + 32;
+    c->norm = reinterpret_cast<double *>(c->P + HEAD);
+    std::vector<float> P(HEAD, 0.f);
     uint64_t st = seed;
     for (int i = 0; i < NH * NI; ++i) P[OW1 + i] = (float)(normal(st) * sqrt(2.0 / NI));
     for (int i = 0; i < NH * NH; ++i) P[OW2 + i] = (float)(normal(st) * sqrt(2.0 / NH));
     for (int i = 0; i < NH; ++i) P[OW3 + i] = (float)(normal(st) * sqrt(2.0 / NH));
-    hipError_t e = hipMemcpy(c->P, P.data(), sizeof(float) * NPAR, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->m, zero.data(), sizeof(float) * NPAR, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->v, zero.data(), sizeof(float) * NPAR, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->mean, mean.data(), sizeof(float) * NI, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->scale, scale.data(), sizeof(float) * NI, hipMemcpyHostToDevice);
+    std::fill(P.begin() + 3 * PP + 32, P.begin() + 3 * PP + 32 + NI, 1.f);
+    hipError_t e = hipMemcpy(c->P, P.data(), sizeof(float) * HEAD, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         destroy_cost(c);
         return set_error(FEA_EHIP, "upload failed: %s", hipGetErrorString(e));
@@ -393,7 +568,9 @@ extern "C" int fea_cost_fit_norm(fea_cost *c, const float *feats, int64_t n, hip
     int rc = check(c);
     if (rc) return rc;
     if (n <= 0 || !feats) return set_error(FEA_EINVAL, "need features");
-    k_norm<<<NI, 256, 0, s>>>(feats, n, c->mean, c->scale);
+    const int rows = (int)std::min<int64_t>(NORM_WG, (n + 20) / 21);
+    k_norm_part<<<rows, 256, 0, s>>>(feats, n, c->norm);
+    k_norm_final<<<1, 2 * NI * NORM_SEG, 0, s>>>(c->norm, rows, n, c->mean, c->scale);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
@@ -404,7 +581,9 @@ extern "C" int fea_cost_predict(const fea_cost *c, const float *feats, int64_t n
     int rc = check(c);
     if (rc) return rc;
     if (n < 0 || (n > 0 && (!feats || !pred))) return set_error(FEA_EINVAL, "bad arguments");
-    if (n) k_mlp_forward<<<grid_for(n, 256), 256, 0, s>>>(c->P, c->mean, c->scale, feats, n, pred, nullptr, nullptr, nullptr);
+    if (n)
+        k_mlp<false><<<(unsigned)std::min<int64_t>(2 * MAX_PART, (n + 63) / 64), 256, 0, s>>>(
+            c->P, c->mean, c->scale, feats, nullptr, n, pred, nullptr);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
@@ -417,7 +596,7 @@ extern "C" int fea_cost_grad(const fea_cost *c, const float *feats, const float 
     if (rc) return rc;
     if (n <= 0 || !feats || !target) return set_error(FEA_EINVAL, "bad arguments");
     if ((rc = ensure_ws(const_cast<fea_cost *>(c), n))) return rc;
-    return grad_impl(c, feats, target, n, grad, loss, s);
+    return grad_impl(c, feats, target, n, grad, loss, nullptr, s);
 }
 
 extern "C" int fea_cost_train(fea_cost *c, const float *feats, const float *target, int64_t n, int steps,
@@ -430,12 +609,11 @@ extern "C" int fea_cost_train(fea_cost *c, const float *feats, const float *targ
     if ((rc = ensure_ws(c, n))) return rc;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     for (int k = 0; k < steps; ++k) {
-        if ((rc = grad_impl(c, feats, target, n, c->g, loss_hist ? loss_hist + k : c->loss, s))) return rc;
+        const float c1 = 1.f - powf(b1, (float)(c->step + 1)), c2 = 1.f - powf(b2, (float)(c->step + 1));
+        const AdamArgs adam = {c->P, c->m, c->v, lr, b1, b2, eps, c1, c2};
+        if ((rc = grad_impl(c, feats, target, n, nullptr, loss_hist ? loss_hist + k : nullptr, &adam, s))) return rc;
         c->step += 1;
-        const float c1 = 1.f - powf(b1, (float)c->step), c2 = 1.f - powf(b2, (float)c->step);
-        k_adam<<<grid_for(NPAR, 256), 256, 0, s>>>(c->P, c->m, c->v, c->g, lr, b1, b2, eps, c1, c2);
     }
-    FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
 
