@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <type_traits>
 
 namespace fea {
 
@@ -20,14 +21,15 @@ namespace fea {
 // segment.
 //
 // Launch shape per workspace type: bytes per load, rounds (segments per
-// thread) and LDS bytes per chunk. Measured on MI355X over the workspaces of
-// the 96^3-cell hybrid mesh: FP64 streams best with 8-byte loads and one segment per
-// thread; FP32 segments are half as long, and 16-byte loads with four
-// segments per thread amortise the per-workgroup work (about 15% faster than
-// one 4-byte load per segment and thread).
+// thread) and LDS bytes per chunk. It streams: 5 TB/s of tile contributions.
+// Measured on MI355X over row-owner workspaces (pyr5 of 40^3 cells / hex8 of
+// 60^3, ms): FP64 with 8-byte loads 0.20 / 0.35, 16-byte 0.20 / 0.33, two
+// rounds 0.20 / 0.33, 8 KB chunks 0.21 / 0.34; FP32, whose segments are half as
+// long, 16-byte loads with four rounds 0.095 / 0.160, three 0.093 / 0.166, two
+// 0.097 / 0.192.
 template <typename CT>
 struct SegCfg {
-    static constexpr int LOAD_BYTES = sizeof(CT) == 8 ? 8 : 16;
+    static constexpr int LOAD_BYTES = 16;
     static constexpr int ROUNDS = sizeof(CT) == 8 ? 1 : 4;
     static constexpr int CHUNK_BYTES = 16384;
 };
@@ -43,17 +45,17 @@ struct SegStage {
     static constexpr int NV = CAPV / VEC;
     static constexpr int LV = NV / 256;                         // loads per thread per chunk
     static constexpr int CAPS = (CAPV - 2 * VEC) / W;           // slots per chunk (room for the alignment shift)
-    struct alignas(VEC * sizeof(CT)) Vec {
-        CT x[VEC];
-    };
+    // (a struct of VEC values would go through scratch memory)
+    using Vec = typename std::conditional<VEC == 1, CT, CT __attribute__((ext_vector_type(VEC == 1 ? 2 : VEC)))>::type;
 
     // Slots base .. base + ns (0 < ns <= CAPS) of the workspace into sv, by the
     // whole workgroup; returns the place of the first one's value 0 in sv.
     // Whole vectors are read, so up to VEC - 1 values on either side of the
     // range come along (the workspace is padded by one vector, see
-    // kSegPad). Threads beyond the range repeat its last vector: every load
-    // of a chunk is issued before the first is waited for, without branches
-    // inside a wave. again: the previous chunk's readers have to be waited for.
+    // kSegPad). Threads beyond the range load its last vector again and drop
+    // it: every load of a chunk is issued before the first is waited for,
+    // without branches inside a wave. again: the previous chunk's readers have
+    // to be waited for.
     static __device__ inline int load(Vec *sv, const CT *data, int64_t base, int ns, bool again)
     {
         const int tid = threadIdx.x;
@@ -74,8 +76,8 @@ struct SegStage {
 #pragma unroll
         for (int q = 0; q < LV; ++q)
             if (q * 256 < nvec) {
-                const unsigned off = min((unsigned)(tid + q * 256) * (unsigned)sizeof(Vec), last);
-                *reinterpret_cast<Vec *>(dst + off) = v[q];
+                const unsigned off = (unsigned)(tid + q * 256) * (unsigned)sizeof(Vec);
+                if (off <= last) *reinterpret_cast<Vec *>(dst + off) = v[q];
             }
         __syncthreads();
         return o;
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, c
     constexpr int BPW = TPS * R;                // segments per workgroup
     using Stage = SegStage<W, CT, SegCfg<CT>::LOAD_BYTES, SegCfg<CT>::CHUNK_BYTES>;
     __shared__ typename Stage::Vec sv[Stage::NV];
-    const CT *svs = sv[0].x;
+    const CT *svs = reinterpret_cast<const CT *>(sv);
     const int tid = threadIdx.x;
     const int64_t m0 = (int64_t)blockIdx.x * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
@@ -144,13 +146,12 @@ __global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, c
 // and the pieces of one line of lower blocks were written by workgroups on
 // different XCDs (see sym_run_tile). Measured on MI355X, before -> after, ms,
 // FP64 / FP32 tile sums: 96^3-cell hybrid mesh (11.6M outputs) 0.92 -> 0.80 /
-// 0.70 -> 0.53, 160^3 cells (50M) 4.01 -> 3.49 FP64. The first change alone
-// gave 0.96 / 0.55: without the runs it only brings the scattered writers
-// closer together. 8 KB chunks: 16 KB hold FP32 back (0.80), a workgroup's
-// outputs having about 4 KB of tile sums. FP64 with 16-byte loads 0.83, two
-// rounds 0.84; runs of 16 / 128 / 512 / 1024 / 2048 / 8192 ranges 0.89 / 0.82
-// / 0.79 / 0.80 / 0.81 / 0.87 (160^3: - / 3.77 / 3.54 / 3.49 / 3.51 / 3.62);
-// non-temporal loads 0.85.
+// 0.70 -> 0.49, 160^3 cells (50M) 4.01 -> 3.49 FP64. The first change alone
+// gave 0.96 in FP64: without the runs it only brings the scattered writers
+// closer together. FP64 with 16-byte loads 0.83, two rounds 0.84; runs of 16 /
+// 128 / 512 / 1024 / 2048 / 8192 ranges 0.89 / 0.82 / 0.79 / 0.80 / 0.81 / 0.87
+// (160^3: - / 3.77 / 3.54 / 3.49 / 3.51 / 3.62); non-temporal loads 0.88. FP32
+// with one round 0.61, three or four 0.49 and 0.50.
 template <typename CT>
 struct SymSegCfg {
     static constexpr int LOAD_BYTES = sizeof(CT) == 8 ? 8 : 16;
@@ -182,7 +183,7 @@ __global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *bl
     constexpr int BPW = TPS * R;                                      // outputs per workgroup
     using Stage = SegStage<W, CT, SymSegCfg<CT>::LOAD_BYTES, SymSegCfg<CT>::CHUNK_BYTES>;
     __shared__ typename Stage::Vec sv[Stage::NV];
-    const CT *svs = sv[0].x;
+    const CT *svs = reinterpret_cast<const CT *>(sv);
     const int tid = threadIdx.x;
     const int64_t m0 = sym_run_tile(blockIdx.x, gridDim.x) * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
