@@ -19,26 +19,6 @@
 namespace fea {
 
 // ------------------------------------------------------------ validation
-__global__ void k_validate(int64_t n_nodes, int64_t n_elems, const uint8_t *types,
-                           const int64_t *conn_ptr, const int32_t *conn, int64_t *bad)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_elems) return;
-    int t = types[e];
-    bool ok = t < 4;
-    int nn = ok ? nodes_of(t) : 0;
-    int64_t b = conn_ptr[e];
-    ok = ok && (conn_ptr[e + 1] - b == nn) && b >= 0 && (e > 0 || b == 0);
-    if (ok) {
-        for (int a = 0; a < nn && ok; ++a) {
-            int32_t v = conn[b + a];
-            ok = v >= 0 && v < n_nodes;
-            for (int c = 0; c < a && ok; ++c) ok = conn[b + c] != v;
-        }
-    }
-    if (!ok) atomicMin((unsigned long long *)bad, (unsigned long long)e);
-}
-
 // Fingerprint of a validated mesh's connectivity: the sum over elements,
 // modulo 2^64, of a SplitMix64-style mix of the element id, its family and
 // its node ids in order (integer addition, so the result does not depend on
@@ -52,264 +32,408 @@ __device__ inline uint64_t fp_mix(uint64_t z)
     return z ^ (z >> 31);
 }
 
-__global__ void k_mesh_fingerprint(int64_t n_elems, const uint8_t *types, const int64_t *conn_ptr,
-                                   const int32_t *conn, unsigned long long *out)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_elems) return;
-    const int t = types[e];
-    uint64_t h = fp_mix((uint64_t)e ^ ((uint64_t)t << 56));
-    for (int64_t p = conn_ptr[e]; p < conn_ptr[e + 1]; ++p) h = fp_mix(h ^ (uint64_t)(uint32_t)conn[p]);
-    atomicAdd(out, (unsigned long long)h);
-}
+// What the host needs to know of a mesh before it sizes anything.
+struct MeshCheck {
+    unsigned long long bad;     // first invalid element, ~0 if there is none
+    unsigned long long fp;      // fingerprint (of a valid mesh)
+    unsigned long long fam[4];  // elements of every family
+};
 
-__global__ void k_slot_count(int64_t n_elems, const uint8_t *types, int64_t *cnt)
+// One thread per element: validity, fingerprint and family in one pass over
+// the connectivity, with one addition per workgroup to each total (one per
+// element to the fingerprint alone cost 0.63 ms on 0.9 M elements). fam_cnt
+// (may be null): the workgroup's elements of family t at [t * gridDim + b].
+__global__ void __launch_bounds__(256) k_mesh_check(int64_t n_nodes, int64_t n_elems, const uint8_t *types,
+                                                    const int64_t *conn_ptr, const int32_t *conn, MeshCheck *out,
+                                                    int32_t *fam_cnt)
 {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_elems) return;
-    int nn = nodes_of(types[e]);
-    cnt[e] = (int64_t)nn * nn;
+    __shared__ unsigned long long part[4];
+    __shared__ int wcnt[4][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    uint64_t h = 0;
+    int t = 4;
+    if (e < n_elems) {
+        t = types[e];
+        bool ok = t < 4;
+        const int nn = ok ? nodes_of(t) : 0;
+        const int64_t b = conn_ptr[e];
+        ok = ok && (conn_ptr[e + 1] - b == nn) && b >= 0 && (e > 0 || b == 0);
+        if (ok) {
+            int32_t v[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a) v[a] = conn[b + (a < nn ? a : nn - 1)];
+            h = fp_mix((uint64_t)e ^ ((uint64_t)t << 56));
+#pragma unroll
+            for (int a = 0; a < 8; ++a)
+                if (a < nn) {
+                    ok = ok && v[a] >= 0 && v[a] < n_nodes;
+#pragma unroll
+                    for (int c = 0; c < a; ++c) ok = ok && v[c] != v[a];
+                    h = fp_mix(h ^ (uint64_t)(uint32_t)v[a]);
+                }
+        }
+        if (!ok) atomicMin(&out->bad, (unsigned long long)e);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) h += (uint64_t)__shfl_xor((unsigned long long)h, o);
+    if (lane == 0) part[wave] = h;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        const uint64_t m = __ballot(t == f);
+        if (lane == 0) wcnt[wave][f] = __popcll(m);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&out->fp, part[0] + part[1] + part[2] + part[3]);
+    if (threadIdx.x < 4) {
+        const int f = threadIdx.x, n = wcnt[0][f] + wcnt[1][f] + wcnt[2][f] + wcnt[3][f];
+        if (n) atomicAdd(&out->fam[f], (unsigned long long)n);
+        if (fam_cnt) fam_cnt[(int64_t)f * gridDim.x + blockIdx.x] = n;
+    }
 }
 
 // ------------------------------------------------------ type segmentation
-__global__ void k_type_flags(int64_t n_elems, const uint8_t *types, int t, uint8_t *flag)
+// Stable partition by family from the scanned per-workgroup counts (base:
+// family-major, as k_mesh_check wrote them): every element's place in the
+// type-sorted order (perm and its inverse epos) and, from the families'
+// counts before it, its first element-matrix slot (map_ptr).
+__global__ void __launch_bounds__(256) k_type_place(int64_t n_elems, const uint8_t *types, const int64_t *base,
+                                                    int32_t *perm, int32_t *epos, int64_t *map_ptr)
 {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n_elems) flag[e] = types[e] == t;
-}
-
-__global__ void k_type_place(int64_t n_elems, const uint8_t *types, int t, const int64_t *pos,
-                             int64_t base, int32_t *perm)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n_elems && types[e] == t) perm[base + pos[e]] = (int32_t)e;
+    __shared__ int wcnt[4][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x, nb = gridDim.x;
+    const int t = e < n_elems ? types[e] : 4;
+    int before[4];  // same family, same wave, lower lane
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        const uint64_t m = __ballot(t == f);
+        before[f] = __popcll(m & ((1ull << lane) - 1));
+        if (lane == 0) wcnt[wave][f] = __popcll(m);
+    }
+    __syncthreads();
+    if (e >= n_elems) return;
+    int64_t slot = 0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        int64_t p = base[f * nb + blockIdx.x] + before[f];
+        for (int w = 0; w < wave; ++w) p += wcnt[w][f];
+        slot += (p - base[f * nb]) * (nodes_of(f) * nodes_of(f));
+        if (t == f) {
+            perm[p] = (int32_t)e;
+            epos[e] = (int32_t)p;
+        }
+    }
+    map_ptr[e] = slot;
+    if (e == n_elems - 1) map_ptr[n_elems] = slot + nodes_of(t) * nodes_of(t);
 }
 
 // --------------------------------------------------------- node incidence
-__global__ void k_node_count(int64_t conn_len, const int32_t *conn, int32_t *cnt)
+// Per node the number of incident elements (high word) and the sum of their
+// node counts, which is the number of element-matrix slots in the node's
+// block row (low word); both totals stay below 2^31. The count before the
+// addition is the incidence's place in the node's unsorted list.
+__global__ void __launch_bounds__(256) k_node_count(int64_t n_elems, const int64_t *conn_ptr, const int32_t *conn,
+                                                    unsigned long long *cnt, int32_t *place)
 {
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < conn_len) atomicAdd(&cnt[conn[p]], 1);
-}
-
-__global__ void k_node_fill(int64_t n_elems, const int64_t *conn_ptr, const int32_t *conn,
-                            const int64_t *n2e_ptr, int32_t *cursor, int32_t *n2e, uint8_t *n2a)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= n_elems) return;
-    for (int64_t p = conn_ptr[e]; p < conn_ptr[e + 1]; ++p) {
-        int32_t v = conn[p];
-        int32_t slot = atomicAdd(&cursor[v], 1);
-        n2e[n2e_ptr[v] + slot] = (int32_t)e;
-        n2a[n2e_ptr[v] + slot] = (uint8_t)(p - conn_ptr[e]);
-    }
+    const int64_t b = conn_ptr[e];
+    const int nn = (int)(conn_ptr[e + 1] - b);
+    int32_t v[8];
+    unsigned long long old[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) v[a] = conn[b + (a < nn ? a : nn - 1)];
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        if (a < nn) old[a] = atomicAdd(&cnt[v[a]], (1ull << 32) | (unsigned)nn);
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        if (a < nn) place[b + a] = (int32_t)(old[a] >> 32);
 }
 
-// Insertion sort of each node's (element, local index) list by element.
-__global__ void k_node_sort(int64_t n_nodes, const int64_t *n2e_ptr, int32_t *n2e, uint8_t *n2a)
+__global__ void __launch_bounds__(256) k_node_fill(int64_t n_elems, const int64_t *conn_ptr, const int32_t *conn,
+                                                   const int64_t *ptr2, const int32_t *place, int32_t *n2e,
+                                                   uint8_t *n2a)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_nodes) return;
-    int64_t b = n2e_ptr[i], e = n2e_ptr[i + 1];
-    for (int64_t p = b + 1; p < e; ++p) {
-        int32_t ke = n2e[p];
-        uint8_t ka = n2a[p];
-        int64_t q = p - 1;
-        while (q >= b && n2e[q] > ke) {
-            n2e[q + 1] = n2e[q];
-            n2a[q + 1] = n2a[q];
-            --q;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= n_elems) return;
+    const int64_t b = conn_ptr[e];
+    const int nn = (int)(conn_ptr[e + 1] - b);
+    int32_t q[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        const int64_t p = b + (a < nn ? a : nn - 1);
+        q[a] = (int32_t)(ptr2[conn[p]] >> 32) + place[p];
+    }
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+        if (a < nn) {
+            n2e[q[a]] = (int32_t)e;
+            n2a[q[a]] = (uint8_t)a;
         }
-        n2e[q + 1] = ke;
-        n2a[q + 1] = ka;
+}
+
+// ------------------------------------------------------- rows of the graph
+// Type-sorted layout: element at place p of the type-sorted order, family t
+// with n nodes, starts at node[t] + n p (node lists) and slot[t] + n^2 p
+// (element-matrix slots).
+struct RowBases {
+    uint32_t node[4], slot[4];  // modulo 2^32 (the places themselves are in range)
+};
+
+// One row's outputs of k_rows, all but the incidence list of the node.
+struct RowOut {
+    const int64_t *conn_ptr;
+    const int32_t *conn;
+    const int64_t *map_ptr;
+    const int32_t *epos;
+    int32_t *vs;      // column of every slot of the row, sorted
+    int32_t *inv;     // its slots, by column, then element
+    int32_t *pdest;   // type-sorted slot -> place in inv
+    int32_t *pnodes;  // type-sorted node lists
+    int32_t *prdest;  // type-sorted node entry -> incidence index
+};
+
+// Element of a row: first connectivity entry, node count, first slot of its
+// element-matrix row, and what takes a slot to its type-sorted place.
+struct RowElem {
+    int32_t c0, nn, s0, dq;
+};
+
+__device__ inline RowElem row_elem(const RowOut &o, const RowBases &bs, int32_t e, int a, int64_t row, int64_t inc)
+{
+    RowElem r;
+    r.c0 = (int32_t)o.conn_ptr[e];
+    r.nn = (int32_t)o.conn_ptr[e + 1] - r.c0;
+    const uint32_t p = (uint32_t)o.epos[e], nn = (uint32_t)r.nn;
+    r.s0 = (int32_t)o.map_ptr[e] + a * r.nn;
+    const int t = r.nn == 8 ? 3 : r.nn - 4;
+    r.dq = (int32_t)(bs.slot[t] + nn * nn * p + a * nn - (uint32_t)r.s0);
+    const uint32_t n = bs.node[t] + nn * p + a;
+    o.pnodes[n] = (int32_t)row;
+    o.prdest[n] = (int32_t)inc;
+    return r;
+}
+
+__device__ inline uint32_t lane_xor(uint32_t x, int mask)
+{
+    switch (mask) {  // constant after unrolling
+    case 1: return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true);   // quad_perm 1 0 3 2
+    case 2: return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true);   // quad_perm 2 3 0 1
+    case 4:                                                             // half-row mirror, then quad mirror
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+    case 8: return __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true);  // row rotate by 8
+    case 16: return __builtin_amdgcn_ds_swizzle(x, 0x401F);
+    default: return __shfl_xor((int)x, 32);
     }
 }
 
-// ------------------------------------------------------------- row pattern
-// Row i's columns are the distinct nodes of i's incident elements. They are
-// produced in ascending order by repeatedly taking the smallest candidate
-// above the last one emitted: no per-row buffer, so any row length works.
-__device__ inline void row_pattern_serial(int64_t i, const int64_t *n2e_ptr, const int32_t *n2e,
-                                          const int64_t *conn_ptr, const int32_t *conn, const int64_t *row_ptr,
-                                          int32_t *col, int32_t *deg)
+// The row's slots sorted by (column, element): candidate f = stride j + b is
+// node b of the row's j-th element (stride: the largest node count in the
+// row, so that rows of one family have no gaps), key (node id, f), K keys a
+// lane, sorted across the wave by a bitonic network over lane exchanges.
+// Returns the number of distinct columns.
+template <int K>
+__device__ inline int row_sort(const RowOut &o, const RowElem &el, int ne, int stride, int32_t r0, int len)
 {
-    int64_t b = n2e_ptr[i], e = n2e_ptr[i + 1];
-    int32_t last = -1;
-    int32_t cnt = 0;
-    int64_t out = col ? row_ptr[i] : 0;
-    for (;;) {
-        int32_t best = INT_MAX;
-        for (int64_t p = b; p < e; ++p) {
-            int32_t el = n2e[p];
-            for (int64_t k = conn_ptr[el]; k < conn_ptr[el + 1]; ++k) {
-                int32_t v = conn[k];
-                if (v > last && v < best) best = v;
+    constexpr uint64_t NONE = ~0ull;
+    const int lane = threadIdx.x & 63;
+    const int magic = 65536 / stride + 1;  // f / stride for f < 512
+    uint64_t key[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int f = lane + 64 * k, j = (f * magic) >> 16, b = f - j * stride;
+        const int nn = __shfl(el.nn, j & 63), c0 = __shfl(el.c0, j & 63);
+        const bool in = j < ne && b < nn;
+        const int32_t v = in ? o.conn[c0 + b] : 0;
+        key[k] = in ? (uint64_t)(uint32_t)v << 9 | (uint32_t)f : NONE;
+    }
+#pragma unroll
+    for (int size = 2; size <= 64 * K; size <<= 1)
+#pragma unroll
+        for (int st = size >> 1; st > 0; st >>= 1) {
+            if (st >= 64) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int q = k ^ (st >> 6);
+                    if (q > k) {
+                        const bool up = ((k * 64) & size) == 0;
+                        const uint64_t x = key[k], y = key[q];
+                        const bool keep = (x < y) == up;
+                        key[k] = keep ? x : y;
+                        key[q] = keep ? y : x;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const bool up = size >= 64 ? ((k * 64) & size) == 0 : (lane & size) == 0;
+                    const uint64_t x = key[k];
+                    const uint64_t y = (uint64_t)lane_xor((uint32_t)(x >> 32), st) << 32 | lane_xor((uint32_t)x, st);
+                    const bool low = (lane & st) == 0;
+                    key[k] = (x < y) == (low == up) ? x : y;
+                }
             }
         }
-        if (best == INT_MAX) break;
-        if (col) col[out + cnt] = best;
-        ++cnt;
-        last = best;
+    int deg = 0, last = -1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int p = lane + 64 * k, f = (int)(key[k] & 511), j = (f * magic) >> 16;
+        const int32_t v = (int32_t)(key[k] >> 9);
+        const int32_t s = __shfl(el.s0, j & 63) + (f - j * stride);
+        const int32_t q = s + __shfl(el.dq, j & 63);
+        int prev = __shfl_up(v, 1);
+        if (lane == 0) prev = last;
+        last = __shfl(v, 63);
+        if (p < len) {
+            o.vs[r0 + p] = v;
+            o.inv[r0 + p] = s;
+            o.pdest[q] = r0 + p;
+        }
+        deg += __popcll(__ballot(p < len && v != prev));
     }
-    if (deg) deg[i] = cnt;
+    return deg;
 }
 
-// One 64-lane wave per row. The row's (element, local node) candidates sit
-// on a fixed stride of 8 per incident element (no family has more nodes), so
-// candidate f = 8 j + a is node a of the row's j-th element; lane l holds
-// candidates l, l + 64, ... in registers (at most 64 elements: 8 each), and
-// the wave emits the columns in ascending order by repeated wave-wide
-// minimum above the last one emitted. A row with more incident elements
-// takes the one-lane loop above.
-__global__ void __launch_bounds__(256) k_row_pattern(int64_t n_nodes, const int64_t *n2e_ptr, const int32_t *n2e,
-                                                     const int64_t *conn_ptr, const int32_t *conn,
-                                                     const int64_t *row_ptr, int32_t *col, int32_t *deg)
+// One 64-lane wave per row (node) sorts the row's slots by column and thereby
+// makes everything that depends on the row alone: the incidence list by
+// element, the columns, the inverse map and the type-sorted maps. Rows of up
+// to 64 elements sort in registers: the incidence list by counting, the slots
+// by a bitonic network (150 to 400 instructions; taking the smallest column
+// above the last one, once per column, needs three times as many, and one
+// thread per row waits for every scattered entry in turn). A row with more
+// elements takes the columns one by one. Bound by the chain list ->
+// connectivity and the scattered 4-byte stores. 96^3 hybrid mesh (0.9 M rows,
+// 31 M slots), with k_row_blocks: 1.65 ms, where the one-thread-per-row
+// and per-element kernels for the same maps took 17.5 ms.
+__global__ void __launch_bounds__(256) k_rows(int64_t n_nodes, const int64_t *ptr2, RowOut o, RowBases bs,
+                                              int64_t *n2e_ptr, int32_t *n2e, uint8_t *n2a, int32_t *deg)
 {
-    constexpr int KMAX = 8;  // candidates per lane: 64 elements of up to 8 nodes
     const int lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n_nodes) return;  // the whole wave
-    const int64_t b = n2e_ptr[i];
-    const int ne = (int)(n2e_ptr[i + 1] - b);
-    if (ne > 64) {
-        if (lane == 0) row_pattern_serial(i, n2e_ptr, n2e, conn_ptr, conn, row_ptr, col, deg);
-        return;
+    const int64_t w0 = ptr2[i], w1 = ptr2[i + 1];
+    const int32_t b = (int32_t)(w0 >> 32), ne = (int32_t)(w1 >> 32) - b;
+    const int32_t r0 = (int32_t)(w0 & 0xffffffff), len = (int32_t)(w1 & 0xffffffff) - r0;
+    if (lane == 0) {
+        if (i == 0) n2e_ptr[0] = 0;
+        n2e_ptr[i + 1] = w1 >> 32;
     }
-    // lane j < ne: the j-th incident element's first node and node count
-    int64_t s = 0;
-    int c = 0;
-    if (lane < ne) {
-        const int32_t el = n2e[b + lane];
-        s = conn_ptr[el];
-        c = (int)(conn_ptr[el + 1] - s);
-    }
-    const int K = (ne * 8 + 63) / 64;  // uniform over the wave
-    int32_t v[KMAX];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        v[k] = INT_MAX;
-        if (k < K) {
-            const int f = lane + 64 * k, j = f >> 3, a = f & 7;
-            const int64_t sj = __shfl(s, j);
-            const int cj = __shfl(c, j);
-            if (j < ne && a < cj) v[k] = conn[sj + a];
+    int d = 0;
+    if (ne <= 64) {
+        int32_t e = lane < ne ? n2e[b + lane] : INT_MAX;
+        int a = lane < ne ? n2a[b + lane] : 0;
+        int rank = lane < ne ? 0 : lane;
+        for (int j = 0; j < ne; ++j) rank += __builtin_amdgcn_readlane(e, j) < e && lane < ne;
+        e = __builtin_amdgcn_ds_permute(rank * 4, e);
+        a = __builtin_amdgcn_ds_permute(rank * 4, a);
+        RowElem el = {0, 0, 0, 0};
+        if (lane < ne) {
+            n2e[b + lane] = e;
+            n2a[b + lane] = (uint8_t)a;
+            el = row_elem(o, bs, e, a, i, b + lane);
         }
-    }
-    int32_t last = -1, cnt = 0;
-    const int64_t out = col ? row_ptr[i] : 0;
-    for (;;) {
-        int32_t m = INT_MAX;
-#pragma unroll
-        for (int k = 0; k < KMAX; ++k) m = (v[k] > last && v[k] < m) ? v[k] : m;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const int32_t w = __shfl_xor(m, o);
-            m = w < m ? w : m;
-        }
-        if (m == INT_MAX) break;
-        if (col && lane == 0) col[out + cnt] = m;
-        ++cnt;
-        last = m;
-    }
-    if (deg && lane == 0) deg[i] = cnt;
-}
-
-// e2nnz by binary search of conn[e][b] in row conn[e][a].
-__global__ void k_e2nnz(int64_t n_elems, const int64_t *conn_ptr, const int32_t *conn,
-                        const int64_t *row_ptr, const int32_t *col, const int64_t *map_ptr,
-                        int32_t *e2nnz)
-{
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_elems) return;
-    int64_t cb = conn_ptr[e];
-    int nn = (int)(conn_ptr[e + 1] - cb);
-    int64_t mb = map_ptr[e];
-    for (int a = 0; a < nn; ++a) {
-        int32_t r = conn[cb + a];
-        int64_t rb = row_ptr[r], re = row_ptr[r + 1];
-        for (int b = 0; b < nn; ++b) {
-            int32_t c = conn[cb + b];
-            int64_t lo = rb, hi = re - 1;
-            while (lo < hi) {
-                int64_t mid = (lo + hi) >> 1;
-                if (col[mid] < c) lo = mid + 1; else hi = mid;
+        const int stride = __ballot(el.nn == 8) ? 8 : __ballot(el.nn == 6) ? 6 : __ballot(el.nn == 5) ? 5 : 4;
+        const int nc = ne * stride;
+        if (nc <= 64) d = row_sort<1>(o, el, ne, stride, r0, len);
+        else if (nc <= 128) d = row_sort<2>(o, el, ne, stride, r0, len);
+        else if (nc <= 256) d = row_sort<4>(o, el, ne, stride, r0, len);
+        else d = row_sort<8>(o, el, ne, stride, r0, len);
+    } else {
+        if (lane == 0)  // insertion sort by element
+            for (int p = b + 1; p < b + ne; ++p) {
+                const int32_t ke = n2e[p];
+                const uint8_t ka = n2a[p];
+                int q = p - 1;
+                while (q >= b && n2e[q] > ke) {
+                    n2e[q + 1] = n2e[q];
+                    n2a[q + 1] = n2a[q];
+                    --q;
+                }
+                n2e[q + 1] = ke;
+                n2a[q + 1] = ka;
             }
-            e2nnz[mb + a * nn + b] = (int32_t)lo;
+        __threadfence_block();
+        __builtin_amdgcn_wave_barrier();
+        for (int j = lane; j < ne; j += 64) row_elem(o, bs, n2e[b + j], n2a[b + j], i, b + j);
+        int32_t last = -1;
+        int pos = 0;
+        for (;;) {
+            int32_t m = INT_MAX;  // smallest column above the last one
+            for (int j = lane; j < ne; j += 64) {
+                const int32_t e = n2e[b + j];
+                for (int64_t p = o.conn_ptr[e]; p < o.conn_ptr[e + 1]; ++p) {
+                    const int32_t v = o.conn[p];
+                    m = v > last && v < m ? v : m;
+                }
+            }
+#pragma unroll
+            for (int x = 32; x >= 1; x >>= 1) {
+                const int32_t y = __shfl_xor(m, x);
+                m = y < m ? y : m;
+            }
+            if (m == INT_MAX) break;
+            for (int j0 = 0; j0 < ne; j0 += 64) {  // its slots, one element per lane
+                const int j = j0 + lane;
+                int32_t s = -1, q = 0;
+                if (j < ne) {
+                    const int32_t e = n2e[b + j], a = n2a[b + j];
+                    const int32_t c0 = (int32_t)o.conn_ptr[e], nn = (int32_t)o.conn_ptr[e + 1] - c0;
+                    const int t = nn == 8 ? 3 : nn - 4;
+                    for (int x = 0; x < nn; ++x)
+                        if (o.conn[c0 + x] == m) {
+                            s = (int32_t)o.map_ptr[e] + a * nn + x;
+                            q = (int32_t)(bs.slot[t] + (uint32_t)(nn * nn) * (uint32_t)o.epos[e] + a * nn + x);
+                        }
+                }
+                const uint64_t hit = __ballot(s >= 0);
+                if (s >= 0) {
+                    const int32_t p = r0 + pos + __popcll(hit & ((1ull << lane) - 1));
+                    o.vs[p] = m;
+                    o.inv[p] = s;
+                    o.pdest[q] = p;
+                }
+                pos += __popcll(hit);
+            }
+            ++d;
+            last = m;
         }
     }
+    if (lane == 0) deg[i] = d;
 }
 
-__global__ void k_inv_count(int64_t map_len, const int32_t *e2nnz, int32_t *cnt)
+// With the rows' first blocks known: one wave per row turns its sorted
+// columns into blocks (col, the start of every block's inverse-map list) and
+// every slot's block (e2nnz).
+__global__ void __launch_bounds__(256) k_row_blocks(int64_t n_nodes, const int64_t *ptr2, const int64_t *row_ptr,
+                                                    const int32_t *vs, const int32_t *inv, int32_t *col,
+                                                    int64_t *inv_ptr, int32_t *e2nnz)
 {
-    int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < map_len) atomicAdd(&cnt[e2nnz[s]], 1);
-}
-
-// Row i's thread owns the blocks of row i, so the per-block fill counters
-// need no atomics, and walking i's elements in ascending order lists every
-// block's slots in ascending element order.
-__global__ void k_inv_fill(int64_t n_nodes, const int64_t *n2e_ptr, const int32_t *n2e,
-                           const uint8_t *n2a, const int64_t *conn_ptr, const int64_t *map_ptr,
-                           const int32_t *e2nnz, const int64_t *inv_ptr, int32_t *fill,
-                           int32_t *inv)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_nodes) return;
-    for (int64_t p = n2e_ptr[i]; p < n2e_ptr[i + 1]; ++p) {
-        int32_t e = n2e[p];
-        int a = n2a[p];
-        int nn = (int)(conn_ptr[e + 1] - conn_ptr[e]);
-        int64_t base = map_ptr[e] + (int64_t)a * nn;
-        for (int b = 0; b < nn; ++b) {
-            int64_t s = base + b;
-            int32_t k = e2nnz[s];
-            inv[inv_ptr[k] + fill[k]] = (int32_t)s;
-            fill[k] += 1;
+    const int lane = threadIdx.x & 63;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= n_nodes) return;  // the whole wave
+    const int32_t r0 = (int32_t)(ptr2[i] & 0xffffffff), len = (int32_t)(ptr2[i + 1] & 0xffffffff) - r0;
+    int32_t k0 = (int32_t)row_ptr[i] - 1;
+    for (int l0 = 0; l0 < len; l0 += 64) {
+        const int l = l0 + lane;
+        int32_t v = -1, prev = -1, s = 0;
+        if (l < len) {
+            v = vs[r0 + l];
+            s = inv[r0 + l];
+            if (l) prev = vs[r0 + l - 1];
         }
+        const bool first = l < len && v != prev;
+        const uint64_t m = __ballot(first);
+        const int32_t k = k0 + __popcll(m & ((2ull << lane) - 1));
+        if (first) {
+            col[k] = v;
+            inv_ptr[k] = r0 + l;
+        }
+        if (l < len) e2nnz[s] = k;
+        k0 += __popcll(m);
     }
-}
-
-// Inverse permutation of the inverse map, and the incidence index of every
-// conn position: the places where the element kernel of the row-owner
-// variant stores its contributions, so that they lie sorted by destination.
-__global__ void k_e2pos(int64_t map_len, const int32_t *inv, int32_t *e2pos)
-{
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < map_len) e2pos[inv[j]] = (int32_t)j;
-}
-
-__global__ void k_rpos(int64_t n_nodes, const int64_t *n2e_ptr, const int32_t *n2e,
-                       const uint8_t *n2a, const int64_t *conn_ptr, int32_t *rpos)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_nodes) return;
-    for (int64_t p = n2e_ptr[i]; p < n2e_ptr[i + 1]; ++p) rpos[conn_ptr[n2e[p]] + n2a[p]] = (int32_t)p;
-}
-
-// Row-owner layout in type-sorted order, one thread per position.
-struct Bases {
-    int64_t seg[5], node[5], slot[5];
-};
-
-__global__ void k_position_maps(int64_t n_elems, Bases bs, const int32_t *perm, const int64_t *conn_ptr,
-                                const int32_t *conn, const int64_t *map_ptr, const int32_t *e2pos,
-                                const int32_t *rpos, int32_t *pnodes, int32_t *pdest, int32_t *prdest)
-{
-    int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pos >= n_elems) return;
-    int t = 0;
-    while (t < 3 && pos >= bs.seg[t + 1]) ++t;
-    const int n = nodes_of(t);
-    const int64_t i = pos - bs.seg[t];
-    const int32_t e = perm[pos];
-    const int64_t c0 = conn_ptr[e], m0 = map_ptr[e];
-    int32_t *pn = pnodes + bs.node[t] + i * n, *pr = prdest + bs.node[t] + i * n;
-    int32_t *pd = pdest + bs.slot[t] + i * n * n;
-    for (int a = 0; a < n; ++a) {
-        pn[a] = conn[c0 + a];
-        pr[a] = rpos[c0 + a];
-    }
-    for (int p = 0; p < n * n; ++p) pd[p] = e2pos[m0 + p];
+    if (i == n_nodes - 1 && lane == 0) inv_ptr[row_ptr[n_nodes]] = r0 + len;
 }
 
 struct TmpBuf {
@@ -755,38 +879,25 @@ static void destroy(fea_graph *g)
 }
 
 
-// Validates a mesh (FEA_EMESH names the first bad element) and returns
-// its connectivity fingerprint.
-static int mesh_fingerprint(int64_t E, const uint8_t *types, const int64_t *conn_ptr, const int32_t *conn,
-                            hipStream_t s, uint64_t *fp)
+// Checks a mesh (FEA_EMESH names the first bad element): its fingerprint,
+// the elements of every family and, if fam_cnt is given (4 per workgroup of
+// 256 elements), the workgroups' counts. Blocks on the stream.
+static int mesh_check(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn_ptr, const int32_t *conn,
+                      int32_t *fam_cnt, hipStream_t s, MeshCheck *mc)
 {
-    TmpBuf acc;
+    TmpBuf out;
     int rc;
-    if ((rc = dalloc(&acc.p, sizeof(unsigned long long)))) return rc;
-    FEA_HIP(hipMemsetAsync(acc.p, 0, sizeof(unsigned long long), s));
-    if (E) k_mesh_fingerprint<<<grid_for(E, 256), 256, 0, s>>>(E, types, conn_ptr, conn, (unsigned long long *)acc.p);
+    if ((rc = dalloc(&out.p, sizeof(MeshCheck)))) return rc;
+    *mc = MeshCheck{~0ull, 0, {0, 0, 0, 0}};
+    if (!E) return FEA_OK;
+    FEA_HIP(hipMemcpyAsync(out.p, mc, sizeof(MeshCheck), hipMemcpyHostToDevice, s));
+    k_mesh_check<<<grid_for(E, 256), 256, 0, s>>>(N, E, types, conn_ptr, conn, (MeshCheck *)out.p, fam_cnt);
     FEA_HIP(hipGetLastError());
-    FEA_HIP(hipMemcpyAsync(fp, acc.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    FEA_HIP(hipMemcpyAsync(mc, out.p, sizeof(MeshCheck), hipMemcpyDeviceToHost, s));
     FEA_HIP(hipStreamSynchronize(s));
-    return FEA_OK;
-}
-
-static int validate(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn_ptr, const int32_t *conn,
-                    hipStream_t s)
-{
-    TmpBuf bad;
-    int rc;
-    if ((rc = dalloc(&bad.p, sizeof(int64_t)))) return rc;
-    int64_t big = INT64_MAX;
-    FEA_HIP(hipMemcpyAsync(bad.p, &big, sizeof(int64_t), hipMemcpyHostToDevice, s));
-    if (E) k_validate<<<grid_for(E, 256), 256, 0, s>>>(N, E, types, conn_ptr, conn, (int64_t *)bad.p);
-    FEA_HIP(hipGetLastError());
-    int64_t first_bad = INT64_MAX;
-    FEA_HIP(hipMemcpyAsync(&first_bad, bad.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    FEA_HIP(hipStreamSynchronize(s));
-    if (first_bad != INT64_MAX)
+    if (mc->bad != ~0ull)
         return set_error(FEA_EMESH, "invalid element %lld (unknown type, wrong node count, node id out "
-                         "of range or repeated node)", (long long)first_bad);
+                         "of range or repeated node)", (long long)mc->bad);
     return FEA_OK;
 }
 
@@ -798,123 +909,89 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
     FEA_HIP(hipGetDevice(&g->device));
     g->n_nodes = N;
     g->n_elems = E;
-    if (E > 0)
-        FEA_HIP(hipMemcpyAsync(&g->conn_len, conn_ptr + E, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    FEA_HIP(hipStreamSynchronize(s));
+    auto one = [](int64_t n) { return std::max<int64_t>(n, 1); };
 
-    // validation
-    TmpBuf tmp, cnt64, cnt32, flag, fillb;
-    if ((rc = validate(N, E, types, conn_ptr, conn, s))) return rc;
-    if ((rc = mesh_fingerprint(E, types, conn_ptr, conn, s, &g->mesh_fp))) return rc;
+    // validation, fingerprint, family counts: every size but the pattern's
+    const int64_t nb = (E + 255) / 256;
+    TmpBuf famc, famp, tmp, epos, cnt, ptr2, deg, vs;
+    if ((rc = dalloc(&famc.p, sizeof(int32_t) * one(4 * nb)))) return rc;
+    MeshCheck mc;
+    if ((rc = mesh_check(N, E, types, conn_ptr, conn, (int32_t *)famc.p, s, &mc))) return rc;
+    g->mesh_fp = mc.fp;
+    RowBases bs;
+    for (int t = 0; t < 4; ++t) {
+        const int64_t n = nodes_of(t), c = (int64_t)mc.fam[t];
+        g->seg[t + 1] = g->seg[t] + c;
+        g->node_base[t + 1] = g->node_base[t] + c * n;
+        g->slot_base[t + 1] = g->slot_base[t] + c * n * n;
+        bs.node[t] = (uint32_t)(g->node_base[t] - g->seg[t] * n);
+        bs.slot[t] = (uint32_t)(g->slot_base[t] - g->seg[t] * n * n);
+    }
+    g->conn_len = g->node_base[4];
+    g->map_len = g->slot_base[4];
     HostColouring hc;  // joined on every return
     if ((rc = colour_start(g, conn_ptr, conn, types, s, hc))) return rc;
-
-    int64_t scan_n = std::max<int64_t>(std::max<int64_t>(E, N), g->conn_len);
-    // slots: map_ptr = prefix sum of n_e^2
-    if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(scan_n) + 64)))) return rc;
-    if ((rc = dalloc(&cnt64.p, sizeof(int64_t) * std::max<int64_t>(E, N) + 8))) return rc;
-    if ((rc = dalloc((void **)&g->map_ptr, sizeof(int64_t) * (E + 1)))) return rc;
-    if (E) k_slot_count<<<grid_for(E, BS), BS, 0, s>>>(E, types, (int64_t *)cnt64.p);
-    if ((rc = scan_to_ptr_i64((int64_t *)cnt64.p, E, g->map_ptr, (int64_t *)tmp.p, s))) return rc;
-    FEA_HIP(hipMemcpyAsync(&g->map_len, g->map_ptr + E, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    FEA_HIP(hipStreamSynchronize(s));
     if (g->map_len > INT32_MAX || g->conn_len > INT32_MAX)
         return set_error(FEA_ERANGE, "%lld element-matrix slots / %lld incidences exceed int32 maps",
                          (long long)g->map_len, (long long)g->conn_len);
 
-    // type segmentation (stable partition by family)
-    if ((rc = dalloc(&flag.p, std::max<int64_t>(E, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->perm, sizeof(int32_t) * std::max<int64_t>(E, 1)))) return rc;
-    {
-        int64_t base = 0;
-        for (int t = 0; t < 4; ++t) {
-            g->seg[t] = base;
-            if (!E) continue;
-            k_type_flags<<<grid_for(E, BS), BS, 0, s>>>(E, types, t, (uint8_t *)flag.p);
-            if ((rc = scan_to_ptr_u8((uint8_t *)flag.p, E, (int64_t *)cnt64.p, (int64_t *)tmp.p, s))) return rc;
-            k_type_place<<<grid_for(E, BS), BS, 0, s>>>(E, types, t, (int64_t *)cnt64.p, base, g->perm);
-            int64_t cnt_t = 0;
-            FEA_HIP(hipMemcpyAsync(&cnt_t, (int64_t *)cnt64.p + E, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            FEA_HIP(hipStreamSynchronize(s));
-            base += cnt_t;
-        }
-        g->seg[4] = base;
+    // type segmentation, first slots
+    if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(std::max(4 * nb, N)) + 64)))) return rc;
+    if ((rc = dalloc(&famp.p, sizeof(int64_t) * (4 * nb + 1)))) return rc;
+    if ((rc = dalloc(&epos.p, sizeof(int32_t) * one(E)))) return rc;
+    if ((rc = dalloc((void **)&g->map_ptr, sizeof(int64_t) * (E + 1)))) return rc;
+    if ((rc = dalloc((void **)&g->perm, sizeof(int32_t) * one(E)))) return rc;
+    if (E) {
+        if ((rc = scan_to_ptr_i32((int32_t *)famc.p, 4 * nb, (int64_t *)famp.p, (int64_t *)tmp.p, s))) return rc;
+        k_type_place<<<(unsigned)nb, 256, 0, s>>>(E, types, (const int64_t *)famp.p, g->perm, (int32_t *)epos.p,
+                                                  g->map_ptr);
+    } else {
+        FEA_HIP(hipMemsetAsync(g->map_ptr, 0, sizeof(int64_t), s));
     }
 
-    // node incidence
-    if ((rc = dalloc(&cnt32.p, sizeof(int32_t) * (N + 1)))) return rc;
+    // node incidence (prdest holds the places in the unsorted lists meanwhile)
+    if ((rc = dalloc(&cnt.p, sizeof(int64_t) * one(N)))) return rc;
+    if ((rc = dalloc(&ptr2.p, sizeof(int64_t) * (N + 1)))) return rc;
+    if ((rc = dalloc(&deg.p, sizeof(int32_t) * one(N)))) return rc;
+    if ((rc = dalloc(&vs.p, sizeof(int32_t) * one(g->map_len)))) return rc;
     if ((rc = dalloc((void **)&g->n2e_ptr, sizeof(int64_t) * (N + 1)))) return rc;
-    if ((rc = dalloc((void **)&g->n2e, sizeof(int32_t) * std::max<int64_t>(g->conn_len, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->n2a, std::max<int64_t>(g->conn_len, 1)))) return rc;
-    FEA_HIP(hipMemsetAsync(cnt32.p, 0, sizeof(int32_t) * (N + 1), s));
-    if (g->conn_len) k_node_count<<<grid_for(g->conn_len, BS), BS, 0, s>>>(g->conn_len, conn, (int32_t *)cnt32.p);
-    if ((rc = scan_to_ptr_i32((int32_t *)cnt32.p, N, g->n2e_ptr, (int64_t *)tmp.p, s))) return rc;
-    FEA_HIP(hipMemsetAsync(cnt32.p, 0, sizeof(int32_t) * (N + 1), s));
-    if (E) k_node_fill<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, g->n2e_ptr, (int32_t *)cnt32.p, g->n2e, g->n2a);
-    if (N) k_node_sort<<<grid_for(N, BS), BS, 0, s>>>(N, g->n2e_ptr, g->n2e, g->n2a);
-    FEA_HIP(hipGetLastError());
-
-    // row pattern: degrees, prefix sum, columns
+    if ((rc = dalloc((void **)&g->n2e, sizeof(int32_t) * one(g->conn_len)))) return rc;
+    if ((rc = dalloc((void **)&g->n2a, one(g->conn_len)))) return rc;
+    if ((rc = dalloc((void **)&g->pnodes, sizeof(int32_t) * one(g->conn_len)))) return rc;
+    if ((rc = dalloc((void **)&g->prdest, sizeof(int32_t) * one(g->conn_len)))) return rc;
+    if ((rc = dalloc((void **)&g->pdest, sizeof(int32_t) * one(g->map_len)))) return rc;
+    if ((rc = dalloc((void **)&g->inv, sizeof(int32_t) * one(g->map_len)))) return rc;
     if ((rc = dalloc((void **)&g->row_ptr, sizeof(int64_t) * (N + 1)))) return rc;
-    if (N) k_row_pattern<<<grid_for(N, 4), 256, 0, s>>>(N, g->n2e_ptr, g->n2e, conn_ptr, conn, nullptr, nullptr, (int32_t *)cnt32.p);
-    if ((rc = scan_to_ptr_i32((int32_t *)cnt32.p, N, g->row_ptr, (int64_t *)tmp.p, s))) return rc;
+    FEA_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int64_t) * one(N), s));
+    if (E) k_node_count<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, (unsigned long long *)cnt.p, g->prdest);
+    if ((rc = scan_to_ptr_i64((int64_t *)cnt.p, N, (int64_t *)ptr2.p, (int64_t *)tmp.p, s))) return rc;
+    if (E) k_node_fill<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, (const int64_t *)ptr2.p, g->prdest, g->n2e, g->n2a);
+
+    // rows: sorted slots, degrees, prefix sum, then blocks
+    const RowOut ro = {conn_ptr, conn, g->map_ptr, (const int32_t *)epos.p, (int32_t *)vs.p, g->inv, g->pdest,
+                       g->pnodes, g->prdest};
+    if (N)
+        k_rows<<<grid_for(N, 4), 256, 0, s>>>(N, (const int64_t *)ptr2.p, ro, bs, g->n2e_ptr, g->n2e, g->n2a,
+                                              (int32_t *)deg.p);
+    else
+        FEA_HIP(hipMemsetAsync(g->n2e_ptr, 0, sizeof(int64_t), s));
+    if ((rc = scan_to_ptr_i32((int32_t *)deg.p, N, g->row_ptr, (int64_t *)tmp.p, s))) return rc;
     FEA_HIP(hipMemcpyAsync(&g->nnz, g->row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     FEA_HIP(hipStreamSynchronize(s));
     if (g->nnz > INT32_MAX)
         return set_error(FEA_ERANGE, "%lld nonzero blocks exceed int32 block indices", (long long)g->nnz);
-    if ((rc = dalloc((void **)&g->col, sizeof(int32_t) * std::max<int64_t>(g->nnz, 1)))) return rc;
-    if (N) k_row_pattern<<<grid_for(N, 4), 256, 0, s>>>(N, g->n2e_ptr, g->n2e, conn_ptr, conn, g->row_ptr, g->col, nullptr);
-    FEA_HIP(hipGetLastError());
-
-    // element -> nonzero map
-    if ((rc = dalloc((void **)&g->e2nnz, sizeof(int32_t) * std::max<int64_t>(g->map_len, 1)))) return rc;
-    if (E) k_e2nnz<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, g->row_ptr, g->col, g->map_ptr, g->e2nnz);
-
-    // inverse map
-    if ((rc = dalloc(&fillb.p, sizeof(int32_t) * (g->nnz + 1)))) return rc;
+    if ((rc = dalloc((void **)&g->col, sizeof(int32_t) * one(g->nnz)))) return rc;
+    if ((rc = dalloc((void **)&g->e2nnz, sizeof(int32_t) * one(g->map_len)))) return rc;
     if ((rc = dalloc((void **)&g->inv_ptr, sizeof(int64_t) * (g->nnz + 1)))) return rc;
-    if ((rc = dalloc((void **)&g->inv, sizeof(int32_t) * std::max<int64_t>(g->map_len, 1)))) return rc;
-    FEA_HIP(hipMemsetAsync(fillb.p, 0, sizeof(int32_t) * (g->nnz + 1), s));
-    if (g->nnz > scan_n) {  // the block-count scan runs over nnz entries
-        FEA_HIP(hipStreamSynchronize(s));
-        dfree(tmp.p);
-        tmp.p = nullptr;
-        if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(g->nnz) + 64)))) return rc;
-    }
-    if (g->map_len) k_inv_count<<<grid_for(g->map_len, BS), BS, 0, s>>>(g->map_len, g->e2nnz, (int32_t *)fillb.p);
-    if ((rc = scan_to_ptr_i32((int32_t *)fillb.p, g->nnz, g->inv_ptr, (int64_t *)tmp.p, s))) return rc;
-    FEA_HIP(hipMemsetAsync(fillb.p, 0, sizeof(int32_t) * (g->nnz + 1), s));
-    if (N) k_inv_fill<<<grid_for(N, BS), BS, 0, s>>>(N, g->n2e_ptr, g->n2e, g->n2a, conn_ptr, g->map_ptr, g->e2nnz, g->inv_ptr, (int32_t *)fillb.p, g->inv);
+    if (N)
+        k_row_blocks<<<grid_for(N, 4), 256, 0, s>>>(N, (const int64_t *)ptr2.p, g->row_ptr, (const int32_t *)vs.p, g->inv,
+                                                    g->col, g->inv_ptr, g->e2nnz);
+    else
+        FEA_HIP(hipMemsetAsync(g->inv_ptr, 0, sizeof(int64_t), s));
     FEA_HIP(hipGetLastError());
+    FEA_HIP(hipStreamSynchronize(s));
 
-    // destination positions for the row-owner workspace, laid out in
-    // type-sorted order
-    {
-        TmpBuf e2pos, rpos;
-        if ((rc = dalloc(&e2pos.p, sizeof(int32_t) * std::max<int64_t>(g->map_len, 1)))) return rc;
-        if ((rc = dalloc(&rpos.p, sizeof(int32_t) * std::max<int64_t>(g->conn_len, 1)))) return rc;
-        if (g->map_len) k_e2pos<<<grid_for(g->map_len, BS), BS, 0, s>>>(g->map_len, g->inv, (int32_t *)e2pos.p);
-        if (N) k_rpos<<<grid_for(N, BS), BS, 0, s>>>(N, g->n2e_ptr, g->n2e, g->n2a, conn_ptr, (int32_t *)rpos.p);
-        Bases bs;
-        for (int t = 0; t <= 4; ++t) bs.seg[t] = g->seg[t];
-        bs.node[0] = bs.slot[0] = 0;
-        for (int t = 0; t < 4; ++t) {
-            const int64_t cnt = g->seg[t + 1] - g->seg[t], n = nodes_of(t);
-            bs.node[t + 1] = bs.node[t] + cnt * n;
-            bs.slot[t + 1] = bs.slot[t] + cnt * n * n;
-        }
-        memcpy(g->node_base, bs.node, sizeof(bs.node));
-        memcpy(g->slot_base, bs.slot, sizeof(bs.slot));
-        if ((rc = dalloc((void **)&g->pnodes, sizeof(int32_t) * std::max<int64_t>(g->conn_len, 1)))) return rc;
-        if ((rc = dalloc((void **)&g->prdest, sizeof(int32_t) * std::max<int64_t>(g->conn_len, 1)))) return rc;
-        if ((rc = dalloc((void **)&g->pdest, sizeof(int32_t) * std::max<int64_t>(g->map_len, 1)))) return rc;
-        if (E) k_position_maps<<<grid_for(E, BS), BS, 0, s>>>(E, bs, g->perm, conn_ptr, conn, g->map_ptr, (int32_t *)e2pos.p, (int32_t *)rpos.p, g->pnodes, g->pdest, g->prdest);
-        FEA_HIP(hipGetLastError());
-        FEA_HIP(hipStreamSynchronize(s));
-    }
-
-    if ((rc = colour_finish(g, hc, s))) return rc;
-    return FEA_OK;
+    return colour_finish(g, hc, s);
 }
 
 }  // namespace fea
@@ -1090,10 +1167,9 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         h.cseg_len != 4 * ((int64_t)h.n_colours + 1))
         return set_error(FEA_EINVAL, "%s: inconsistent header", path);
     // the mesh must be the one the graph was built for
-    if ((rc = validate(n_nodes, n_elems, types, conn_ptr, conn, stream))) return rc;
-    uint64_t fp = 0;
-    if ((rc = mesh_fingerprint(n_elems, types, conn_ptr, conn, stream, &fp))) return rc;
-    if (fp != h.mesh_fp) return set_error(FEA_EINVAL, "%s was built for another mesh (connectivity differs)", path);
+    MeshCheck mc;
+    if ((rc = mesh_check(n_nodes, n_elems, types, conn_ptr, conn, nullptr, stream, &mc))) return rc;
+    if (mc.fp != h.mesh_fp) return set_error(FEA_EINVAL, "%s was built for another mesh (connectivity differs)", path);
     fea_graph *g = new (std::nothrow) fea_graph();
     if (!g) return set_error(FEA_ENOMEM, "host allocation failed");
     FEA_HIP(hipGetDevice(&g->device));
