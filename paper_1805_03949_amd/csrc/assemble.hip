@@ -67,13 +67,20 @@ static void launch_type(int t, const ElemArgs &a, hipStream_t s)
     }
 }
 
-static int ensure_ws(void **p, size_t *have, size_t need)
+// A workspace of at least `need` bytes, kept until the graph goes or a larger
+// one is needed. Under capture nothing comes from the pool or returns to it.
+static int ensure_ws(void **p, size_t *have, size_t need, hipStream_t s)
 {
     if (*have >= need && *p) return FEA_OK;
-    dfree(*p);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool pooled = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (*p) {
+        if (pooled) FEA_HIP(hipDeviceSynchronize());
+        pooled ? pool_free(*p) : dfree(*p);
+    }
     *p = nullptr;
     *have = 0;
-    int rc = dalloc(p, need);
+    int rc = pooled ? dalloc_pool(p, need) : dalloc(p, need);
     if (rc) return rc;
     *have = need;
     return FEA_OK;
@@ -106,8 +113,8 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         // sums (no workspace of its own); 1x1: its own workspace and sums
         constexpr bool RHSD = B == 3;
         if (!g->sready && (rc = sym_prepare(g, s))) return rc;
-        if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)std::max<int64_t>(g->ulen, 1) * BB + kSegPad))) return rc;
-        if (!RHSD && (rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
+        if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)std::max<int64_t>(g->ulen, 1) * BB + kSegPad, s))) return rc;
+        if (!RHSD && (rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad, s))) return rc;
         a.contrib = g->contrib;
         a.rcontrib = RHSD ? nullptr : g->rcontrib;
         a.tb_rng = g->tb_rng;
@@ -148,10 +155,10 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
     if (o->variant == FEA_TILECOLOUR) {
         if (!g->sready && (rc = sym_prepare(g, s))) return rc;
         if (!g->tcready && (rc = tile_colour_prepare(g, s))) return rc;
-        if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
+        if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad, s))) return rc;
         double *tv = (double *)vals;
         if (f32) {
-            if ((rc = ensure_ws((void **)&g->acc64, &g->acc64_bytes, sizeof(double) * (size_t)std::max<int64_t>(nv, 1)))) return rc;
+            if ((rc = ensure_ws((void **)&g->acc64, &g->acc64_bytes, sizeof(double) * (size_t)std::max<int64_t>(nv, 1), s))) return rc;
             tv = g->acc64;
         }
         a.rcontrib = g->rcontrib;
@@ -193,8 +200,8 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.contrib = ws.contrib;
             a.rcontrib = ws.rcontrib;
         } else {
-            if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)g->map_len * BB + kSegPad))) return rc;
-            if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad))) return rc;
+            if ((rc = ensure_ws(&g->contrib, &g->contrib_bytes, sizeof(CT) * (size_t)g->map_len * BB + kSegPad, s))) return rc;
+            if ((rc = ensure_ws(&g->rcontrib, &g->rcontrib_bytes, sizeof(CT) * (size_t)g->conn_len * B + kSegPad, s))) return rc;
             a.contrib = g->contrib;
             a.rcontrib = g->rcontrib;
         }
@@ -226,7 +233,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
     // FP64, else in a workspace converted at the end.
     double *tv, *tr;
     if (f32) {
-        if ((rc = ensure_ws((void **)&g->acc64, &g->acc64_bytes, sizeof(double) * (size_t)(nv + nr)))) return rc;
+        if ((rc = ensure_ws((void **)&g->acc64, &g->acc64_bytes, sizeof(double) * (size_t)(nv + nr), s))) return rc;
         tv = g->acc64;
         tr = g->acc64 + nv;
     } else {

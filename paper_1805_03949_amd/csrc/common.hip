@@ -1,7 +1,10 @@
 // Error reporting, allocation and a device-wide prefix sum.
 #include <cstdarg>
 #include <cstdio>
+#include <algorithm>
 #include <cstdlib>
+#include <map>
+#include <mutex>
 
 #include "fea_internal.h"
 
@@ -23,19 +26,30 @@ int set_error(int code, const char *fmt, ...)
 void clear_error() { g_error.clear(); }
 
 // Allocation-failure injection for tests of the error path: when the
-// environment variable FEA_FAIL_ALLOC_AT=n is set, the n-th device
-// allocation of the process (1-based) fails.
+// environment variable FEA_FAIL_ALLOC_AT=n is set, the allocation of the
+// n-th device array of the process (1-based) fails.
 static long g_alloc_count = 0;
+
+static bool alloc_injected()
+{
+    static const char *fail_at = getenv("FEA_FAIL_ALLOC_AT");
+    ++g_alloc_count;
+    return fail_at && atol(fail_at) == g_alloc_count;
+}
 
 int dalloc(void **p, size_t bytes)
 {
     *p = nullptr;
-    static const char *fail_at = getenv("FEA_FAIL_ALLOC_AT");
-    ++g_alloc_count;
-    if (fail_at && atol(fail_at) == g_alloc_count)
+    if (alloc_injected())
         return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed (injected)", bytes);
     if (bytes == 0) bytes = 8;
     hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {  // once more with the pool given back
+        int dev = 0;
+        (void)hipGetLastError();
+        if (hipGetDevice(&dev) == hipSuccess) pool_flush(dev);
+        e = hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -45,9 +59,214 @@ int dalloc(void **p, size_t bytes)
     return FEA_OK;
 }
 
+// ------------------------------------------------------------------ pool
+// Freed device memory that the next allocation may take instead of the
+// driver's: a program that rebuilds its graph for every new mesh allocates
+// and frees the same sizes each time, and the driver clears what is freed.
+// 48^3 hybrid mesh (0.4 GB a build, assembly and destruction): 4.9 ms or,
+// once the driver is behind with its clearing, 16.6 ms a pass without the
+// pool, 3.2 ms with it.
+// Bounded: at most kPoolBytes and kPoolBlocks unused a device; the longest
+// unused goes back to the driver first, and also one that kPoolAge later
+// allocations have passed over; all of them do before an allocation fails.
+// A block enters the pool with no work on it pending (pool_free's callers
+// see to that), so any stream and thread may have it next.
+namespace {
+
+constexpr size_t kPoolBytes = size_t(1) << 30;
+constexpr size_t kPoolBlocks = 16;
+constexpr uint64_t kPoolAge = 64;
+
+struct PoolBlock {
+    void *p;
+    size_t bytes;
+    int device;
+    uint64_t stamp;
+};
+
+struct Pool {
+    std::mutex mtx;
+    std::vector<PoolBlock> idle;   // oldest first
+    std::map<void *, PoolBlock> used;
+    uint64_t clock = 0;
+};
+
+Pool &pool()
+{
+    static Pool *p = new Pool;  // never destroyed: graphs may outlive static objects
+    return *p;
+}
+
+// With the lock held: unlists blocks of the device, oldest first, while
+// `more` says so.
+template <typename F>
+void pool_drop(Pool &q, int device, std::vector<void *> &out, F &&more)
+{
+    for (size_t i = 0; i < q.idle.size();) {
+        if (q.idle[i].device == device && more(q.idle[i])) {
+            out.push_back(q.idle[i].p);
+            q.idle.erase(q.idle.begin() + (ptrdiff_t)i);
+        } else {
+            ++i;
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t pool_alloc(void **p, size_t bytes)
+{
+    *p = nullptr;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    constexpr size_t G = size_t(2) << 20;
+    if (bytes >= G) bytes = (bytes + G - 1) / G * G;
+    Pool &q = pool();
+    std::vector<void *> old;
+    try {
+        std::lock_guard<std::mutex> lock(q.mtx);
+        ++q.clock;
+        size_t best = q.idle.size();
+        for (size_t i = 0; i < q.idle.size(); ++i) {
+            const PoolBlock &b = q.idle[i];
+            // no more than half of a block unused
+            if (b.device == dev && b.bytes >= bytes && b.bytes / 2 <= bytes &&
+                (best == q.idle.size() || b.bytes < q.idle[best].bytes))
+                best = i;
+        }
+        if (best < q.idle.size()) {
+            const PoolBlock b = q.idle[best];
+            q.used[b.p] = b;
+            q.idle.erase(q.idle.begin() + (ptrdiff_t)best);
+            *p = b.p;
+        }
+        old.reserve(q.idle.size());
+        pool_drop(q, dev, old, [&](const PoolBlock &b) { return q.clock - b.stamp > kPoolAge; });
+    } catch (...) {
+        return hipErrorOutOfMemory;
+    }
+    for (void *o : old) (void)hipFree(o);
+    if (*p) return hipSuccess;
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {  // once more with the pool given back
+        (void)hipGetLastError();
+        pool_flush(dev);
+        e = hipMalloc(p, bytes);
+        if (e != hipSuccess) {
+            *p = nullptr;
+            return e;
+        }
+    }
+    try {
+        std::lock_guard<std::mutex> lock(q.mtx);
+        q.used[*p] = PoolBlock{*p, bytes, dev, 0};
+    } catch (...) {  // not listed: pool_free hands it to hipFree
+    }
+    return hipSuccess;
+}
+
+void pool_flush(int device)
+{
+    Pool &q = pool();
+    std::vector<void *> old;
+    {
+        std::lock_guard<std::mutex> lock(q.mtx);
+        try {
+            old.reserve(q.idle.size());
+        } catch (...) {
+            return;
+        }
+        pool_drop(q, device, old, [](const PoolBlock &) { return true; });
+    }
+    for (void *o : old) (void)hipFree(o);
+}
+
+void pool_free(void *p)
+{
+    if (!p) return;
+    Pool &q = pool();
+    std::vector<void *> old;
+    bool kept = false;
+    try {
+        std::lock_guard<std::mutex> lock(q.mtx);
+        auto it = q.used.find(p);
+        if (it != q.used.end()) {
+            PoolBlock b = it->second;
+            q.used.erase(it);
+            if (b.bytes <= kPoolBytes) {
+                size_t bytes = b.bytes, blocks = 1;
+                for (const PoolBlock &o : q.idle)
+                    if (o.device == b.device) {
+                        bytes += o.bytes;
+                        ++blocks;
+                    }
+                old.reserve(q.idle.size());
+                q.idle.reserve(q.idle.size() + 1);
+                pool_drop(q, b.device, old, [&](const PoolBlock &o) {
+                    const bool go = bytes > kPoolBytes || blocks > kPoolBlocks;
+                    if (go) {
+                        bytes -= o.bytes;
+                        --blocks;
+                    }
+                    return go;
+                });
+                b.stamp = q.clock;
+                q.idle.push_back(b);
+                kept = true;
+            }
+        }
+    } catch (...) {
+    }
+    for (void *o : old) (void)hipFree(o);
+    if (!kept) (void)hipFree(p);
+}
+
+int dalloc_pool(void **p, size_t bytes)
+{
+    *p = nullptr;
+    if (alloc_injected()) return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed (injected)", bytes);
+    hipError_t e = pool_alloc(p, bytes ? bytes : 8);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+    }
+    return FEA_OK;
+}
+
+int dalloc_arrays(void **base, const std::vector<DevArray> &arrays)
+{
+    *base = nullptr;
+    size_t total = 0;
+    bool injected = false;
+    auto room = [](const DevArray &a) { return (std::max<size_t>(a.bytes, 1) + 255) / 256 * 256; };
+    for (const DevArray &a : arrays) {
+        *a.p = nullptr;
+        injected = alloc_injected() || injected;
+        total += room(a);
+    }
+    if (injected) return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed (injected)", total);
+    hipError_t e = pool_alloc(base, total);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed: %s", total, hipGetErrorString(e));
+    }
+    char *at = (char *)*base;
+    for (const DevArray &a : arrays) {
+        *a.p = at;
+        at += room(a);
+    }
+    return FEA_OK;
+}
+
 void dfree(void *p)
 {
-    if (p) (void)hipFree(p);
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lock(pool().mtx);
+        pool().used.erase(p);
+    }
+    (void)hipFree(p);
 }
 
 // ------------------------------------------------------------------ scan

@@ -47,6 +47,21 @@ void clear_error();
 
 // Device allocation that records an error message on failure.
 int dalloc(void **p, size_t bytes);
+// Device memory from the pool of freed blocks (common.hip) or the driver.
+// pool_free: no work on the memory may be pending; takes any device pointer.
+hipError_t pool_alloc(void **p, size_t bytes);
+void pool_free(void *p);
+void pool_flush(int device);
+int dalloc_pool(void **p, size_t bytes);
+// One allocation (*base, for pool_free) for several arrays, each 256-byte
+// aligned and (an empty one too) at least that long: hipFree takes 0.3 to
+// 0.5 ms a call for megabytes that kernels have used, and a graph with its
+// upper-triangle layout has 30 arrays.
+struct DevArray {
+    void **p;
+    size_t bytes;
+};
+int dalloc_arrays(void **base, const std::vector<DevArray> &arrays);
 void dfree(void *p);
 
 // ptr[0] = 0, ptr[i+1] = in[0] + ... + in[i] for i < n (int64 result).
@@ -102,6 +117,9 @@ struct fea_graph {
     int64_t n_nodes = 0, n_elems = 0, nnz = 0, map_len = 0, conn_len = 0;
     uint64_t mesh_fp = 0;  // connectivity fingerprint of the mesh it was built for
     int n_colours = 0;
+    // device allocations that hold the graph's arrays (mem[0], mem[1]) and
+    // those of the upper-triangle layout (mem[2])
+    void *mem[3] = {nullptr, nullptr, nullptr};
     // block pattern, element-to-nonzero map and its inverse
     int64_t *row_ptr = nullptr;
     int32_t *col = nullptr;
@@ -150,11 +168,9 @@ struct fea_graph {
     hipEvent_t gev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     bool gtimed = false;
     // Upper-triangle layout (built by the first FEA_ROWSYM assembly).
-    // upart[k] = block k itself if col >= row, else the block at the
-    // transposed position; ublk = the nup upper (and diagonal) blocks in CSR
+    // ublk = the nup upper (and diagonal) blocks in CSR
     // order; lpart[k] = lower partner of upper block k (-1 for diagonal and
     // lower blocks).
-    int32_t *upart = nullptr;
     int32_t *ublk = nullptr;
     int32_t *lpart = nullptr;
     int64_t nup = 0;
@@ -173,8 +189,7 @@ struct fea_graph {
     // tile's distinct blocks are tile-blocks ttb_ptr[τ] .. ttb_ptr[τ+1],
     // tile-block d holding the entries from tb_rng[d] & 255 on, (tb_rng[d]
     // >> 8) + 1 of them, block id tb_blk[d] and workspace slot tb_slot[d].
-    // The workspace lies sorted by block, then tile: block k's tile sums are
-    // ts_ptr[k] .. ts_ptr[k+1]; ulen = tile-blocks.
+    // The workspace lies sorted by block, then tile; ulen = tile-blocks.
     int64_t tile_base[5] = {0, 0, 0, 0, 0};
     int64_t pair_base[5] = {0, 0, 0, 0, 0};
     int64_t *ttb_ptr = nullptr;
@@ -182,7 +197,6 @@ struct fea_graph {
     uint16_t *tb_rng = nullptr;
     int32_t *tb_blk = nullptr;
     int32_t *tb_slot = nullptr;
-    int64_t *ts_ptr = nullptr;
     int64_t ulen = 0, nent = 0;
     // Tile colouring (built by the first FEA_TILECOLOUR assembly): greedy
     // first-fit over the tiles in descending neighbour count, no two tiles

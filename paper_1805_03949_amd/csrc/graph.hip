@@ -10,6 +10,7 @@
 #include <climits>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <thread>
 #include <vector>
 
@@ -436,9 +437,17 @@ __global__ void __launch_bounds__(256) k_row_blocks(int64_t n_nodes, const int64
     if (i == n_nodes - 1 && lane == 0) inv_ptr[row_ptr[n_nodes]] = r0 + len;
 }
 
+// Scratch memory of one stream's work.
 struct TmpBuf {
+    hipStream_t s;
     void *p = nullptr;
-    ~TmpBuf() { dfree(p); }
+    explicit TmpBuf(hipStream_t stream) : s(stream) {}
+    ~TmpBuf()
+    {
+        if (!p) return;
+        (void)hipStreamSynchronize(s);
+        pool_free(p);
+    }
 };
 
 // ---------------------------------------------- upper-triangle row-owner
@@ -629,27 +638,16 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     constexpr int BS = 256;
     const int64_t N = g->n_nodes, nnz = g->nnz;
     int rc;
-    void **bufs[] = {(void **)&g->upart, (void **)&g->ublk,    (void **)&g->lpart,
-                     (void **)&g->ttb_ptr, (void **)&g->tpos,  (void **)&g->tb_rng, (void **)&g->tb_blk,
-                     (void **)&g->tb_slot, (void **)&g->ts_ptr, (void **)&g->ulp, (void **)&g->uptr};
-    for (void **b : bufs) {
-        dfree(*b);
-        *b = nullptr;
+    if (g->mem[2]) {
+        FEA_HIP(hipDeviceSynchronize());
+        pool_free(g->mem[2]);
+        g->mem[2] = nullptr;
     }
     g->nup = 0;
     g->ulen = 0;
     g->nent = 0;
     g->sready = false;
     g->tcready = false;
-    // partners and the upper-block list
-    TmpBuf flag, uoff, tmp;
-    const int64_t nn1 = std::max<int64_t>(nnz, 1);
-    if ((rc = dalloc((void **)&g->upart, sizeof(int32_t) * nn1))) return rc;
-    if ((rc = dalloc((void **)&g->lpart, sizeof(int32_t) * nn1))) return rc;
-    if ((rc = dalloc((void **)&g->ublk, sizeof(int32_t) * nn1))) return rc;
-    if ((rc = dalloc(&flag.p, sizeof(int32_t) * nn1))) return rc;
-    if ((rc = dalloc(&uoff.p, sizeof(int64_t) * (nnz + 1)))) return rc;
-    // the scan scratch serves the tile and block scans below as well
     TileBases tb;
     int64_t nt = 0, nent = 0;  // tiles; entries, one per (element, pair a <= b)
     for (int t = 0; t < 4; ++t) {
@@ -669,63 +667,81 @@ int sym_prepare(fea_graph *g, hipStream_t s)
         g->tile_base[t] = tb.tile[t];
         g->pair_base[t] = tb.pair[t];
     }
+    // upart[k] = block k itself if col >= row, else the block at the
+    // transposed position; block k's tile sums are ts_ptr[k] .. ts_ptr[k+1]
+    TmpBuf mem(s), big(s);
+    int32_t *upart, *flag, *cblk;
+    int64_t *ts_ptr, *uoff, *tptr, *tmp;
     const int64_t nscan = std::max<int64_t>(std::max<int64_t>(nnz, nt), 1);
-    if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(nscan) + 64)))) return rc;
-    if (N) k_sym_partner<<<grid_for(N, BS), BS, 0, s>>>(N, g->row_ptr, g->col, g->upart);
+    if ((rc = dalloc_arrays(&mem.p, {{(void **)&upart, sizeof(int32_t) * nnz},
+                                     {(void **)&flag, sizeof(int32_t) * nnz},
+                                     {(void **)&cblk, sizeof(int32_t) * nt},
+                                     {(void **)&ts_ptr, sizeof(int64_t) * (nnz + 1)},
+                                     {(void **)&uoff, sizeof(int64_t) * (nnz + 1)},
+                                     {(void **)&tptr, sizeof(int64_t) * (nt + 1)},
+                                     {(void **)&tmp, sizeof(int64_t) * (scan_tmp_elems(nscan) + 64)}})))
+        return rc;
+    // partners; tile-block counts and offsets
+    int64_t nup = 0, ntb = 0;
     if (nnz) {
-        k_flag_upper<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, g->upart, (int32_t *)flag.p);
-        if ((rc = scan_to_ptr_i32((int32_t *)flag.p, nnz, (int64_t *)uoff.p, (int64_t *)tmp.p, s))) return rc;
-        FEA_HIP(hipMemsetAsync(g->lpart, 0xff, sizeof(int32_t) * nnz, s));
-        k_sym_lists<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, g->upart, (const int64_t *)uoff.p, g->lpart, g->ublk);
-        FEA_HIP(hipMemcpyAsync(&g->nup, (int64_t *)uoff.p + nnz, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        k_sym_partner<<<grid_for(N, BS), BS, 0, s>>>(N, g->row_ptr, g->col, upart);
+        k_flag_upper<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, upart, flag);
+        if ((rc = scan_to_ptr_i32(flag, nnz, uoff, tmp, s))) return rc;
+        FEA_HIP(hipMemcpyAsync(&nup, uoff + nnz, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    }
+    if (nt) {
+        k_tile_entries<false><<<(unsigned)nt, 256, 0, s>>>(tb, g->perm, g->pnodes, g->map_ptr, g->e2nnz, cblk, nullptr,
+                                                          nullptr, nullptr, nullptr);
+        if ((rc = scan_to_ptr_i32(cblk, nt, tptr, tmp, s))) return rc;
+        FEA_HIP(hipMemcpyAsync(&ntb, tptr + nt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    } else {
+        FEA_HIP(hipMemsetAsync(tptr, 0, sizeof(int64_t), s));
     }
     FEA_HIP(hipGetLastError());
-    // tiles: tile-block counts, offsets, then the pairs' places
-    TmpBuf cblk;
-    if ((rc = dalloc(&cblk.p, sizeof(int32_t) * std::max<int64_t>(nt, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->ttb_ptr, sizeof(int64_t) * (nt + 1)))) return rc;
-    int64_t ntb = 0;
-    if (nt) {
-        k_tile_entries<false><<<(unsigned)nt, 256, 0, s>>>(tb, g->perm, g->pnodes, g->map_ptr, g->e2nnz,
-                                                          (int32_t *)cblk.p, nullptr, nullptr, nullptr, nullptr);
-        if ((rc = scan_to_ptr_i32((int32_t *)cblk.p, nt, g->ttb_ptr, (int64_t *)tmp.p, s))) return rc;
-        FEA_HIP(hipMemcpyAsync(&ntb, g->ttb_ptr + nt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    } else {
-        FEA_HIP(hipMemsetAsync(g->ttb_ptr, 0, sizeof(int64_t), s));
-    }
     FEA_HIP(hipStreamSynchronize(s));
     if (ntb > INT32_MAX) return set_error(FEA_ERANGE, "%lld tile-blocks exceed the int32 slot range", (long long)ntb);
-    if ((rc = dalloc((void **)&g->tpos, sizeof(uint16_t) * std::max<int64_t>(nent, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->tb_rng, sizeof(uint16_t) * std::max<int64_t>(ntb, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->tb_blk, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->tb_slot, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->ts_ptr, sizeof(int64_t) * (nnz + 1)))) return rc;
+    if ((rc = dalloc_arrays(&g->mem[2], {{(void **)&g->lpart, sizeof(int32_t) * nnz},
+                                         {(void **)&g->ublk, sizeof(int32_t) * nup},
+                                         {(void **)&g->ulp, sizeof(int32_t) * nup},
+                                         {(void **)&g->uptr, sizeof(int64_t) * (nup + 1)},
+                                         {(void **)&g->ttb_ptr, sizeof(int64_t) * (nt + 1)},
+                                         {(void **)&g->tpos, sizeof(uint16_t) * nent},
+                                         {(void **)&g->tb_rng, sizeof(uint16_t) * ntb},
+                                         {(void **)&g->tb_blk, sizeof(int32_t) * ntb},
+                                         {(void **)&g->tb_slot, sizeof(int32_t) * ntb}})))
+        return rc;
+    FEA_HIP(hipMemcpyAsync(g->ttb_ptr, tptr, sizeof(int64_t) * (nt + 1), hipMemcpyDeviceToDevice, s));
+    if (nnz) {
+        FEA_HIP(hipMemsetAsync(g->lpart, 0xff, sizeof(int32_t) * nnz, s));
+        k_sym_lists<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, upart, uoff, g->lpart, g->ublk);
+    }
     if (nt)
         k_tile_entries<true><<<(unsigned)nt, 256, 0, s>>>(tb, g->perm, g->pnodes, g->map_ptr, g->e2nnz, nullptr,
                                                          g->ttb_ptr, g->tpos, g->tb_blk, g->tb_rng);
-    // workspace segments: per block its tile-blocks, ascending tile
-    TmpBuf lst;
-    if ((rc = dalloc(&lst.p, sizeof(int32_t) * std::max<int64_t>(ntb, 1)))) return rc;
+    // workspace segments: per block its tile-blocks, ascending tile (listed
+    // in uoff's memory, which nothing reads any more, where they fit)
+    int32_t *lst = (int32_t *)uoff;
+    if (ntb > 2 * (nnz + 1)) {
+        if ((rc = dalloc_pool(&big.p, sizeof(int32_t) * ntb))) return rc;
+        lst = (int32_t *)big.p;
+    }
     if (nnz) {
-        FEA_HIP(hipMemsetAsync(flag.p, 0, sizeof(int32_t) * nnz, s));
-        if (ntb) k_tb_count<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, (int32_t *)flag.p);
-        if ((rc = scan_to_ptr_i32((int32_t *)flag.p, nnz, g->ts_ptr, (int64_t *)tmp.p, s))) return rc;
-        FEA_HIP(hipMemsetAsync(flag.p, 0, sizeof(int32_t) * nnz, s));
+        FEA_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t) * nnz, s));
+        if (ntb) k_tb_count<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, flag);
+        if ((rc = scan_to_ptr_i32(flag, nnz, ts_ptr, tmp, s))) return rc;
+        FEA_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t) * nnz, s));
         if (ntb) {
-            k_tb_fill<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, g->ts_ptr, (int32_t *)flag.p,
-                                                       (int32_t *)lst.p);
-            k_tb_slots<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, g->ts_ptr, (int32_t *)lst.p, g->tb_slot);
+            k_tb_fill<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, ts_ptr, flag, lst);
+            k_tb_slots<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, ts_ptr, lst, g->tb_slot);
         }
     } else {
-        FEA_HIP(hipMemsetAsync(g->ts_ptr, 0, sizeof(int64_t), s));
+        FEA_HIP(hipMemsetAsync(ts_ptr, 0, sizeof(int64_t), s));
     }
-    const int64_t nup = g->nup;
-    if ((rc = dalloc((void **)&g->ulp, sizeof(int32_t) * std::max<int64_t>(nup, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->uptr, sizeof(int64_t) * (nup + 1)))) return rc;
-    k_sym_compact<<<grid_for(nup + 1, BS), BS, 0, s>>>(nup, nnz, N, g->ublk, g->lpart, g->ts_ptr, g->row_ptr, g->ulp,
+    k_sym_compact<<<grid_for(nup + 1, BS), BS, 0, s>>>(nup, nnz, N, g->ublk, g->lpart, ts_ptr, g->row_ptr, g->ulp,
                                                        g->uptr);
     FEA_HIP(hipGetLastError());
     FEA_HIP(hipStreamSynchronize(s));
+    g->nup = nup;
     g->ulen = ntb;
     g->nent = nent;
     // every row an element touches has one diagonal block: nnz = 2 nup - rows
@@ -789,54 +805,194 @@ int tile_colour_prepare(fea_graph *g, hipStream_t s)
 // definition, so it runs on the host over per-node masks of used colours,
 // on a thread of its own that starts once the mesh is validated and works
 // while the device builds the pattern and the maps.
+// A first fit needs one element at a time, so a large mesh's connectivity
+// comes in chunks through two small pinned buffers, the next one's copy
+// beside this one's colouring: at 3.3 M elements 10 ms of colouring is then
+// all there is, where copying everything first (pageable, and every page new)
+// took 17 to 20 ms more before the device could go on.
 struct HostColouring {
-    std::vector<int64_t> cp;
-    std::vector<int32_t> cn;
-    std::vector<uint8_t> ty;
+    static constexpr int64_t kChunk = 65536;  // elements
+    int device = 0;
+    int64_t N = 0, E = 0;
+    const uint8_t *types_d = nullptr;
+    const int32_t *conn_d = nullptr;
+    std::unique_ptr<uint8_t[]> ty;
+    std::unique_ptr<int32_t[]> cn;  // connectivity of a mesh of one chunk
     std::vector<int16_t> colour;
     std::vector<int64_t> cseg;
     std::vector<int32_t> cperm;
     int64_t ncol = 0;
     bool nomem = false;
+    hipError_t err = hipSuccess;
     std::thread th;
+
+    // Pinned buffers and a stream (open() on the colouring's thread)
+    struct Feed {
+        hipStream_t st = nullptr;
+        int32_t *conn[2] = {nullptr, nullptr};
+        uint8_t *types = nullptr;
+        ~Feed()
+        {
+            if (st) {
+                (void)hipStreamSynchronize(st);
+                (void)hipStreamDestroy(st);
+            }
+            if (conn[0]) (void)hipHostFree(conn[0]);
+        }
+        hipError_t open()
+        {
+            const size_t cb = sizeof(int32_t) * 8 * kChunk;
+            hipError_t e = hipHostMalloc((void **)&conn[0], 2 * cb + kChunk, hipHostMallocDefault);
+            if (e != hipSuccess) return e;
+            conn[1] = conn[0] + 8 * kChunk;
+            types = (uint8_t *)(conn[0] + 2 * 8 * kChunk);
+            return hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+        }
+        // Device copy of pageable memory, through the two buffers.
+        hipError_t put(void *dst, const void *src, size_t bytes)
+        {
+            const size_t cb = sizeof(int32_t) * 8 * kChunk;
+            hipError_t e = hipSuccess;
+            for (size_t off = 0, i = 0; off < bytes && e == hipSuccess; off += cb, ++i) {
+                const size_t n = std::min(cb, bytes - off);
+                if (i >= 2) e = hipStreamSynchronize(st);
+                memcpy(conn[i & 1], (const char *)src + off, n);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync((char *)dst + off, conn[i & 1], n, hipMemcpyHostToDevice, st);
+            }
+            const hipError_t w = hipStreamSynchronize(st);
+            return e == hipSuccess ? w : e;
+        }
+        hipError_t fetch(void *dst, const void *src, size_t bytes)
+        {
+            return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
+        }
+    };
+
+    Feed f;
+
     ~HostColouring()
     {
         if (th.joinable()) th.join();
     }
-    void run(int64_t N, int64_t E)
+
+    int64_t entries(int64_t e0, int64_t n) const
+    {
+        int64_t len = 0;
+        for (int64_t e = e0; e < e0 + n; ++e) len += nodes_of(ty[e]);
+        return len;
+    }
+
+    // Colours elements e0 .. e0 + n (their nodes at v): the first that finds
+    // no colour, or -1.
+    template <int W>
+    int64_t place(host::FirstFit<W> &ff, int64_t e0, int64_t n, const int32_t *v)
+    {
+        for (int64_t e = e0; e < e0 + n; ++e) {
+            const int nn = nodes_of(ty[e]);
+            int c;
+            switch (nn) {  // constant lengths
+            case 4: c = ff.place(v, 4); break;
+            case 5: c = ff.place(v, 5); break;
+            case 6: c = ff.place(v, 6); break;
+            default: c = ff.place(v, 8); break;
+            }
+            if (c < 0) return e;
+            colour[(size_t)e] = (int16_t)c;
+            v += nn;
+        }
+        return -1;
+    }
+
+    // Number of colours, or -(1 + e) when element e would need more than 64 W.
+    template <int W>
+    int64_t first_fit()
+    {
+        host::FirstFit<W> ff(N);
+        int64_t bad = -1;
+        if (cn) {
+            bad = place(ff, 0, E, cn.get());
+            return bad < 0 ? ff.colours() : -(1 + bad);
+        }
+        // chunk c's connectivity and chunk c + 1's types are on their way
+        // while chunk c - 1 is coloured
+        int64_t n = std::min(kChunk, E), pos = 0;
+        if ((err = f.fetch(f.types, types_d, (size_t)n)) != hipSuccess) return 0;
+        if ((err = hipStreamSynchronize(f.st)) != hipSuccess) return 0;
+        memcpy(ty.get(), f.types, (size_t)n);
+        int64_t len = entries(0, n);
+        if ((err = f.fetch(f.conn[0], conn_d, sizeof(int32_t) * len)) != hipSuccess) return 0;
+        int64_t n1 = std::min(kChunk, E - n);
+        if (n1 && (err = f.fetch(f.types, types_d + n, (size_t)n1)) != hipSuccess) return 0;
+        for (int64_t e0 = 0, c = 0; e0 < E; ++c) {
+            if ((err = hipStreamSynchronize(f.st)) != hipSuccess) return 0;
+            const int64_t e1 = e0 + n, next = n1;
+            int64_t len1 = 0;
+            if (next) {
+                memcpy(ty.get() + e1, f.types, (size_t)next);
+                len1 = entries(e1, next);
+                if ((err = f.fetch(f.conn[(c + 1) & 1], conn_d + pos + len, sizeof(int32_t) * len1)) != hipSuccess)
+                    return 0;
+                n1 = std::min(kChunk, E - e1 - next);
+                if (n1 && (err = f.fetch(f.types, types_d + e1 + next, (size_t)n1)) != hipSuccess) return 0;
+            }
+            if ((bad = place(ff, e0, n, f.conn[c & 1])) >= 0) return -(1 + bad);
+            e0 = e1;
+            n = next;
+            pos += len;
+            len = len1;
+        }
+        return ff.colours();
+    }
+
+    void run()
     {
         try {
+            if (!cn && E) {
+                if ((err = hipSetDevice(device)) != hipSuccess) return;
+                if ((err = f.open()) != hipSuccess) return;
+            }
             colour.assign((size_t)std::max<int64_t>(E, 1), 0);
-            ncol = host::greedy_first_fit(N, E, cp.data(), cn.data(), nullptr, colour.data());
+            // one mask word per node first; with the full masks, in the same
+            // order, only if an element needs a 65th colour
+            if (E) ncol = first_fit<1>();
+            if (ncol < 0) {
+                if (f.st) (void)hipStreamSynchronize(f.st);
+                ncol = first_fit<host::kMaxColours / 64>();
+            }
             // stable buckets by (family, colour) of element ids
-            if (ncol >= 0) host::buckets(E, 4, ty.data(), colour.data(), (int)ncol, nullptr, nullptr, cseg, cperm);
+            if (err == hipSuccess && ncol >= 0)
+                host::buckets(E, 4, ty.get(), colour.data(), (int)ncol, nullptr, nullptr, cseg, cperm);
         } catch (...) {
             nomem = true;
         }
     }
 };
 
-// Copies the (validated) connectivity to the host and starts the colouring.
-static int colour_start(fea_graph *g, const int64_t *conn_ptr_d, const int32_t *conn_d, const uint8_t *types_d,
-                        hipStream_t s, HostColouring &hc)
+// Starts the colouring of the (validated) mesh.
+static int colour_start(fea_graph *g, const int32_t *conn_d, const uint8_t *types_d, hipStream_t s, HostColouring &hc)
 {
-    const int64_t E = g->n_elems, N = g->n_nodes;
+    const int64_t E = g->n_elems;
+    hc.device = g->device;
+    hc.N = g->n_nodes;
+    hc.E = E;
+    hc.types_d = types_d;
+    hc.conn_d = conn_d;
     try {
-        hc.cp.resize(E + 1);
-        hc.cn.resize(g->conn_len);
-        hc.ty.resize(E);
+        hc.ty.reset(new uint8_t[(size_t)std::max<int64_t>(E, 1)]);
+        if (E <= HostColouring::kChunk) hc.cn.reset(new int32_t[(size_t)std::max<int64_t>(g->conn_len, 1)]);
     } catch (...) {
         return set_error(FEA_ENOMEM, "host allocation failed (colouring)");
     }
-    FEA_HIP(hipMemcpyAsync(hc.cp.data(), conn_ptr_d, sizeof(int64_t) * (E + 1), hipMemcpyDeviceToHost, s));
-    if (g->conn_len)
-        FEA_HIP(hipMemcpyAsync(hc.cn.data(), conn_d, sizeof(int32_t) * g->conn_len, hipMemcpyDeviceToHost, s));
-    if (E) FEA_HIP(hipMemcpyAsync(hc.ty.data(), types_d, E, hipMemcpyDeviceToHost, s));
-    FEA_HIP(hipStreamSynchronize(s));
+    if (hc.cn && E) {  // one chunk: without buffers and a stream for it
+        FEA_HIP(hipMemcpyAsync(hc.ty.get(), types_d, (size_t)E, hipMemcpyDeviceToHost, s));
+        FEA_HIP(hipMemcpyAsync(hc.cn.get(), conn_d, sizeof(int32_t) * g->conn_len, hipMemcpyDeviceToHost, s));
+        FEA_HIP(hipStreamSynchronize(s));
+    }
     try {
-        hc.th = std::thread([&hc, N, E] { hc.run(N, E); });
+        hc.th = std::thread([&hc] { hc.run(); });
     } catch (...) {
-        hc.run(N, E);  // no thread to be had: colour here
+        hc.run();  // no thread to be had: colour here
     }
     return FEA_OK;
 }
@@ -847,30 +1003,31 @@ static int colour_finish(fea_graph *g, HostColouring &hc, hipStream_t s)
     const int64_t E = g->n_elems;
     if (hc.th.joinable()) hc.th.join();
     if (hc.nomem) return set_error(FEA_ENOMEM, "host allocation failed (colouring)");
+    if (hc.err != hipSuccess)
+        return set_error(FEA_EHIP, "copy of the connectivity to the host failed: %s", hipGetErrorString(hc.err));
     if (hc.ncol < 0)
         return set_error(FEA_ERANGE, "element %lld needs more than %d colours", (long long)(-hc.ncol - 1),
                          host::kMaxColours);
-    int rc;
-    if ((rc = dalloc((void **)&g->colour, sizeof(int16_t) * std::max<int64_t>(E, 1)))) return rc;
-    if ((rc = dalloc((void **)&g->cperm, sizeof(int32_t) * std::max<int64_t>(E, 1)))) return rc;
-    if (E) {
+    if (E && hc.cn) {
         FEA_HIP(hipMemcpyAsync(g->colour, hc.colour.data(), sizeof(int16_t) * E, hipMemcpyHostToDevice, s));
         FEA_HIP(hipMemcpyAsync(g->cperm, hc.cperm.data(), sizeof(int32_t) * E, hipMemcpyHostToDevice, s));
+        FEA_HIP(hipStreamSynchronize(s));
+    } else if (E) {
+        FEA_HIP(hc.f.put(g->colour, hc.colour.data(), sizeof(int16_t) * E));
+        FEA_HIP(hc.f.put(g->cperm, hc.cperm.data(), sizeof(int32_t) * E));
     }
-    FEA_HIP(hipStreamSynchronize(s));
     g->n_colours = (int)hc.ncol;
     g->cseg = std::move(hc.cseg);
     return FEA_OK;
 }
 
+// No work on the graph's arrays may be pending.
 static void destroy(fea_graph *g)
 {
     if (!g) return;
-    void *bufs[] = {g->row_ptr, g->col, g->map_ptr, g->e2nnz, g->inv_ptr, g->inv, g->pnodes, g->pdest, g->prdest,
-                    g->n2e_ptr, g->n2e, g->n2a, g->perm, g->colour, g->cperm,
-                    g->contrib, g->rcontrib, g->acc64, g->gtile, g->gnodes, g->gdesc, g->upart, g->ublk, g->lpart, g->ttb_ptr,
-                    g->tpos, g->tb_rng, g->tb_blk, g->tb_slot, g->ts_ptr, g->ctile, g->gp_ptr, g->ulp, g->uptr};
-    for (void *b : bufs) dfree(b);
+    void *bufs[] = {g->mem[0], g->mem[1], g->mem[2], g->contrib, g->rcontrib, g->acc64,
+                    g->gtile, g->gnodes, g->gdesc, g->ctile, g->gp_ptr};
+    for (void *b : bufs) pool_free(b);
     for (hipEvent_t e : g->ev)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : g->gev)
@@ -881,19 +1038,17 @@ static void destroy(fea_graph *g)
 
 // Checks a mesh (FEA_EMESH names the first bad element): its fingerprint,
 // the elements of every family and, if fam_cnt is given (4 per workgroup of
-// 256 elements), the workgroups' counts. Blocks on the stream.
+// 256 elements), the workgroups' counts. out: device memory. Blocks on the
+// stream.
 static int mesh_check(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn_ptr, const int32_t *conn,
-                      int32_t *fam_cnt, hipStream_t s, MeshCheck *mc)
+                      MeshCheck *out, int32_t *fam_cnt, hipStream_t s, MeshCheck *mc)
 {
-    TmpBuf out;
-    int rc;
-    if ((rc = dalloc(&out.p, sizeof(MeshCheck)))) return rc;
     *mc = MeshCheck{~0ull, 0, {0, 0, 0, 0}};
     if (!E) return FEA_OK;
-    FEA_HIP(hipMemcpyAsync(out.p, mc, sizeof(MeshCheck), hipMemcpyHostToDevice, s));
-    k_mesh_check<<<grid_for(E, 256), 256, 0, s>>>(N, E, types, conn_ptr, conn, (MeshCheck *)out.p, fam_cnt);
+    FEA_HIP(hipMemcpyAsync(out, mc, sizeof(MeshCheck), hipMemcpyHostToDevice, s));
+    k_mesh_check<<<grid_for(E, 256), 256, 0, s>>>(N, E, types, conn_ptr, conn, out, fam_cnt);
     FEA_HIP(hipGetLastError());
-    FEA_HIP(hipMemcpyAsync(mc, out.p, sizeof(MeshCheck), hipMemcpyDeviceToHost, s));
+    FEA_HIP(hipMemcpyAsync(mc, out, sizeof(MeshCheck), hipMemcpyDeviceToHost, s));
     FEA_HIP(hipStreamSynchronize(s));
     if (mc->bad != ~0ull)
         return set_error(FEA_EMESH, "invalid element %lld (unknown type, wrong node count, node id out "
@@ -909,14 +1064,15 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
     FEA_HIP(hipGetDevice(&g->device));
     g->n_nodes = N;
     g->n_elems = E;
-    auto one = [](int64_t n) { return std::max<int64_t>(n, 1); };
 
     // validation, fingerprint, family counts: every size but the pattern's
     const int64_t nb = (E + 255) / 256;
-    TmpBuf famc, famp, tmp, epos, cnt, ptr2, deg, vs;
-    if ((rc = dalloc(&famc.p, sizeof(int32_t) * one(4 * nb)))) return rc;
-    MeshCheck mc;
-    if ((rc = mesh_check(N, E, types, conn_ptr, conn, (int32_t *)famc.p, s, &mc))) return rc;
+    TmpBuf chk(s), tmp(s);
+    MeshCheck *out, mc;
+    int32_t *famc;
+    if ((rc = dalloc_arrays(&chk.p, {{(void **)&out, sizeof(MeshCheck)}, {(void **)&famc, sizeof(int32_t) * 4 * nb}})))
+        return rc;
+    if ((rc = mesh_check(N, E, types, conn_ptr, conn, out, famc, s, &mc))) return rc;
     g->mesh_fp = mc.fp;
     RowBases bs;
     for (int t = 0; t < 4; ++t) {
@@ -930,62 +1086,66 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
     g->conn_len = g->node_base[4];
     g->map_len = g->slot_base[4];
     HostColouring hc;  // joined on every return
-    if ((rc = colour_start(g, conn_ptr, conn, types, s, hc))) return rc;
-    if (g->map_len > INT32_MAX || g->conn_len > INT32_MAX)
-        return set_error(FEA_ERANGE, "%lld element-matrix slots / %lld incidences exceed int32 maps",
-                         (long long)g->map_len, (long long)g->conn_len);
+    if ((rc = colour_start(g, conn, types, s, hc))) return rc;
+    const int64_t C = g->conn_len, M = g->map_len;
+    if (M > INT32_MAX || C > INT32_MAX)
+        return set_error(FEA_ERANGE, "%lld element-matrix slots / %lld incidences exceed int32 maps", (long long)M,
+                         (long long)C);
+    int64_t *scan, *famp, *cnt, *ptr2;
+    int32_t *epos, *deg, *vs;
+    if ((rc = dalloc_arrays(&g->mem[0], {{(void **)&g->map_ptr, sizeof(int64_t) * (E + 1)},
+                                         {(void **)&g->perm, sizeof(int32_t) * E},
+                                         {(void **)&g->n2e_ptr, sizeof(int64_t) * (N + 1)},
+                                         {(void **)&g->n2e, sizeof(int32_t) * C},
+                                         {(void **)&g->n2a, sizeof(uint8_t) * C},
+                                         {(void **)&g->pnodes, sizeof(int32_t) * C},
+                                         {(void **)&g->prdest, sizeof(int32_t) * C},
+                                         {(void **)&g->pdest, sizeof(int32_t) * M},
+                                         {(void **)&g->inv, sizeof(int32_t) * M},
+                                         {(void **)&g->e2nnz, sizeof(int32_t) * M},
+                                         {(void **)&g->row_ptr, sizeof(int64_t) * (N + 1)},
+                                         {(void **)&g->colour, sizeof(int16_t) * E},
+                                         {(void **)&g->cperm, sizeof(int32_t) * E}})))
+        return rc;
+    if ((rc = dalloc_arrays(&tmp.p, {{(void **)&scan, sizeof(int64_t) * (scan_tmp_elems(std::max(4 * nb, N)) + 64)},
+                                     {(void **)&famp, sizeof(int64_t) * (4 * nb + 1)},
+                                     {(void **)&epos, sizeof(int32_t) * E},
+                                     {(void **)&cnt, sizeof(int64_t) * N},
+                                     {(void **)&ptr2, sizeof(int64_t) * (N + 1)},
+                                     {(void **)&deg, sizeof(int32_t) * N},
+                                     {(void **)&vs, sizeof(int32_t) * M}})))
+        return rc;
 
     // type segmentation, first slots
-    if ((rc = dalloc(&tmp.p, sizeof(int64_t) * (scan_tmp_elems(std::max(4 * nb, N)) + 64)))) return rc;
-    if ((rc = dalloc(&famp.p, sizeof(int64_t) * (4 * nb + 1)))) return rc;
-    if ((rc = dalloc(&epos.p, sizeof(int32_t) * one(E)))) return rc;
-    if ((rc = dalloc((void **)&g->map_ptr, sizeof(int64_t) * (E + 1)))) return rc;
-    if ((rc = dalloc((void **)&g->perm, sizeof(int32_t) * one(E)))) return rc;
     if (E) {
-        if ((rc = scan_to_ptr_i32((int32_t *)famc.p, 4 * nb, (int64_t *)famp.p, (int64_t *)tmp.p, s))) return rc;
-        k_type_place<<<(unsigned)nb, 256, 0, s>>>(E, types, (const int64_t *)famp.p, g->perm, (int32_t *)epos.p,
-                                                  g->map_ptr);
+        if ((rc = scan_to_ptr_i32(famc, 4 * nb, famp, scan, s))) return rc;
+        k_type_place<<<(unsigned)nb, 256, 0, s>>>(E, types, famp, g->perm, epos, g->map_ptr);
     } else {
         FEA_HIP(hipMemsetAsync(g->map_ptr, 0, sizeof(int64_t), s));
     }
 
     // node incidence (prdest holds the places in the unsorted lists meanwhile)
-    if ((rc = dalloc(&cnt.p, sizeof(int64_t) * one(N)))) return rc;
-    if ((rc = dalloc(&ptr2.p, sizeof(int64_t) * (N + 1)))) return rc;
-    if ((rc = dalloc(&deg.p, sizeof(int32_t) * one(N)))) return rc;
-    if ((rc = dalloc(&vs.p, sizeof(int32_t) * one(g->map_len)))) return rc;
-    if ((rc = dalloc((void **)&g->n2e_ptr, sizeof(int64_t) * (N + 1)))) return rc;
-    if ((rc = dalloc((void **)&g->n2e, sizeof(int32_t) * one(g->conn_len)))) return rc;
-    if ((rc = dalloc((void **)&g->n2a, one(g->conn_len)))) return rc;
-    if ((rc = dalloc((void **)&g->pnodes, sizeof(int32_t) * one(g->conn_len)))) return rc;
-    if ((rc = dalloc((void **)&g->prdest, sizeof(int32_t) * one(g->conn_len)))) return rc;
-    if ((rc = dalloc((void **)&g->pdest, sizeof(int32_t) * one(g->map_len)))) return rc;
-    if ((rc = dalloc((void **)&g->inv, sizeof(int32_t) * one(g->map_len)))) return rc;
-    if ((rc = dalloc((void **)&g->row_ptr, sizeof(int64_t) * (N + 1)))) return rc;
-    FEA_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int64_t) * one(N), s));
-    if (E) k_node_count<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, (unsigned long long *)cnt.p, g->prdest);
-    if ((rc = scan_to_ptr_i64((int64_t *)cnt.p, N, (int64_t *)ptr2.p, (int64_t *)tmp.p, s))) return rc;
-    if (E) k_node_fill<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, (const int64_t *)ptr2.p, g->prdest, g->n2e, g->n2a);
+    if (N) FEA_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * N, s));
+    if (E) k_node_count<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, (unsigned long long *)cnt, g->prdest);
+    if ((rc = scan_to_ptr_i64(cnt, N, ptr2, scan, s))) return rc;
+    if (E) k_node_fill<<<grid_for(E, BS), BS, 0, s>>>(E, conn_ptr, conn, ptr2, g->prdest, g->n2e, g->n2a);
 
     // rows: sorted slots, degrees, prefix sum, then blocks
-    const RowOut ro = {conn_ptr, conn, g->map_ptr, (const int32_t *)epos.p, (int32_t *)vs.p, g->inv, g->pdest,
-                       g->pnodes, g->prdest};
+    const RowOut ro = {conn_ptr, conn, g->map_ptr, epos, vs, g->inv, g->pdest, g->pnodes, g->prdest};
     if (N)
-        k_rows<<<grid_for(N, 4), 256, 0, s>>>(N, (const int64_t *)ptr2.p, ro, bs, g->n2e_ptr, g->n2e, g->n2a,
-                                              (int32_t *)deg.p);
+        k_rows<<<grid_for(N, 4), 256, 0, s>>>(N, ptr2, ro, bs, g->n2e_ptr, g->n2e, g->n2a, deg);
     else
         FEA_HIP(hipMemsetAsync(g->n2e_ptr, 0, sizeof(int64_t), s));
-    if ((rc = scan_to_ptr_i32((int32_t *)deg.p, N, g->row_ptr, (int64_t *)tmp.p, s))) return rc;
+    if ((rc = scan_to_ptr_i32(deg, N, g->row_ptr, scan, s))) return rc;
     FEA_HIP(hipMemcpyAsync(&g->nnz, g->row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     FEA_HIP(hipStreamSynchronize(s));
     if (g->nnz > INT32_MAX)
         return set_error(FEA_ERANGE, "%lld nonzero blocks exceed int32 block indices", (long long)g->nnz);
-    if ((rc = dalloc((void **)&g->col, sizeof(int32_t) * one(g->nnz)))) return rc;
-    if ((rc = dalloc((void **)&g->e2nnz, sizeof(int32_t) * one(g->map_len)))) return rc;
-    if ((rc = dalloc((void **)&g->inv_ptr, sizeof(int64_t) * (g->nnz + 1)))) return rc;
+    if ((rc = dalloc_arrays(&g->mem[1], {{(void **)&g->col, sizeof(int32_t) * g->nnz},
+                                         {(void **)&g->inv_ptr, sizeof(int64_t) * (g->nnz + 1)}})))
+        return rc;
     if (N)
-        k_row_blocks<<<grid_for(N, 4), 256, 0, s>>>(N, (const int64_t *)ptr2.p, g->row_ptr, (const int32_t *)vs.p, g->inv,
-                                                    g->col, g->inv_ptr, g->e2nnz);
+        k_row_blocks<<<grid_for(N, 4), 256, 0, s>>>(N, ptr2, g->row_ptr, vs, g->inv, g->col, g->inv_ptr, g->e2nnz);
     else
         FEA_HIP(hipMemsetAsync(g->inv_ptr, 0, sizeof(int64_t), s));
     FEA_HIP(hipGetLastError());
@@ -1069,12 +1229,7 @@ int device_arch(int dev, char *arch)
 }
 
 // The graph's arrays that the cache holds, with their lengths in bytes.
-struct GraphArray {
-    void **p;
-    size_t bytes;
-};
-
-std::vector<GraphArray> graph_arrays(fea_graph *g)
+std::vector<DevArray> graph_arrays(fea_graph *g)
 {
     const size_t N = (size_t)g->n_nodes, E = (size_t)g->n_elems, nnz = (size_t)g->nnz,
                  ml = (size_t)g->map_len, cl = (size_t)g->conn_len;
@@ -1121,7 +1276,7 @@ extern "C" int fea_graph_save(const fea_graph *gc, const char *path)
     PinnedBuf stage;
     FEA_HIP(hipHostMalloc(&stage.p, kStage, hipHostMallocDefault));
     FEA_HIP(hipDeviceSynchronize());
-    for (const GraphArray &a : graph_arrays(g)) {
+    for (const DevArray &a : graph_arrays(g)) {
         const uint64_t nb = a.bytes;
         ok = ok && fwrite(&nb, 8, 1, f.f) == 1;
         for (size_t off = 0; ok && off < a.bytes; off += kStage) {
@@ -1168,7 +1323,10 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         return set_error(FEA_EINVAL, "%s: inconsistent header", path);
     // the mesh must be the one the graph was built for
     MeshCheck mc;
-    if ((rc = mesh_check(n_nodes, n_elems, types, conn_ptr, conn, nullptr, stream, &mc))) return rc;
+    TmpBuf chk(stream);
+    if ((rc = dalloc_pool(&chk.p, sizeof(MeshCheck)))) return rc;
+    if ((rc = mesh_check(n_nodes, n_elems, types, conn_ptr, conn, (MeshCheck *)chk.p, nullptr, stream, &mc)))
+        return rc;
     if (mc.fp != h.mesh_fp) return set_error(FEA_EINVAL, "%s was built for another mesh (connectivity differs)", path);
     fea_graph *g = new (std::nothrow) fea_graph();
     if (!g) return set_error(FEA_ENOMEM, "host allocation failed");
@@ -1193,15 +1351,24 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
             return set_error(FEA_ENOMEM, "pinned staging buffer: %s", hipGetErrorString(e));
         }
     }
-    for (const GraphArray &a : graph_arrays(g)) {
+    const std::vector<DevArray> arrays = graph_arrays(g);
+    // every array's byte count first: a file that does not match allocates nothing
+    const long data = ftell(f.f);
+    ok = ok && data >= 0;
+    for (const DevArray &a : arrays) {
+        uint64_t nb = 0;
+        ok = ok && fread(&nb, 8, 1, f.f) == 1 && nb == a.bytes && fseek(f.f, (long)a.bytes, SEEK_CUR) == 0;
+    }
+    ok = ok && fseek(f.f, data, SEEK_SET) == 0;
+    if (ok && (rc = dalloc_arrays(&g->mem[0], arrays))) {
+        destroy(g);
+        return rc;
+    }
+    for (const DevArray &a : arrays) {
         if (!ok) break;
         uint64_t nb = 0;
         ok = fread(&nb, 8, 1, f.f) == 1 && nb == a.bytes;
         if (!ok) break;
-        if ((rc = dalloc(a.p, a.bytes))) {
-            destroy(g);
-            return rc;
-        }
         for (size_t off = 0; ok && off < a.bytes; off += kStage) {
             const size_t n = std::min(kStage, a.bytes - off);
             ok = fread(stage.p, 1, n, f.f) == n;

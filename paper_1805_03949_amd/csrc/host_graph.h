@@ -18,29 +18,46 @@ namespace host {
 
 constexpr int kMaxColours = 256;
 
-// Greedy first fit over per-node masks of W 64-bit words (64 W colours):
-// returns the number of colours, or -(1 + i) when item i would need more.
+// Greedy first fit over per-node masks of W 64-bit words (64 W colours).
+template <int W>
+class FirstFit {
+    std::vector<uint64_t> used;
+    int ncol = 0;
+
+public:
+    explicit FirstFit(int64_t n_nodes) : used((size_t)std::max<int64_t>(n_nodes, 1) * W, 0) {}
+    int colours() const { return ncol; }
+    // The smallest colour that none of the item's nodes has seen, or -1.
+    int place(const int32_t *v, int64_t n)
+    {
+        uint64_t m[W];
+        for (int w = 0; w < W; ++w) m[w] = 0;
+        for (int64_t p = 0; p < n; ++p)
+            for (int w = 0; w < W; ++w) m[w] |= used[(size_t)v[p] * W + w];
+        int c = -1;
+        for (int w = 0; w < W && c < 0; ++w)
+            if (~m[w]) c = w * 64 + __builtin_ctzll(~m[w]);
+        if (c < 0) return -1;
+        ncol = std::max(ncol, c + 1);
+        for (int64_t p = 0; p < n; ++p) used[(size_t)v[p] * W + c / 64] |= 1ull << (c % 64);
+        return c;
+    }
+};
+
+// First fit of all items: returns the number of colours, or -(1 + i) when
+// item i would need more.
 template <int W>
 inline int64_t greedy_first_fit_words(int64_t n_nodes, int64_t n_items, const int64_t *ptr, const int32_t *nodes,
                                       const int64_t *order, int16_t *colour)
 {
-    std::vector<uint64_t> used((size_t)std::max<int64_t>(n_nodes, 1) * W, 0);
-    int ncol = 0;
+    FirstFit<W> ff(n_nodes);
     for (int64_t k = 0; k < n_items; ++k) {
         const int64_t i = order ? order[k] : k;
-        uint64_t m[W];
-        for (int w = 0; w < W; ++w) m[w] = 0;
-        for (int64_t p = ptr[i]; p < ptr[i + 1]; ++p)
-            for (int w = 0; w < W; ++w) m[w] |= used[(size_t)nodes[p] * W + w];
-        int c = -1;
-        for (int w = 0; w < W && c < 0; ++w)
-            if (~m[w]) c = w * 64 + __builtin_ctzll(~m[w]);
+        const int c = ff.place(nodes + ptr[i], ptr[i + 1] - ptr[i]);
         if (c < 0) return -(1 + i);
         colour[i] = (int16_t)c;
-        ncol = std::max(ncol, c + 1);
-        for (int64_t p = ptr[i]; p < ptr[i + 1]; ++p) used[(size_t)nodes[p] * W + c / 64] |= 1ull << (c % 64);
     }
-    return ncol;
+    return ff.colours();
 }
 
 // Greedy first fit (Algorithm 5's colouring): items are visited in `order`
@@ -108,14 +125,14 @@ inline std::vector<int64_t> priority_order(int64_t n_items, const int32_t *nneig
 // A stable counting sort over consecutive chunks of the visit order, one
 // thread each: per-chunk bucket counts, then each chunk places its items
 // from its own offsets, so the result is the one-thread result. threads: 0
-// = one per 2^20 items, at most 8; failing to start a thread runs its chunk
+// = one per 2^17 items, at most 8; failing to start a thread runs its chunk
 // on the calling thread.
 inline void buckets(int64_t n_items, int n_groups, const uint8_t *group, const int16_t *colour, int ncol,
                     const int64_t *order, const int64_t *first, std::vector<int64_t> &seg,
                     std::vector<int32_t> &list, int threads = 0)
 {
     const int64_t nb = (int64_t)n_groups * ncol;
-    if (threads <= 0) threads = (int)std::min<int64_t>(8, n_items >> 20);
+    if (threads <= 0) threads = (int)std::min<int64_t>(8, n_items >> 17);
     threads = (int)std::max<int64_t>(1, std::min<int64_t>(threads, n_items));
     std::vector<int64_t> cnt((size_t)threads * std::max<int64_t>(nb, 1), 0);
     auto item = [&](int64_t k) { return order ? order[k] : k; };

@@ -2,9 +2,12 @@
 up to 64, 128, 256 and 512 slots, rows of 64, 65 and 200 elements, nodes of no
 element and meshes of few nodes (long block lists), in shuffled order, every
 exported and stored array equal to the one the definitions give."""
+import threading
+
 import numpy as np
 import pytest
 
+import meshgen as mg
 import oracle
 
 torch = pytest.importorskip("torch")
@@ -81,3 +84,58 @@ def test_rows(n, elems, fams, hub, tmp_path):
     assert np.array_equal(prdest, place[entries])
     assert np.array_equal(pdest, back[slots])
     g.destroy()
+
+
+@pytest.mark.parametrize("elems,hub", [(65536, 1), (65537, 1), (131075, 1), (70000, 70)])
+def test_colouring_in_chunks(elems, hub):
+    """Meshes of one chunk of the colouring's connectivity stream, one element
+    more, two chunks and a remainder, and one that needs the wide masks: the
+    colours are the first fit in element order."""
+    rng = np.random.default_rng(elems)
+    types = rng.choice([0, 0, 1, 2, 3], elems)
+    cp = np.concatenate([[0], np.cumsum(NODES[types])]).astype(np.int64)
+    # nodes 7 k + (0 .. n - 1) from a random k: distinct, neighbours by chance
+    first = 1 + 7 * rng.integers(0, 30000, elems)
+    conn = (np.repeat(first - cp[:-1], NODES[types]) + np.arange(cp[-1])).astype(np.int32)
+    conn[cp[np.sort(rng.choice(elems, hub, replace=False))]] = 0
+    n = int(conn.max()) + 1
+    dev = [torch.from_numpy(a).to("cuda:0") for a in (types.astype(np.uint8), cp, conn)]
+    g = fea.Graph(n, *dev)
+    colour, nc = oracle.colour_greedy(n, cp, conn)
+    assert g.n_colours == nc and (hub < 65 or nc > 64)
+    assert np.array_equal(g.export()["colour"].cpu().numpy(), colour)
+    g.destroy()
+
+
+def test_graphs_of_two_threads_share_freed_memory():
+    """Two threads, each on a stream of its own, build, assemble and destroy
+    graphs of changing sizes, so that each takes memory that the other gave
+    back: every result equals the one of a graph that lives alone."""
+    cells = [6, 9, 12, 9, 6, 12]
+    meshes = {n: fea.DeviceMesh(mg.hybrid_bands(n, seed=n, jitter=0.2)) for n in set(cells)}
+    ref = {}
+    for n, dm in meshes.items():
+        g = dm.graph()
+        ref[n] = [x.clone() for x in dm.assemble(g, variant=fea.ROWSYM)]
+        torch.cuda.synchronize()
+        g.destroy()
+    wrong = []
+
+    def work(order):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for n in order * 3:
+                    g = meshes[n].graph()
+                    got = meshes[n].assemble(g, variant=fea.ROWSYM)
+                    torch.cuda.current_stream().synchronize()
+                    wrong.extend(n for a, b in zip(got, ref[n]) if not torch.equal(a, b))
+                    g.destroy()
+        except Exception as e:  # noqa: BLE001
+            wrong.append(e)
+
+    threads = [threading.Thread(target=work, args=(o,)) for o in (cells, cells[::-1])]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
