@@ -1,9 +1,11 @@
 // Element quadrature and scatter kernels (paper Section 2.1.1, Algorithm 1;
 // race treatments of Section 3.2: Algorithm 4 ATOMIC, Algorithm 5 colouring).
 // The element device code lives in elem.h.
+#include <algorithm>
 #include <climits>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "elem.h"
 #include "segsum.h"
@@ -38,10 +40,35 @@ __global__ void k_to_f32(const double *in, float *out, int64_t n)
     if (i < n) out[i] = (float)in[i];
 }
 
-__global__ void k_status_init(int32_t *s) { *s = INT_MAX; }
-__global__ void k_status_final(int32_t *s)
+__global__ void k_status_init(int32_t *s) { *s = -1; }
+
+// The four families' tiles in one launch, family t's from first[t] on.
+struct ElemArgs4 {
+    ElemArgs a[4];
+    uint32_t first[4];
+};
+
+template <int MODEL, int VAR, typename CT>
+union ElemSmem4 {
+    ElemSmem<0, MODEL, VAR, CT> s0;
+    ElemSmem<1, MODEL, VAR, CT> s1;
+    ElemSmem<2, MODEL, VAR, CT> s2;
+    ElemSmem<3, MODEL, VAR, CT> s3;
+};
+
+template <int MODEL, int VAR, typename CT>
+__global__ void __launch_bounds__(256) k_element4(ElemArgs4 A)
 {
-    if (*s == INT_MAX) *s = -1;
+    __shared__ ElemSmem4<MODEL, VAR, CT> S;
+    const uint32_t b = blockIdx.x;
+    if (b < A.first[1])
+        elem_tile<0, MODEL, VAR, CT>(A.a[0], (int64_t)b * ElemSmem<0, MODEL, VAR, CT>::EPB, S.s0);
+    else if (b < A.first[2])
+        elem_tile<1, MODEL, VAR, CT>(A.a[1], (int64_t)(b - A.first[1]) * ElemSmem<1, MODEL, VAR, CT>::EPB, S.s1);
+    else if (b < A.first[3])
+        elem_tile<2, MODEL, VAR, CT>(A.a[2], (int64_t)(b - A.first[2]) * ElemSmem<2, MODEL, VAR, CT>::EPB, S.s2);
+    else
+        elem_tile<3, MODEL, VAR, CT>(A.a[3], (int64_t)(b - A.first[3]) * ElemSmem<3, MODEL, VAR, CT>::EPB, S.s3);
 }
 
 template <int T, int MODEL, int VAR, typename CT>
@@ -65,6 +92,55 @@ static void launch_type(int t, const ElemArgs &a, hipStream_t s)
     case 2: launch_fam<2, MODEL, VAR, CT>(a, s); break;
     default: launch_fam<3, MODEL, VAR, CT>(a, s); break;
     }
+}
+
+// The four families' elements (a[t], n may be 0), in one launch up to a number
+// of tiles. A launch of one family ends when its last workgroup does: every
+// family costs the latency of a tile (4 to 5 us) and a last wave that is partly
+// empty. In the common kernel every workgroup has the registers and LDS of the
+// largest family, so it keeps fewer waves in flight, which is what counts once
+// the chip is full; by how much depends on the kernel (the neo-Hookean hex8
+// tile is the largest by far) and on whether one family has nearly all tiles
+// and would have run better alone. Measured on MI355X, us a call, four launches
+// -> one, bands of the four families, n^3 cells (n = 10: 240 tiles, 16: 920, 32:
+// 7400, 40: 14400, 48: 24900, 64: 59000 upper-triangle tiles):
+//   FP64        n = 10: 25 -> 12, 16: 34 -> 18, 32: 83 -> 63, 48: 260 -> 247, 64: 590 -> 568, 80: 1102 -> 1106
+//   mixed       n = 10: 23 -> 11, 16: 27 -> 15, 32: 64 -> 47, 48: 193 -> 182, 64: 410 -> 397, 80: 768 -> 772
+//   residual    n = 10: 33 -> 15, 16: 41 -> 26, 32: 127 -> 122, 40: 244 -> 261
+//   row-owner   n = 10: 31 -> 20, 16: 47 -> 32, 32: 159 -> 158, 36: 241 -> 233, 44: 431 -> 443
+// and with 98% tet4 cells: FP64 n = 32 (7800 tiles): 50 -> 48, 48: 183 -> 193;
+// residual n = 16 (980): 22.5 -> 21.5, 24: 38 -> 50; row-owner n = 32 (12300):
+// 150 -> 140, 40: 313 -> 327 (98% pyr5, 19600: 249 -> 267).
+template <int MODEL, int VAR>
+constexpr int64_t fuse_tiles(const bool lopsided)
+{
+    if (MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES) return lopsided ? 1024 : 8192;
+    if (VAR == V_ROWOWNER) return lopsided ? 8192 : 16384;
+    return lopsided ? 8192 : 32768;
+}
+
+template <int MODEL, int VAR, typename CT>
+static void launch_families(const ElemArgs *a, hipStream_t s)
+{
+    ElemArgs4 q;
+    constexpr int EPB[4] = {ElemSmem<0, MODEL, VAR, CT>::EPB, ElemSmem<1, MODEL, VAR, CT>::EPB,
+                            ElemSmem<2, MODEL, VAR, CT>::EPB, ElemSmem<3, MODEL, VAR, CT>::EPB};
+    int64_t tiles = 0, most = 0;
+    int fams = 0;
+    for (int t = 0; t < 4; ++t) {
+        const int64_t n = (a[t].n + EPB[t] - 1) / EPB[t];
+        q.first[t] = (uint32_t)tiles;
+        if (n > 0) ++fams;
+        tiles += n;
+        most = std::max(most, n);
+    }
+    // lopsided: one family has more than three quarters of the tiles
+    if (fams < 2 || tiles > fuse_tiles<MODEL, VAR>(most > tiles / 4 * 3)) {
+        for (int t = 0; t < 4; ++t) launch_type<MODEL, VAR, CT>(t, a[t], s);
+        return;
+    }
+    for (int t = 0; t < 4; ++t) q.a[t] = a[t];
+    k_element4<MODEL, VAR, CT><<<(unsigned)tiles, 256, 0, s>>>(q);
 }
 
 // A workspace of at least `need` bytes, kept until the graph goes or a larger
@@ -120,6 +196,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         a.tb_rng = g->tb_rng;
         a.tb_slot = g->tb_slot;
         mark(g, 0, o, s);
+        ElemArgs fam[4];
         for (int t = 0; t < 4; ++t) {
             a.elems = g->perm + g->seg[t];
             a.n = g->seg[t + 1] - g->seg[t];
@@ -127,26 +204,27 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.prdest = g->prdest + g->node_base[t];
             a.tpos = g->tpos + g->pair_base[t];
             a.ttb_ptr = g->ttb_ptr + g->tile_base[t];
-            launch_type<MODEL, V_ROWSYM, CT>(t, a, s);
+            fam[t] = a;
         }
-        // 1x1: the right-hand side first, while its workspace (just written)
-        // is still in the caches; then the block values (3x3: with the
-        // right-hand side, rows that no element touches set to zero first)
-        if (f32) {
-            if (RHSD && g->sym_empty_rows && nr) k_zero<float><<<grid_for(nr, 256), 256, 0, s>>>(nr, (float *)rhs);
-            if (!RHSD && nr) launch_segsum<B, CT, float>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, (float *)rhs, s);
-            mark(g, 1, o, s);
-            if (g->nup)
-                launch_segsum_sym<BB, CT, float>(g->nup, g->ublk, g->ulp, g->uptr, (const CT *)g->contrib, (float *)vals,
-                                                 (float *)rhs, s);
-        } else {
-            if (RHSD && g->sym_empty_rows && nr) k_zero<double><<<grid_for(nr, 256), 256, 0, s>>>(nr, (double *)rhs);
-            if (!RHSD && nr) launch_segsum<B, CT, double>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, (double *)rhs, s);
-            mark(g, 1, o, s);
-            if (g->nup)
-                launch_segsum_sym<BB, CT, double>(g->nup, g->ublk, g->ulp, g->uptr, (const CT *)g->contrib,
-                                                  (double *)vals, (double *)rhs, s);
-        }
+        launch_families<MODEL, V_ROWSYM, CT>(fam, s);
+        // then the block values with the right-hand side (3x3: rows that no
+        // element touches set to zero first)
+        mark(g, 1, o, s);
+        auto sums = [&](auto *v, auto *r) {
+            using OT = std::remove_pointer_t<decltype(v)>;
+            if constexpr (RHSD) {
+                if (g->sym_empty_rows && nr) k_zero<OT><<<grid_for(nr, 256), 256, 0, s>>>(nr, r);
+                if (g->nup)
+                    launch_segsum_sym<BB, CT, OT>(g->nup, g->ublk, g->ulp, g->uptr, (const CT *)g->contrib, v, r, s);
+            } else {
+                launch_segsum_rhs_sym<CT, OT>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, r, g->nup, g->ublk,
+                                              g->ulp, g->uptr, (const CT *)g->contrib, v, s);
+            }
+        };
+        if (f32)
+            sums((float *)vals, (float *)rhs);
+        else
+            sums((double *)vals, (double *)rhs);
         mark(g, 2, o, s);
         mark(g, 3, o, s);
         FEA_HIP(hipGetLastError());
@@ -206,14 +284,16 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.rcontrib = g->rcontrib;
         }
         mark(g, 0, o, s);
+        ElemArgs fam[4];
         for (int t = 0; t < 4; ++t) {
             a.elems = g->perm + g->seg[t];
             a.n = g->seg[t + 1] - g->seg[t];
             a.pnodes = g->pnodes + g->node_base[t];
             a.prdest = g->prdest + g->node_base[t];
             a.pdest = g->pdest + g->slot_base[t];
-            launch_type<MODEL, V_ROWOWNER, CT>(t, a, s);
+            fam[t] = a;
         }
+        launch_families<MODEL, V_ROWOWNER, CT>(fam, s);
         // the right-hand side first (its workspace is still cached)
         if (f32) {
             if (nr) launch_segsum<B, CT, float>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, (float *)rhs, s);
@@ -357,7 +437,6 @@ static int assemble_impl(fea_graph *g, const double *x, const double *y, const d
         if (nv) k_zero_u32<<<grid_for(nv, 256), 256, 0, stream>>>((uint32_t *)vals, nv);
         if (nr) k_zero_u32<<<grid_for(nr, 256), 256, 0, stream>>>((uint32_t *)rhs, nr);
     }
-    k_status_final<<<1, 1, 0, stream>>>(st);
     FEA_HIP(hipGetLastError());
     g->timed = o->timing && g->n_elems > 0;
     return FEA_OK;

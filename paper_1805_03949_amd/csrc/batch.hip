@@ -125,16 +125,13 @@ __global__ void k_batch_begin(int32_t *head, int32_t *status, int n_meshes)
 {
     int i = blockIdx.x * 256 + threadIdx.x;
     if (i < 4) head[i] = 0;  // one queue head per family
-    if (i < n_meshes) status[i] = INT_MAX;
+    if (i < n_meshes) status[i] = -1;
 }
 
-__global__ void k_batch_end(int32_t *status, int n_meshes, int32_t *out)
+__global__ void k_batch_end(const int32_t *status, int n_meshes, int32_t *out)
 {
     int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n_meshes) {
-        int32_t v = status[i] == INT_MAX ? -1 : status[i];
-        if (out) out[i] = v;
-    }
+    if (i < n_meshes) out[i] = status[i];
 }
 
 
@@ -629,7 +626,7 @@ int launch_batch(fea_batch *b, const fea_options *o, hipStream_t s, void *vals, 
     } else if (nv) {
         launch_segsum<BB, CT, OT>(b->total_blocks, b->d_vseg, (const CT *)b->contrib, (OT *)vals, s);
     }
-    k_batch_end<<<grid_for(std::max(b->n_meshes, 1), 256), 256, 0, s>>>(b->d_status, b->n_meshes, status);
+    if (status) k_batch_end<<<grid_for(std::max(b->n_meshes, 1), 256), 256, 0, s>>>(b->d_status, b->n_meshes, status);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
@@ -657,7 +654,7 @@ int dispatch_gather(fea_batch *b, const fea_options *o, hipStream_t s, void *val
                                     rhs, b->d_status)))
         return rc;
     if (o->timing) FEA_HIP(hipEventRecord(b->ev[1], s));
-    k_batch_end<<<grid_for(std::max(b->n_meshes, 1), 256), 256, 0, s>>>(b->d_status, b->n_meshes, status);
+    if (status) k_batch_end<<<grid_for(std::max(b->n_meshes, 1), 256), 256, 0, s>>>(b->d_status, b->n_meshes, status);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }

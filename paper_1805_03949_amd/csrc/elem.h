@@ -539,6 +539,14 @@ __device__ inline double &elem_ref(ElemSmem<T, MODEL, VAR, CT> &S, const int i)
     return S.sRef[i / R][i % R];
 }
 
+// Records element e in a status word, which holds the smallest element id
+// recorded and, as an unsigned number, starts at its maximum: -1, the value for
+// no element, so that nothing has to translate it afterwards.
+__device__ inline void status_min(int32_t *status, const int32_t e)
+{
+    atomicMin(reinterpret_cast<uint32_t *>(status), (uint32_t)e);
+}
+
 // Lame parameters.
 __device__ __forceinline__ void lame(const double E, const double nu, double lm[2])
 {
@@ -722,7 +730,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
 #pragma unroll
             for (int r = 0; r < 3; ++r) geo_row<T>(pt, [&](int a) { return S.sX[el][a][r]; }, J[r]);
             const double d = det3(J);
-            if (!(d > 0.0)) atomicMin(A.status, e);
+            if (!(d > 0.0)) status_min(A.status, e);
             inv3(J, d, Ji);
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
@@ -748,7 +756,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
 #pragma unroll
                         for (int j = 0; j < 3; ++j) H[j][j] += 1.0;  // F
                         const double jf = det3(H);
-                        if (!(jf > 0.0)) atomicMin(A.status, e);
+                        if (!(jf > 0.0)) status_min(A.status, e);
                         inv3(H, jf, Fi);
 #pragma unroll
                         for (int r = 0; r < 3; ++r) {
@@ -800,7 +808,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
     geo_nodes<T>(pt, Ji, [&](int a, double v) { sG[el].v[q][a][r] = (CT)v; });
     const double wd = Fam<T>::W * d;
     if (r == 0) {
-        if (!(d > 0.0)) atomicMin(A.status, e);
+        if (!(d > 0.0)) status_min(A.status, e);
         S.sC[el][q][0] = (CT)wd;
     }
     if constexpr (NHK) {
@@ -829,7 +837,7 @@ __device__ inline void elem_geometry(const ElemArgs &A, ElemSmem<T, MODEL, VAR, 
                 geo_nodes<T>(pt, Q, [&](int a, double v) { sH[el].v[q][a][r] = (CT)v; });
                 const double c2 = mu - lam * log(jf);
                 if (r == 0) {
-                    if (!(jf > 0.0)) atomicMin(A.status, e);
+                    if (!(jf > 0.0)) status_min(A.status, e);
                     S.sC[el][q][1] = (CT)(wd * lam);
                     S.sC[el][q][2] = (CT)(wd * c2);
                     S.sC[el][q][3] = (CT)(wd * mu);

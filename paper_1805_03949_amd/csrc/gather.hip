@@ -232,7 +232,7 @@ __device__ inline void g_geometry(Sm &S, int32_t *status, int p, int x0, int q, 
 #pragma unroll
             for (int j = 0; j < 3; ++j) J[i][j] += S.sL[x0 + a].x[i] * S.sDN[tf][q][a][j];
     const double d = det3(J);
-    if (!(d > 0.0)) atomicMin(status, S.sE[p]);
+    if (!(d > 0.0)) status_min(status, S.sE[p]);
     double Ji[3][3];
     inv3(J, d, Ji);
     const int a = S.sA[p];
@@ -269,7 +269,7 @@ __device__ inline void g_geometry(Sm &S, int32_t *status, int p, int x0, int q, 
                     Fd[i][j] = acc;
                 }
             const double jf = det3(Fd);
-            if (!(jf > 0.0)) atomicMin(status, S.sE[p]);
+            if (!(jf > 0.0)) status_min(status, S.sE[p]);
             double Fi[3][3];
             inv3(Fd, jf, Fi);
             const double ga0 = Ji[0][0] * da0 + Ji[1][0] * da1 + Ji[2][0] * da2;

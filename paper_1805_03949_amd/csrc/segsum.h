@@ -84,17 +84,21 @@ struct SegStage {
     }
 };
 
+template <int W, typename CT>
+using RowStage = SegStage<W, CT, SegCfg<CT>::LOAD_BYTES, SegCfg<CT>::CHUNK_BYTES>;
+
+// Workgroup b's segments.
 template <int W, typename CT, typename OT>
-__global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, const CT *data, OT *out)
+__device__ __forceinline__ void segsum_range(const int64_t b, int64_t n, const int64_t *ptr, const CT *data, OT *out,
+                                             typename RowStage<W, CT>::Vec *sv)
 {
     constexpr int TPS = 256 / W;                // segments per round
     constexpr int R = SegCfg<CT>::ROUNDS;       // rounds per workgroup
     constexpr int BPW = TPS * R;                // segments per workgroup
-    using Stage = SegStage<W, CT, SegCfg<CT>::LOAD_BYTES, SegCfg<CT>::CHUNK_BYTES>;
-    __shared__ typename Stage::Vec sv[Stage::NV];
+    using Stage = RowStage<W, CT>;
     const CT *svs = reinterpret_cast<const CT *>(sv);
     const int tid = threadIdx.x;
-    const int64_t m0 = (int64_t)blockIdx.x * BPW;
+    const int64_t m0 = b * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
     const int64_t s0 = ptr[m0], s1 = ptr[mend];
     const int lb = tid / W, c = tid - lb * W;
@@ -124,6 +128,13 @@ __global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, c
         const int64_t m = m0 + lb + r * TPS;
         if (lb < TPS && m < mend) out[m * W + c] = (OT)acc[r];
     }
+}
+
+template <int W, typename CT, typename OT>
+__global__ void __launch_bounds__(256) k_segsum(int64_t n, const int64_t *ptr, const CT *data, OT *out)
+{
+    __shared__ typename RowStage<W, CT>::Vec sv[RowStage<W, CT>::NV];
+    segsum_range<W, CT, OT>(blockIdx.x, n, ptr, data, out, sv);
 }
 
 // The upper-triangle form's block values: output m of the upper-block list
@@ -174,18 +185,22 @@ __device__ inline int64_t sym_run_tile(int64_t b, int64_t nblk)
     return g + x * q + (x < rem ? x : rem) + r;
 }
 
+template <int W, typename CT>
+using SymStage = SegStage<W, CT, SymSegCfg<CT>::LOAD_BYTES, SymSegCfg<CT>::CHUNK_BYTES>;
+
+// Workgroup b of nblk.
 template <int W, typename CT, typename OT, bool RHSD>
-__global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *blk, const int32_t *lp,
-                                                    const int64_t *uptr, const CT *data, OT *out, OT *rhs)
+__device__ __forceinline__ void segsum_sym_range(const int64_t b, const int64_t nblk, int64_t n, const int32_t *blk,
+                                                 const int32_t *lp, const int64_t *uptr, const CT *data, OT *out,
+                                                 OT *rhs, typename SymStage<W, CT>::Vec *sv)
 {
     constexpr int TPS = 256 / W;                                      // outputs per round
     constexpr int R = SymSegCfg<CT>::ROUNDS;                          // rounds per workgroup
     constexpr int BPW = TPS * R;                                      // outputs per workgroup
-    using Stage = SegStage<W, CT, SymSegCfg<CT>::LOAD_BYTES, SymSegCfg<CT>::CHUNK_BYTES>;
-    __shared__ typename Stage::Vec sv[Stage::NV];
+    using Stage = SymStage<W, CT>;
     const CT *svs = reinterpret_cast<const CT *>(sv);
     const int tid = threadIdx.x;
-    const int64_t m0 = sym_run_tile(blockIdx.x, gridDim.x) * BPW;
+    const int64_t m0 = sym_run_tile(b, nblk) * BPW;
     const int64_t mend = m0 + BPW < n ? m0 + BPW : n;
     const int64_t s0 = uptr[m0], s1 = uptr[mend];
     const int lb = tid / W, c = tid - lb * W;
@@ -230,6 +245,46 @@ __global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *bl
         *p = (OT)acc[r];
         if (q != p) *q = (OT)acc[r];
     }
+}
+
+template <int W, typename CT, typename OT, bool RHSD>
+__global__ void __launch_bounds__(256) k_segsum_sym(int64_t n, const int32_t *blk, const int32_t *lp,
+                                                    const int64_t *uptr, const CT *data, OT *out, OT *rhs)
+{
+    __shared__ typename SymStage<W, CT>::Vec sv[SymStage<W, CT>::NV];
+    segsum_sym_range<W, CT, OT, RHSD>(blockIdx.x, gridDim.x, n, blk, lp, uptr, data, out, rhs, sv);
+}
+
+// 1x1 blocks: the right-hand side's rows and the block values in one launch,
+// the right-hand side's workgroups (the first nrb) first, while its workspace,
+// just written, is still in the caches. A launch of its own costs as much as
+// both sums take on a small mesh.
+template <typename CT, typename OT>
+__global__ void __launch_bounds__(256) k_segsum_rhs_sym(int64_t nrb, int64_t nr, const int64_t *ptr, const CT *rdata,
+                                                        OT *rhs, int64_t n, const int32_t *blk, const int32_t *lp,
+                                                        const int64_t *uptr, const CT *data, OT *out)
+{
+    __shared__ union {
+        typename RowStage<1, CT>::Vec r[RowStage<1, CT>::NV];
+        typename SymStage<1, CT>::Vec v[SymStage<1, CT>::NV];
+    } S;
+    const int64_t b = blockIdx.x;
+    if (b < nrb)
+        segsum_range<1, CT, OT>(b, nr, ptr, rdata, rhs, S.r);
+    else
+        segsum_sym_range<1, CT, OT, false>(b - nrb, gridDim.x - nrb, n, blk, lp, uptr, data, out, (OT *)nullptr, S.v);
+}
+
+template <typename CT, typename OT>
+inline void launch_segsum_rhs_sym(int64_t nr, const int64_t *ptr, const CT *rdata, OT *rhs, int64_t n,
+                                  const int32_t *blk, const int32_t *lp, const int64_t *uptr, const CT *data, OT *out,
+                                  hipStream_t s)
+{
+    constexpr int RPW = 256 * SegCfg<CT>::ROUNDS, BPW = 256 * SymSegCfg<CT>::ROUNDS;
+    const int64_t nrb = (nr + RPW - 1) / RPW, nvb = (n + BPW - 1) / BPW;
+    if (nrb + nvb)
+        k_segsum_rhs_sym<CT, OT><<<(unsigned)(nrb + nvb), 256, 0, s>>>(nrb, nr, ptr, rdata, rhs, n, blk, lp, uptr, data,
+                                                                     out);
 }
 
 template <int W, typename CT, typename OT>

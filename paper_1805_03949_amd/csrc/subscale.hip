@@ -299,7 +299,7 @@ __device__ void sub_group(const SubArgs &A, int64_t p0, int64_t pend, SubSmem<T,
         Ji[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
         Ji[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
         const double det = J[0][0] * Ji[0][0] + J[0][1] * Ji[1][0] + J[0][2] * Ji[2][0];
-        if (!(det > 0.0)) atomicMin(A.status, e);
+        if (!(det > 0.0)) status_min(A.status, e);
         const double id = 1.0 / det;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -411,11 +411,7 @@ __global__ void __launch_bounds__(256) k_subscale_batch(const SubArgs *__restric
     }
 }
 
-__global__ void k_sub_status_init(int32_t *s) { *s = INT_MAX; }
-__global__ void k_sub_status_final(int32_t *s)
-{
-    if (*s == INT_MAX) *s = -1;
-}
+__global__ void k_sub_status_init(int32_t *s) { *s = -1; }
 
 // Gauss points per element, in element order, from the type segmentation.
 template <int T>
@@ -549,7 +545,6 @@ extern "C" int fea_subscale(const fea_graph *gc, const double *x, const double *
         else
             run_sub<FEA_ELASTIC>(g, a, stream);
     }
-    k_sub_status_final<<<1, 1, 0, stream>>>(st);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }
@@ -563,13 +558,7 @@ __global__ void k_sub_batch_begin(int32_t *head, int32_t *status, int n)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < 4) head[i] = 0;
-    if (i < n) status[i] = INT_MAX;
-}
-
-__global__ void k_sub_batch_end(int32_t *status, int n)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n && status[i] == INT_MAX) status[i] = -1;
+    if (i < n) status[i] = -1;
 }
 
 // Resident workgroups of the batched kernel of family T on a device.
@@ -751,7 +740,6 @@ extern "C" int fea_batch_subscale(fea_batch *b, hipStream_t stream, double *out,
     if ((rc = launch_sub_batch<1>(v, d_args, stream)) || (rc = launch_sub_batch<3>(v, d_args, stream)) ||
         (rc = launch_sub_batch<2>(v, d_args, stream)) || (rc = launch_sub_batch<0>(v, d_args, stream)))
         return rc;
-    k_sub_batch_end<<<nb, 256, 0, stream>>>(status, v.n_meshes);
     FEA_HIP(hipGetLastError());
     return FEA_OK;
 }

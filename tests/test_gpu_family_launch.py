@@ -1,0 +1,65 @@
+"""All element families in one launch (meshes of few tiles) and one launch per
+family, on both sides of the rule's tile counts, against the CPU oracle; and the
+status word, which the families share."""
+import numpy as np
+import pytest
+
+import meshgen as mg
+import oracle
+from tests.helpers import fp64_errors
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_1805_03949_amd as fea  # noqa: E402
+
+
+def _mesh(n, fams):
+    """The first family in nearly all cells, the others in a few."""
+    rng = np.random.default_rng(n)
+    cells = np.full(n ** 3, fams[0], dtype=np.uint8)
+    cells[rng.choice(n ** 3, max(len(fams) - 1, n ** 3 // 50), replace=False)] = rng.choice(fams[1:], 1)
+    cells[:len(fams)] = fams
+    m = mg.cube_mesh(n, cells, jitter=0.2, seed=n)
+    m.nh_flag = (rng.random(len(m.types)) < 0.3).astype(np.uint8)
+    m.u = 1e-3 * rng.standard_normal(3 * m.n_nodes)
+    return m
+
+
+# tet4 in nearly all cells: 6 n^3 / 25 tiles (row-owner 6 n^3 / 16); the lines
+# are at 1024 (neo-Hookean) and 8192 tiles
+@pytest.mark.parametrize("n,fams,variant,nh", [
+    (2, [0, 1, 2, 3], fea.ROWSYM, False), (2, [3, 2, 1, 0], fea.ROWOWNER, True), (3, [1, 3], fea.ROWSYM, True),
+    (5, [2, 0], fea.ROWOWNER, False), (16, [0, 3], fea.ROWSYM, True), (17, [0, 3], fea.ROWSYM, True),
+    (27, [0, 1, 2, 3], fea.ROWOWNER, False), (29, [0, 1, 2, 3], fea.ROWOWNER, False),
+    (32, [0, 2], fea.ROWSYM, False), (33, [0, 2], fea.ROWSYM, False)])
+def test_both_sides_of_the_rule(n, fams, variant, nh):
+    m = _mesh(n, fams)
+    dm = fea.DeviceMesh(m)
+    g = dm.graph()
+    og = oracle.mesh_graph(m)
+    ref, rrhs = oracle.assemble(m, og, model=oracle.ELASTIC, use_nh=nh)
+    vals, rhs, st = dm.assemble(g, model=fea.ELASTIC, variant=variant, use_nh=nh)
+    assert int(st.item()) == -1
+    ev, er = fp64_errors(vals.cpu().numpy(), ref, og.row_ptr, 3, rhs.cpu().numpy(), rrhs)
+    assert ev <= 1e-12 and er <= 1e-12
+
+
+@pytest.mark.parametrize("variant", [fea.ROWSYM, fea.ROWOWNER, fea.ATOMIC, fea.ROWGATHER])
+@pytest.mark.parametrize("turned", [[0], [40, 3], [-1], [-1, -30, 60]])
+def test_smallest_inverted_element(variant, turned):
+    """Elements of any family turned inside out: the smallest id is reported."""
+    m = mg.hybrid_bands(4, seed=3, jitter=0.1)
+    ids = [e % len(m.types) for e in turned]
+    conn = m.conn.copy()
+    swap = {4: [0, 2, 1, 3], 5: [0, 3, 2, 1, 4], 6: [0, 2, 1, 3, 5, 4], 8: [0, 3, 2, 1, 4, 7, 6, 5]}
+    for e in ids:
+        a, b = m.conn_ptr[e], m.conn_ptr[e + 1]
+        conn[a:b] = conn[a:b][swap[int(b - a)]]
+    m.conn = conn
+    dm = fea.DeviceMesh(m)
+    _, _, st = dm.assemble(dm.graph(), model=fea.ELASTIC, variant=variant)
+    assert int(st.item()) == min(ids)
