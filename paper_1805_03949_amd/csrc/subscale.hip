@@ -18,24 +18,29 @@
 // entries (xi eta, xi zeta, eta zeta). For tet4 all of them vanish:
 // L(u_h) = 0 identically and u is not read.
 //
-// Work layout: one launch per element family over its type-sorted
-// elements; one lane per (element, Gauss point), NQ consecutive lanes per
-// element, 256 / NQ elements per workgroup. The element's first NN lanes
-// each gather one node's coordinates and field values into LDS (one
-// dependent load chain per lane instead of one per node: gathers walked
-// node by node left the kernel waiting on memory latency). Over the
-// reference element every field is a polynomial with as many coefficients
-// as the family has Gauss points (hex8 and the pyramid: the eight
-// monomials of the trilinear hexahedron; pen6: A(r, s) + t B(r, s) with A,
-// B linear), so lane q forms coefficient q of every field from the node
-// values, the coefficients replace the node values in LDS, and each lane
-// evaluates J, grad_xi u and the mixed second reference derivatives at its
-// Gauss point from them (a few FMAs per field instead of a sum over the
-// nodes: about 5% faster, the lanes holding fewer registers). tet4, one
-// lane per element and no second derivatives, sums its four nodes
-// directly. The element volume is summed over the element's Gauss points
-// in ascending order through LDS, and each lane writes its B values at
-// the element's Gauss-point offset.
+// Work layout: the elements of a family in type-sorted order, one lane per
+// (element, Gauss point). hex8 and the pyramid (a hexahedron whose top corners
+// coincide) have as many Gauss points as corners: lane (b0, b1, b2) of an
+// element gathers the corner with these coordinate signs, and the tensor
+// products are formed one direction at a time by exchanges between lanes (see
+// sub_tensor), without LDS and without a barrier. pen6: over the reference
+// element every field is A(r, s) + t B(r, s) with A, B linear, as many
+// coefficients as Gauss points; the element's lanes each gather one node into
+// LDS, form one coefficient of every field from the node values and evaluate
+// the fields at their Gauss point from the coefficients. tet4: one lane per
+// element, no second derivatives.
+//
+// What bounds it: the FP64 instructions of a point (about 400) and the chain
+// ids -> values -> results of a wave that lives for one group of elements. All
+// global loads are therefore issued in two levels (ids; then coordinates,
+// field, material, source and output place together), and material constants
+// cost two divisions instead of three. Measured on MI355X, us a call,
+// before -> after (before: coefficients of every field through LDS, five
+// barriers, loads behind each other): elasticity, 96^3 cells of one family, pyr5
+// (42M points) 996 -> 731, hex8 (7M) 179 -> 131, pen6 (11M) 237 -> 220, tet4 (5M)
+// 128 -> 103; Poisson 489 -> 369, 96 -> 69, 116 -> 115, 86 -> 61; 16^3 cells, all
+// families, 18.9 -> 7.0 (one launch for all, see run_sub). The pyramid issues 472
+// vector instructions a wave, 0.51 of its 0.73 ms.
 #include <algorithm>
 #include <climits>
 
@@ -102,274 +107,313 @@ __device__ __forceinline__ SubArgs from_global(const SubArgsGlobal &g)
     return a;
 }
 
-// LDS of one workgroup. Strides padded to 2 (mod 4) doubles: the 8 Gauss
-// points or elements that a wave reads at once then start in distinct
-// 16-byte bank slots (hex8's 48-double element records aliased every
-// second element).
+// LDS of one workgroup (pen6 only): per element its nodes' values, then (same
+// space) its coefficients. Strides padded to 2 (mod 4) doubles: the elements
+// that a wave reads at once then start in distinct 16-byte bank slots.
 template <int T, int MODEL>
 struct SubSmem {
     static constexpr int NN = Fam<T>::NN, NQ = Fam<T>::NQ, EPW = 256 / NQ;
     static constexpr int B = MODEL == FEA_POISSON ? 1 : 3;
     static constexpr int NV = 3 + B;                                    // node values
-    static constexpr int SQ = NN * 3 + ((2 - (NN * 3) % 4) + 4) % 4;    // per Gauss point of a table
-    // per element: its nodes' values, then (same space) its NQ coefficients
-    static constexpr int NR = NN > NQ ? NN : NQ;
-    static constexpr int SE = NR * NV + ((2 - (NR * NV) % 4) + 4) % 4;
-    double sDN[T == 0 ? NQ * SQ : 1];  // reference gradients (tet4; the others use coefficients)
-    double sWq[NQ];
-    double sWd[256];
-    double sNode[(T == 0 ? 1 : EPW) * SE];  // node coordinates and field values
+    static constexpr int SE = NQ * NV + ((2 - (NQ * NV) % 4) + 4) % 4;
+    double sNode[T == 2 ? EPW * SE : 1];
+    double sWd[T == 2 ? 256 : 1];
 };
 
-// Reference tables of family T into LDS (the caller synchronises).
-template <int T, int MODEL>
-__device__ inline void sub_tables(SubSmem<T, MODEL> &S)
+// x of the lane whose index differs by the mask M, all lanes active.
+template <int M>
+__device__ __forceinline__ double lane_x(const double x)
 {
-    using Sm = SubSmem<T, MODEL>;
-    constexpr int NN = Sm::NN, NQ = Sm::NQ, SQ = Sm::SQ;
-    const int tid = threadIdx.x;
-    if constexpr (T == 0) {
-        for (int i = tid; i < NQ * NN * 3; i += 256) {
-            const int q = i / (NN * 3), a = (i / 3) % NN, j = i % 3;
-            S.sDN[q * SQ + a * 3 + j] = c_ref.dN[T][q][a][j];
-        }
-    }
-    if (tid < NQ) S.sWq[tid] = c_ref.w[T][tid];
+    static_assert(M == 1 || M == 2 || M == 7, "one DPP move each");
+    constexpr int CTRL = M == 1 ? 0xB1 : M == 2 ? 0x4E : 0x141;  // quad_perm 1 0 3 2, 2 3 0 1, half-row mirror
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+
+// A trilinear field with value v at this lane's corner: its first (d) and
+// mixed second (m2: pairs (0, 1), (0, 2), (1, 2)) derivatives at the Gauss point
+// on the corner's side, with respect to reference coordinates that run from the
+// opposite corner to this one over a length of 1 (xi_k = h_k eta_k, h_k = +-2:
+// what follows from them does not depend on the scaling, but for det J, which
+// is 8 times too large and has the sign of the corner's three signs).
+// Neighbours in directions 0, 1, 2 are the lanes 1, 2 and 7 apart (three masks
+// that one DPP move serves each, and that span the eight lanes); the difference
+// v - v' is the derivative, v - (1 - g) / 2 (v - v') the interpolated value.
+__device__ __forceinline__ void sub_tensor(const double v, double d[3], double m2[3])
+{
+    constexpr double C = 0.5 * (1.0 - kGauss);
+    const double D = v - lane_x<1>(v), I = v - C * D;
+    const double ID = I - lane_x<2>(I), II = I - C * ID;
+    const double DD = D - lane_x<2>(D), DI = D - C * DD;
+    d[2] = II - lane_x<7>(II);
+    m2[2] = ID - lane_x<7>(ID);
+    d[1] = ID - C * m2[2];
+    m2[1] = DI - lane_x<7>(DI);
+    d[0] = DI - C * m2[1];
+    m2[0] = DD - C * (DD - lane_x<7>(DD));
 }
 
 // First and mixed second reference derivatives of field f at Gauss point q
-// of family T (pyr5, pen6, hex8) from the element's NQ polynomial
-// coefficients c[m * NV + f] (see sub_group): d[j] = df/dxi_j, m2 = the
-// mixed pairs (0, 1), (0, 2), (1, 2).
-template <int T, int NV>
+// of pen6 from the element's six coefficients c[m * NV + f] (see sub_group):
+// d[j] = df/dxi_j, m2 = the mixed pairs (0, 1), (0, 2), (1, 2).
+template <int NV>
 __device__ inline void sub_eval(const double *c, const int f, const int q, double d[3], double m2[3])
 {
-    if constexpr (T == 2) {
-        // A(r, s) + t B(r, s): coefficients A0, A1, A2, B0, B1, B2
-        constexpr double tr[3][2] = {{1.0 / 6, 1.0 / 6}, {2.0 / 3, 1.0 / 6}, {1.0 / 6, 2.0 / 3}};
-        const double r = tr[q % 3][0], sc = tr[q % 3][1], t = q < 3 ? -kGauss : kGauss;
-        const double A1 = c[1 * NV + f], A2 = c[2 * NV + f], B0 = c[3 * NV + f], B1 = c[4 * NV + f],
-                     B2 = c[5 * NV + f];
-        d[0] = A1 + t * B1;
-        d[1] = A2 + t * B2;
-        d[2] = B0 + B1 * r + B2 * sc;
-        m2[0] = 0.0;
-        m2[1] = B1;
-        m2[2] = B2;
-    } else {
-        // sum_m c_m xi^m, m a bit mask of the coordinates
-        const double x0 = (q & 1) ? kGauss : -kGauss, x1 = (q & 2) ? kGauss : -kGauss, x2 = (q & 4) ? kGauss : -kGauss;
-        const double c1 = c[1 * NV + f], c2 = c[2 * NV + f], c3 = c[3 * NV + f], c4 = c[4 * NV + f],
-                     c5 = c[5 * NV + f], c6 = c[6 * NV + f], c7 = c[7 * NV + f];
-        m2[0] = c3 + c7 * x2;
-        m2[1] = c5 + c7 * x1;
-        m2[2] = c6 + c7 * x0;
-        d[0] = c1 + c3 * x1 + m2[1] * x2;
-        d[1] = c2 + c3 * x0 + m2[2] * x2;
-        d[2] = c4 + c5 * x0 + m2[2] * x1;
+    // A(r, s) + t B(r, s): coefficients A0, A1, A2, B0, B1, B2
+    constexpr double tr[3][2] = {{1.0 / 6, 1.0 / 6}, {2.0 / 3, 1.0 / 6}, {1.0 / 6, 2.0 / 3}};
+    const double r = tr[q % 3][0], sc = tr[q % 3][1], t = q < 3 ? -kGauss : kGauss;
+    const double A1 = c[1 * NV + f], A2 = c[2 * NV + f], B0 = c[3 * NV + f], B1 = c[4 * NV + f], B2 = c[5 * NV + f];
+    d[0] = A1 + t * B1;
+    d[1] = A2 + t * B2;
+    d[2] = B0 + B1 * r + B2 * sc;
+    m2[0] = 0.0;
+    m2[1] = B1;
+    m2[2] = B2;
+}
+
+// An element's material and source, and where its results go. tau (f + mu Lap
+// u + (lam + mu) grad div u) with tau = h^2 / (4 mu) is h^2 / 2 (f / (2 mu) + (Lap
+// u + grad div u / (1 - 2 nu)) / 2).
+template <int B>
+struct SubElem {
+    double E, nu, f[B];
+    int64_t gp;
+};
+
+template <int MODEL, int B>
+__device__ __forceinline__ SubElem<B> sub_elem(const SubArgs &A, const int32_t e)
+{
+    SubElem<B> r;
+    r.E = 1.0;
+    r.nu = 0.0;
+    if constexpr (MODEL != FEA_POISSON) {
+        r.nu = A.nu[e];
+        if (A.young) r.E = A.young[e];
+    }
+#pragma unroll
+    for (int c = 0; c < B; ++c) r.f[c] = A.source[(int64_t)e * B + c];
+    r.gp = A.gp_ptr[e];
+    return r;
+}
+
+// J^-1 (columns scaled by 1 / det) and det J by the adjugate.
+__device__ __forceinline__ double sub_inverse(const double J[3][3], double Ji[3][3])
+{
+    Ji[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+    Ji[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+    Ji[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+    Ji[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+    Ji[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+    Ji[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+    Ji[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+    Ji[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+    Ji[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+    const double det = J[0][0] * Ji[0][0] + J[0][1] * Ji[1][0] + J[0][2] * Ji[2][0];
+    const double id = 1.0 / det;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) Ji[i][j] *= id;
+    return det;
+}
+
+// M^c on the mixed pairs, H_xi(u_c) - sum_k du_c/dx_k H_xi(x_k), from the
+// reference derivatives of u_c (Gu, Du) and of the coordinates (Dx).
+__device__ __forceinline__ void sub_mixed(const double Gu[3], const double Du[3], const double Ji[3][3],
+                                          const double Dx[3][3], double M[3])
+{
+    double g[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g[k] = Gu[0] * Ji[0][k] + Gu[1] * Ji[1][k] + Gu[2] * Ji[2][k];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) M[m] = Du[m] - (g[0] * Dx[0][m] + g[1] * Dx[1][m] + g[2] * Dx[2][m]);
+}
+
+// L(u_h) / (2 k): half of Lap u (Poisson), of Lap u + grad div u / (1 - 2 nu)
+// (elasticity; gd = 1 / (1 - 2 nu)).
+template <int MODEL, int B>
+__device__ __forceinline__ void sub_operator(const double M[B][3], const double Ji[3][3], const double gd, double L[B])
+{
+    constexpr int PJ[3] = {0, 0, 1}, PL[3] = {1, 2, 2};  // mixed pairs (j, l)
+    // Lap u_c = tr(J^-T M^c J^-1) = 2 sum_m M^c_m (J^-1 J^-T)_(j_m, l_m)
+    double S[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        S[m] = Ji[PJ[m]][0] * Ji[PL[m]][0] + Ji[PJ[m]][1] * Ji[PL[m]][1] + Ji[PJ[m]][2] * Ji[PL[m]][2];
+#pragma unroll
+    for (int i = 0; i < B; ++i) L[i] = M[i][0] * S[0] + M[i][1] * S[1] + M[i][2] * S[2];
+    if constexpr (MODEL != FEA_POISSON) {
+        // (grad div u)_i = sum_k (H_x u_k)_ik = sum_j Ji[j][i] W_j with
+        // W_j = sum_k sum_l M^k_jl Ji[l][k] (M^k symmetric, zero diagonal)
+        double W[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            W[0] += M[k][0] * Ji[1][k] + M[k][1] * Ji[2][k];
+            W[1] += M[k][0] * Ji[0][k] + M[k][2] * Ji[2][k];
+            W[2] += M[k][1] * Ji[0][k] + M[k][2] * Ji[1][k];
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) W[j] *= 0.5 * gd;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) L[i] += Ji[0][i] * W[0] + Ji[1][i] * W[1] + Ji[2][i] * W[2];
     }
 }
 
+// 1 / (2 k) and 1 / (1 - 2 nu) with one division.
+template <int MODEL, int B>
+__device__ __forceinline__ void sub_material(const SubElem<B> &el, double &ik, double &gd)
+{
+    ik = 0.5;
+    gd = 0.0;
+    if constexpr (MODEL != FEA_POISSON) {
+        const double s = 1.0 - 2.0 * el.nu, r = 1.0 / (el.E * s);
+        ik = (1.0 + el.nu) * (s * r);
+        gd = el.E * r;
+    }
+}
+
+// Writes Gauss point q's values: tau (f + k L) of an element of volume V.
+template <int MODEL, int B>
+__device__ __forceinline__ void sub_store(const SubArgs &A, const SubElem<B> &el, const double ik, const int q,
+                                          const double V, const double L[B])
+{
+    const double h = cbrt(V), t = 0.5 * (h * h);
+    double *o = A.out + (el.gp + q) * B;
+#pragma unroll
+    for (int c = 0; c < B; ++c) o[c] = t * (el.f[c] * ik + L[c]);
+}
+
 // One group of up to EPW consecutive elements of a family, type-sorted
-// positions p0 .. min(p0 + EPW, pend). Every lane of the workgroup calls it;
-// it starts with a barrier (the previous group's readers of S are done)
-// and lanes without an element only take part in the barriers.
+// positions p0 .. min(p0 + EPW, pend), p0 < pend. Every lane of the workgroup
+// calls it. Lanes without an element follow with the group's last one and
+// write nothing (hex8 and the pyramid: the exchanges want all lanes). pen6
+// starts with a barrier: the previous group's readers of S are done.
 template <int T, int MODEL>
 __device__ void sub_group(const SubArgs &A, int64_t p0, int64_t pend, SubSmem<T, MODEL> &S)
 {
     using Sm = SubSmem<T, MODEL>;
-    constexpr int NN = Sm::NN, NQ = Sm::NQ, EPW = Sm::EPW, B = Sm::B, NV = Sm::NV, SQ = Sm::SQ, SE = Sm::SE;
-    const double *sDN = S.sDN, *sWq = S.sWq;
-    double *sWd = S.sWd, *sNode = S.sNode;
+    constexpr int NN = Sm::NN, NQ = Sm::NQ, EPW = Sm::EPW, B = Sm::B, NV = Sm::NV;
     const int tid = threadIdx.x;
-    __syncthreads();
     const int el = tid / NQ, q = tid - el * NQ;
-    const int64_t p = p0 + el;
-    const bool act = el < EPW && p < pend;
-    const int32_t e = act ? A.perm[p] : 0;
-    double wd = 0.0, kmat = 1.0;  // w_q detJ; tau's material constant k
-    double r[B];
-#pragma unroll
-    for (int c = 0; c < B; ++c) r[c] = 0.0;
-    if constexpr (T != 0) {
-        if (act && q < NN) {
-            const int32_t v = A.pnodes[p * NN + q];
-            double *rec = sNode + el * SE + q * NV;
-            rec[0] = A.x[v];
-            rec[1] = A.y[v];
-            rec[2] = A.z[v];
-#pragma unroll
-            for (int c = 0; c < B; ++c) rec[3 + c] = A.u[(int64_t)v * B + c];
-        }
-        __syncthreads();  // every lane, active or not
-    }
-    double J[3][3] = {}, Dx[3][3] = {};
+    const bool act = el < EPW && p0 + el < pend;
+    const int64_t p = act ? p0 + el : pend - 1;
+    const int32_t e = A.perm[p];
+    double J[3][3], Ji[3][3];
     if constexpr (T == 0) {
-        if (act) {
-            // tet4: constant gradients, no second derivatives
-            const int32_t *pn = A.pnodes + p * NN;
-#pragma unroll 1
-            for (int a = 0; a < NN; ++a) {
-                const int32_t v = pn[a];
-                const double X[3] = {A.x[v], A.y[v], A.z[v]};
+        int32_t v[4];
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const double dn = sDN[q * SQ + a * 3 + j];
+        for (int a = 0; a < 4; ++a) v[a] = A.pnodes[p * 4 + a];
+        double X[4][3];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) J[i][j] += X[i] * dn;
-                }
-            }
+        for (int a = 0; a < 4; ++a) {
+            X[a][0] = A.x[v[a]];
+            X[a][1] = A.y[v[a]];
+            X[a][2] = A.z[v[a]];
         }
-    } else {
-        // Every field f (coordinates, then the field's B components) is,
-        // over the reference element, a polynomial with NQ coefficients:
-        // hex8 and the collapsed-hexahedron pyramid sum_m c_m xi^m over the
-        // eight monomials m of {1, xi0, xi1, xi0 xi1, xi2, ...} (m read as
-        // a bit mask of the coordinates), pen6 A(r, s) + t B(r, s) with A
-        // and B linear. Lane q of an element forms coefficient q of every
-        // field from the node values, the coefficients replace the node
-        // values in LDS, and each lane evaluates the first and mixed second
-        // reference derivatives at its Gauss point from them.
-        double cf[NV];
+        const SubElem<B> se = sub_elem<MODEL, B>(A, e);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) J[i][j] = X[j + 1][i] - X[0][i];
+        const double det = sub_inverse(J, Ji);
         if (act) {
-            const double *nv = sNode + el * SE;
+            if (!(det > 0.0)) status_min(A.status, e);
+            const double L[B] = {}, ik = MODEL == FEA_POISSON ? 0.5 : (1.0 + se.nu) / se.E;
+            sub_store<MODEL, B>(A, se, ik, 0, Fam<T>::W * det, L);
+        }
+    } else if constexpr (T != 2) {
+        const int b2 = q >> 2, b0 = (q & 1) ^ b2, b1 = ((q >> 1) & 1) ^ b2;  // corner signs (see sub_tensor)
+        const int low = b0 | b1 << 1, node = (T == 1 && b2) ? 4 : (low ^ (low >> 1)) + 4 * b2;
+        const int32_t v = A.pnodes[p * NN + node];
+        const double X[3] = {A.x[v], A.y[v], A.z[v]};
+        double U[B];
 #pragma unroll
-            for (int f = 0; f < NV; ++f) cf[f] = 0.0;
-            if constexpr (T == 2) {
-                // P_k = (v_k + v_k+3) / 2, Q_k = (v_k+3 - v_k) / 2; coefficients
-                // A0 = P0, A1 = P1 - P0, A2 = P2 - P0, B0 = Q0, B1 = Q1 - Q0, B2 = Q2 - Q0
-                const int k = q % 3, top = q / 3;
+        for (int c = 0; c < B; ++c) U[c] = A.u[(int64_t)v * B + c];
+        const SubElem<B> se = sub_elem<MODEL, B>(A, e);
+        double ik, gd;
+        sub_material<MODEL, B>(se, ik, gd);
+        double Dx[3][3];
 #pragma unroll
-                for (int f = 0; f < NV; ++f) {
-                    const double v0 = nv[0 * NV + f], v3 = nv[3 * NV + f];
-                    const double vk = nv[k * NV + f], vk3 = nv[(k + 3) * NV + f];
-                    const double c0 = top ? 0.5 * (v3 - v0) : 0.5 * (v0 + v3);
-                    const double ck = top ? 0.5 * (vk3 - vk) : 0.5 * (vk + vk3);
-                    cf[f] = k == 0 ? c0 : ck - c0;
-                }
-            } else {
-                // c_m = 1/8 sum_a s_m(a) v_a, s_m(a) the product of node a's
-                // corner signs over the coordinates in m; the pyramid's apex
-                // stands for the four collapsed top corners
-                constexpr int PLUS[8] = {0, 1, 3, 2, 4, 5, 7, 6};  // corner a: bit d set where its sign is +
+        for (int i = 0; i < 3; ++i) sub_tensor(X[i], J[i], Dx[i]);
+        const double det = sub_inverse(J, Ji) * ((b0 ^ b1 ^ b2) ? 0.125 : -0.125);
+        if (act && !(det > 0.0)) status_min(A.status, e);
+        double M[B][3];
 #pragma unroll
-                for (int a = 0; a < 8; ++a) {
-                    const int node = (T == 1 && a > 4) ? 4 : a;
-                    const bool neg = __builtin_popcount(q & ~PLUS[a] & 7) & 1;
+        for (int c = 0; c < B; ++c) {
+            double Gu[3], Du[3];
+            sub_tensor(U[c], Gu, Du);
+            sub_mixed(Gu, Du, Ji, Dx, M[c]);
+        }
+        double L[B];
+        sub_operator<MODEL, B>(M, Ji, gd, L);
+        double V = det;  // all weights are 1
+        V += lane_x<1>(V);
+        V += lane_x<2>(V);
+        V += lane_x<7>(V);
+        if (act) sub_store<MODEL, B>(A, se, ik, low + 4 * b2, V, L);
+    } else {
+        constexpr int SE = Sm::SE;
+        double *sNode = S.sNode + (el < EPW ? el : 0) * SE;
+        const int32_t v = A.pnodes[p * NN + q];
+        const double X[3] = {A.x[v], A.y[v], A.z[v]};
+        double U[B];
 #pragma unroll
-                    for (int f = 0; f < NV; ++f) {
-                        const double v = nv[node * NV + f];
-                        cf[f] += neg ? -v : v;
-                    }
-                }
+        for (int c = 0; c < B; ++c) U[c] = A.u[(int64_t)v * B + c];
+        const SubElem<B> se = sub_elem<MODEL, B>(A, e);
+        __syncthreads();
+        if (act) {
 #pragma unroll
-                for (int f = 0; f < NV; ++f) cf[f] *= 0.125;
+            for (int i = 0; i < 3; ++i) sNode[q * NV + i] = X[i];
+#pragma unroll
+            for (int c = 0; c < B; ++c) sNode[q * NV + 3 + c] = U[c];
+        }
+        __syncthreads();
+        // lane q forms coefficient q of every field: with P_k = (v_k + v_k+3) /
+        // 2, Q_k = (v_k+3 - v_k) / 2 they are A0 = P0, A1 = P1 - P0, A2 = P2 - P0,
+        // B0 = Q0, B1 = Q1 - Q0, B2 = Q2 - Q0
+        double cf[NV];
+        {
+            const int k = q % 3, top = q / 3;
+#pragma unroll
+            for (int f = 0; f < NV; ++f) {
+                const double v0 = sNode[0 * NV + f], v3 = sNode[3 * NV + f];
+                const double vk = sNode[k * NV + f], vk3 = sNode[(k + 3) * NV + f];
+                const double c0 = top ? 0.5 * (v3 - v0) : 0.5 * (v0 + v3);
+                const double ck = top ? 0.5 * (vk3 - vk) : 0.5 * (vk + vk3);
+                cf[f] = k == 0 ? c0 : ck - c0;
             }
         }
         __syncthreads();  // every lane has read the node values
         if (act) {
 #pragma unroll
-            for (int f = 0; f < NV; ++f) sNode[el * SE + q * NV + f] = cf[f];
+            for (int f = 0; f < NV; ++f) sNode[q * NV + f] = cf[f];
         }
         __syncthreads();
+        double Dx[3][3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) sub_eval<NV>(sNode, i, q, J[i], Dx[i]);
+        const double det = sub_inverse(J, Ji);
+        if (act && !(det > 0.0)) status_min(A.status, e);
+        S.sWd[tid] = Fam<T>::W * det;
+        double M[B][3];
+#pragma unroll
+        for (int c = 0; c < B; ++c) {
+            double Gu[3], Du[3];
+            sub_eval<NV>(sNode, 3 + c, q, Gu, Du);
+            sub_mixed(Gu, Du, Ji, Dx, M[c]);
+        }
+        double L[B], ik, gd;
+        sub_material<MODEL, B>(se, ik, gd);
+        sub_operator<MODEL, B>(M, Ji, gd, L);
+        __syncthreads();
         if (act) {
-            const double *c = sNode + el * SE;
+            double V = 0.0;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                double d[3], m2[3];
-                sub_eval<T, NV>(c, i, q, d, m2);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    J[i][j] = d[j];
-                    Dx[i][j] = m2[j];
-                }
-            }
+            for (int k = 0; k < NQ; ++k) V += S.sWd[el * NQ + k];
+            sub_store<MODEL, B>(A, se, ik, q, V, L);
         }
-    }
-    if (act) {
-        // J^-1 by the adjugate
-        double Ji[3][3];
-        Ji[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-        Ji[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-        Ji[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-        Ji[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-        Ji[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-        Ji[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-        Ji[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-        Ji[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-        Ji[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-        const double det = J[0][0] * Ji[0][0] + J[0][1] * Ji[1][0] + J[0][2] * Ji[2][0];
-        if (!(det > 0.0)) status_min(A.status, e);
-        const double id = 1.0 / det;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) Ji[i][j] *= id;
-        wd = sWq[q] * det;
-
-        double lam = 0.0, mu = 1.0;
-        if constexpr (MODEL != FEA_POISSON) {
-            const double E = A.young ? A.young[e] : 1.0, nu = A.nu[e];
-            lam = E * nu / ((1.0 + nu) * (1.0 - 2.0 * nu));
-            mu = E / (2.0 * (1.0 + nu));
-            kmat = mu;
-        }
-#pragma unroll
-        for (int c = 0; c < B; ++c) r[c] = A.source[(int64_t)e * B + c];
-        if constexpr (T != 0) {
-            constexpr int PJ[3] = {0, 0, 1}, PL[3] = {1, 2, 2};  // mixed pairs (j, l)
-            // M^c on the mixed pairs: H_xi(u_c) - sum_k du_c/dx_k H_xi(x_k)
-            double M[B][3];
-#pragma unroll
-            for (int c = 0; c < B; ++c) {
-                // grad_xi u_c and its mixed second derivatives, one field at
-                // a time
-                double Gu[3], Du[3], g[3];
-                sub_eval<T, NV>(sNode + el * SE, 3 + c, q, Gu, Du);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) g[k] = Gu[0] * Ji[0][k] + Gu[1] * Ji[1][k] + Gu[2] * Ji[2][k];
-#pragma unroll
-                for (int m = 0; m < 3; ++m) M[c][m] = Du[m] - (g[0] * Dx[0][m] + g[1] * Dx[1][m] + g[2] * Dx[2][m]);
-            }
-            // Lap u_c = tr(J^-T M^c J^-1) = 2 sum_m M^c_m (J^-1 J^-T)_(j_m, l_m)
-            double S[3];
-#pragma unroll
-            for (int m = 0; m < 3; ++m)
-                S[m] = Ji[PJ[m]][0] * Ji[PL[m]][0] + Ji[PJ[m]][1] * Ji[PL[m]][1] + Ji[PJ[m]][2] * Ji[PL[m]][2];
-            if constexpr (MODEL == FEA_POISSON) {
-                r[0] += 2.0 * (M[0][0] * S[0] + M[0][1] * S[1] + M[0][2] * S[2]);
-            } else {
-                // (grad div u)_i = sum_k (H_x u_k)_ik = sum_j Ji[j][i] W_j with
-                // W_j = sum_k sum_l M^k_jl Ji[l][k] (M^k symmetric, zero diagonal)
-                double W[3];
-                W[0] = W[1] = W[2] = 0.0;
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    W[0] += M[k][0] * Ji[1][k] + M[k][1] * Ji[2][k];
-                    W[1] += M[k][0] * Ji[0][k] + M[k][2] * Ji[2][k];
-                    W[2] += M[k][1] * Ji[0][k] + M[k][2] * Ji[1][k];
-                }
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const double lap = 2.0 * (M[i][0] * S[0] + M[i][1] * S[1] + M[i][2] * S[2]);
-                    const double gdiv = Ji[0][i] * W[0] + Ji[1][i] * W[1] + Ji[2][i] * W[2];
-                    r[i] += mu * lap + (lam + mu) * gdiv;
-                }
-            }
-        }
-    }
-    // every lane reaches the barrier, active or not
-    sWd[tid] = wd;
-    __syncthreads();
-    if (act) {
-        double V = 0.0;
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) V += sWd[el * NQ + k];
-        const double h = cbrt(V);
-        const double tau = h * h / (4.0 * kmat);
-        double *o = A.out + (A.gp_ptr[e] + q) * B;
-#pragma unroll
-        for (int c = 0; c < B; ++c) o[c] = tau * r[c];
     }
 }
 
@@ -377,8 +421,33 @@ template <int T, int MODEL>
 __global__ void __launch_bounds__(256) k_subscale(SubArgs A)
 {
     __shared__ SubSmem<T, MODEL> S;
-    sub_tables(S);
     sub_group(A, (int64_t)blockIdx.x * SubSmem<T, MODEL>::EPW, A.n, S);
+}
+
+// All families in one launch, family t's workgroups from first[t] on.
+struct SubArgs4 {
+    SubArgs a[4];
+    uint32_t first[4];
+};
+
+template <int MODEL>
+__global__ void __launch_bounds__(256) k_subscale4(SubArgs4 A)
+{
+    __shared__ union {
+        SubSmem<0, MODEL> s0;
+        SubSmem<1, MODEL> s1;
+        SubSmem<2, MODEL> s2;
+        SubSmem<3, MODEL> s3;
+    } S;
+    const uint32_t b = blockIdx.x;
+    if (b < A.first[1])
+        sub_group<0, MODEL>(A.a[0], (int64_t)b * SubSmem<0, MODEL>::EPW, A.a[0].n, S.s0);
+    else if (b < A.first[2])
+        sub_group<1, MODEL>(A.a[1], (int64_t)(b - A.first[1]) * SubSmem<1, MODEL>::EPW, A.a[1].n, S.s1);
+    else if (b < A.first[3])
+        sub_group<2, MODEL>(A.a[2], (int64_t)(b - A.first[2]) * SubSmem<2, MODEL>::EPW, A.a[2].n, S.s2);
+    else
+        sub_group<3, MODEL>(A.a[3], (int64_t)(b - A.first[3]) * SubSmem<3, MODEL>::EPW, A.a[3].n, S.s3);
 }
 
 // Batched form: persistent workgroups of one family dequeue work items
@@ -393,7 +462,6 @@ __global__ void __launch_bounds__(256) k_subscale_batch(const SubArgs *__restric
     constexpr int EPW = SubSmem<T, MODEL>::EPW;
     __shared__ SubSmem<T, MODEL> S;
     __shared__ int32_t s_item;
-    sub_tables(S);
     for (;;) {
         __syncthreads();  // every lane has read the previous item
         if (threadIdx.x == 0) {
@@ -462,24 +530,50 @@ static int gauss_points_prepare(fea_graph *g, hipStream_t s)
 }
 
 template <int T, int MODEL>
-static void launch_sub(const fea_graph *g, SubArgs a, hipStream_t s)
+static void launch_sub(const SubArgs &a, hipStream_t s)
 {
     constexpr int EPW = 256 / Fam<T>::NQ;
-    a.n = g->seg[T + 1] - g->seg[T];
-    if (a.n == 0) return;
-    a.perm = g->perm + g->seg[T];
-    a.pnodes = g->pnodes + g->node_base[T];
-    k_subscale<T, MODEL><<<grid_for(a.n, EPW), 256, 0, s>>>(a);
+    if (a.n) k_subscale<T, MODEL><<<grid_for(a.n, EPW), 256, 0, s>>>(a);
 }
+
+// One launch for all families saves a launch and a partly empty last wave per
+// family; its workgroups all have the registers of the pyramid's kernel (3
+// waves in flight per SIMD where tet4 alone has 8), which costs more than that
+// on a large mesh that is nearly all tet4 or pen6. Measured on MI355X, us a
+// call, four launches -> one, elasticity, bands of the families, n^3 cells: n =
+// 8: 13.0 -> 6.0, 16: 13.8 -> 7.0, 32: 23 -> 17, 48: 52 -> 45, 64 (19000
+// workgroups): 99 -> 91, 96: 324 -> 325; 98% tet4: 48 (2600): 19 -> 18, 64 (6100):
+// 34 -> 34, 96: 113 -> 130; 98% pen6: 48 (5200): 38.5 -> 37.6, 64 (12400): 74 -> 77.
+constexpr int64_t kSubFuse = 32768, kSubFuseLopsided = 4096;  // workgroups
 
 template <int MODEL>
 static void run_sub(const fea_graph *g, const SubArgs &a, hipStream_t s)
 {
+    SubArgs4 q;
+    int64_t wgs = 0, most = 0;
+    int fams = 0;
+    for (int t = 0; t < 4; ++t) {
+        const int epw = 256 / (t == 0 ? 1 : t == 2 ? 6 : 8);
+        q.a[t] = a;
+        q.a[t].n = g->seg[t + 1] - g->seg[t];
+        q.a[t].perm = g->perm + g->seg[t];
+        q.a[t].pnodes = g->pnodes + g->node_base[t];
+        q.first[t] = (uint32_t)wgs;
+        const int64_t w = (q.a[t].n + epw - 1) / epw;
+        wgs += w;
+        most = std::max(most, w);
+        if (w) ++fams;
+    }
+    // lopsided: one family has more than three quarters of the workgroups
+    if (fams > 1 && wgs <= (most > wgs / 4 * 3 ? kSubFuseLopsided : kSubFuse)) {
+        k_subscale4<MODEL><<<(unsigned)wgs, 256, 0, s>>>(q);
+        return;
+    }
     // the costliest family first, so the cheap launches fill the tail
-    launch_sub<1, MODEL>(g, a, s);
-    launch_sub<3, MODEL>(g, a, s);
-    launch_sub<2, MODEL>(g, a, s);
-    launch_sub<0, MODEL>(g, a, s);
+    launch_sub<1, MODEL>(q.a[1], s);
+    launch_sub<3, MODEL>(q.a[3], s);
+    launch_sub<2, MODEL>(q.a[2], s);
+    launch_sub<0, MODEL>(q.a[0], s);
 }
 
 }  // namespace fea
@@ -521,7 +615,7 @@ extern "C" int fea_subscale(const fea_graph *gc, const double *x, const double *
     FEA_HIP(hipGetDevice(&dev));
     if (dev != g->device) return set_error(FEA_EINVAL, "graph lives on device %d, current is %d", g->device, dev);
     int rc;
-    if ((rc = ensure_tables()) || (rc = gauss_points_prepare(g, stream))) return rc;
+    if ((rc = gauss_points_prepare(g, stream))) return rc;
 
     int32_t *st = status;
     if (!st) {
@@ -694,7 +788,6 @@ extern "C" int fea_batch_subscale(fea_batch *b, hipStream_t stream, double *out,
     int dev = 0;
     FEA_HIP(hipGetDevice(&dev));
     if (dev != v.device) return set_error(FEA_EINVAL, "batch lives on device %d, current is %d", v.device, dev);
-    if ((rc = ensure_tables())) return rc;
     std::vector<int64_t> off;
     if ((rc = batch_gauss_offsets(v, stream, off))) return rc;
     if (off.back() > 0 && !out) return set_error(FEA_EINVAL, "NULL output");
