@@ -1243,21 +1243,13 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
     // lower entries to the right-hand side
     auto stage = [&] {
         CT *k = sK + pr.place * BB;
-        if constexpr (B == 3) {
-            const bool tr = pr.transposed;
-            k[0] = Ks[0];
-            k[4] = Ks[4];
-            k[8] = Ks[8];
-            k[1] = tr ? Ks[3] : Ks[1];
-            k[2] = tr ? Ks[6] : Ks[2];
-            k[5] = tr ? Ks[7] : Ks[5];
-            if (!(RHSD && diag)) {
-                k[3] = tr ? Ks[1] : Ks[3];
-                k[6] = tr ? Ks[2] : Ks[6];
-                k[7] = tr ? Ks[5] : Ks[7];
-            }
-        } else {
-            k[0] = Ks[0];
+#pragma unroll
+        for (int c = 0; c < BB; ++c)
+            if (c % B >= c / B) k[c] = Ks[c];
+        if (!(RHSD && diag)) {
+#pragma unroll
+            for (int c = 0; c < BB; ++c)
+                if (c % B < c / B) k[c] = Ks[c];
         }
     };
     if (pact) {
@@ -1298,54 +1290,45 @@ __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODE
     __syncthreads();
 
     // tile sums, the block's entries added in ascending lane (element)
-    // order, in FP64: either one thread per tile-block adding all BB
-    // components (FP32), or one thread per (tile-block, component) (FP64).
-    // Both give bitwise the same sums.
+    // order, in FP64: PB threads per tile-block, each W consecutive values
+    // written with one store, a step of the loop taking whole tile-blocks.
+    // FP32: a row of the block, 12 bytes, so that a wave's store is contiguous
+    // within a block (all nine by one thread left a quarter of the threads
+    // idle and stored in nine passes: element phase of pure meshes, mixed, ms,
+    // before -> after: hex8 0.62 -> 0.49, pen6 0.39 -> 0.35, tet4 0.19 -> 0.15,
+    // pyr5 0.35 -> 0.34). FP64: one value; two or three a thread leave gaps
+    // between the lanes of a store (hex8 0.77 -> 0.85 / 0.83).
     CT *out = (CT *)A.contrib;
-    constexpr bool PER_BLOCK = sizeof(CT) == 4;
-    if constexpr (PER_BLOCK) {
-        for (int d = tid; d < nd; d += 256) {
-            const auto t = S.sTb[d];
-            const CT *k = sK + (t.rng & 255) * BB;
-            double acc[BB];
+    constexpr int W = sizeof(CT) == 4 ? B : 1, PB = BB / W, STEP = 256 / PB;
+    typedef CT Out __attribute__((ext_vector_type(W), aligned(sizeof(CT))));
+    const int d_first = tid / PB, c0 = (tid - d_first * PB) * W;
+    for (int d = d_first < STEP ? d_first : nd; d < nd; d += STEP) {
+        const auto t = S.sTb[d];
+        const CT *k = sK + (t.rng & 255) * BB + c0;
+        double acc[W];
 #pragma unroll
-            for (int c = 0; c < BB; ++c) acc[c] = (double)k[c];
-            for (int q = t.rng >> 8; q > 0; --q) {
-                k += BB;
+        for (int c = 0; c < W; ++c) acc[c] = (double)k[c];
+        for (int q = t.rng >> 8; q > 0; --q) {
+            k += BB;
 #pragma unroll
-                for (int c = 0; c < BB; ++c) acc[c] += (double)k[c];
-            }
-            const int64_t blk = t.slot;
-            if constexpr (TCOL) {
-                // blk is the block; no other tile of this colour touches it
-                // or its partner
-                const int64_t l = S.sLp[d];
-#pragma unroll
-                for (int c = 0; c < BB; ++c) A.vals[blk * BB + c] += acc[c];
-                if (l >= 0) {
-#pragma unroll
-                    for (int c = 0; c < BB; ++c) A.vals[l * BB + (c % B) * B + c / B] += acc[c];
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < BB; ++c) out[blk * BB + c] = (CT)acc[c];
-            }
+            for (int c = 0; c < W; ++c) acc[c] += (double)k[c];
         }
-    } else {
-        for (int idx = tid; idx < nd * BB; idx += 256) {
-            const int d = idx / BB, c = idx - d * BB;
-            const auto t = S.sTb[d];
-            const CT *k = sK + (t.rng & 255) * BB + c;
-            double acc = (double)*k;
-            for (int q = t.rng >> 8; q > 0; --q) acc += (double)*(k += BB);
-            const int64_t blk = t.slot;
-            if constexpr (TCOL) {
-                const int64_t l = S.sLp[d];
-                A.vals[blk * BB + c] += acc;
-                if (l >= 0) A.vals[l * BB + (c % B) * B + c / B] += acc;
-            } else {
-                out[blk * BB + c] = (CT)acc;
+        const int64_t blk = t.slot;
+        if constexpr (TCOL) {
+            // blk is the block; no other tile of this colour touches it or
+            // its partner
+            const int64_t l = S.sLp[d];
+#pragma unroll
+            for (int c = 0; c < W; ++c) A.vals[blk * BB + c0 + c] += acc[c];
+            if (l >= 0) {
+#pragma unroll
+                for (int c = 0; c < W; ++c) A.vals[l * BB + ((c0 + c) % B) * B + (c0 + c) / B] += acc[c];
             }
+        } else {
+            Out v;
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[c] = (CT)acc[c];
+            *reinterpret_cast<Out *>(out + blk * BB + c0) = v;
         }
     }
 }

@@ -17,20 +17,19 @@ __host__ __device__ constexpr inline int nodes_of(int t) { return 4 + t + (t == 
 // a <= b, 256 lanes per workgroup.
 __host__ __device__ constexpr inline int sym_epb(int t) { return 256 / (nodes_of(t) * (nodes_of(t) + 1) / 2); }
 
-// A pair of the upper-triangle form in 16 bits: the place of its block among
-// the tile's entries (ordered by destination block, then lane), whether the
-// destination holds it transposed, and its local nodes a <= b.
+// One pair of an upper-triangle tile in 16 bits: its place among the tile's
+// entries and its local nodes, a the one with the smaller node id (a's row and
+// b's column of the element matrix are then what the destination block holds).
 struct SymPair {
     int place, a, b;
-    bool transposed;
 };
 __host__ __device__ inline SymPair sym_pair(unsigned w)
 {
-    return {(int)(w & 255u), (int)(w >> 9 & 7u), (int)(w >> 12 & 7u), (w >> 8 & 1u) != 0};
+    return {(int)(w & 255u), (int)(w >> 8 & 7u), (int)(w >> 11 & 7u)};
 }
-__host__ __device__ inline uint16_t sym_pair_word(int place, bool transposed, int a, int b)
+__host__ __device__ inline uint16_t sym_pair_word(int place, int a, int b)
 {
-    return (uint16_t)(place | (transposed ? 256 : 0) | a << 9 | b << 12);
+    return (uint16_t)(place | a << 8 | b << 11);
 }
 
 // Records a message for fea_last_error() and returns `code`.

@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(256) k_tile_entries(TileBases tb, const int32_
     __shared__ uint64_t key[K];
     __shared__ int part[4];
     __shared__ uint16_t beg[K + 1];  // first entry of every tile-block
-    __shared__ uint16_t word[K];     // lane -> transposed, a, b
+    __shared__ uint16_t word[K];     // lane -> its nodes, smaller id first
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
     int t = 0;
@@ -530,8 +530,9 @@ __global__ void __launch_bounds__(256) k_tile_entries(TileBases tb, const int32_
         const int b = a + w;
         const int32_t *pn = pnodes + tb.node[t] + (i0 + el) * n;
         const bool tr = pn[a] > pn[b];
-        mine = (uint64_t)e2nnz[map_ptr[perm[p]] + (tr ? b * n + a : a * n + b)] << 8 | (uint64_t)tid;
-        word[tid] = sym_pair_word(0, tr, a, b);
+        const int lo = tr ? b : a, hi = tr ? a : b;
+        mine = (uint64_t)e2nnz[map_ptr[perm[p]] + lo * n + hi] << 8 | (uint64_t)tid;
+        word[tid] = sym_pair_word(0, lo, hi);
     }
     key[tid] = mine;
     __syncthreads();
