@@ -42,10 +42,15 @@ __global__ void k_to_f32(const double *in, float *out, int64_t n)
 
 __global__ void k_status_init(int32_t *s) { *s = -1; }
 
-// The four families' tiles in one launch, family t's from first[t] on.
+// The four families' tiles in one launch: family after family, family t's
+// tiles from workgroup first[t] on; or, with slices (a multiple of 8), slice
+// after slice, slice s holding the tiles [s n / slices, (s + 1) n / slices) of
+// every family of n tiles, in `room` workgroups (the last few may be idle), XCD
+// x the slices x slices / 8 to (x + 1) slices / 8.
 struct ElemArgs4 {
     ElemArgs a[4];
-    uint32_t first[4];
+    uint32_t first[5];
+    uint32_t slices, room;
 };
 
 template <int MODEL, int VAR, typename CT>
@@ -60,15 +65,39 @@ template <int MODEL, int VAR, typename CT>
 __global__ void __launch_bounds__(256) k_element4(ElemArgs4 A)
 {
     __shared__ ElemSmem4<MODEL, VAR, CT> S;
-    const uint32_t b = blockIdx.x;
-    if (b < A.first[1])
-        elem_tile<0, MODEL, VAR, CT>(A.a[0], (int64_t)b * ElemSmem<0, MODEL, VAR, CT>::EPB, S.s0);
-    else if (b < A.first[2])
-        elem_tile<1, MODEL, VAR, CT>(A.a[1], (int64_t)(b - A.first[1]) * ElemSmem<1, MODEL, VAR, CT>::EPB, S.s1);
-    else if (b < A.first[3])
-        elem_tile<2, MODEL, VAR, CT>(A.a[2], (int64_t)(b - A.first[2]) * ElemSmem<2, MODEL, VAR, CT>::EPB, S.s2);
-    else
-        elem_tile<3, MODEL, VAR, CT>(A.a[3], (int64_t)(b - A.first[3]) * ElemSmem<3, MODEL, VAR, CT>::EPB, S.s3);
+    uint32_t at[4], n[4], b = blockIdx.x;  // families' first tiles and counts, place among them
+    if (A.slices) {
+        const uint32_t x = b & 7, i = b >> 3, s = x * (A.slices >> 3) + i / A.room;
+        b = i % A.room;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint64_t m = A.first[t + 1] - A.first[t];
+            at[t] = (uint32_t)(s * m / A.slices);
+            n[t] = (uint32_t)((s + 1) * m / A.slices) - at[t];
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            at[t] = 0;
+            n[t] = A.first[t + 1] - A.first[t];
+        }
+    }
+    if (b < n[0]) {
+        elem_tile<0, MODEL, VAR, CT>(A.a[0], (int64_t)(at[0] + b) * ElemSmem<0, MODEL, VAR, CT>::EPB, S.s0);
+        return;
+    }
+    b -= n[0];
+    if (b < n[1]) {
+        elem_tile<1, MODEL, VAR, CT>(A.a[1], (int64_t)(at[1] + b) * ElemSmem<1, MODEL, VAR, CT>::EPB, S.s1);
+        return;
+    }
+    b -= n[1];
+    if (b < n[2]) {
+        elem_tile<2, MODEL, VAR, CT>(A.a[2], (int64_t)(at[2] + b) * ElemSmem<2, MODEL, VAR, CT>::EPB, S.s2);
+        return;
+    }
+    b -= n[2];
+    if (b < n[3]) elem_tile<3, MODEL, VAR, CT>(A.a[3], (int64_t)(at[3] + b) * ElemSmem<3, MODEL, VAR, CT>::EPB, S.s3);
 }
 
 template <int T, int MODEL, int VAR, typename CT>
@@ -119,8 +148,24 @@ constexpr int64_t fuse_tiles(const bool lopsided)
     return lopsided ? 8192 : 32768;
 }
 
+// Families that share their nodes (an unordered mixture of element types)
+// write the same cache lines of the workspace, which lies sorted by block.
+// Beyond the 256 MB of the memory-side cache a family's kernel leaves those
+// lines in memory half written and the next one's fetches and completes them;
+// slices of all families, each on one XCD, write them while they are in its L2.
+// Measured on MI355X, element phase, ms, four launches -> slices of about 128
+// tiles, random mixtures: row-owner 47^3 cells (0.7 GB) FP64 0.53 -> 0.41, mixed
+// 0.32 -> 0.28, 80^3 2.88 -> 2.35 and 1.53 -> 1.13; upper triangle 96^3 1.55 ->
+// 1.24 and 1.11 -> 0.92, but 47^3 (0.1 GB) 0.19 -> 0.20; bands, whose families
+// meet in three planes only, 96^3 1.00 -> 1.12, and the neo-Hookean upper
+// triangle, whose common kernel has the fewest waves, 96^3 2.04 -> 2.27 (row-owner
+// 80^3 2.89 -> 2.37). Slices of 64 and 256 tiles: 2.34, 2.39 for 2.35.
+constexpr size_t kSliceBytes = size_t(256) << 20;
+constexpr int64_t kSliceTiles = 128;
+
+// ws_bytes: the tiles' output; mixed: most nodes belong to several families.
 template <int MODEL, int VAR, typename CT>
-static void launch_families(const ElemArgs *a, hipStream_t s)
+static void launch_families(const ElemArgs *a, size_t ws_bytes, bool mixed, hipStream_t s)
 {
     ElemArgs4 q;
     constexpr int EPB[4] = {ElemSmem<0, MODEL, VAR, CT>::EPB, ElemSmem<1, MODEL, VAR, CT>::EPB,
@@ -134,13 +179,26 @@ static void launch_families(const ElemArgs *a, hipStream_t s)
         tiles += n;
         most = std::max(most, n);
     }
+    q.first[4] = (uint32_t)tiles;
+    constexpr bool NH = MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES;
+    const bool sliced = mixed && ws_bytes > kSliceBytes && !(NH && VAR == V_ROWSYM);
     // lopsided: one family has more than three quarters of the tiles
-    if (fams < 2 || tiles > fuse_tiles<MODEL, VAR>(most > tiles / 4 * 3)) {
+    if (fams < 2 || (!sliced && tiles > fuse_tiles<MODEL, VAR>(most > tiles / 4 * 3))) {
         for (int t = 0; t < 4; ++t) launch_type<MODEL, VAR, CT>(t, a[t], s);
         return;
     }
+    q.slices = q.room = 0;
+    int64_t grid = tiles;
+    if (sliced) {
+        const int64_t k = std::max<int64_t>(8, tiles / kSliceTiles / 8 * 8);
+        int64_t room = 0;  // of the fullest slice
+        for (int t = 0; t < 4; ++t) room += ((int64_t)(q.first[t + 1] - q.first[t]) + k - 1) / k;
+        q.slices = (uint32_t)k;
+        q.room = (uint32_t)room;
+        grid = k * room;
+    }
     for (int t = 0; t < 4; ++t) q.a[t] = a[t];
-    k_element4<MODEL, VAR, CT><<<(unsigned)tiles, 256, 0, s>>>(q);
+    k_element4<MODEL, VAR, CT><<<(unsigned)grid, 256, 0, s>>>(q);
 }
 
 // A workspace of at least `need` bytes, kept until the graph goes or a larger
@@ -206,7 +264,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.ttb_ptr = g->ttb_ptr + g->tile_base[t];
             fam[t] = a;
         }
-        launch_families<MODEL, V_ROWSYM, CT>(fam, s);
+        launch_families<MODEL, V_ROWSYM, CT>(fam, sizeof(CT) * (size_t)g->ulen * BB, g->mixed, s);
         // then the block values with the right-hand side (3x3: rows that no
         // element touches set to zero first)
         mark(g, 1, o, s);
@@ -293,7 +351,7 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
             a.pdest = g->pdest + g->slot_base[t];
             fam[t] = a;
         }
-        launch_families<MODEL, V_ROWOWNER, CT>(fam, s);
+        launch_families<MODEL, V_ROWOWNER, CT>(fam, sizeof(CT) * (size_t)g->map_len * BB, g->mixed, s);
         // the right-hand side first (its workspace is still cached)
         if (f32) {
             if (nr) launch_segsum<B, CT, float>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, (float *)rhs, s);

@@ -404,6 +404,27 @@ __global__ void __launch_bounds__(256) k_rows(int64_t n_nodes, const int64_t *pt
     if (lane == 0) deg[i] = d;
 }
 
+// Of every 16th node: how many belong to elements of different node counts.
+constexpr int kMixedStep = 16;
+__global__ void __launch_bounds__(256) k_mixed_nodes(int64_t n_sampled, const int64_t *n2e_ptr, const int32_t *n2e,
+                                                     const int64_t *conn_ptr, unsigned long long *count)
+{
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    bool mixed = false;
+    if (s < n_sampled) {
+        const int64_t b = n2e_ptr[s * kMixedStep], e = n2e_ptr[s * kMixedStep + 1];
+        int64_t first = -1;
+        for (int64_t p = b; p < e && !mixed; ++p) {
+            const int32_t el = n2e[p];
+            const int64_t nn = conn_ptr[el + 1] - conn_ptr[el];
+            mixed = first >= 0 && nn != first;
+            first = nn;
+        }
+    }
+    const uint64_t m = __ballot(mixed);
+    if (m && (threadIdx.x & 63) == 0) atomicAdd(count, (unsigned long long)__popcll(m));
+}
+
 // With the rows' first blocks known: one wave per row turns its sorted
 // columns into blocks (col, the start of every block's inverse-map list) and
 // every slot's block (e2nnz).
@@ -1139,7 +1160,17 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
         FEA_HIP(hipMemsetAsync(g->n2e_ptr, 0, sizeof(int64_t), s));
     if ((rc = scan_to_ptr_i32(deg, N, g->row_ptr, scan, s))) return rc;
     FEA_HIP(hipMemcpyAsync(&g->nnz, g->row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    // cnt is free again: the first word takes the mixed nodes
+    unsigned long long mixed = 0;
+    const int64_t sampled = (N + kMixedStep - 1) / kMixedStep;
+    if (N) {
+        FEA_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t), s));
+        k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, s>>>(sampled, g->n2e_ptr, g->n2e, conn_ptr,
+                                                             (unsigned long long *)cnt);
+        FEA_HIP(hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, s));
+    }
     FEA_HIP(hipStreamSynchronize(s));
+    g->mixed = N > 0 && 2 * (int64_t)mixed >= sampled;
     if (g->nnz > INT32_MAX)
         return set_error(FEA_ERANGE, "%lld nonzero blocks exceed int32 block indices", (long long)g->nnz);
     if ((rc = dalloc_arrays(&g->mem[1], {{(void **)&g->col, sizeof(int32_t) * g->nnz},
@@ -1382,6 +1413,21 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
     if (!ok) {
         destroy(g);
         return set_error(FEA_EINVAL, "%s is truncated or does not match its header", path);
+    }
+    if (n_nodes) {
+        unsigned long long mixed = 0, *cnt = (unsigned long long *)chk.p;
+        const int64_t sampled = (n_nodes + kMixedStep - 1) / kMixedStep;
+        hipError_t e = hipMemsetAsync(cnt, 0, sizeof(mixed), stream);
+        if (e == hipSuccess) {
+            k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, stream>>>(sampled, g->n2e_ptr, g->n2e, conn_ptr, cnt);
+            e = hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, stream);
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) {
+            destroy(g);
+            return set_error(FEA_EHIP, "graph load: %s", hipGetErrorString(e));
+        }
+        g->mixed = 2 * (int64_t)mixed >= sampled;
     }
     if ((rc = noalloc_setup())) {
         destroy(g);

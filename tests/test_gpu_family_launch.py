@@ -63,3 +63,28 @@ def test_smallest_inverted_element(variant, turned):
     dm = fea.DeviceMesh(m)
     _, _, st = dm.assemble(dm.graph(), model=fea.ELASTIC, variant=variant)
     assert int(st.item()) == min(ids)
+
+
+@pytest.mark.parametrize("n,variant,nh", [(30, fea.ROWOWNER, False), (36, fea.ROWOWNER, False), (36, fea.ROWOWNER, True),
+                                          (50, fea.ROWSYM, False)])
+def test_slices_of_mixed_families(n, variant, nh, tmp_path):
+    """An unordered mixture of the families: below (n = 30) and above the
+    workspace size from which the families go in slices; the graph and the one
+    loaded from its cache give the same bits, within the bound of the oracle."""
+    cells = np.random.default_rng(n).integers(0, 4, n ** 3).astype(np.uint8)
+    m = mg.cube_mesh(n, cells, jitter=0.1, seed=n)
+    m.nh_flag = (np.arange(len(m.types)) % 3 == 0).astype(np.uint8)
+    m.u = 1e-3 * np.random.default_rng(1).standard_normal(3 * m.n_nodes)
+    dm = fea.DeviceMesh(m)
+    g = dm.graph()
+    og = oracle.mesh_graph(m)
+    ref, rrhs = oracle.assemble(m, og, model=oracle.ELASTIC, use_nh=nh)
+    vals, rhs, st = dm.assemble(g, model=fea.ELASTIC, variant=variant, use_nh=nh)
+    assert int(st.item()) == -1
+    ev, er = fp64_errors(vals.cpu().numpy(), ref, og.row_ptr, 3, rhs.cpu().numpy(), rrhs)
+    assert ev <= 1e-12 and er <= 1e-12
+    g.save(str(tmp_path / "g"))
+    g.destroy()
+    g = dm.graph(cache=str(tmp_path / "g"))
+    again = dm.assemble(g, model=fea.ELASTIC, variant=variant, use_nh=nh)
+    assert torch.equal(vals, again[0]) and torch.equal(rhs, again[1])
