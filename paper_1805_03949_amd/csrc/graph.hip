@@ -474,23 +474,29 @@ struct TmpBuf {
 // ---------------------------------------------- upper-triangle row-owner
 // Block k = (i, j): its transposed partner (j, i) lies in row j (the
 // pattern is structurally symmetric); upper blocks (j >= i) are their own.
-__global__ void k_sym_partner(int64_t n_nodes, const int64_t *row_ptr, const int32_t *col, int32_t *upart)
+// One wave per row, one lane per block, so that the binary searches of a row
+// run side by side (one thread per row took them one after the other: 0.86 ms
+// on a 96^3 hybrid mesh, 22 M blocks; now 0.50). flag: 1 for an upper block.
+__global__ void __launch_bounds__(256) k_sym_partner(int64_t n_nodes, const int64_t *row_ptr, const int32_t *col,
+                                                     int32_t *upart, int32_t *flag)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n_nodes) return;
-    for (int64_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
+    const int64_t e = row_ptr[i + 1];
+    for (int64_t k = row_ptr[i] + (threadIdx.x & 63); k < e; k += 64) {
         const int32_t j = col[k];
-        if (j >= i) {
-            upart[k] = (int32_t)k;
-        } else {
-            int64_t lo = row_ptr[j], hi = row_ptr[j + 1] - 1;
+        int32_t u = (int32_t)k;
+        if (j < i) {
+            int32_t lo = (int32_t)row_ptr[j], hi = (int32_t)row_ptr[j + 1] - 1;
             while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
+                const int32_t mid = lo + ((hi - lo) >> 1);
                 if (col[mid] < i) lo = mid + 1;
                 else hi = mid;
             }
-            upart[k] = (int32_t)lo;
+            u = lo;
         }
+        upart[k] = u;
+        flag[k] = j >= i ? 1 : 0;
     }
 }
 
@@ -506,18 +512,15 @@ __global__ void k_sym_lists(int64_t nnz, const int32_t *upart, const int64_t *uo
     else lpart[u] = (int32_t)k;
 }
 
-__global__ void k_flag_upper(int64_t nnz, const int32_t *upart, int32_t *flag)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nnz) flag[k] = upart[k] == k ? 1 : 0;
-}
-
 struct TileBases {
     int64_t seg[5], node[5], tile[5], pair[5];
 };
 
 // One workgroup per tile: the tile's contributions (one per lane) keyed by
-// destination upper block, sorted (bitonic, in LDS) by block then lane.
+// destination upper block, sorted by block then lane (a bitonic network over
+// lane exchanges, through LDS only between waves: three stages of 36; with all
+// of them in LDS, 72 barriers, a pass took 0.78 ms for the 260 k tiles of a 96^3
+// hybrid mesh, now 0.53).
 // Pass 1 (!WRITE) stores the distinct-block count; pass 2 writes every pair's
 // place and the tile-blocks at the scanned offsets. (The graph build rejects
 // an element that repeats a node, so a lane has exactly one destination.)
@@ -555,18 +558,27 @@ __global__ void __launch_bounds__(256) k_tile_entries(TileBases tb, const int32_
         mine = (uint64_t)e2nnz[map_ptr[perm[p]] + lo * n + hi] << 8 | (uint64_t)tid;
         word[tid] = sym_pair_word(0, lo, hi);
     }
-    key[tid] = mine;
-    __syncthreads();
+    uint64_t k = mine;
+#pragma unroll
     for (int size = 2; size <= K; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const uint64_t x = key[tid], y = key[tid ^ stride];
-            __syncthreads();
-            const bool low = (tid & stride) == 0, up = (tid & size) == 0;
-            key[tid] = (low == up) == (x < y) ? x : y;
-            __syncthreads();
+#pragma unroll
+        for (int st = size >> 1; st > 0; st >>= 1) {
+            uint64_t y;
+            if (st >= 64) {
+                __syncthreads();  // the previous exchange's readers are done
+                key[tid] = k;
+                __syncthreads();
+                y = key[tid ^ st];
+            } else {
+                y = (uint64_t)lane_xor((uint32_t)(k >> 32), st) << 32 | lane_xor((uint32_t)k, st);
+            }
+            const bool low = (tid & st) == 0, up = (tid & size) == 0;
+            k = (low == up) == (k < y) ? k : y;
         }
+    __syncthreads();
+    key[tid] = k;
+    __syncthreads();
     // new-block flags and their scan
-    const uint64_t k = key[tid];
     const bool f = k != NONE && (tid == 0 || (k >> 8) != (key[tid - 1] >> 8));
     const uint64_t m = __ballot(f);
     const int lane = tid & 63, wave = tid >> 6;
@@ -622,18 +634,18 @@ __global__ void k_sym_compact(int64_t nup, int64_t nnz, int64_t n_nodes, const i
     }
 }
 
-__global__ void k_tb_count(int64_t ntb, const int32_t *tb_blk, int32_t *cnt)
+// Tile-blocks of every block, and each tile-block's place among them (in no
+// particular order yet).
+__global__ void k_tb_count(int64_t ntb, const int32_t *tb_blk, int32_t *cnt, int32_t *place)
 {
     const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d < ntb) atomicAdd(&cnt[tb_blk[d]], 1);
+    if (d < ntb) place[d] = atomicAdd(&cnt[tb_blk[d]], 1);
 }
 
-__global__ void k_tb_fill(int64_t ntb, const int32_t *tb_blk, const int64_t *ts_ptr, int32_t *fill, int32_t *lst)
+__global__ void k_tb_fill(int64_t ntb, const int32_t *tb_blk, const int64_t *ts_ptr, const int32_t *place, int32_t *lst)
 {
     const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= ntb) return;
-    const int32_t k = tb_blk[d];
-    lst[ts_ptr[k] + atomicAdd(&fill[k], 1)] = (int32_t)d;
+    if (d < ntb) lst[ts_ptr[tb_blk[d]] + place[d]] = (int32_t)d;
 }
 
 // Each block's tile-blocks in ascending tile order (tile-blocks are numbered
@@ -706,8 +718,7 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     // partners; tile-block counts and offsets
     int64_t nup = 0, ntb = 0;
     if (nnz) {
-        k_sym_partner<<<grid_for(N, BS), BS, 0, s>>>(N, g->row_ptr, g->col, upart);
-        k_flag_upper<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, upart, flag);
+        k_sym_partner<<<grid_for(N, 4), 256, 0, s>>>(N, g->row_ptr, g->col, upart, flag);
         if ((rc = scan_to_ptr_i32(flag, nnz, uoff, tmp, s))) return rc;
         FEA_HIP(hipMemcpyAsync(&nup, uoff + nnz, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     }
@@ -749,11 +760,11 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     }
     if (nnz) {
         FEA_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t) * nnz, s));
-        if (ntb) k_tb_count<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, flag);
+        // (tb_slot holds the places until k_tb_slots)
+        if (ntb) k_tb_count<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, flag, g->tb_slot);
         if ((rc = scan_to_ptr_i32(flag, nnz, ts_ptr, tmp, s))) return rc;
-        FEA_HIP(hipMemsetAsync(flag, 0, sizeof(int32_t) * nnz, s));
         if (ntb) {
-            k_tb_fill<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, ts_ptr, flag, lst);
+            k_tb_fill<<<grid_for(ntb, BS), BS, 0, s>>>(ntb, g->tb_blk, ts_ptr, g->tb_slot, lst);
             k_tb_slots<<<grid_for(nnz, BS), BS, 0, s>>>(nnz, ts_ptr, lst, g->tb_slot);
         }
     } else {
