@@ -266,12 +266,18 @@ static int run(fea_graph *g, ElemArgs a, const fea_options *o, hipStream_t s, vo
         }
         launch_families<MODEL, V_ROWSYM, CT>(fam, sizeof(CT) * (size_t)g->ulen * BB, g->mixed, s);
         // then the block values with the right-hand side (3x3: rows that no
-        // element touches set to zero first)
-        mark(g, 1, o, s);
+        // element touches set to zero first; 1x1: in one launch, but a timed
+        // call, whose phases count the right-hand side apart, has two)
         auto sums = [&](auto *v, auto *r) {
             using OT = std::remove_pointer_t<decltype(v)>;
             if constexpr (RHSD) {
                 if (g->sym_empty_rows && nr) k_zero<OT><<<grid_for(nr, 256), 256, 0, s>>>(nr, r);
+                mark(g, 1, o, s);
+                if (g->nup)
+                    launch_segsum_sym<BB, CT, OT>(g->nup, g->ublk, g->ulp, g->uptr, (const CT *)g->contrib, v, r, s);
+            } else if (o->timing) {
+                if (nr) launch_segsum<B, CT, OT>(g->n_nodes, g->n2e_ptr, (const CT *)g->rcontrib, r, s);
+                mark(g, 1, o, s);
                 if (g->nup)
                     launch_segsum_sym<BB, CT, OT>(g->nup, g->ublk, g->ulp, g->uptr, (const CT *)g->contrib, v, r, s);
             } else {
