@@ -1194,7 +1194,8 @@ __device__ void elem_tile_full(const ElemArgs &A, int64_t first, ElemSmem<T, MOD
 // / mixed: tet4 (1.3M elements) 0.29 -> 0.22 / 0.25 -> 0.20, pyr5 (1.3M) 0.62
 // -> 0.48 / 0.43 -> 0.37, pen6 (1.0M) 0.64 -> 0.54 / 0.48 -> 0.41, hex8 (885k)
 // 1.06 -> 0.86 / 0.83 -> 0.70; 96^3-cell hybrid mesh 1.39 -> 1.12 / 1.09 ->
-// 0.92.
+// 0.92 (with the factored geometry and the tile sums as they are now 1.00 /
+// 0.76).
 template <int T, int MODEL, int VAR, typename CT>
 __device__ void elem_tile_sym(const ElemArgs &A, int64_t first, ElemSmem<T, MODEL, VAR, CT> &S, const int tid)
 {
