@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <map>
 #include <mutex>
+#include <new>
 
 #include "fea_internal.h"
 
@@ -93,7 +94,9 @@ struct Pool {
 
 Pool &pool()
 {
-    static Pool *p = new Pool;  // never destroyed: graphs may outlive static objects
+    // never destroyed: graphs may outlive static objects
+    alignas(Pool) static unsigned char mem[sizeof(Pool)];
+    static Pool *p = new (mem) Pool;
     return *p;
 }
 
@@ -126,6 +129,7 @@ hipError_t pool_alloc(void **p, size_t bytes)
     std::vector<void *> old;
     try {
         std::lock_guard<std::mutex> lock(q.mtx);
+        old.reserve(q.idle.size());
         ++q.clock;
         size_t best = q.idle.size();
         for (size_t i = 0; i < q.idle.size(); ++i) {
@@ -141,7 +145,6 @@ hipError_t pool_alloc(void **p, size_t bytes)
             q.idle.erase(q.idle.begin() + (ptrdiff_t)best);
             *p = b.p;
         }
-        old.reserve(q.idle.size());
         pool_drop(q, dev, old, [&](const PoolBlock &b) { return q.clock - b.stamp > kPoolAge; });
     } catch (...) {
         return hipErrorOutOfMemory;
@@ -234,13 +237,14 @@ int dalloc_pool(void **p, size_t bytes)
     return FEA_OK;
 }
 
-int dalloc_arrays(void **base, const std::vector<DevArray> &arrays)
+int dalloc_arrays(void **base, const DevArray *arrays, size_t n)
 {
     *base = nullptr;
     size_t total = 0;
     bool injected = false;
     auto room = [](const DevArray &a) { return (std::max<size_t>(a.bytes, 1) + 255) / 256 * 256; };
-    for (const DevArray &a : arrays) {
+    for (size_t i = 0; i < n; ++i) {
+        const DevArray &a = arrays[i];
         *a.p = nullptr;
         injected = alloc_injected() || injected;
         total += room(a);
@@ -252,9 +256,9 @@ int dalloc_arrays(void **base, const std::vector<DevArray> &arrays)
         return set_error(FEA_ENOMEM, "device allocation of %zu bytes failed: %s", total, hipGetErrorString(e));
     }
     char *at = (char *)*base;
-    for (const DevArray &a : arrays) {
-        *a.p = at;
-        at += room(a);
+    for (size_t i = 0; i < n; ++i) {
+        *arrays[i].p = at;
+        at += room(arrays[i]);
     }
     return FEA_OK;
 }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -60,7 +61,11 @@ struct DevArray {
     void **p;
     size_t bytes;
 };
-int dalloc_arrays(void **base, const std::vector<DevArray> &arrays);
+int dalloc_arrays(void **base, const DevArray *arrays, size_t n);
+inline int dalloc_arrays(void **base, std::initializer_list<DevArray> arrays)
+{
+    return dalloc_arrays(base, arrays.begin(), arrays.size());
+}
 void dfree(void *p);
 
 // ptr[0] = 0, ptr[i+1] = in[0] + ... + in[i] for i < n (int64 result).

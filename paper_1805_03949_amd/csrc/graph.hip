@@ -1403,7 +1403,7 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         ok = ok && fread(&nb, 8, 1, f.f) == 1 && nb == a.bytes && fseek(f.f, (long)a.bytes, SEEK_CUR) == 0;
     }
     ok = ok && fseek(f.f, data, SEEK_SET) == 0;
-    if (ok && (rc = dalloc_arrays(&g->mem[0], arrays))) {
+    if (ok && (rc = dalloc_arrays(&g->mem[0], arrays.data(), arrays.size()))) {
         destroy(g);
         return rc;
     }
