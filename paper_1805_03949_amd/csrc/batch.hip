@@ -71,18 +71,16 @@ k_batch(const ElemArgs *__restrict__ itemargs, const int4 *items,
     constexpr int B = MODEL == FEA_POISSON ? 1 : 3;
     __shared__ ElemSmem<T, MODEL, VAR, CT> S;
     __shared__ int32_t s_item;
-    // static partition: this workgroup runs order[part[w] .. part[w+1]). From
-    // the queue workgroup w takes item w first, then one after another from
-    // the head behind those (next: thread 0's), so that a launch does not start
-    // with an atomic addition of 1,500 to 2,000 workgroups to one word, past the
-    // XCDs' L2s: 15 us a launch, four launches a call (24 meshes of 8 to 36 cells
-    // a side, mixed, 890 -> 830 us; 5 meshes of 6 to 16, 133 -> 62). More rounds
-    // without the head gained 1 to 2% more and would cost balance.
-    int32_t next = part ? part[blockIdx.x] : (int32_t)blockIdx.x;
-    const int32_t last = part ? part[blockIdx.x + 1] : n_items;
+    // static partition: this workgroup runs order[part[w] .. part[w+1])
+    int32_t next = part ? part[blockIdx.x] : 0;
+    const int32_t last = part ? part[blockIdx.x + 1] : 0;
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) s_item = next < last ? order[next] : -1;
+        if (threadIdx.x == 0) {
+            int32_t q = part ? next : atomicAdd(head, 1);
+            s_item = q < (part ? last : n_items) ? order[q] : -1;
+        }
+        ++next;
         __syncthreads();
         // the item is the same for the whole workgroup: keep it (and the
         // mesh view it selects) in scalar registers
@@ -97,7 +95,6 @@ k_batch(const ElemArgs *__restrict__ itemargs, const int4 *items,
             cycles[it] = clock64() - t0;
             worker[it] = blockIdx.x;
             cu[it] = (int32_t)__smid();
-            next = part ? next + 1 : (int32_t)gridDim.x + atomicAdd(head, 1);
         }
     }
 }
