@@ -71,16 +71,21 @@ k_batch(const ElemArgs *__restrict__ itemargs, const int4 *items,
     constexpr int B = MODEL == FEA_POISSON ? 1 : 3;
     __shared__ ElemSmem<T, MODEL, VAR, CT> S;
     __shared__ int32_t s_item;
-    // static partition: this workgroup runs order[part[w] .. part[w+1])
-    int32_t next = part ? part[blockIdx.x] : 0;
-    const int32_t last = part ? part[blockIdx.x + 1] : 0;
+    // static partition: this workgroup runs order[part[w] .. part[w+1]). No
+    // more items than workgroups: workgroup w runs item w; there is nothing to
+    // queue for, and the additions of 1,500 to 2,000 workgroups to one word,
+    // past the XCDs' L2s, took 15 us a launch (5 meshes of 6 to 16 cells a side,
+    // mixed precision: 133 -> 55 us a call). With more items the queue also
+    // spreads the workgroups' starts, without which the first items' recorded
+    // cycles hold the contention of a common start (balance of a learned split
+    // of a 48^3 neo-Hookean mesh 0.90 -> 0.85, its assembly 300 -> 261 us).
+    const bool queue = !part && n_items > (int32_t)gridDim.x;
+    int32_t next = part ? part[blockIdx.x] : (int32_t)blockIdx.x;
+    const int32_t last = part ? part[blockIdx.x + 1] : n_items;
+    if (queue && threadIdx.x == 0) next = atomicAdd(head, 1);
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int32_t q = part ? next : atomicAdd(head, 1);
-            s_item = q < (part ? last : n_items) ? order[q] : -1;
-        }
-        ++next;
+        if (threadIdx.x == 0) s_item = next < last ? order[next] : -1;
         __syncthreads();
         // the item is the same for the whole workgroup: keep it (and the
         // mesh view it selects) in scalar registers
@@ -95,6 +100,7 @@ k_batch(const ElemArgs *__restrict__ itemargs, const int4 *items,
             cycles[it] = clock64() - t0;
             worker[it] = blockIdx.x;
             cu[it] = (int32_t)__smid();
+            next = queue ? atomicAdd(head, 1) : part ? next + 1 : last;
         }
     }
 }
