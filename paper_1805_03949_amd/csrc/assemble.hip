@@ -210,7 +210,7 @@ static int ensure_ws(void **p, size_t *have, size_t need, hipStream_t s)
     const bool pooled = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
     if (*p) {
         if (pooled) FEA_HIP(hipDeviceSynchronize());
-        pooled ? pool_free(*p) : dfree(*p);
+        pooled ? pool_free(*p, hipSuccess) : dfree(*p);
     }
     *p = nullptr;
     *have = 0;

@@ -70,8 +70,10 @@ int dalloc(void **p, size_t bytes)
 // Bounded: at most kPoolBytes and kPoolBlocks unused a device; the longest
 // unused goes back to the driver first, and also one that kPoolAge later
 // allocations have passed over; all of them do before an allocation fails.
-// A block enters the pool with no work on it pending (pool_free's callers
-// see to that), so any stream and thread may have it next.
+// A block enters the pool with no work on it pending: pool_free takes the
+// result of the wait for that work and hands the block to the driver if the
+// wait failed (hipFree then waits itself, or refuses). Any stream and thread may
+// have it next.
 namespace {
 
 constexpr size_t kPoolBytes = size_t(1) << 30;
@@ -185,9 +187,14 @@ void pool_flush(int device)
     for (void *o : old) (void)hipFree(o);
 }
 
-void pool_free(void *p)
+void pool_free(void *p, hipError_t waited)
 {
     if (!p) return;
+    if (waited != hipSuccess) {
+        dfree(p);
+        (void)hipGetLastError();  // of the wait, or of a free refused under a capture
+        return;
+    }
     Pool &q = pool();
     std::vector<void *> old;
     bool kept = false;

@@ -48,9 +48,10 @@ void clear_error();
 // Device allocation that records an error message on failure.
 int dalloc(void **p, size_t bytes);
 // Device memory from the pool of freed blocks (common.hip) or the driver.
-// pool_free: no work on the memory may be pending; takes any device pointer.
+// pool_free takes any device pointer; `waited` is the result of the wait for all
+// work on that memory, and only after one that succeeded is it pooled.
 hipError_t pool_alloc(void **p, size_t bytes);
-void pool_free(void *p);
+void pool_free(void *p, hipError_t waited);
 void pool_flush(int device);
 int dalloc_pool(void **p, size_t bytes);
 // One allocation (*base, for pool_free) for several arrays, each 256-byte

@@ -465,9 +465,7 @@ struct TmpBuf {
     explicit TmpBuf(hipStream_t stream) : s(stream) {}
     ~TmpBuf()
     {
-        if (!p) return;
-        (void)hipStreamSynchronize(s);
-        pool_free(p);
+        if (p) pool_free(p, hipStreamSynchronize(s));
     }
 };
 
@@ -674,7 +672,7 @@ int sym_prepare(fea_graph *g, hipStream_t s)
     int rc;
     if (g->mem[2]) {
         FEA_HIP(hipDeviceSynchronize());
-        pool_free(g->mem[2]);
+        pool_free(g->mem[2], hipSuccess);
         g->mem[2] = nullptr;
     }
     g->nup = 0;
@@ -1054,13 +1052,13 @@ static int colour_finish(fea_graph *g, HostColouring &hc, hipStream_t s)
     return FEA_OK;
 }
 
-// No work on the graph's arrays may be pending.
-static void destroy(fea_graph *g)
+// waited: result of the wait for all work on the graph's arrays.
+static void destroy(fea_graph *g, hipError_t waited)
 {
     if (!g) return;
     void *bufs[] = {g->mem[0], g->mem[1], g->mem[2], g->contrib, g->rcontrib, g->acc64,
                     g->gtile, g->gnodes, g->gdesc, g->ctile, g->gp_ptr};
-    for (void *b : bufs) pool_free(b);
+    for (void *b : bufs) pool_free(b, waited);
     for (hipEvent_t e : g->ev)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : g->gev)
@@ -1218,8 +1216,9 @@ extern "C" int fea_graph_build(int64_t n_nodes, int64_t n_elems, const uint8_t *
     int rc = build(n_nodes, n_elems, types, conn_ptr, conn, stream, g);
     if (rc == FEA_OK) rc = noalloc_setup();
     if (rc != FEA_OK) {
-        (void)hipStreamSynchronize(stream);
-        destroy(g);
+        // an error of the runtime may have left work on the colouring's stream too
+        const hipError_t w = hipStreamSynchronize(stream);
+        destroy(g, w == hipSuccess && rc == FEA_EHIP ? hipDeviceSynchronize() : w);
         return rc;
     }
     *out = g;
@@ -1390,7 +1389,7 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
     if (ok) {
         hipError_t e = hipHostMalloc(&stage.p, kStage, hipHostMallocDefault);
         if (e != hipSuccess) {
-            destroy(g);
+            destroy(g, hipSuccess);
             return set_error(FEA_ENOMEM, "pinned staging buffer: %s", hipGetErrorString(e));
         }
     }
@@ -1404,7 +1403,7 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
     }
     ok = ok && fseek(f.f, data, SEEK_SET) == 0;
     if (ok && (rc = dalloc_arrays(&g->mem[0], arrays.data(), arrays.size()))) {
-        destroy(g);
+        destroy(g, hipSuccess);
         return rc;
     }
     for (const DevArray &a : arrays) {
@@ -1416,13 +1415,13 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
             const size_t n = std::min(kStage, a.bytes - off);
             ok = fread(stage.p, 1, n, f.f) == n;
             if (ok && hipMemcpy((char *)*a.p + off, stage.p, n, hipMemcpyHostToDevice) != hipSuccess) {
-                destroy(g);
+                destroy(g, hipDeviceSynchronize());
                 return set_error(FEA_EHIP, "copy of %s to the device failed", path);
             }
         }
     }
     if (!ok) {
-        destroy(g);
+        destroy(g, hipSuccess);  // every copy was waited for
         return set_error(FEA_EINVAL, "%s is truncated or does not match its header", path);
     }
     if (n_nodes) {
@@ -1435,13 +1434,13 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         }
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) {
-            destroy(g);
+            destroy(g, hipDeviceSynchronize());
             return set_error(FEA_EHIP, "graph load: %s", hipGetErrorString(e));
         }
         g->mixed = 2 * (int64_t)mixed >= sampled;
     }
     if ((rc = noalloc_setup())) {
-        destroy(g);
+        destroy(g, hipSuccess);  // every copy and kernel was waited for
         return rc;
     }
     *out = g;
@@ -1516,8 +1515,7 @@ extern "C" void fea_graph_destroy(fea_graph *g)
         int cur = 0;
         (void)hipGetDevice(&cur);
         (void)hipSetDevice(g->device);
-        (void)hipDeviceSynchronize();
-        destroy(g);
+        destroy(g, hipDeviceSynchronize());
         (void)hipSetDevice(cur);
     }
 }

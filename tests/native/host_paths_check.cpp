@@ -1,0 +1,169 @@
+// The library's host paths on the CPU: this program defines the runtime calls
+// that libfea.so makes (device memory is host memory, kernels do nothing, waits
+// and allocations fail on demand), loads the library and goes through its C
+// entry points with meshes of nodes without elements. Checks where freed
+// device memory goes. Usage: host_paths_check LIBFEA CHECK DIRECTORY; exit status 0 on
+// success.
+#include <dlfcn.h>
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+#include <vector>
+
+#include "../../include/fea.h"
+
+// ------------------------------------------------------------ the runtime
+static std::mutex mtx;
+static std::map<void *, size_t> live;  // device memory the driver has given out
+static int n_malloc = 0, fail_malloc = 0;
+static size_t largest_freed = 0;
+static bool fail_device_wait = false, fail_stream_wait = false;
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n)
+{
+    std::lock_guard<std::mutex> lock(mtx);
+    *p = nullptr;
+    if (fail_malloc > 0) {
+        --fail_malloc;
+        return hipErrorOutOfMemory;
+    }
+    ++n_malloc;
+    *p = calloc(1, n);
+    live[*p] = n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    std::lock_guard<std::mutex> lock(mtx);
+    auto it = live.find(p);
+    if (it == live.end()) return p ? hipErrorInvalidValue : hipSuccess;
+    if (it->second > largest_freed) largest_freed = it->second;
+    live.erase(it);
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned)
+{
+    *p = malloc(n);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p)
+{
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d)
+{
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int)
+{
+    memset(p, 0, sizeof(*p));
+    strcpy(p->gcnArchName, "gfx950");
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { return fail_device_wait ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return fail_stream_wait ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind)
+{
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return hipSuccess; }  // memory starts as zeros
+hipError_t hipMemcpyToSymbol(const void *, const void *, size_t, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *)
+{
+    static char symbol[64];
+    *p = symbol;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipSuccess; }
+}
+
+// ------------------------------------------------------------- the library
+static decltype(&fea_graph_build) graph_build;
+static decltype(&fea_graph_destroy) graph_destroy;
+
+static int failures = 0;
+#define CHECK(c)                                                              \
+    do {                                                                      \
+        if (!(c)) {                                                           \
+            std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); \
+            ++failures;                                                       \
+        }                                                                     \
+    } while (0)
+
+static fea_graph *build(int64_t nodes, int expect = FEA_OK)
+{
+    fea_graph *g = nullptr;
+    const int rc = graph_build(nodes, 0, nullptr, nullptr, nullptr, nullptr, &g);
+    CHECK(rc == expect);
+    return g;
+}
+
+static size_t live_bytes()
+{
+    size_t n = 0;
+    for (const auto &b : live) n += b.second;
+    return n;
+}
+
+constexpr int64_t M = 1000000;
+
+// The memory of a destroyed graph serves the next one only if the wait for
+// the work on it succeeded.
+static void check_waits()
+{
+    graph_destroy(build(M));
+    int before = n_malloc;
+    fea_graph *g = build(M);
+    CHECK(n_malloc == before);  // all of it from freed blocks
+    largest_freed = 0;
+    fail_device_wait = true;
+    graph_destroy(g);
+    fail_device_wait = false;
+    CHECK(largest_freed >= 16 * (size_t)M);  // its two tables of M + 1 offsets went to the driver
+    before = n_malloc;
+    g = build(M);
+    CHECK(n_malloc > before);
+    graph_destroy(g);
+    // a build whose waits fail: neither its scratch memory nor its arrays stay
+    const size_t have = live.size();
+    CHECK(have > 0);
+    fail_device_wait = fail_stream_wait = true;
+    build(M, FEA_EHIP);
+    fail_device_wait = fail_stream_wait = false;
+    before = n_malloc;
+    graph_destroy(build(M));
+    CHECK(n_malloc > before);
+}
+
+int main(int argc, char **argv)
+{
+    if (argc != 4) return 2;
+    void *lib = dlopen(argv[1], RTLD_NOW | RTLD_LOCAL);
+    if (!lib) {
+        std::fprintf(stderr, "%s\n", dlerror());
+        return 2;
+    }
+    graph_build = (decltype(graph_build))dlsym(lib, "fea_graph_build");
+    graph_destroy = (decltype(graph_destroy))dlsym(lib, "fea_graph_destroy");
+    const std::string what = argv[2], dir = argv[3];
+    if (what == "waits") check_waits();
+    else return 2;
+    return failures ? 1 : 0;
+}
