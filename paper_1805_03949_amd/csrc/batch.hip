@@ -248,6 +248,9 @@ struct fea_batch {
     int32_t *d_head = nullptr;
     int32_t *d_status = nullptr;
     int64_t *d_vseg = nullptr, *d_rseg = nullptr;
+    // zeros in the place of the flags and fields that a mesh of a batch with
+    // neo-Hookean elements leaves out: its kernels read both for every mesh
+    void *d_none = nullptr;
     uint64_t *d_cycles = nullptr;
     int32_t *d_worker = nullptr, *d_cu = nullptr;
     size_t items_cap = 0;
@@ -320,7 +323,7 @@ void destroy_batch(fea_batch *b)
     void *bufs[] = {b->d_meshes, b->d_items, b->d_order, b->d_head, b->d_status, b->d_vseg,
                     b->d_rseg, b->d_cycles, b->d_worker, b->d_cu, b->contrib, b->rcontrib,
                     b->d_part, b->d_sym_ublk, b->d_sym_lp, b->d_sym_ptr, b->d_itemargs,
-                    b->d_sub_head, b->d_subargs, b->d_sub_items, b->d_sub_order};
+                    b->d_sub_head, b->d_subargs, b->d_sub_items, b->d_sub_order, b->d_none};
     for (void *p : bufs) dfree(p);
     for (hipEvent_t e : b->ev)
         if (e) (void)hipEventDestroy(e);
@@ -648,7 +651,7 @@ int dispatch_gather(fea_batch *b, const fea_options *o, hipStream_t s, void *val
         for (int m = 0; m < b->n_meshes; ++m) {
             const fea_mesh_desc &d = b->desc[m];
             in[m] = {d.x, d.y, d.z, d.types, d.conn_ptr, d.conn, d.young, d.nu, d.source, nullptr,
-                     b->model == FEA_ELASTIC ? d.nh_flag : nullptr, d.u};
+                     b->hmeshes[m].a.nh_flag, b->hmeshes[m].a.u};
         }
         if ((rc = gather_batch_build(&b->gbatch, b->n_meshes, b->graphs.data(), in.data(), b->vals_off.data(),
                                      b->rhs_off.data(), s)))
@@ -786,6 +789,21 @@ int build(int n, const fea_mesh_desc *md, int model, const int32_t *tile, hipStr
         std::copy(g->slot_base, g->slot_base + 5, bm[m].slot_base);
         bm[m].coff = b->slot_off[m];
         bm[m].roff = b->inc_off[m];
+    }
+    if (b->has_nh) {
+        size_t none = 0;
+        for (int m = 0; m < n; ++m) {
+            if (!bm[m].a.nh_flag) none = std::max(none, (size_t)md[m].n_elems);
+            if (!bm[m].a.u) none = std::max(none, sizeof(double) * 3 * (size_t)md[m].n_nodes);
+        }
+        if (none) {
+            if ((rc = dalloc(&b->d_none, none))) return rc;
+            FEA_HIP(hipMemsetAsync(b->d_none, 0, none, s));
+        }
+        for (int m = 0; m < n; ++m) {
+            if (!bm[m].a.nh_flag) bm[m].a.nh_flag = (const uint8_t *)b->d_none;
+            if (!bm[m].a.u) bm[m].a.u = (const double *)b->d_none;
+        }
     }
     b->hmeshes = bm;
     if ((rc = dalloc((void **)&b->d_meshes, sizeof(BatchMesh) * std::max(n, 1)))) return rc;
