@@ -1,5 +1,6 @@
 """Batches at their edges: meshes that leave out the neo-Hookean flags or the
-displacement next to one that gives them."""
+displacement next to one that gives them, and numbers of items around the
+number of workgroups, from which on there is a queue."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,72 @@ def test_flags_and_field_may_be_left_out(variant, precision):
             ev, er = fp64_errors(got[0][b.vals_off[m]:b.vals_off[m + 1]].cpu().numpy(), ov, og.row_ptr, 3,
                                  got[1][b.rhs_off[m]:b.rhs_off[m + 1]].cpu().numpy(), orr)
             assert ev <= 1e-12 and er <= 1e-12, (m, ev, er)
+
+
+EPB = (25, 17, 12, 7)  # elements per tile and least item: tet4, pyr5, pen6, hex8
+
+
+def _items(full, family, n):
+    """Two meshes of one family with n items of one tile, the last item of each
+    a partial one."""
+    a = max(1, n // 3)
+    return [mg.submesh(full, np.arange(k * EPB[family] - 1)) for k in (a, n - a) if k]
+
+
+@pytest.mark.parametrize("variant", [fea.ROWOWNER, fea.ROWSYM])
+@pytest.mark.parametrize("family", [0, 1, 2, 3])
+def test_item_counts_around_the_workgroups(family, variant):
+    """One item less than the family's workgroups, as many, one more (the
+    queue starts) and three times as many: in type-sorted and in permuted
+    order, in a static partition and in replays of a captured launch the
+    results equal, bit for bit, those of items of many tiles (fewer items than
+    workgroups, no queue), and to 1e-13 of the row scale one mesh's."""
+    def batch(meshes, tile):
+        return fea.Batch(meshes, tile=[tile] * 4)
+
+    side = int(np.ceil((3 * 2048 * EPB[family] / int(mg.SUBELEMS[family])) ** (1 / 3))) + 1
+    full = mg.cube_mesh(side, np.full(side ** 3, family, dtype=np.uint8), jitter=0.2, seed=family)
+    # the family's workgroups, from the records of a launch that has three items for each
+    b = batch([fea.DeviceMesh(m) for m in _items(full, family, 3 * 2048)], 1)
+    b.assemble(variant=variant)
+    assert b.n_items >= 3 * b.workers()
+    w = int(b.cycles()[1].max()) + 1
+    assert 256 <= w <= b.workers()
+    rng = np.random.default_rng(family)
+    for n in (w - 1, w, w + 1, 3 * w + 1):
+        meshes = _items(full, family, n)
+        dms = [fea.DeviceMesh(m) for m in meshes]
+        ref = batch(dms, 64 * EPB[family]).assemble(variant=variant)
+        b = batch(dms, 1)
+        assert b.n_items == n
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            out = b.outputs()
+
+            def same(what):
+                assert all(torch.equal(x, y) for x, y in zip(out, ref)), (n, w, what)
+                for x in out:
+                    x.fill_(123)
+
+            def run(what):
+                b.assemble(vals=out[0], rhs=out[1], status=out[2], variant=variant)
+                same(what)
+
+            run("type-sorted")
+            b.set_order(rng.permutation(n))
+            run("permuted")
+            b.capture(*out, variant=variant)
+            for k in range(3):
+                b.replay(1)
+                same("replay")
+                run("between replays")
+            b.partition(fea.TYPE_SORTED)
+            run("static partition")
+        for m, dm in enumerate(dms):
+            g = dm.graph()
+            v1, r1, _ = dm.assemble(g, variant=variant)
+            ev, er = fp64_errors(ref[0][b.vals_off[m]:b.vals_off[m + 1]].cpu().numpy(), v1.cpu().numpy(),
+                                 g.export()["row_ptr"].cpu().numpy(), 3,
+                                 ref[1][b.rhs_off[m]:b.rhs_off[m + 1]].cpu().numpy(), r1.cpu().numpy())
+            assert ev <= 1e-13 and er <= 1e-13, (m, ev, er)
