@@ -122,7 +122,7 @@ struct fea_graph {
     int64_t n_nodes = 0, n_elems = 0, nnz = 0, map_len = 0, conn_len = 0;
     uint64_t mesh_fp = 0;  // connectivity fingerprint of the mesh it was built for
     int n_colours = 0;
-    bool mixed = false;  // at least half of the nodes belong to several element families
+    bool mixed = false;  // at least half of a sample of the nodes belongs to several element families
     // device allocations that hold the graph's arrays (mem[0], mem[1]) and
     // those of the upper-triangle layout (mem[2])
     void *mem[3] = {nullptr, nullptr, nullptr};

@@ -404,15 +404,17 @@ __global__ void __launch_bounds__(256) k_rows(int64_t n_nodes, const int64_t *pt
     if (lane == 0) deg[i] = d;
 }
 
-// Of every 16th node: how many belong to elements of different node counts.
-constexpr int kMixedStep = 16;
-__global__ void __launch_bounds__(256) k_mixed_nodes(int64_t n_sampled, const int64_t *n2e_ptr, const int32_t *n2e,
-                                                     const int64_t *conn_ptr, unsigned long long *count)
+// Of a sample of the nodes, one of every group of host::kMixedStep: how many
+// belong to elements of different node counts.
+static int64_t mixed_groups(int64_t n_nodes) { return (n_nodes + host::kMixedStep - 1) / host::kMixedStep; }
+__global__ void __launch_bounds__(256) k_mixed_nodes(int64_t n_nodes, int64_t n_sampled, const int64_t *n2e_ptr,
+                                                     const int32_t *n2e, const int64_t *conn_ptr,
+                                                     unsigned long long *count)
 {
     const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
     bool mixed = false;
     if (s < n_sampled) {
-        const int64_t b = n2e_ptr[s * kMixedStep], e = n2e_ptr[s * kMixedStep + 1];
+        const int64_t v = host::mixed_sample(s, n_nodes), b = n2e_ptr[v], e = n2e_ptr[v + 1];
         int64_t first = -1;
         for (int64_t p = b; p < e && !mixed; ++p) {
             const int32_t el = n2e[p];
@@ -1171,10 +1173,10 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
     FEA_HIP(hipMemcpyAsync(&g->nnz, g->row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     // cnt is free again: the first word takes the mixed nodes
     unsigned long long mixed = 0;
-    const int64_t sampled = (N + kMixedStep - 1) / kMixedStep;
+    const int64_t sampled = mixed_groups(N);
     if (N) {
         FEA_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t), s));
-        k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, s>>>(sampled, g->n2e_ptr, g->n2e, conn_ptr,
+        k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, s>>>(N, sampled, g->n2e_ptr, g->n2e, conn_ptr,
                                                              (unsigned long long *)cnt);
         FEA_HIP(hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, s));
     }
@@ -1426,10 +1428,10 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
     }
     if (n_nodes) {
         unsigned long long mixed = 0, *cnt = (unsigned long long *)chk.p;
-        const int64_t sampled = (n_nodes + kMixedStep - 1) / kMixedStep;
+        const int64_t sampled = mixed_groups(n_nodes);
         hipError_t e = hipMemsetAsync(cnt, 0, sizeof(mixed), stream);
         if (e == hipSuccess) {
-            k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, stream>>>(sampled, g->n2e_ptr, g->n2e, conn_ptr, cnt);
+            k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, stream>>>(n_nodes, sampled, g->n2e_ptr, g->n2e, conn_ptr, cnt);
             e = hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(stream);

@@ -18,6 +18,21 @@ namespace host {
 
 constexpr int kMaxColours = 256;
 
+// The node that group g of kMixedStep consecutive nodes sends to the count of
+// the nodes that belong to several element families. Its place in the group is
+// hashed (a SplitMix64 step): every 16th node would see only some planes of a grid
+// whose lines have a multiple of 16 nodes, and an interface between two families
+// always or never. (constexpr: the device calls it too.)
+constexpr int kMixedStep = 16;
+constexpr int64_t mixed_sample(int64_t g, int64_t n_nodes)
+{
+    const int64_t first = g * kMixedStep, left = n_nodes - first;
+    uint64_t z = ((uint64_t)g + 1) * 0x9e3779b97f4a7c15ull;
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z ^= z >> 27;
+    return first + (int64_t)(z % (uint64_t)(left < kMixedStep ? left : kMixedStep));
+}
+
 // Greedy first fit over per-node masks of W 64-bit words (64 W colours).
 template <int W>
 class FirstFit {

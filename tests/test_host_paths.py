@@ -1,5 +1,6 @@
 """Host paths of libfea.so on the CPU, with the runtime calls it makes played
-by the test program (tests/native/host_paths_check.cpp)."""
+by the test program (tests/native/host_paths_check.cpp), and host code of its
+own (tests/native/mixed_sample_check.cpp)."""
 import os
 import shutil
 import subprocess
@@ -25,4 +26,12 @@ def test_host_paths(program, check, tmp_path):
     import paper_1805_03949_amd as fea
     p = subprocess.run([program, fea.LIB_PATH, check, str(tmp_path)], stdout=subprocess.PIPE,
                        stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert p.returncode == 0, p.stdout[-4000:]
+
+
+def test_sampled_nodes(tmp_path):
+    exe = str(tmp_path / "check")
+    subprocess.run(["g++", "-std=c++17", "-O1", os.path.join(ROOT, "tests", "native", "mixed_sample_check.cpp"), "-o", exe],
+                   check=True)
+    p = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert p.returncode == 0, p.stdout[-4000:]
