@@ -1396,14 +1396,16 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         }
     }
     const std::vector<DevArray> arrays = graph_arrays(g);
-    // every array's byte count first: a file that does not match allocates nothing
+    // every array's byte count first: a file that does not match allocates
+    // nothing (a pipe cannot seek: its counts are checked as they come)
     const long data = ftell(f.f);
-    ok = ok && data >= 0;
-    for (const DevArray &a : arrays) {
-        uint64_t nb = 0;
-        ok = ok && fread(&nb, 8, 1, f.f) == 1 && nb == a.bytes && fseek(f.f, (long)a.bytes, SEEK_CUR) == 0;
+    if (ok && data >= 0) {
+        for (const DevArray &a : arrays) {
+            uint64_t nb = 0;
+            ok = ok && fread(&nb, 8, 1, f.f) == 1 && nb == a.bytes && fseek(f.f, (long)a.bytes, SEEK_CUR) == 0;
+        }
+        ok = ok && fseek(f.f, data, SEEK_SET) == 0;
     }
-    ok = ok && fseek(f.f, data, SEEK_SET) == 0;
     if (ok && (rc = dalloc_arrays(&g->mem[0], arrays.data(), arrays.size()))) {
         destroy(g, hipSuccess);
         return rc;

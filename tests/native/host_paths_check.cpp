@@ -2,17 +2,20 @@
 // that libfea.so makes (device memory is host memory, kernels do nothing, waits
 // and allocations fail on demand), loads the library and goes through its C
 // entry points with meshes of nodes without elements. Checks where freed
-// device memory goes. Usage: host_paths_check LIBFEA CHECK DIRECTORY; exit status 0 on
+// device memory goes and what a graph can be loaded from. Usage: host_paths_check LIBFEA CHECK DIRECTORY; exit status 0 on
 // success.
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
+#include <sys/stat.h>
 
+#include <csignal>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/fea.h"
@@ -97,6 +100,9 @@ hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_
 // ------------------------------------------------------------- the library
 static decltype(&fea_graph_build) graph_build;
 static decltype(&fea_graph_destroy) graph_destroy;
+static decltype(&fea_graph_save) graph_save;
+static decltype(&fea_graph_load) graph_load;
+static decltype(&fea_last_error) last_error;
 
 static int failures = 0;
 #define CHECK(c)                                                              \
@@ -152,6 +158,40 @@ static void check_waits()
     CHECK(n_malloc > before);
 }
 
+// A graph cache is read from a file and from a pipe (which cannot seek); a
+// truncated one is refused either way.
+static void check_pipe(const std::string &dir)
+{
+    const std::string file = dir + "/graph", pipe = dir + "/pipe";
+    fea_graph *g = build(1000);
+    CHECK(graph_save(g, file.c_str()) == FEA_OK);
+    graph_destroy(g);
+    std::vector<char> data;
+    FILE *f = fopen(file.c_str(), "rb");
+    for (int c; (c = fgetc(f)) != EOF;) data.push_back((char)c);
+    fclose(f);
+    CHECK(mkfifo(pipe.c_str(), 0600) == 0);
+    auto load = [&](const std::string &from, size_t bytes) {
+        std::thread writer([&] {
+            FILE *w = fopen(from.c_str(), "wb");
+            fwrite(data.data(), 1, bytes, w);  // may end early: the reader gives up
+            fclose(w);
+        });
+        if (from == file) writer.join();
+        fea_graph *h = nullptr;
+        const int rc = graph_load(from.c_str(), 1000, 0, nullptr, nullptr, nullptr, nullptr, &h);
+        if (rc != FEA_OK) std::printf("%zu bytes: %s\n", bytes, last_error());
+        if (writer.joinable()) writer.join();
+        if (h) graph_destroy(h);
+        return rc;
+    };
+    for (const std::string &from : {file, pipe}) {
+        CHECK(load(from, data.size()) == FEA_OK);
+        CHECK(load(from, data.size() - 1) == FEA_EINVAL);
+        CHECK(load(from, data.size() / 2) == FEA_EINVAL);
+    }
+}
+
 int main(int argc, char **argv)
 {
     if (argc != 4) return 2;
@@ -162,8 +202,13 @@ int main(int argc, char **argv)
     }
     graph_build = (decltype(graph_build))dlsym(lib, "fea_graph_build");
     graph_destroy = (decltype(graph_destroy))dlsym(lib, "fea_graph_destroy");
+    graph_save = (decltype(graph_save))dlsym(lib, "fea_graph_save");
+    graph_load = (decltype(graph_load))dlsym(lib, "fea_graph_load");
+    last_error = (decltype(last_error))dlsym(lib, "fea_last_error");
+    signal(SIGPIPE, SIG_IGN);
     const std::string what = argv[2], dir = argv[3];
     if (what == "waits") check_waits();
+    else if (what == "pipe") check_pipe(dir);
     else return 2;
     return failures ? 1 : 0;
 }
