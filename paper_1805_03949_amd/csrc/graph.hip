@@ -405,26 +405,31 @@ __global__ void __launch_bounds__(256) k_rows(int64_t n_nodes, const int64_t *pt
 }
 
 // Of a sample of the nodes, one of every group of host::kMixedStep: how many
-// belong to elements of different node counts.
+// belong to elements of different node counts (count[0]). The lists may come from
+// a file: entries out of range are not followed (count[1] nodes have some).
 static int64_t mixed_groups(int64_t n_nodes) { return (n_nodes + host::kMixedStep - 1) / host::kMixedStep; }
-__global__ void __launch_bounds__(256) k_mixed_nodes(int64_t n_nodes, int64_t n_sampled, const int64_t *n2e_ptr,
-                                                     const int32_t *n2e, const int64_t *conn_ptr,
-                                                     unsigned long long *count)
+__global__ void __launch_bounds__(256) k_mixed_nodes(int64_t n_nodes, int64_t n_sampled, int64_t n_elems,
+                                                     int64_t n_inc, const int64_t *n2e_ptr, const int32_t *n2e,
+                                                     const int64_t *conn_ptr, unsigned long long *count)
 {
     const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    bool mixed = false;
+    bool mixed = false, bad = false;
     if (s < n_sampled) {
         const int64_t v = host::mixed_sample(s, n_nodes), b = n2e_ptr[v], e = n2e_ptr[v + 1];
+        bad = b < 0 || b > e || e > n_inc;
         int64_t first = -1;
-        for (int64_t p = b; p < e && !mixed; ++p) {
+        for (int64_t p = b; p < e && !mixed && !bad; ++p) {
             const int32_t el = n2e[p];
+            bad = el < 0 || el >= n_elems;
+            if (bad) break;
             const int64_t nn = conn_ptr[el + 1] - conn_ptr[el];
             mixed = first >= 0 && nn != first;
             first = nn;
         }
     }
-    const uint64_t m = __ballot(mixed);
+    const uint64_t m = __ballot(mixed), w = __ballot(bad);
     if (m && (threadIdx.x & 63) == 0) atomicAdd(count, (unsigned long long)__popcll(m));
+    if (w && (threadIdx.x & 63) == 0) atomicAdd(count + 1, (unsigned long long)__popcll(w));
 }
 
 // With the rows' first blocks known: one wave per row turns its sorted
@@ -1171,12 +1176,13 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
         FEA_HIP(hipMemsetAsync(g->n2e_ptr, 0, sizeof(int64_t), s));
     if ((rc = scan_to_ptr_i32(deg, N, g->row_ptr, scan, s))) return rc;
     FEA_HIP(hipMemcpyAsync(&g->nnz, g->row_ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    // cnt is free again: the first word takes the mixed nodes
+    // cnt is free again: its first two words take the counts (an array has at
+    // least 256 bytes)
     unsigned long long mixed = 0;
     const int64_t sampled = mixed_groups(N);
     if (N) {
-        FEA_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t), s));
-        k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, s>>>(N, sampled, g->n2e_ptr, g->n2e, conn_ptr,
+        FEA_HIP(hipMemsetAsync(cnt, 0, 2 * sizeof(int64_t), s));
+        k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, s>>>(N, sampled, E, C, g->n2e_ptr, g->n2e, conn_ptr,
                                                              (unsigned long long *)cnt);
         FEA_HIP(hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, s));
     }
@@ -1429,19 +1435,24 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
         return set_error(FEA_EINVAL, "%s is truncated or does not match its header", path);
     }
     if (n_nodes) {
-        unsigned long long mixed = 0, *cnt = (unsigned long long *)chk.p;
+        unsigned long long count[2] = {0, 0}, *cnt = (unsigned long long *)chk.p;
         const int64_t sampled = mixed_groups(n_nodes);
-        hipError_t e = hipMemsetAsync(cnt, 0, sizeof(mixed), stream);
+        hipError_t e = hipMemsetAsync(cnt, 0, sizeof(count), stream);
         if (e == hipSuccess) {
-            k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, stream>>>(n_nodes, sampled, g->n2e_ptr, g->n2e, conn_ptr, cnt);
-            e = hipMemcpyAsync(&mixed, cnt, sizeof(mixed), hipMemcpyDeviceToHost, stream);
+            k_mixed_nodes<<<grid_for(sampled, 256), 256, 0, stream>>>(n_nodes, sampled, n_elems, g->conn_len, g->n2e_ptr,
+                                                                      g->n2e, conn_ptr, cnt);
+            e = hipMemcpyAsync(count, cnt, sizeof(count), hipMemcpyDeviceToHost, stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) {
             destroy(g, hipDeviceSynchronize());
             return set_error(FEA_EHIP, "graph load: %s", hipGetErrorString(e));
         }
-        g->mixed = 2 * (int64_t)mixed >= sampled;
+        if (count[1]) {
+            destroy(g, hipSuccess);
+            return set_error(FEA_EINVAL, "%s does not match its header (incidence lists out of range)", path);
+        }
+        g->mixed = 2 * (int64_t)count[0] >= sampled;
     }
     if ((rc = noalloc_setup())) {
         destroy(g, hipSuccess);  // every copy and kernel was waited for
