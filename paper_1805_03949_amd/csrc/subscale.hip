@@ -261,7 +261,8 @@ __device__ __forceinline__ void sub_operator(const double M[B][3], const double 
     }
 }
 
-// 1 / (2 k) and 1 / (1 - 2 nu) with one division.
+// 1 / (2 k) and 1 / (1 - 2 nu) with one division (two where E (1 - 2 nu) has no
+// reciprocal).
 template <int MODEL, int B>
 __device__ __forceinline__ void sub_material(const SubElem<B> &el, double &ik, double &gd)
 {
@@ -271,6 +272,10 @@ __device__ __forceinline__ void sub_material(const SubElem<B> &el, double &ik, d
         const double s = 1.0 - 2.0 * el.nu, r = 1.0 / (el.E * s);
         ik = (1.0 + el.nu) * (s * r);
         gd = el.E * r;
+        if (!__builtin_isnormal(r)) {  // no stiffness: tau is infinite, not its product with L undefined
+            ik = (1.0 + el.nu) / el.E;
+            gd = 1.0 / s;
+        }
     }
 }
 
