@@ -194,7 +194,16 @@ int fea_graph_export(const fea_graph *g, int64_t *row_ptr, int32_t *col, int64_t
                      int32_t *e2nnz, int64_t *inv_ptr, int32_t *inv, int16_t *colour,
                      int32_t *type_perm, int64_t *type_seg, hipStream_t stream);
 
+/* Waits for the device. The graph's memory may serve later graphs: the library
+ * keeps up to 1 GiB (16 blocks) of unused device memory a device, gives back
+ * what 64 later allocations have passed over, and all of it before an
+ * allocation of its own fails or when told to (fea_release_memory). */
 void fea_graph_destroy(fea_graph *g);
+
+/* Gives the unused device memory that the library keeps on the current device
+ * back to the driver, for other allocators. FEA_EHIP if the driver does not take
+ * it (during a stream capture); it is then kept. */
+int fea_release_memory(void);
 
 /*
  * Assembles A (vals, nnz*b*b) and b (rhs, n_nodes*b), b = 1 for Poisson and

@@ -56,6 +56,7 @@ _lib.fea_graph_export.argtypes = [_P] * 9 + [ctypes.POINTER(_I64), _P]
 _lib.fea_graph_tile_colouring.argtypes = [_P, ctypes.POINTER(ctypes.c_int), _P, _P, _P, _P]
 _lib.fea_graph_destroy.argtypes = [_P]
 _lib.fea_graph_destroy.restype = None
+_lib.fea_release_memory.argtypes = []
 _lib.fea_assemble.argtypes = [_P, _P, _P, _P, _P, _P, _P, ctypes.POINTER(Material), _P,
                               ctypes.POINTER(Options), _P, _P, _P, _P]
 _lib.fea_assemble_noalloc.argtypes = _lib.fea_assemble.argtypes
@@ -118,7 +119,7 @@ N_FEATURES, N_PARAMS = 12, 5057
 
 # every exported symbol declared in include/fea.h
 EXPORTS = ("fea_graph_build", "fea_graph_save", "fea_graph_load", "fea_graph_sizes", "fea_graph_sym_sizes",
-           "fea_graph_export", "fea_graph_destroy",
+           "fea_graph_export", "fea_graph_destroy", "fea_release_memory",
            "fea_graph_tile_colouring",
            "fea_assemble", "fea_assemble_noalloc", "fea_last_timing", "fea_graph_gauss_points", "fea_subscale",
            "fea_batch_gauss_points", "fea_batch_subscale", "fea_last_class_timing", "fea_last_error", "fea_version",
@@ -175,6 +176,12 @@ def _ptr(t):
 def _stream(stream):
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def release_memory():
+    """Gives the device memory that the library keeps unused (of destroyed graphs,
+    at most 1 GiB) back to the driver, for instance to torch's allocator."""
+    _check(_lib.fea_release_memory())
 
 
 def version():

@@ -69,7 +69,8 @@ int dalloc(void **p, size_t bytes)
 // pool, 3.2 ms with it.
 // Bounded: at most kPoolBytes and kPoolBlocks unused a device; the longest
 // unused goes back to the driver first, and also one that kPoolAge later
-// allocations have passed over; all of them do before an allocation fails.
+// allocations have passed over; all of them do before an allocation fails, and
+// when the caller says so (fea_release_memory).
 // A block enters the pool with no work on it pending: pool_free takes the
 // result of the wait for that work and hands the block to the driver if the
 // wait failed (hipFree then waits itself, or refuses). Any stream and thread may
@@ -105,16 +106,34 @@ Pool &pool()
 // With the lock held: unlists blocks of the device, oldest first, while
 // `more` says so.
 template <typename F>
-void pool_drop(Pool &q, int device, std::vector<void *> &out, F &&more)
+void pool_drop(Pool &q, int device, std::vector<PoolBlock> &out, F &&more)
 {
     for (size_t i = 0; i < q.idle.size();) {
         if (q.idle[i].device == device && more(q.idle[i])) {
-            out.push_back(q.idle[i].p);
+            out.push_back(q.idle[i]);
             q.idle.erase(q.idle.begin() + (ptrdiff_t)i);
         } else {
             ++i;
         }
     }
+}
+
+// Unlisted blocks to the driver; those that it refuses (under a capture) are
+// listed again. Returns whether it took all of them.
+bool pool_give_back(Pool &q, const std::vector<PoolBlock> &old)
+{
+    bool all = true;
+    for (const PoolBlock &b : old) {
+        if (hipFree(b.p) == hipSuccess) continue;
+        (void)hipGetLastError();
+        all = false;
+        try {
+            std::lock_guard<std::mutex> lock(q.mtx);
+            q.idle.insert(q.idle.begin(), b);
+        } catch (...) {
+        }
+    }
+    return all;
 }
 
 }  // namespace
@@ -128,7 +147,7 @@ hipError_t pool_alloc(void **p, size_t bytes)
     constexpr size_t G = size_t(2) << 20;
     if (bytes >= G) bytes = (bytes + G - 1) / G * G;
     Pool &q = pool();
-    std::vector<void *> old;
+    std::vector<PoolBlock> old;
     try {
         std::lock_guard<std::mutex> lock(q.mtx);
         old.reserve(q.idle.size());
@@ -151,7 +170,7 @@ hipError_t pool_alloc(void **p, size_t bytes)
     } catch (...) {
         return hipErrorOutOfMemory;
     }
-    for (void *o : old) (void)hipFree(o);
+    pool_give_back(q, old);
     if (*p) return hipSuccess;
     e = hipMalloc(p, bytes);
     if (e != hipSuccess) {  // once more with the pool given back
@@ -171,20 +190,20 @@ hipError_t pool_alloc(void **p, size_t bytes)
     return hipSuccess;
 }
 
-void pool_flush(int device)
+bool pool_flush(int device)
 {
     Pool &q = pool();
-    std::vector<void *> old;
+    std::vector<PoolBlock> old;
     {
         std::lock_guard<std::mutex> lock(q.mtx);
         try {
             old.reserve(q.idle.size());
         } catch (...) {
-            return;
+            return false;
         }
         pool_drop(q, device, old, [](const PoolBlock &) { return true; });
     }
-    for (void *o : old) (void)hipFree(o);
+    return pool_give_back(q, old);
 }
 
 void pool_free(void *p, hipError_t waited)
@@ -196,7 +215,7 @@ void pool_free(void *p, hipError_t waited)
         return;
     }
     Pool &q = pool();
-    std::vector<void *> old;
+    std::vector<PoolBlock> old;
     bool kept = false;
     try {
         std::lock_guard<std::mutex> lock(q.mtx);
@@ -228,7 +247,7 @@ void pool_free(void *p, hipError_t waited)
         }
     } catch (...) {
     }
-    for (void *o : old) (void)hipFree(o);
+    pool_give_back(q, old);
     if (!kept) (void)hipFree(p);
 }
 
@@ -385,6 +404,15 @@ int scan_to_ptr_i64(const int64_t *in, int64_t n, int64_t *ptr, int64_t *tmp, hi
 }
 
 }  // namespace fea
+
+extern "C" int fea_release_memory(void)
+{
+    fea::clear_error();
+    int dev = 0;
+    FEA_HIP(hipGetDevice(&dev));
+    if (!fea::pool_flush(dev)) return fea::set_error(FEA_EHIP, "the driver did not take back all unused memory");
+    return FEA_OK;
+}
 
 extern "C" const char *fea_last_error(void) { return fea::g_error.c_str(); }
 

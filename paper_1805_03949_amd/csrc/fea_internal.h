@@ -52,7 +52,7 @@ int dalloc(void **p, size_t bytes);
 // work on that memory, and only after one that succeeded is it pooled.
 hipError_t pool_alloc(void **p, size_t bytes);
 void pool_free(void *p, hipError_t waited);
-void pool_flush(int device);
+bool pool_flush(int device);  // false: the driver refused some
 int dalloc_pool(void **p, size_t bytes);
 // One allocation (*base, for pool_free) for several arrays, each 256-byte
 // aligned and (an empty one too) at least that long: hipFree takes 0.3 to

@@ -25,7 +25,7 @@ static std::mutex mtx;
 static std::map<void *, size_t> live;  // device memory the driver has given out
 static int n_malloc = 0, fail_malloc = 0;
 static size_t largest_freed = 0;
-static bool fail_device_wait = false, fail_stream_wait = false;
+static bool fail_device_wait = false, fail_stream_wait = false, refuse_free = false;
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n)
@@ -44,6 +44,7 @@ hipError_t hipMalloc(void **p, size_t n)
 hipError_t hipFree(void *p)
 {
     std::lock_guard<std::mutex> lock(mtx);
+    if (refuse_free) return hipErrorStreamCaptureUnsupported;
     auto it = live.find(p);
     if (it == live.end()) return p ? hipErrorInvalidValue : hipSuccess;
     if (it->second > largest_freed) largest_freed = it->second;
@@ -103,6 +104,7 @@ static decltype(&fea_graph_destroy) graph_destroy;
 static decltype(&fea_graph_save) graph_save;
 static decltype(&fea_graph_load) graph_load;
 static decltype(&fea_last_error) last_error;
+static decltype(&fea_release_memory) release_memory;
 
 static int failures = 0;
 #define CHECK(c)                                                              \
@@ -158,6 +160,70 @@ static void check_waits()
     CHECK(n_malloc > before);
 }
 
+constexpr size_t GiB = (size_t)1 << 30;
+
+// Unused memory is bounded in bytes and blocks, and what later allocations pass
+// over goes back.
+static void check_bounds()
+{
+    std::vector<fea_graph *> g;
+    for (int k = 0; k < 6; ++k) g.push_back(build((20 + 3 * k) * M));  // 0.3 to 0.6 GB and as much scratch each
+    CHECK(live_bytes() > 2 * GiB);
+    for (fea_graph *x : g) graph_destroy(x);
+    CHECK(live_bytes() <= GiB && live_bytes() > GiB / 4);
+    g.clear();
+    for (int k = 0; k < 40; ++k) g.push_back(build((1 + k) * M / 20));
+    for (fea_graph *x : g) graph_destroy(x);
+    CHECK(live.size() <= 16 && live_bytes() <= GiB);
+    graph_destroy(build(80 * M));  // one block beyond the bound: not kept
+    CHECK(live_bytes() <= GiB);
+    graph_destroy(build(30 * M));
+    CHECK(live_bytes() > GiB / 4);
+    for (int k = 0; k < 40; ++k) graph_destroy(build(10));
+    CHECK(live_bytes() < GiB / 64);
+}
+
+// Before an allocation fails, the unused memory goes back; after one that does
+// the library goes on.
+static void check_full()
+{
+    graph_destroy(build(30 * M));
+    CHECK(live_bytes() > GiB / 4);
+    fail_malloc = 1;
+    fea_graph *g = build(M);  // too small for the blocks kept: new memory, on the second try
+    CHECK(fail_malloc == 0 && live_bytes() < GiB / 4);
+    graph_destroy(g);
+    fail_malloc = 1000;
+    build(10 * M, FEA_ENOMEM);
+    fail_malloc = 0;
+    graph_destroy(build(10 * M));
+}
+
+// fea_release_memory gives back what no graph uses, and nothing else; memory
+// that the driver does not take (under a capture) stays in use.
+static void check_release()
+{
+    fea_graph *g = build(M);
+    const size_t used = live_bytes();
+    graph_destroy(build(2 * M));
+    CHECK(live_bytes() > used);
+    CHECK(release_memory() == FEA_OK);
+    CHECK(live_bytes() <= used && live_bytes() >= 16 * (size_t)M);
+    graph_destroy(g);
+    CHECK(live_bytes() > 0);
+    const size_t kept = live_bytes();
+    refuse_free = true;
+    CHECK(release_memory() == FEA_EHIP);
+    refuse_free = false;
+    CHECK(live_bytes() == kept);
+    const int before = n_malloc;
+    g = build(M / 2 + M / 4);
+    CHECK(n_malloc < before + 4);  // not all of it new
+    graph_destroy(g);
+    CHECK(release_memory() == FEA_OK);
+    CHECK(live.empty());
+}
+
 // A graph cache is read from a file and from a pipe (which cannot seek); a
 // truncated one is refused either way.
 static void check_pipe(const std::string &dir)
@@ -205,10 +271,14 @@ int main(int argc, char **argv)
     graph_save = (decltype(graph_save))dlsym(lib, "fea_graph_save");
     graph_load = (decltype(graph_load))dlsym(lib, "fea_graph_load");
     last_error = (decltype(last_error))dlsym(lib, "fea_last_error");
+    release_memory = (decltype(release_memory))dlsym(lib, "fea_release_memory");
     signal(SIGPIPE, SIG_IGN);
     const std::string what = argv[2], dir = argv[3];
     if (what == "waits") check_waits();
     else if (what == "pipe") check_pipe(dir);
+    else if (what == "bounds") check_bounds();
+    else if (what == "full") check_full();
+    else if (what == "release") check_release();
     else return 2;
     return failures ? 1 : 0;
 }
