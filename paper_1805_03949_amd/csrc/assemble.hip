@@ -123,29 +123,48 @@ static void launch_type(int t, const ElemArgs &a, hipStream_t s)
     }
 }
 
-// The four families' elements (a[t], n may be 0), in one launch up to a number
-// of tiles. A launch of one family ends when its last workgroup does: every
-// family costs the latency of a tile (4 to 5 us) and a last wave that is partly
-// empty. In the common kernel every workgroup has the registers and LDS of the
-// largest family, so it keeps fewer waves in flight, which is what counts once
-// the chip is full; by how much depends on the kernel (the neo-Hookean hex8
-// tile is the largest by far) and on whether one family has nearly all tiles
-// and would have run better alone. Measured on MI355X, us a call, four launches
-// -> one, bands of the four families, n^3 cells (n = 10: 240 tiles, 16: 920, 32:
-// 7400, 40: 14400, 48: 24900, 64: 59000 upper-triangle tiles):
-//   FP64        n = 10: 25 -> 12, 16: 34 -> 18, 32: 83 -> 63, 48: 260 -> 247, 64: 590 -> 568, 80: 1102 -> 1106
-//   mixed       n = 10: 23 -> 11, 16: 27 -> 15, 32: 64 -> 47, 48: 193 -> 182, 64: 410 -> 397, 80: 768 -> 772
-//   residual    n = 10: 33 -> 15, 16: 41 -> 26, 32: 127 -> 122, 40: 244 -> 261
-//   row-owner   n = 10: 31 -> 20, 16: 47 -> 32, 32: 159 -> 158, 36: 241 -> 233, 44: 431 -> 443
-// and with 98% tet4 cells: FP64 n = 32 (7800 tiles): 50 -> 48, 48: 183 -> 193;
-// residual n = 16 (980): 22.5 -> 21.5, 24: 38 -> 50; row-owner n = 32 (12300):
-// 150 -> 140, 40: 313 -> 327 (98% pyr5, 19600: 249 -> 267).
-template <int MODEL, int VAR>
-constexpr int64_t fuse_tiles(const bool lopsided)
+// Whether the families go in one launch: `tiles` of them in all, `most` in the
+// largest family, `pyr5` in that family, `fams` families. A launch of one family
+// ends when its last workgroup does: every family costs the latency of a tile (4
+// to 5 us) and a last wave that is partly empty. In the common kernel every
+// workgroup has the registers and LDS of the largest family, so it keeps fewer
+// waves in flight, which is what counts once the chip is full; it counts most
+// for the neo-Hookean upper triangle, whose pyr5 tile has by far the most LDS
+// (FP64, KB, tangent / with the residual: tet4 20/20, pyr5 45/54, pen6 30/35, hex8
+// 31/34): there the tiles of the other families count, against the launches
+// saved. Measured on MI355X, us a call, four launches -> one, n^3 cells in bands of
+// the four families (n = 10: 230 tiles, 16: 930, 24: 3100, 32: 7400, 40: 14400,
+// 48: 24900, 64: 59000 upper-triangle tiles):
+//   FP64        n = 10: 24 -> 11, 16: 33 -> 18, 32: 84 -> 63, 48: 257 -> 246, 64: 586 -> 566
+//   mixed       n = 10: 23 -> 11, 16: 27 -> 15, 32: 64 -> 46, 48: 178 -> 164, 64: 375 -> 359
+//   Poisson     n = 10: 22 -> 13, 16: 23 -> 15, 32: 50 -> 37, 48: 103 -> 93, 64: 237 -> 243
+//   tangent     n = 10: 31 -> 13, 16: 38 -> 22, 32: 102 -> 90, 40: 204 -> 206 (mixed 32: 76 -> 60, 40: 120 -> 106)
+//   residual    n = 10: 33 -> 14, 16: 40 -> 25, 32: 126 -> 123, 40: 243 -> 267
+//   row-owner   n = 10: 29 -> 20, 16: 47 -> 33, 32: 156 -> 150, 36: 237 -> 230, 44: 422 -> 445
+// Two families in equal halves (one launch saved), hex8 and tet4 / pyr5 and pen6:
+//   FP64        n = 32 (6270 / 8510 tiles): 57 -> 53 / 82 -> 77, 44: 163 -> 166 / 228 -> 219, 64: 461 -> 471 / 655 -> 657
+//   Poisson     n = 32: 34 -> 31 / 48 -> 44, 44: 54 -> 55 / 95 -> 91, 56: 97 -> 102 / 194 -> 195
+//   tangent     n = 24 (2650 / 3590): 42 -> 40 / 62 -> 55, 28: 51 -> 53 / 83 -> 79, 32: 66 -> 74 / 111 -> 111
+//   residual    n = 18 (1120 / 1520): 30 -> 28 / 44 -> 39, 24: 45 -> 49 / 77 -> 72, 32: 72 -> 98 / 147 -> 153
+//   row-owner   n = 32 (10200 / 14500): 129 -> 123 / 176 -> 167, mixed 77 -> 76 / 95 -> 98, 36: 95 -> 99 / 168 -> 182
+//   with the residual n = 24 (4300 / 6100): 62 -> 59 / 90 -> 83, 28: 81 -> 84 / 136 -> 133
+// hex8, tet4 and pen6, residual: n = 24 (2530): 55 -> 48, 28: 69 -> 69, 32: 85 -> 98. 98% tet4
+// cells (lopsided: one family has more than three quarters of the tiles): FP64 n =
+// 32 (7800): 51 -> 49, 44: 151 -> 163; residual 16 (980): 22 -> 21, 24: 38 -> 50;
+// row-owner 32 (12200): 141 -> 129, 40: 304 -> 330 (98% pyr5, 19400: 243 -> 266).
+template <int MODEL, int VAR, typename CT>
+constexpr bool one_launch(int64_t tiles, int64_t most, int64_t pyr5, int fams)
 {
-    if (MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES) return lopsided ? 1024 : 8192;
-    if (VAR == V_ROWOWNER) return lopsided ? 8192 : 16384;
-    return lopsided ? 8192 : 32768;
+    constexpr bool NH = MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES, RO = VAR == V_ROWOWNER;
+    const bool lopsided = most > tiles / 4 * 3;
+    if (NH) {
+        constexpr bool RES = MODEL == M_ELASTIC_RES;
+        const int64_t saved = fams - 1;
+        const int64_t tangent = !RO && sizeof(CT) == 8 ? 3400 * saved : 8192;
+        const int64_t others = !RES ? tangent : RO ? 6000 * saved : 800 + 1350 * saved;
+        return tiles <= (lopsided ? 1024 : 8192) && tiles - pyr5 <= others;
+    }
+    return tiles <= (lopsided ? 8192 : RO ? 16384 : 32768);
 }
 
 // Families that share their nodes (an unordered mixture of element types)
@@ -163,17 +182,19 @@ constexpr int64_t fuse_tiles(const bool lopsided)
 constexpr size_t kSliceBytes = size_t(256) << 20;
 constexpr int64_t kSliceTiles = 128;
 
-// ws_bytes: the tiles' output; mixed: most nodes belong to several families.
+// The four families' elements (a[t], n may be 0). ws_bytes: the tiles' output;
+// mixed: most nodes belong to several families.
 template <int MODEL, int VAR, typename CT>
 static void launch_families(const ElemArgs *a, size_t ws_bytes, bool mixed, hipStream_t s)
 {
     ElemArgs4 q;
     constexpr int EPB[4] = {ElemSmem<0, MODEL, VAR, CT>::EPB, ElemSmem<1, MODEL, VAR, CT>::EPB,
                             ElemSmem<2, MODEL, VAR, CT>::EPB, ElemSmem<3, MODEL, VAR, CT>::EPB};
-    int64_t tiles = 0, most = 0;
+    int64_t tiles = 0, most = 0, pyr5 = 0;
     int fams = 0;
     for (int t = 0; t < 4; ++t) {
         const int64_t n = (a[t].n + EPB[t] - 1) / EPB[t];
+        if (t == 1) pyr5 = n;
         q.first[t] = (uint32_t)tiles;
         if (n > 0) ++fams;
         tiles += n;
@@ -182,8 +203,7 @@ static void launch_families(const ElemArgs *a, size_t ws_bytes, bool mixed, hipS
     q.first[4] = (uint32_t)tiles;
     constexpr bool NH = MODEL == M_ELASTIC_NH || MODEL == M_ELASTIC_RES;
     const bool sliced = mixed && ws_bytes > kSliceBytes && !(NH && VAR == V_ROWSYM);
-    // lopsided: one family has more than three quarters of the tiles
-    if (fams < 2 || (!sliced && tiles > fuse_tiles<MODEL, VAR>(most > tiles / 4 * 3))) {
+    if (fams < 2 || (!sliced && !one_launch<MODEL, VAR, CT>(tiles, most, pyr5, fams))) {
         for (int t = 0; t < 4; ++t) launch_type<MODEL, VAR, CT>(t, a[t], s);
         return;
     }
