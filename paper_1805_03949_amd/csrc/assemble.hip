@@ -142,7 +142,7 @@ static void launch_type(int t, const ElemArgs &a, hipStream_t s)
 //   residual    n = 10: 33 -> 14, 16: 40 -> 25, 32: 126 -> 123, 40: 243 -> 267
 //   row-owner   n = 10: 29 -> 20, 16: 47 -> 33, 32: 156 -> 150, 36: 237 -> 230, 44: 422 -> 445
 // Two families in equal halves (one launch saved), hex8 and tet4 / pyr5 and pen6:
-//   FP64        n = 32 (6270 / 8510 tiles): 57 -> 53 / 82 -> 77, 44: 163 -> 166 / 228 -> 219, 64: 461 -> 471 / 655 -> 657
+//   FP64        n = 32 (6270 / 8510 tiles): 57 -> 53 / 82 -> 77, 44: 163 -> 166 / 228 -> 219, 56: 317 -> 316 / 450 -> 445
 //   Poisson     n = 32: 34 -> 31 / 48 -> 44, 44: 54 -> 55 / 95 -> 91, 56: 97 -> 102 / 194 -> 195
 //   tangent     n = 24 (2650 / 3590): 42 -> 40 / 62 -> 55, 28: 51 -> 53 / 83 -> 79, 32: 66 -> 74 / 111 -> 111
 //   residual    n = 18 (1120 / 1520): 30 -> 28 / 44 -> 39, 24: 45 -> 49 / 77 -> 72, 32: 72 -> 98 / 147 -> 153

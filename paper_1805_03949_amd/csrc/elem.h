@@ -14,11 +14,13 @@
 // form is algebraically identical to contracting the 81-entry tangent
 // AA_iJjL = mu d_ij d_JL + (mu - lam lnJ) Finv_Jj Finv_Li + lam Finv_Ji Finv_Lj.
 //
-// Work layout: one 256-thread workgroup holds EPB = 256 / n^2 elements of
-// one family; geometry runs one thread per (element, Gauss point) and
-// writes gradients to LDS; the element matrix runs one thread per
-// (element, block a-b), each accumulating its b x b block over the Gauss
-// points; the right-hand side one thread per (element, node).
+// Work layout: one 256-thread workgroup holds a tile of EPB elements of one
+// family. Upper-triangle forms: EPB = 256 / (n(n+1)/2), one thread per
+// (element, pair a <= b) for the matrix; the others EPB = 256 / n^2, one thread per
+// (element, block a-b). Each accumulates its b x b block over the Gauss points
+// from the gradients in LDS; the right-hand side takes one thread per (element,
+// node). The gradients come from the geometry, with three lanes per (element,
+// Gauss point) where a tile has at most 84 points, one otherwise.
 #pragma once
 #include <climits>
 #include <cstddef>

@@ -1,4 +1,4 @@
-// Host-side graph steps that are sequential by definition: greedy
+// Host-side graph steps: greedy
 // first-fit colouring of items (elements, or element tiles) over the
 // node-sharing graph, the neighbour count of every item, and the
 // (family, colour) buckets the colour-by-colour launches walk. Plain C++

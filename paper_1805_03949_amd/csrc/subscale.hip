@@ -30,17 +30,19 @@
 // the fields at their Gauss point from the coefficients. tet4: one lane per
 // element, no second derivatives.
 //
-// What bounds it: the FP64 instructions of a point (about 400) and the chain
-// ids -> values -> results of a wave that lives for one group of elements. All
+// What bounds it: the vector instructions of a point (pyr5 and hex8 elasticity
+// 496, 315 of them FP64, 23 of all only where an element has no stiffness) and the
+// chain ids -> values -> results of a wave that lives for one group of elements. All
 // global loads are therefore issued in two levels (ids; then coordinates,
 // field, material, source and output place together), and material constants
 // cost two divisions instead of three. Measured on MI355X, us a call,
 // before -> after (before: coefficients of every field through LDS, five
 // barriers, loads behind each other): elasticity, 96^3 cells of one family, pyr5
-// (42M points) 996 -> 731, hex8 (7M) 179 -> 131, pen6 (11M) 237 -> 220, tet4 (5M)
-// 128 -> 103; Poisson 489 -> 369, 96 -> 69, 116 -> 115, 86 -> 61; 16^3 cells, all
-// families, 18.9 -> 7.0 (one launch for all, see run_sub). The pyramid issues 472
-// vector instructions a wave, 0.51 of its 0.73 ms.
+// (42M points) 996 -> 670, hex8 (7M) 179 -> 130, pen6 (11M) 237 -> 224, tet4 (5M)
+// 128 -> 103; Poisson 489 -> 367, 96 -> 68, 116 -> 121, 86 -> 62; 16^3 cells, all
+// families, 18.9 -> 7.2 (one launch for all, see run_sub). Issuing the pyramid's
+// instructions takes 0.51 of its 0.67 ms (122 VGPRs: four waves per SIMD; at 138
+// and three 0.73).
 #include <algorithm>
 #include <climits>
 
@@ -542,13 +544,16 @@ static void launch_sub(const SubArgs &a, hipStream_t s)
 }
 
 // One launch for all families saves a launch and a partly empty last wave per
-// family; its workgroups all have the registers of the pyramid's kernel (3
+// family; its workgroups all have the registers of the pyramid's kernel (4
 // waves in flight per SIMD where tet4 alone has 8), which costs more than that
 // on a large mesh that is nearly all tet4 or pen6. Measured on MI355X, us a
-// call, four launches -> one, elasticity, bands of the families, n^3 cells: n =
-// 8: 13.0 -> 6.0, 16: 13.8 -> 7.0, 32: 23 -> 17, 48: 52 -> 45, 64 (19000
-// workgroups): 99 -> 91, 96: 324 -> 325; 98% tet4: 48 (2600): 19 -> 18, 64 (6100):
-// 34 -> 34, 96: 113 -> 130; 98% pen6: 48 (5200): 38.5 -> 37.6, 64 (12400): 74 -> 77.
+// call, four launches -> one, elasticity / Poisson, n^3 cells in bands of the
+// families: n = 8: 13.3 -> 6.2 / 11.4 -> 5.4, 16: 13.9 -> 7.2 / 11.9 -> 6.2, 32: 22 ->
+// 16 / 15 -> 11, 48: 48 -> 37 / 32 -> 24, 64 (19000 workgroups): 93 -> 77 / 57 -> 48,
+// 96 (64000): 287 -> 280 / 168 -> 152; hex8 and pyr5 in halves 56 (19200): 79 -> 82 /
+// 42 -> 43; 98% tet4: 48 (2600): 19 -> 18 / 15 -> 13, 64 (6200): 34 -> 33 / 26 -> 23,
+// 96 (20900): 114 -> 120 / 69 -> 69; 98% pen6: 48 (5200): 36 -> 32 / 21 -> 20, 96
+// (41800): 220 -> 221 / 110 -> 115.
 constexpr int64_t kSubFuse = 32768, kSubFuseLopsided = 4096;  // workgroups
 
 template <int MODEL>
