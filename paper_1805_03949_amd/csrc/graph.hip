@@ -1096,6 +1096,21 @@ static int mesh_check(int64_t N, int64_t E, const uint8_t *types, const int64_t 
     return FEA_OK;
 }
 
+// Where the families' elements, node entries and element-matrix slots start in
+// the type-sorted order, from the elements of every family.
+struct FamilyBases {
+    int64_t seg[5] = {0}, node[5] = {0}, slot[5] = {0};
+    explicit FamilyBases(const MeshCheck &mc)
+    {
+        for (int t = 0; t < 4; ++t) {
+            const int64_t n = nodes_of(t), c = (int64_t)mc.fam[t];
+            seg[t + 1] = seg[t] + c;
+            node[t + 1] = node[t] + c * n;
+            slot[t + 1] = slot[t] + c * n * n;
+        }
+    }
+};
+
 static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn_ptr,
                  const int32_t *conn, hipStream_t s, fea_graph *g)
 {
@@ -1114,12 +1129,13 @@ static int build(int64_t N, int64_t E, const uint8_t *types, const int64_t *conn
         return rc;
     if ((rc = mesh_check(N, E, types, conn_ptr, conn, out, famc, s, &mc))) return rc;
     g->mesh_fp = mc.fp;
+    const FamilyBases fb(mc);
+    std::copy(fb.seg, fb.seg + 5, g->seg);
+    std::copy(fb.node, fb.node + 5, g->node_base);
+    std::copy(fb.slot, fb.slot + 5, g->slot_base);
     RowBases bs;
     for (int t = 0; t < 4; ++t) {
-        const int64_t n = nodes_of(t), c = (int64_t)mc.fam[t];
-        g->seg[t + 1] = g->seg[t] + c;
-        g->node_base[t + 1] = g->node_base[t] + c * n;
-        g->slot_base[t + 1] = g->slot_base[t] + c * n * n;
+        const int64_t n = nodes_of(t);
         bs.node[t] = (uint32_t)(g->node_base[t] - g->seg[t] * n);
         bs.slot[t] = (uint32_t)(g->slot_base[t] - g->seg[t] * n * n);
     }
@@ -1380,6 +1396,11 @@ extern "C" int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems
     if ((rc = mesh_check(n_nodes, n_elems, types, conn_ptr, conn, (MeshCheck *)chk.p, nullptr, stream, &mc)))
         return rc;
     if (mc.fp != h.mesh_fp) return set_error(FEA_EINVAL, "%s was built for another mesh (connectivity differs)", path);
+    const FamilyBases fb(mc);
+    if (h.n_colours > host::kMaxColours || h.conn_len != fb.node[4] || h.map_len != fb.slot[4] || h.nnz > h.map_len ||
+        memcmp(h.seg, fb.seg, sizeof(h.seg)) != 0 || memcmp(h.node_base, fb.node, sizeof(h.node_base)) != 0 ||
+        memcmp(h.slot_base, fb.slot, sizeof(h.slot_base)) != 0)
+        return set_error(FEA_EINVAL, "%s: inconsistent header", path);
     fea_graph *g = new (std::nothrow) fea_graph();
     if (!g) return set_error(FEA_ENOMEM, "host allocation failed");
     FEA_HIP(hipGetDevice(&g->device));

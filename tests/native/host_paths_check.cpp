@@ -258,6 +258,43 @@ static void check_pipe(const std::string &dir)
     }
 }
 
+// A header that no build writes is refused before anything is sized by it:
+// more colours than there can be, sizes and family offsets that are not the mesh's.
+static void check_header(const std::string &dir)
+{
+    const std::string file = dir + "/graph";
+    fea_graph *g = build(1000);
+    CHECK(graph_save(g, file.c_str()) == FEA_OK);
+    graph_destroy(g);
+    std::vector<char> data;
+    FILE *f = fopen(file.c_str(), "rb");
+    for (int c; (c = fgetc(f)) != EOF;) data.push_back((char)c);
+    fclose(f);
+    // header: magic 8, version 4, colours 4, arch 64, then int64: nodes, elements, blocks, map and connectivity
+    // lengths, fingerprint, 3 x 5 family offsets, length of the colour buckets
+    auto load = [&](size_t at32, int32_t v32, size_t at64, int64_t v64) {
+        std::vector<char> d = data;
+        if (at32) memcpy(d.data() + at32, &v32, 4);
+        if (at64) memcpy(d.data() + at64, &v64, 8);
+        FILE *w = fopen(file.c_str(), "wb");
+        fwrite(d.data(), 1, d.size(), w);
+        fclose(w);
+        fea_graph *h = nullptr;
+        const int before = n_malloc, rc = graph_load(file.c_str(), 1000, 0, nullptr, nullptr, nullptr, nullptr, &h);
+        CHECK(rc == FEA_OK || n_malloc <= before + 1);  // (the mesh check's scratch memory)
+        if (h) graph_destroy(h);
+        release_memory();
+        return rc;
+    };
+    const int32_t many = 0x7ffffffe;
+    CHECK(load(0, 0, 0, 0) == FEA_OK);
+    CHECK(load(12, many, 248, 4 * ((int64_t)many + 1)) == FEA_EINVAL);
+    CHECK(load(12, 257, 248, 4 * 258) == FEA_EINVAL);
+    CHECK(load(0, 0, 104, 1) == FEA_EINVAL);   // map length
+    CHECK(load(0, 0, 112, 1) == FEA_EINVAL);   // connectivity length
+    for (size_t k = 0; k < 15; ++k) CHECK(load(0, 0, 128 + 8 * k, 1) == FEA_EINVAL);
+}
+
 int main(int argc, char **argv)
 {
     if (argc != 4) return 2;
@@ -276,6 +313,7 @@ int main(int argc, char **argv)
     const std::string what = argv[2], dir = argv[3];
     if (what == "waits") check_waits();
     else if (what == "pipe") check_pipe(dir);
+    else if (what == "header") check_header(dir);
     else if (what == "bounds") check_bounds();
     else if (what == "full") check_full();
     else if (what == "release") check_release();

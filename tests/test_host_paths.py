@@ -21,7 +21,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["waits", "pipe", "bounds", "full", "release"])
+@pytest.mark.parametrize("check", ["waits", "pipe", "header", "bounds", "full", "release"])
 def test_host_paths(program, check, tmp_path):
     import paper_1805_03949_amd as fea
     p = subprocess.run([program, fea.LIB_PATH, check, str(tmp_path)], stdout=subprocess.PIPE,
