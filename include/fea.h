@@ -148,7 +148,8 @@ int fea_graph_build(int64_t n_nodes, int64_t n_elems, const uint8_t *types,
  * that assemble the same mesh in several processes. Errors: FEA_EINVAL
  * (cannot open or write the file, not a graph cache, another format
  * version, written on another GPU architecture, mesh sizes or connectivity
- * fingerprint differ from the saved graph's, file truncated), FEA_EMESH
+ * fingerprint differ from the saved graph's, file truncated, header or
+ * incidence lists that the mesh contradicts), FEA_EMESH
  * (invalid mesh), FEA_ENOMEM, FEA_EHIP. */
 int fea_graph_save(const fea_graph *g, const char *path);
 int fea_graph_load(const char *path, int64_t n_nodes, int64_t n_elems, const uint8_t *types,
